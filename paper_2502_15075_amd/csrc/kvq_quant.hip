@@ -1,5 +1,4 @@
-// Quantize-append (token-wise groups; channel-wise key groups with their residual buffer), dequantize and
-// reconstruction-error kernels (gfx950).
+// Quantize-append kernels: token-wise groups; channel-wise key groups with their residual buffer (gfx950).
 //
 // The quantizer is the b-bit uniform scalar quantizer of App. B ("Preliminaries": scale factor,
 // round, clip, reconstruct) of arXiv 2502.15075 in its group-wise asymmetric min-max form; the
@@ -248,27 +247,13 @@ __global__ __launch_bounds__(256) void quantize_append_kernel(Geom g, kvq_cache 
   }
 }
 
-// The 8 fields of channels d0 .. d0+7 (d0 a multiple of 8) of token u in a 32-token block of B-bit fields: the same
-// field of 8 words one lane piece (16 bytes, 8 for 1-bit fields) apart.
-template <int B> __device__ __forceinline__ void block_fields8(const uint8_t* blkp, int u, int d0, uint32_t code[8]) {
+// The 16-bit patterns of channels d0 .. d0+7 (d0 a multiple of 8) of value row t of a residual buffer.
+__device__ __forceinline__ void value_patterns8(const uint8_t* vr, int t, int d0, uint32_t code[8]) {
   int dw, bit;
-  v_field(u, d0, B, &dw, &bit);
-  const uint32_t* blk = reinterpret_cast<const uint32_t*>(blkp) + dw;
+  v_field(t & 31, d0, 16, &dw, &bit);
+  const uint32_t* blk = reinterpret_cast<const uint32_t*>(vr + (t >> 5) * (512 * 16)) + dw;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) code[e] = (blk[(B == 1 ? 2 : 4) * e] >> bit) & (B == 16 ? 0xFFFFu : ((1u << B) - 1u));
-}
-// The 8 codes of channels d0 .. d0+7 of value row t (3- and 6-bit codes: low parts from the block's first part, high
-// parts from its second).
-template <int B> __device__ __forceinline__ void value_codes8(const uint8_t* cs, int64_t t, int d0, uint32_t code[8]) {
-  constexpr int LO = code_lo_bits<B>(), HI = code_hi_bits<B>();
-  const uint8_t* blk = cs + (t >> 5) * (int64_t)(512 * B);
-  block_fields8<LO>(blk, (int)(t & 31), d0, code);
-  if constexpr (HI != 0) {
-    uint32_t high[8];
-    block_fields8<HI>(blk + 512 * LO, (int)(t & 31), d0, high);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) code[e] |= high[e] << LO;
-  }
+  for (int e = 0; e < 8; ++e) code[e] = (blk[4 * e] >> bit) & 0xFFFFu;
 }
 
 // Channel-wise keys (Sec. 4 "Downstream Task Accuracy": the per-column back-end with its residual buffer).
@@ -324,7 +309,7 @@ __global__ __launch_bounds__(256) void seq_append_kernel(Geom g, kvq_cache c, co
     } else if (complete && row < lo) {                     // older tokens of the block being flushed
       kraw[it] = *reinterpret_cast<const uint4*>(kr + row * (kHeadDim * 2) + d0 * 2);
       uint32_t code[8];
-      value_codes8<16>(vr, row, d0, code);
+      value_patterns8(vr, row, d0, code);
       vraw[it] = make_uint4(code[0] | (code[1] << 16), code[2] | (code[3] << 16), code[4] | (code[5] << 16),
                             code[6] | (code[7] << 16));
     }
@@ -440,154 +425,6 @@ __global__ __launch_bounds__(256) void seq_append_kernel(Geom g, kvq_cache c, co
   }
 }
 
-// Reconstruction x^ = code * scale + zero of 8 consecutive channels d0..d0+7 (d0 a multiple of 8) of the token with
-// number t in plane order (virtual_token: contiguous and paged planes alike), as binary32 values; a 16-bit plane is
-// widened exactly.  B: what a code takes in its plane (compile time); IS_V: values, else keys.
-template <int B, bool IS_V>
-__device__ __forceinline__ void reconstruct8_t(const Geom& g, const kvq_cache& c, int64_t t, int d0, float val[8]) {
-  uint32_t code[8];
-  if constexpr (IS_V) value_codes8<B>((const uint8_t*)c.v_codes, t, d0, code);
-  else load_key_codes<B>((const uint8_t*)c.k_codes + t * (16 * B), d0 >> 3, code);
-  if constexpr (B == 16) {
-    const bool raw_bf16 = g.raw_dtype == KVQ_BF16;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) val[e] = widen16((uint16_t)code[e], raw_bf16);
-  } else {
-    const uint32_t* ms = (const uint32_t*)(IS_V ? c.v_meta : c.k_meta);
-    if (!IS_V && g.axis_k == KVQ_AXIS_SEQ) {       // channel-wise keys: one scale/zero per channel and group of seq_g tokens
-      const uint4* mp = reinterpret_cast<const uint4*>(ms + (t / g.seq_g) * kHeadDim + d0);
-      const uint4 m0 = mp[0], m1 = mp[1];
-      const uint32_t mm[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        val[e] = (float)code[e] * widen16((uint16_t)(mm[e] & 0xFFFF), false) + widen16((uint16_t)(mm[e] >> 16), false);
-      return;
-    }
-    const int G = IS_V ? g.g_v : g.g_k, ng = IS_V ? g.ng_v : g.ng_k;
-    const uint32_t m = ms[meta_index(t, d0 / G, ng)];
-    const float s = widen16((uint16_t)(m & 0xFFFF), false);
-    const float z = widen16((uint16_t)(m >> 16), false);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) val[e] = (float)code[e] * s + z;
-  }
-}
-
-// The same with the widths read from the geometry (the dequantize kernel: one token per thread, no loop to specialize).
-__device__ __forceinline__ void reconstruct8(const Geom& g, const kvq_cache& c, int which, int64_t t, int d0, float val[8]) {
-  if (which) {
-    switch (g.bits_v) {
-      case 1: return reconstruct8_t<1, true>(g, c, t, d0, val);
-      case 2: return reconstruct8_t<2, true>(g, c, t, d0, val);
-      case 3: return reconstruct8_t<3, true>(g, c, t, d0, val);
-      case 4: return reconstruct8_t<4, true>(g, c, t, d0, val);
-      case 6: return reconstruct8_t<6, true>(g, c, t, d0, val);
-      case 8: return reconstruct8_t<8, true>(g, c, t, d0, val);
-      default: return reconstruct8_t<16, true>(g, c, t, d0, val);
-    }
-  }
-  switch (g.bits_k) {
-    case 1: return reconstruct8_t<1, false>(g, c, t, d0, val);
-    case 2: return reconstruct8_t<2, false>(g, c, t, d0, val);
-    case 3: return reconstruct8_t<3, false>(g, c, t, d0, val);
-    case 4: return reconstruct8_t<4, false>(g, c, t, d0, val);
-    case 6: return reconstruct8_t<6, false>(g, c, t, d0, val);
-    case 8: return reconstruct8_t<8, false>(g, c, t, d0, val);
-    default: return reconstruct8_t<16, false>(g, c, t, d0, val);
-  }
-}
-
-// One thread = 8 consecutive channels of one token.
-__global__ __launch_bounds__(256) void dequantize_kernel(Geom g, kvq_cache c, int32_t t0, int32_t t1, void* k_out,
-                                                         void* v_out, int out_dtype) {
-  const int64_t nt = t1 - t0;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;   // (bh, token, octet)
-  const int64_t total = (int64_t)g.batch * g.kv_heads * nt * 16;
-  if (idx >= total) return;
-  const int oct = (int)(idx & 15);
-  const int64_t row = idx >> 4;
-  const int64_t bh = row / nt;
-  const int64_t t = virtual_token(g, c.page_table, (int)(bh / g.kv_heads), (int)(bh % g.kv_heads), t0 + row % nt);
-  const int d0 = oct * 8;
-
-  for (int which = 0; which < 2; ++which) {
-    void* out = which ? v_out : k_out;
-    if (!out) continue;
-    float val[8];
-    reconstruct8(g, c, which, t, d0, val);
-    if (which ? g.rotate_v : g.rotate_k)                                             // 16 threads = one row, all here
-      unrotate8(val, oct, rot_sign_bits(which ? g.signs_v : g.signs_k, oct));
-    const int64_t o = row * kHeadDim + d0;
-    if (out_dtype == KVQ_F32) {
-      float* p = (float*)out + o;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) p[e] = val[e];
-    } else {
-      uint16_t* p = (uint16_t*)out + o;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) p[e] = out_dtype == KVQ_F16 ? f32_to_f16_bits(val[e]) : f32_to_bf16_bits(val[e]);
-    }
-  }
-}
-
-// Squared reconstruction error (numerator of the MSE of App. B, "Frobenius Norm (MSE) Perspective").
-// One thread = 8 consecutive channels of one token; a workgroup walks 16-token slabs of one (b,h) stream with
-// stride gridDim.x; differences and the squares of a thread's 8 channels in binary32, everything above that summed
-// in binary64, one atomic add per wavefront and tensor.
-template <int BK, int BV>
-__global__ __launch_bounds__(256) void sq_error_kernel(Geom g, kvq_cache c, const uint16_t* __restrict__ k_ref,
-                                                       const uint16_t* __restrict__ v_ref, int ref_bf16, int64_t sb,
-                                                       int64_t sh, int64_t st, int32_t t0, int32_t t1,
-                                                       double* __restrict__ sums) {
-  const int tid = threadIdx.x;
-  const int64_t bh = blockIdx.y;
-  const int64_t b = bh / g.kv_heads, h = bh % g.kv_heads;
-  const int d0 = (tid & 15) * 8;
-  const int64_t nt = t1 - t0;
-  double acc[2] = {0.0, 0.0};
-  for (int64_t r = (int64_t)blockIdx.x * 16 + (tid >> 4); r < nt; r += (int64_t)gridDim.x * 16) {
-    const int64_t src = b * sb + h * sh + r * st + d0;
-    uint4 raw[2];
-    if (k_ref) raw[0] = *reinterpret_cast<const uint4*>(k_ref + src);
-    if (v_ref) raw[1] = *reinterpret_cast<const uint4*>(v_ref + src);
-#pragma unroll
-    for (int which = 0; which < 2; ++which) {
-      if (!(which ? v_ref : k_ref)) continue;
-      float val[8];
-      const int64_t tv = virtual_token(g, c.page_table, (int)b, (int)h, t0 + r);
-      if (which) reconstruct8_t<BV, true>(g, c, tv, d0, val);
-      else reconstruct8_t<BK, false>(g, c, tv, d0, val);
-      const uint32_t rw[4] = {raw[which].x, raw[which].y, raw[which].z, raw[which].w};
-      float x[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) x[e] = widen16((uint16_t)(rw[e >> 1] >> (16 * (e & 1))), ref_bf16 != 0);
-      // rotated rows are compared in the rotated basis: ||R x - y||_2 = ||x - R^T y||_2
-      if (which ? g.rotate_v : g.rotate_k) rotate8(x, tid & 15, rot_sign_bits(which ? g.signs_v : g.signs_k, tid & 15));
-      float sq = 0.f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float err = x[e] - val[e];
-        sq += err * err;
-      }
-      acc[which] += (double)sq;
-    }
-  }
-  // one atomic per workgroup and tensor: every head's two sums are hit by all the workgroups of that head, and atomics
-  // on one address are served one after the other
-  __shared__ double part[2][4];
-#pragma unroll
-  for (int which = 0; which < 2; ++which) {
-    double v = acc[which];
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-    if ((tid & 63) == 0) part[which][tid >> 6] = v;
-  }
-  __syncthreads();
-  if (tid < 2) {
-    const double v = (part[tid][0] + part[tid][1]) + (part[tid][2] + part[tid][3]);
-    if (v != 0.0) atomicAdd(sums + bh * 2 + tid, v);
-  }
-}
-
 // Checks the quantizer's fast divisions on the device it runs on: counters[0] counts the binary16 scales whose fast
 // reciprocal differs from IEEE division (all 31743 positive finite patterns), counters[1] the sampled quotients
 // (2^24 numerators per level count, spread over the binary32 exponent range) that differ.
@@ -616,11 +453,6 @@ __global__ __launch_bounds__(256) void selftest_quantizer_kernel(uint32_t* count
 
 __global__ __launch_bounds__(64) void zero_u32_kernel(uint32_t* p, int n) {
   if ((int)threadIdx.x < n) p[threadIdx.x] = 0u;
-}
-
-__global__ __launch_bounds__(256) void zero_f64_kernel(double* p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = 0.0;
 }
 
 }  // namespace
@@ -747,45 +579,9 @@ hipError_t launch_seq_append(const Geom& g, const kvq_cache& c, const void* k_ne
   return launch_sa_bits(g, c, k_new, v_new, in_dtype, sb, sh, st, pos, n_new, nullptr, 0, stream);
 }
 
-hipError_t launch_dequantize(const Geom& g, const kvq_cache& c, int32_t t0, int32_t t1, void* k_out, void* v_out,
-                             int out_dtype, hipStream_t stream) {
-  const int64_t total = (int64_t)g.batch * g.kv_heads * (t1 - t0) * 16;
-  if (total == 0) return hipSuccess;
-  const int64_t blocks = (total + 255) / 256;
-  if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;      // more than one launch can take: the caller splits [t0, t1)
-  hipLaunchKernelGGL(dequantize_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, g, c, t0, t1, k_out, v_out, out_dtype);
-  return hipGetLastError();
-}
-
 hipError_t launch_selftest_quantizer(uint32_t* counters, hipStream_t stream) {
   hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(64), 0, stream, counters, 2);
   hipLaunchKernelGGL(selftest_quantizer_kernel, dim3(256), dim3(256), 0, stream, counters);
-  return hipGetLastError();
-}
-
-hipError_t launch_reconstruction_error(const Geom& g, const kvq_cache& c, const void* k_ref, const void* v_ref,
-                                       int ref_dtype, int64_t sb, int64_t sh, int64_t st, int32_t t0, int32_t t1,
-                                       double* sums, hipStream_t stream) {
-  const int streams = g.batch * g.kv_heads;
-  const int64_t n = (int64_t)streams * 2;
-  // cleared by a kernel, not a memset, so that the call can be captured into a graph
-  hipLaunchKernelGGL(zero_f64_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, sums, n);
-  if (t1 == t0) return hipGetLastError();
-  const int64_t slabs = ((int64_t)(t1 - t0) + 15) / 16;
-  // about 32 workgroups per compute unit in all (measured: fewer leave latency exposed, more pile up on the atomics)
-  int64_t per_stream = (8192 + streams - 1) / streams;
-  if (per_stream > slabs) per_stream = slabs;
-  const dim3 grid((unsigned)per_stream, streams);
-  const int bf = ref_dtype == KVQ_BF16 ? 1 : 0;
-#define KVQ_ERR_CASE(BK_, BV_)                                                                                          \
-  if (g.bits_k == BK_ && g.bits_v == BV_)                                                                               \
-    hipLaunchKernelGGL((sq_error_kernel<BK_, BV_>), grid, dim3(256), 0, stream, g, c, (const uint16_t*)k_ref,           \
-                       (const uint16_t*)v_ref, bf, sb, sh, st, t0, t1, sums);
-#define KVQ_ERR_ROW(BK_) KVQ_ERR_CASE(BK_, 1) KVQ_ERR_CASE(BK_, 2) KVQ_ERR_CASE(BK_, 3) KVQ_ERR_CASE(BK_, 4) \
-  KVQ_ERR_CASE(BK_, 6) KVQ_ERR_CASE(BK_, 8) KVQ_ERR_CASE(BK_, 16)
-  KVQ_ERR_ROW(1) KVQ_ERR_ROW(2) KVQ_ERR_ROW(3) KVQ_ERR_ROW(4) KVQ_ERR_ROW(6) KVQ_ERR_ROW(8) KVQ_ERR_ROW(16)
-#undef KVQ_ERR_ROW
-#undef KVQ_ERR_CASE
   return hipGetLastError();
 }
 

@@ -92,31 +92,6 @@ __device__ __forceinline__ void store_key_codes(uint8_t* rowp, int lane16, const
   }
 }
 
-// The 8 codes of channels 8*oct .. 8*oct+7 of a key row.
-template <int B> __device__ __forceinline__ void load_key_codes(const uint8_t* rowp, int oct, uint32_t code[8]) {
-  constexpr int LO = code_lo_bits<B>(), HI = code_hi_bits<B>();
-  if constexpr (B == 16) {
-    const uint4 w = *reinterpret_cast<const uint4*>(rowp + oct * 16);
-    const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-    for (int e = 0; e < 8; ++e) code[e] = (ww[e >> 1] >> (16 * (e & 1))) & 0xFFFFu;
-  } else if constexpr (B == 8) {
-    const uint2 w = *reinterpret_cast<const uint2*>(rowp + oct * 8);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) code[e] = ((e < 4 ? w.x : w.y) >> (8 * (e & 3))) & 0xFFu;
-  } else if constexpr (HI == 0) {
-    const uint32_t w = load_bytes<B>(rowp + oct * B);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) code[e] = (w >> (B * e)) & ((1u << B) - 1u);
-  } else {
-    const uint8_t* chunk = rowp + (oct >> 2) * (4 * B);
-    const uint32_t lo = load_bytes<LO>(chunk + (oct & 3) * LO), hi = load_bytes<HI>(chunk + 4 * LO + (oct & 3) * HI);
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-      code[e] = ((lo >> (LO * e)) & ((1u << LO) - 1u)) | (((hi >> (HI * e)) & ((1u << HI) - 1u)) << LO);
-  }
-}
-
 // ---- randomized Hadamard rotation of a 128-channel row (Sec. 4 "Integration with Rotation-Based Methods") ----
 // The row is held 8 consecutive channels per lane by 16 neighbouring lanes (lane16 = channel / 8).  R = H diag(s) /
 // sqrt(128): signs, then the butterflies over strides 1, 2, 4 (inside the lane) and 8, 16, 32, 64 (partner lane

@@ -2043,3 +2043,39 @@ def test_random_residual_buffer_layouts(kvq, oracle, case):
         ref = oracle.seq_decode_attention(Lo, planes, qn, pos + 1, scale, bf16=bf16)
         assert _rel_err(outs.cpu().numpy(), ref) < TOL, (tag, pos)
 
+
+
+@pytest.mark.parametrize("kw,dtype", [(dict(), torch.bfloat16), (dict(bits_k=3, bits_v=6, group_k=32, group_v=128), torch.float16),
+                                      (dict(bits_k=8, bits_v=8, rotate_k=1, rotate_v=1, signs_k=(5, 6, 7, 8), signs_v=(1, 2, 3, 4)), torch.float32),
+                                      (dict(bits_k=16, bits_v=16), torch.float16), (dict(axis_k=1, rotate_k=1, signs_k=(9, 0, 1, 2)), torch.bfloat16),
+                                      (dict(page_tokens=64, n_pages=16 * 99), torch.float32)])
+def test_reading_back_in_one_call_and_in_ranges_is_the_same(kvq, kw, dtype):
+    """A call of 24576 blocks of 32 tokens and more walks several blocks per workgroup; ranges of it with ends inside a
+    block, calls for one tensor alone and output pointers aligned to their elements only go the other way (which the
+    tests above hold to the oracle), and must give the same bits.  The squared errors of the ranges add up to those of
+    the whole (sums of binary64 terms: 1e-12)."""
+    B, H, T, D = 16, 8, 99 * 64 - (0 if kw.get("axis_k") else 7), 128
+    L = kvq.Layout(B, H, T, raw_dtype=kvq.KVQ_BF16, **kw)
+    cache = kvq.Cache(L, fill=0)
+    if L.page_tokens:
+        cache.page_table = torch.randperm(L.n_pages, device="cuda").to(torch.int32).view(B, -1).contiguous()
+    K, V, _ = synth.make_kvq(5, B, H, H, T, D, dtype=torch.bfloat16, device="cuda")
+    kvq.quantize_append(L, cache, K, V, 0)
+    assert 2 * B * H * (T // 32) > 24576
+    k, v = (torch.empty(B, H, T, D, dtype=dtype, device="cuda") for _ in range(2))
+    kvq.dequantize(L, cache, 0, T, k, v)
+    n_el = B * H * 320 * D
+    for t0, t1 in ((0, 1), (31, 33), (T - 70, T), (4099, 4100), (777, 1097)):
+        n = t1 - t0
+        k2, v2 = (torch.empty(n_el + 1, dtype=dtype, device="cuda")[1:1 + B * H * n * D].view(B, H, n, D) for _ in range(2))
+        kvq.dequantize(L, cache, t0, t1, k2, None)
+        kvq.dequantize(L, cache, t0, t1, None, v2)
+        assert torch.equal(k2, k[:, :, t0:t1]) and torch.equal(v2, v[:, :, t0:t1]), (t0, t1)
+    whole = kvq.reconstruction_error(L, cache, K, V, 0, torch.empty(B, H, 2, dtype=torch.float64, device="cuda"))
+    parts = torch.zeros_like(whole)
+    for t0, t1 in ((0, 31), (31, 4000), (4000, 4001), (4001, T)):
+        one = torch.empty_like(whole)
+        parts += kvq.reconstruction_error(L, cache, K[:, :, t0:t1], V[:, :, t0:t1], t0, one)
+        alone = kvq.reconstruction_error(L, cache, None, V[:, :, t0:t1], t0, torch.empty_like(whole))
+        assert float((alone[..., 1] - one[..., 1]).abs().max()) <= 1e-12 * float(one[..., 1].abs().max()) and not alone[..., 0].any()
+    assert float((whole - parts).abs().max()) <= 1e-12 * float(whole.abs().max()) + 1e-300
