@@ -67,6 +67,12 @@ __device__ __forceinline__ float sum_over_groups(float x) {
 }
 
 // ---- key codes: one lane holds 32 consecutive channels of one token (BK dwords) -------------
+// (Channels 32j .. 32j+31 in the lanes of row quarter j.  A row of 16-bit patterns is 256 bytes, of which a lane would hold
+// 4 neighbouring 16-byte pieces: every load instruction would touch every line of the tile and use a quarter of each.
+// There a lane's pieces lie 64 bytes apart instead, so that the 4 lanes of a row read 64 bytes in one piece
+// (k_lane_chan; any assignment of channels to slots is as good as another for the matrix product, as long as the query
+// operand follows it): the unquantized 8B layer at B=8, T=32768 takes 159 us = 6.74 TB/s where it took 201.  The same
+// for the two pieces of 8-bit rows changes nothing (86.4 against 86.1 us for K8V8 there): lines are halves, not quarters.)
 // Matrix step m (0..3) consumes 8 of them; slot i of that step is channel k_slot_elem(m,i) of the
 // lane's 32, left at bit k of its 16-bit lane, i.e. read as code * 2^k * 2^-24, so the query operand of the slot is
 // divided by k_slot_scale(i) = 2^k.
@@ -90,6 +96,12 @@ template <int BK> __device__ __forceinline__ constexpr int k_slot_elem(int m, in
   if (BK == 8) return 8 * m + 4 * (v >> 1) + (v & 1) + 2 * x;
   return 16 * (m >> 1) + 4 * (m & 1) + v + 8 * x;  // BK == 2
 }
+template <int BK> constexpr int k_piece_stride() { return BK == 16 ? 64 : 16; }
+// Row channel of element x (0..31) of the lanes of row quarter j, and bytes from the row's start to their first piece.
+template <int BK> __device__ __forceinline__ constexpr int k_lane_chan(int j, int x) {
+  return BK == 16 ? 32 * (x >> 3) + 8 * j + (x & 7) : 32 * j + x;
+}
+template <int BK> __device__ __forceinline__ constexpr int k_lane_offset(int j) { return j * (BK == 16 ? 16 : 4 * BK); }
 template <int BK> constexpr int k_default_base() { return BK == 2 ? 4 : BK == 1 ? 3 : 0; }
 template <int BK, int BASE = k_default_base<BK>()> __device__ __forceinline__ constexpr float k_slot_scale(int i) {
   const int v = i >> 1;
@@ -248,7 +260,8 @@ __device__ __forceinline__ u32x4 ld16(const uint8_t* p) {
 // address is formed in 64 bits; otherwise it counts inside the (b,h) stream that the bases point to.
 // N consecutive dwords of a key tile (4 N bytes per lane: the lane's 32 channels), non-temporal; the address is a
 // multiple of 4 N bytes only when N is a power of two (3- and 6-bit rows), so the vector types carry that alignment.
-template <int N> __device__ __forceinline__ void load_dwords(uint32_t* dst, const uint8_t* p) {
+// STRIDE: bytes between a lane's 16-byte pieces (pieces of 16 bytes and more)
+template <int N, int STRIDE = 16> __device__ __forceinline__ void load_dwords(uint32_t* dst, const uint8_t* p) {
   typedef uint32_t v2 __attribute__((ext_vector_type(2), aligned(8)));
   typedef uint32_t v3 __attribute__((ext_vector_type(3), aligned(4)));
   typedef uint32_t v4a8 __attribute__((ext_vector_type(4), aligned(8)));
@@ -268,7 +281,7 @@ template <int N> __device__ __forceinline__ void load_dwords(uint32_t* dst, cons
     static_assert(N % 4 == 0, "key tile piece");
 #pragma unroll
     for (int k = 0; k < N / 4; ++k) {
-      const u32x4 v = ld16(p + 16 * k);
+      const u32x4 v = ld16(p + STRIDE * k);
       dst[4 * k + 0] = v.x; dst[4 * k + 1] = v.y; dst[4 * k + 2] = v.z; dst[4 * k + 3] = v.w;
     }
   }
@@ -286,7 +299,7 @@ __device__ __forceinline__ void load_step(StepRegs<BK, BV>& r, const LaneCtx& L,
   const uint8_t* mbase = WIDE ? L.meta_base + (step & (int64_t)(int32_t)L.meta_step_mask) * L.meta_mul : L.meta_base;
   const uint32_t ko = (WIDE ? 0u : (uint32_t)step * (512 * BK)) + (L.kc_off & lane_mask);
 #pragma unroll
-  for (int x4 = 0; x4 < 2; ++x4) load_dwords<BK>(r.kc[x4], kbase + (ko + x4 * (256 * BK)));
+  for (int x4 = 0; x4 < 2; ++x4) load_dwords<BK, k_piece_stride<BK>()>(r.kc[x4], kbase + (ko + x4 * (256 * BK)));
   // (every lane loads, for the same reason: lanes beyond the scale/zero bytes repeat the last 16 of them)
   if constexpr (BK != 16 || BV != 16)
     r.meta = ld16(mbase + ((WIDE ? 0u : ((uint32_t)step & L.meta_step_mask) * L.meta_mul) + (L.meta_off & lane_mask)));
@@ -844,7 +857,7 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   const int64_t bh_base = PAGED ? 0 : bh;           // paged: rows are numbered from the plane base (virtual_token)
   L.kc = (const uint8_t*)cache.k_codes + bh_base * g.kc_stream;
   L.vc = (const uint8_t*)cache.v_codes + bh_base * g.vc_stream;
-  L.kc_off = L.c * (16 * BK) + L.j * (4 * BK);
+  L.kc_off = L.c * (16 * BK) + k_lane_offset<BK>(L.j);
   L.vc_off = lane * (BV == 1 ? 8 : 16);
   {
     // channel-wise keys: 512 bytes of scale/zero per group of seq_g = 32, 64 or 128 tokens (32 lanes), fetched with
@@ -1043,8 +1056,7 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
       }
     }
   }
-  // column c of set cs carries head h restricted to key group grp + cs*kSetGroups (zero elsewhere); this lane's 32
-  // channels are 32j..32j+31 and lie in one group
+  // column c of set cs carries head h restricted to key group grp + cs*kSetGroups (zero elsewhere)
   constexpr int KLO = k_lo<BK>(), KHI = k_hi<BK>();
   u32x4 qb[NCK][4];
   u32x4 qbh[NCK][4];                             // operand of the high run of 3- and 6-bit key codes (else unused)
@@ -1053,7 +1065,7 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
     uint16_t mych[32];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const u32x4 v = reinterpret_cast<const u32x4*>(&sm_q[h][32 * L.j])[k];
+      const u32x4 v = *reinterpret_cast<const u32x4*>(&sm_q[h][k_lane_chan<BK>(L.j, 8 * k)]);
       const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
       for (int e = 0; e < 8; ++e) mych[8 * k + e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
@@ -1062,7 +1074,7 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
     for (int cs = 0; cs < NCK; ++cs) {
       const int gcs = grp + cs * kSetGroups;
       const bool act = gcs < g.ng_k;
-      const bool mine = act && ((32 * L.j) / g.g_k == gcs);
+      const bool mine = act && (RAW || (32 * L.j) / g.g_k == gcs);        // (unquantized: one group)
 #pragma unroll
       for (int m = 0; m < 4; ++m) {
         uint32_t w[4] = {0u, 0u, 0u, 0u}, wh[4] = {0u, 0u, 0u, 0u};
