@@ -110,6 +110,30 @@ template <int BK, int BASE = k_default_base<BK>()> __device__ __forceinline__ co
   if (BK == 1) return (float)(1 << (BASE + v));
   return (float)(1 << (BASE + 2 * (v & 1)));       // BK == 2
 }
+// One run of a key row's codes: B-bit fields left at BASE, whose query operand carries FACTOR.
+template <int B, int BASE, int FACTOR> struct KRun { static constexpr int bits = B, base = BASE; static constexpr float factor = (float)FACTOR; };
+// The query operand is staged by lanes that hold 8 neighbouring channels 8 o .. 8 o + 7 of a row, in operand order
+// [row quarter j = o / 4][matrix step m][slot i].  For 4- and 8-bit fields these are the 8 slots of step o % 4; for 1- and
+// 2-bit fields every other slot of two steps: channel e goes 16 (e / 4) + 4 (e % 4) bytes behind k_octet_offset.
+template <int B> __device__ __forceinline__ constexpr int k_octet_offset(int o) {
+  return (o >> 2) * 64 + (B == 2 ? ((o >> 1) & 1) * 32 + (o & 1) * 2 : (o & 1) * 32 + ((o >> 1) & 1) * 2);
+}
+template <int B, int BASE> __device__ __forceinline__ constexpr float k_octet_scale(int e) {
+  return B == 8 || B == 16 ? 1.0f : k_slot_scale<B, BASE>(2 * (e & 3));
+}
+template <int B, int BASE> constexpr bool k_octet_matches() {
+  for (int o = 0; o < 4; ++o)
+    for (int e = 0; e < 8; ++e) {
+      const int at = B == 4 ? o * 16 + 4 * (e & 3) + 2 * (e >> 2)
+                   : B == 8 ? o * 16 + 8 * (e >> 2) + 4 * (e & 1) + 2 * ((e >> 1) & 1)
+                            : k_octet_offset<B>(o) + 16 * (e >> 2) + 4 * (e & 3);
+      const int m = at / 16, i = (at % 16) / 2;
+      if (k_slot_elem<B>(m, i) != 8 * o + e || k_slot_scale<B, BASE>(i) != k_octet_scale<B, BASE>(e)) return false;
+    }
+  return true;
+}
+static_assert(k_octet_matches<1, k_default_base<1>()>() && k_octet_matches<2, k_default_base<2>()>() && k_octet_matches<4, 0>() &&
+              k_octet_matches<8, 0>() && k_octet_matches<1, 5>() && k_octet_matches<2, 6>(), "staged query operands");
 // The same factor as a function of the channel (the slot a channel lands in fixes it), default BASE.
 template <int BK> __device__ __forceinline__ constexpr float k_chan_scale(int d) {
   return BK == 4 ? ((d & 1) ? 16.0f : 1.0f) : BK == 2 ? ((d & 1) ? 64.0f : 16.0f) : 1.0f;
@@ -230,8 +254,8 @@ constexpr int ring_stages() {
 // Everything one lane loads for one 32-token step (two 16-token tiles).
 template <int BK, int BV>
 struct StepRegs {
-  uint32_t kc[2][BK];            // tile x4: row 16*x4 + c, this lane's 32 channels
-  uint32_t vc[2 * BV];           // value codes: piece k, dword m at [4k + m]
+  __attribute__((aligned(16))) uint32_t kc[2][BK];            // tile x4: row 16*x4 + c, this lane's 32 channels
+  __attribute__((aligned(16))) uint32_t vc[2 * BV];           // value codes: piece k, dword m at [4k + m]
   u32x4 meta;                    // 16 bytes of the step's scale/zero bytes, in plane order (lane l < 8 (ng_k + ng_v) holds
                                  // bytes 16 l ..); redistributed through LDS when the step is computed
 };
@@ -250,6 +274,16 @@ struct LaneCtx {
 };
 // Kernels for caches whose values are stored rotated (the output goes through R_v^T) mark their context so.
 struct LaneCtxRotV : LaneCtx { static constexpr bool kRotV = true; };
+
+// Addresses formed by integer arithmetic name global memory explicitly: a pointer of unknown address space becomes a flat
+// access, which may return out of order with everything else, so that the compiler drains ALL loads in flight at the
+// next wait (the ring's first fill among them).
+template <typename T> __device__ __forceinline__ T load_global(uintptr_t p) {
+  return *reinterpret_cast<const __attribute__((address_space(1))) T*>(p);
+}
+template <typename T> __device__ __forceinline__ void store_global(uintptr_t p, T v) {
+  *reinterpret_cast<__attribute__((address_space(1))) T*>(p) = v;
+}
 
 // Cache bytes are read exactly once per decode step: streaming (non-temporal) loads.
 __device__ __forceinline__ u32x4 ld16(const uint8_t* p) {
@@ -282,7 +316,7 @@ template <int N, int STRIDE = 16> __device__ __forceinline__ void load_dwords(ui
 #pragma unroll
     for (int k = 0; k < N / 4; ++k) {
       const u32x4 v = ld16(p + STRIDE * k);
-      dst[4 * k + 0] = v.x; dst[4 * k + 1] = v.y; dst[4 * k + 2] = v.z; dst[4 * k + 3] = v.w;
+      *reinterpret_cast<u32x4*>(dst + 4 * k) = v;
     }
   }
 }
@@ -310,7 +344,7 @@ __device__ __forceinline__ void load_step(StepRegs<BK, BV>& r, const LaneCtx& L,
 #pragma unroll
   for (int k = 0; k < VLO / 2; ++k) {
     const u32x4 v = ld16(vbase + (vo + k * 1024));
-    r.vc[4 * k + 0] = v.x; r.vc[4 * k + 1] = v.y; r.vc[4 * k + 2] = v.z; r.vc[4 * k + 3] = v.w;
+    *reinterpret_cast<u32x4*>(r.vc + 4 * k) = v;
   }
   // the block of high parts follows the block of low parts: 8 bytes per lane (single bits) or 16 (pairs)
   if constexpr (VHI == 1) load_dwords<2>(r.vc + 2 * VLO, vbase + (vstep + 512 * VLO + ((L.vc_off >> 1) & lane_mask)));
@@ -722,8 +756,9 @@ __device__ __forceinline__ void append_one(const DecodeArgs& a, int bh, int sbh,
   // (picked by integer arithmetic: a per-lane choice among pointers of the argument block becomes a lookup in private memory)
   const uintptr_t km = reinterpret_cast<uintptr_t>(a.cache.k_meta) + (uintptr_t)((int64_t)bh * g.km_stream);
   const uintptr_t vm = reinterpret_cast<uintptr_t>(a.cache.v_meta) + (uintptr_t)((int64_t)bh * g.vm_stream);
-  uint32_t* meta = reinterpret_cast<uint32_t*>(km + (is_v ? vm - km : (uintptr_t)0));
-  if ((lane16 & (lpg - 1)) == 0) meta[meta_index(t, lane16 >> lpg_shift(lpg), ng)] = (uint32_t)S | ((uint32_t)Z << 16);
+  const uintptr_t meta = km + (is_v ? vm - km : (uintptr_t)0);
+  if ((lane16 & (lpg - 1)) == 0)
+    store_global<uint32_t>(meta + 4 * (uintptr_t)meta_index(t, lane16 >> lpg_shift(lpg), ng), (uint32_t)S | ((uint32_t)Z << 16));
   if (!is_v) {
     store_key_codes<BK>((uint8_t*)a.cache.k_codes + (int64_t)bh * g.kc_stream + t * (16 * BK), lane16, codes);
   } else {
@@ -816,16 +851,15 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   // scale, the value side's into the final accumulator
   constexpr float kUnit = RAWK ? 1.0f : kCodeUnit, kInvUnit = RAWK ? 1.0f : kInvCodeUnit;
   constexpr float kInvUnitV = RAWV ? 1.0f : kInvCodeUnit;
-  __shared__ float sm_o[NW][R][kHeadDim];
+  // a wavefront's output rows at the end; until then the wavefront's own copy of the query (see "query" below)
+  __shared__ __attribute__((aligned(16))) float sm_o[NW][R][kHeadDim];
   __shared__ float sm_m[NW][R], sm_l[NW][R];
-  __shared__ __attribute__((aligned(16))) uint16_t sm_q[R][kHeadDim];
-  // channel-wise keys: the query in binary32, channel d divided by k_chan_scale(d); row R is all zero
-  __shared__ __attribute__((aligned(16))) float sm_qf[KSEQ ? R + 1 : 1][kHeadDim];
   __shared__ __attribute__((aligned(16))) uint8_t sm_meta[NW][1024];
+  __shared__ __attribute__((aligned(16))) float sm_zero[KSEQ ? kHeadDim : 16];   // query of a column that carries nothing
   __shared__ uint8_t sm_vnew[kHeadDim];          // fused step: the new token's value codes,
   __shared__ float sm_hat[2][kHeadDim];           // its reconstructed key and value rows,
   __shared__ float sm_mnew[R];                    // and its logit per head in log2 units
-  __shared__ float sm_qsum[R][4];
+  __shared__ float sm_qsum[NW][R][4];
   const Geom& g = a.g;
   const kvq_cache& cache = a.cache;
   const uint16_t* __restrict__ q = a.q;
@@ -837,8 +871,8 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int split = blockIdx.x, bh = blockIdx.y;
-  const int b = bh / g.kv_heads, hk = bh % g.kv_heads;
+  const int split = blockIdx.x, hk = blockIdx.y, b = blockIdx.z;
+  const int bh = b * g.kv_heads + hk;
   // this sequence's length: its own when the caller gave per-sequence lengths, inside what the launch was planned for
   int seq_len = a.seq_len;
   if (a.seq_lens) {
@@ -894,73 +928,77 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   const int n_full = own_tail ? n_my - 1 : n_my;   // complete steps of this wavefront
   // A step that is always there to load from: wavefronts with nothing to do still issue the ring's loads (see refill).
   const int safe_step = min(step_begin, max(n_steps - 1, 0));
-  // paged: logical step -> step number in plane order (page of the pool, this head's share of it, step inside it)
-  // (this workgroup's slice of its table row is copied to LDS first: a page number is needed before every step's
-  // loads can be issued, and a global load in front of them costs the ring most of its depth)
-  constexpr int kPageSlots = PAGED ? 2048 : 1;
-  __shared__ int32_t sm_pages[kPageSlots];
+  // paged: logical step -> step number in plane order (page of the pool, this head's share of it, step inside it).  The
+  // page numbers of a wavefront's own steps are copied to LDS by the wavefront first: one is needed before every step's
+  // loads can be issued, and a global load in front of them costs the ring most of its depth.
+  constexpr int kPageSlots = PAGED ? 512 : 1;    // (steps of one wavefront; a longer walk reads the table itself)
+  __shared__ int32_t sm_pages[PAGED ? NW : 1][kPageSlots];
   const int32_t* __restrict__ my_pages = PAGED ? cache.page_table + (int64_t)b * g.pages_per_seq : nullptr;
   const int step_shift = g.page_shift - 5;
-  const int page0 = safe_step >> step_shift;
-  const int last_needed = max(max(step_end - 1, safe_step), do_append ? (seq_len - 1) >> 5 : 0);
-  const int n_pages_mine = (last_needed >> step_shift) - page0 + 1;
-  const bool pages_in_lds = n_pages_mine <= kPageSlots;
   if constexpr (PAGED) {
-    if (pages_in_lds) {
-      for (int i = tid; i < n_pages_mine; i += 64 * NW) sm_pages[i] = my_pages[page0 + i];
-      __syncthreads();
-    }
+    for (int i = lane; i < min(n_my, kPageSlots); i += 64) sm_pages[wave][i] = my_pages[step_of(i) >> step_shift];
+    if (n_my == 0 && lane == 0) sm_pages[wave][0] = my_pages[safe_step >> step_shift];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
-  auto page_of_step = [&](int step) -> int64_t {
-    return pages_in_lds ? sm_pages[(step >> step_shift) - page0] : my_pages[step >> step_shift];
-  };
-  auto fetch = [&](StepRegs<BK, BV>& dst, int step, uint32_t lane_mask = ~0u) {
+  // (i: the step's place in the wavefront's walk)
+  auto fetch = [&](StepRegs<BK, BV>& dst, int i, int step, uint32_t lane_mask) {
     if constexpr (PAGED) {
-      load_step<BK, BV, true>(dst, L, ((page_of_step(step) * g.kv_heads + hk) << step_shift) + (step & ((1 << step_shift) - 1)), lane_mask);
+      const int64_t page = i < kPageSlots ? sm_pages[wave][i] : my_pages[step >> step_shift];
+      load_step<BK, BV, true>(dst, L, ((page * g.kv_heads + hk) << step_shift) + (step & ((1 << step_shift) - 1)), lane_mask);
     } else {
       load_step<BK, BV>(dst, L, step, lane_mask);
     }
   };
 
   // ---- the small loads of the prologue go first, none of them behind a branch, so that they return ahead of the
-  // ring's first fill and the compiler can count what is in flight behind each: the query rows (every thread loads;
-  // threads beyond the rows re-read the first 16 bytes), and in a fused step the new token's rows and the words of the
-  // value block that take its codes (threads that have none of these re-read the query).
+  // ring's first fill and the compiler can count what is in flight behind each: the query rows (every wavefront loads
+  // them all; lanes beyond the rows re-read the first 16 bytes), and in a fused step the new token's rows and the words
+  // of the value block that take its codes (lanes that have none of these re-read the query).
   int stream_scale_exp = 0;                        // largest exponent field of the stream's value scales (weight_headroom)
   if constexpr (!RAWV) stream_scale_exp = cache.v_scale_exp[bh];
   const int r_act = a.heads_per_kv;                // heads that exist (R is the next power of two)
-  const bool q_lane = tid < R * 16 && (tid >> 4) < r_act;
-  const uint16_t* qsrc = q + ((int64_t)b * q_heads + hk * r_act) * kHeadDim + (q_lane ? tid * 8 : 0);
-  u32x4 qraw = *reinterpret_cast<const u32x4*>(qsrc);
+  constexpr int kQItems = R > 4 ? 2 : 1;           // 16-byte pieces of the query rows per lane: item lane + 64 t
+  const uint16_t* qbase = q + ((int64_t)b * q_heads + hk * r_act) * kHeadDim;
+  u32x4 qraw[kQItems];
+#pragma unroll
+  for (int t = 0; t < kQItems; ++t) {
+    const int item = lane + 64 * t;
+    qraw[t] = *reinterpret_cast<const u32x4*>(qbase + (item < R * 16 && (item >> 4) < r_act ? item * 8 : 0));
+  }
+  // the fused append is one wavefront's work, the last one's: where the steps do not divide evenly it has one less
   constexpr int VLO_ = v_lo<BV>(), VHI_ = v_hi<BV>();
+  const bool app_wave = do_append && wave == NW - 1;
   u32x4 nraw = u32x4{0u, 0u, 0u, 0u};
-  uint32_t vw_lo = 0u, vw_hi = 0u;
-  uint32_t* vw_lo_p = nullptr; uint32_t* vw_hi_p = nullptr;
+  uint32_t vw_lo[2] = {0u, 0u}, vw_hi[2] = {0u, 0u};
+  uintptr_t vblk = 0;                              // the new token's 32-token block of value codes
   int64_t t_new = 0;
-  int u_new = 0;                                   // the new token's place in its 32-token block
+  int u_new = 0;                                   // its place in that block
   if constexpr (kCanAppend) {
     // (paged: the new token's row number in plane order, with the stream index 0)
     if constexpr (PAGED) {
-      const int64_t pg = do_append ? page_of_step((seq_len - 1) >> 5) : 0;
+      const int64_t pg = my_pages[app_wave ? (seq_len - 1) >> g.page_shift : safe_step >> step_shift];
       t_new = ((pg * g.kv_heads + hk) << g.page_shift) + ((seq_len - 1) & ((1 << g.page_shift) - 1));
     } else {
       t_new = seq_len - 1;
     }
     // (the address is picked by integer arithmetic: a per-lane choice among pointers held in the argument block would
     // be turned into a lookup in private memory)
-    const bool new_lane = do_append && tid < 32;
-    const int64_t row_off = ((int64_t)b * a.nsb + (int64_t)hk * a.nsh + (tid & 15) * 8) * 2;
-    const uintptr_t qp = reinterpret_cast<uintptr_t>(qsrc), kp = reinterpret_cast<uintptr_t>(a.k_new),
+    const bool new_lane = app_wave && lane < 32;
+    const int64_t row_off = ((int64_t)b * a.nsb + (int64_t)hk * a.nsh + (lane & 15) * 8) * 2;
+    const uintptr_t qp = reinterpret_cast<uintptr_t>(qbase), kp = reinterpret_cast<uintptr_t>(a.k_new),
                     vp = reinterpret_cast<uintptr_t>(a.v_new);
-    const uintptr_t nsrc = qp + (new_lane ? (kp - qp) + (tid >= 16 ? vp - kp : (uintptr_t)0) + (uintptr_t)row_off : (uintptr_t)0);
-    nraw = *reinterpret_cast<const u32x4*>(nsrc);
-    uint32_t* vblk = (uint32_t*)((uint8_t*)cache.v_codes + bh_base * g.vc_stream) + (t_new >> 5) * (int64_t)(128 * BV);
+    const uintptr_t nsrc = qp + (new_lane ? (kp - qp) + (lane >= 16 ? vp - kp : (uintptr_t)0) + (uintptr_t)row_off : (uintptr_t)0);
+    nraw = load_global<u32x4>(nsrc);
+    vblk = reinterpret_cast<uintptr_t>(cache.v_codes) + (uintptr_t)(bh_base * g.vc_stream + (t_new >> 5) * (int64_t)(512 * BV));
     u_new = (int)(t_new & 31);
-    vw_lo_p = do_append && field_owner<VLO_>(tid) ? vblk + field_word<VLO_>(tid, u_new) : nullptr;
-    vw_lo = *(vw_lo_p ? vw_lo_p : reinterpret_cast<const uint32_t*>(qsrc));
-    if constexpr (VHI_ != 0) {
-      vw_hi_p = do_append && field_owner<VHI_>(tid) ? vblk + 128 * VLO_ + field_word<VHI_>(tid, u_new) : nullptr;
-      vw_hi = *(vw_hi_p ? vw_hi_p : reinterpret_cast<const uint32_t*>(qsrc));
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {                  // channels lane and lane + 64
+      const bool own_lo = app_wave && field_owner<VLO_>(lane + 64 * t);
+      vw_lo[t] = load_global<uint32_t>(qp + (own_lo ? vblk - qp + 4 * (uintptr_t)field_word<VLO_>(lane + 64 * t, u_new) : (uintptr_t)0));
+      if constexpr (VHI_ != 0) {
+        const bool own_hi = app_wave && field_owner<VHI_>(lane + 64 * t);
+        vw_hi[t] = load_global<uint32_t>(qp + (own_hi ? vblk - qp + 4 * (uintptr_t)(128 * VLO_ + field_word<VHI_>(lane + 64 * t, u_new)) : (uintptr_t)0));
+      }
     }
   }
 
@@ -970,133 +1008,151 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   // each (see load_step), so that no load of the ring is conditional.
   StepRegs<BK, BV> buf[kStages];
   auto refill = [&](int k, int i) {
-    fetch(buf[k], n_my > 0 ? step_of(min(i, n_my - 1)) : safe_step, i < n_my ? ~0u : 0u);
+    const int ic = max(min(i, n_my - 1), 0);
+    fetch(buf[k], ic, n_my > 0 ? step_of(ic) : safe_step, i < n_my ? ~0u : 0u);
   };
   // Only the first half of the ring goes out in front of the query staging: the memory pipeline of a compute unit
-  // takes in about what two steps of eight wavefronts ask for, a wavefront that issues more waits at the load until
-  // earlier data has come back, and the barrier of the staging below would wait for the slowest of them.  The second
-  // half follows the barrier, by when the first is on its way out of memory.
+  // takes in about what two steps of eight wavefronts ask for, and a wavefront that issues more waits at the load until
+  // earlier data has come back.  The second half follows the staging, by when the first is on its way out of memory.
   constexpr int kEarly = (kStages + 1) / 2;
 #pragma unroll
   for (int k = 0; k < kEarly; ++k) refill(k, k);
 
-  // ---- fused step: quantize the new token (two 16-lane rows of the first wavefront), store keys and scale/zero, stage
-  // the value codes for the threads that own the block's words
-  if constexpr (kCanAppend) {
-    if (do_append && tid < 32) append_one<BK, BV>(a, PAGED ? 0 : bh, bh, tid, nraw, sm_vnew, t_new, &sm_hat[0][0]);
-  }
-
-  // ---- query rows of this kv head -> LDS, then per-lane operands
+  // ---- query: every wavefront stages the rows for itself, in its own part of sm_o, already in the form its lanes want
+  // them in -- the matrix operands of the key side (binary16, divided by the slots' position factors, in operand order;
+  // the unquantized kernel: the patterns themselves), or for channel-wise keys binary32 rows -- so that no barrier
+  // stands between a wavefront's first loads and its first step, and a lane converts its own 8 channels and no more.
+  // What bounds a short launch is this chain of latencies.  Fused steps with the rows staged once per workgroup (a
+  // barrier that waited for the first half of the ring, then every lane built its operands from 32 channels; the append
+  // spread over two wavefronts) and like this: 1024 tokens of 8 heads 10.4 and 9.2 us, the 8B layer at B=8 and 8192
+  // tokens 19.9 and 18.3, 8 x 64 heads x 2048 tokens 14.5 and 12.6; the 70B layer, where the chain is 2 % of the step, 150.8
+  // and 150.6.
+  constexpr int KLO = k_lo<BK>(), KHI = k_hi<BK>();
+  constexpr int kOpRow = KHI != 0 ? 512 : 256;     // bytes of one head's staged operands: [j][m][slot], the high run's behind
+  uint8_t* const q_lds = reinterpret_cast<uint8_t*>(&sm_o[wave][0][0]);
   bool q_is_bf16 = q_bf16 != 0;
-  if (tid < R * 16) {
-    u32x4 raw = q_lane ? qraw : u32x4{0u, 0u, 0u, 0u};   // a surplus head is an all-zero query: uniform weights, never stored
-    if constexpr (!RAW) {
-      if (g.rotate_k) {
-        // rotated keys: the scores need R q, rounded once to binary16 (16 threads hold one query row, 8 channels each)
-        const uint32_t rw[4] = {raw.x, raw.y, raw.z, raw.w};
-        float x[8];
+  float xq[kQItems][8];                            // this lane's channels of the staged rows
+  {
+    typedef u32x4 __attribute__((may_alias)) u32x4_lds;
+    typedef uint16_t __attribute__((may_alias)) u16_lds;
+    typedef float4v __attribute__((may_alias)) f32x4_lds;
+    constexpr int kZeroBytes = KSEQ ? 512 : 64;
+    if (lane < kZeroBytes / 16) reinterpret_cast<u32x4_lds*>(sm_zero)[lane] = u32x4{0u, 0u, 0u, 0u};   // (every wavefront: the same)
+#pragma unroll
+    for (int t = 0; t < kQItems; ++t) {
+      const int item = lane + 64 * t, hh = item >> 4, o = item & 15;
+      const bool have = hh < r_act;                // a surplus head is an all-zero query: uniform weights, never stored
+      const u32x4 raw = have ? qraw[t] : u32x4{0u, 0u, 0u, 0u};
+      const uint32_t rw[4] = {raw.x, raw.y, raw.z, raw.w};
+      if constexpr (RAWK) {
+        if (item < R * 16) *reinterpret_cast<u32x4_lds*>(q_lds + hh * 256 + (o & 3) * 64 + (o >> 2) * 16) = raw;
+      } else {
+        float (&x)[8] = xq[t];
 #pragma unroll
         for (int e = 0; e < 8; ++e) x[e] = widen16((uint16_t)(rw[e >> 1] >> (16 * (e & 1))), q_is_bf16);
-        rotate8(x, tid & 15, rot_sign_bits(g.signs_k, tid & 15));
-        uint32_t w[4];
+        if (g.rotate_k) {
+          // rotated keys: the scores need R q, rounded once to binary16 (16 lanes hold one query row, 8 channels each)
+          rotate8(x, o, rot_sign_bits(g.signs_k, o));
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          w[e] = (uint32_t)f32_to_f16_bits(x[2 * e]) | ((uint32_t)f32_to_f16_bits(x[2 * e + 1]) << 16);
-        raw = u32x4{w[0], w[1], w[2], w[3]};
+          for (int e = 0; e < 8; ++e) x[e] = widen16(f32_to_f16_bits(x[e]), false);
+        }
+        if constexpr (KSEQ) {
+          if (item < R * 16) {
+            f32x4_lds* dst = reinterpret_cast<f32x4_lds*>(q_lds + hh * 512 + o * 32);
+            float y[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) y[e] = x[e] / (kseq_prescaled<BK>() ? k_chan_scale<BK>(e) : 1.0f);
+            dst[0] = float4v{y[0], y[1], y[2], y[3]};
+            dst[1] = float4v{y[4], y[5], y[6], y[7]};
+          }
+        } else {
+          auto stage = [&](auto run, uint8_t* row) {           // the operand of one run of the codes: see stage_slot
+            constexpr int B = decltype(run)::bits, BASE = decltype(run)::base;
+            uint16_t y[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) y[e] = __builtin_bit_cast(uint16_t, (_Float16)(x[e] * (decltype(run)::factor / k_octet_scale<B, BASE>(e))));
+            if constexpr (B == 4) {
+              *reinterpret_cast<u32x4_lds*>(row + o * 16) = u32x4{y[0] | (uint32_t)y[4] << 16, y[1] | (uint32_t)y[5] << 16,
+                                                                  y[2] | (uint32_t)y[6] << 16, y[3] | (uint32_t)y[7] << 16};
+            } else if constexpr (B == 8) {
+              *reinterpret_cast<u32x4_lds*>(row + o * 16) = u32x4{y[0] | (uint32_t)y[2] << 16, y[1] | (uint32_t)y[3] << 16,
+                                                                  y[4] | (uint32_t)y[6] << 16, y[5] | (uint32_t)y[7] << 16};
+            } else {
+#pragma unroll
+              for (int e = 0; e < 8; ++e) *reinterpret_cast<u16_lds*>(row + k_octet_offset<B>(o) + 16 * (e >> 2) + 4 * (e & 3)) = y[e];
+            }
+          };
+          if (item < R * 16) {
+            stage(KRun<KLO, k_default_base<KLO>(), 1>{}, q_lds + hh * kOpRow);
+            if constexpr (KHI != 0) stage(KRun<KHI, k_hi_base<BK>(), (1 << KLO)>{}, q_lds + hh * kOpRow + 256);
+          }
+          // per-group sums of the (staged) query: the zero points of a key group enter the scores through them
+          float part = 0.f;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) part += x[e];
+          const int lpg = g.g_k >> 3;              // lanes per key group: 4, 8 or 16
+          for (int off = 1; off < lpg; off <<= 1) part += __shfl_xor(part, off, 16);
+          if (item < R * 16 && (o & (lpg - 1)) == 0) sm_qsum[wave][hh][o >> lpg_shift(lpg)] = part;
+        }
       }
-    }
-    reinterpret_cast<u32x4*>(&sm_q[0][0])[tid] = raw;
-    if constexpr (KSEQ) {
-      const uint32_t rw[4] = {raw.x, raw.y, raw.z, raw.w};
-      const bool staged_bf16 = q_is_bf16 && !g.rotate_k;       // (a rotated query has been rounded to binary16 above)
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        sm_qf[tid >> 4][8 * (tid & 15) + e] = widen16((uint16_t)(rw[e >> 1] >> (16 * (e & 1))), staged_bf16) /
-                                              (kseq_prescaled<BK>() ? k_chan_scale<BK>(e) : 1.0f);
-    }
-    if constexpr (!RAW) {
-      // per-group sums of the (staged) query: the zero points of a key group enter the scores through them
-      const uint32_t rw[4] = {raw.x, raw.y, raw.z, raw.w};
-      const bool f16_now = !q_is_bf16 || g.rotate_k;
-      float part = 0.f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) part += widen16((uint16_t)(rw[e >> 1] >> (16 * (e & 1))), !f16_now);
-      const int lpg = g.g_k >> 3;                    // lanes per key group: 4, 8 or 16
-      for (int off = 1; off < lpg; off <<= 1) part += __shfl_xor(part, off, 16);
-      if (((tid & 15) & (lpg - 1)) == 0) sm_qsum[tid >> 4][(tid & 15) >> lpg_shift(lpg)] = part;
     }
   }
-  if constexpr (KSEQ) { if (tid < kHeadDim) sm_qf[R][tid] = 0.f; }
-  if constexpr (!RAW) q_is_bf16 = q_is_bf16 && !g.rotate_k;      // the staged rotated query is binary16
-  __syncthreads();
-#pragma unroll
-  for (int k = kEarly; k < kStages; ++k) refill(k, k);       // the second half of the ring's first fill
-  auto widen = [&](uint16_t bits) -> float {
-    return q_is_bf16 ? __uint_as_float((uint32_t)bits << 16) : (float)__builtin_bit_cast(_Float16, bits);
-  };
-  // ---- fused step, second half: the value codes go into their words (loaded at the top), and the new token becomes a
-  // partial record of its own: logit of every head against the reconstructed key row (maximum = that logit, sum = one
-  // weight of 1, accumulator = the reconstructed value row), which the merge below adds to the wavefronts' records
+  // ---- fused step: one wavefront quantizes the new token (two 16-lane rows), stores keys and scale/zero, inserts the value
+  // codes into their words (loaded at the top), and the new token becomes a partial record of its own: logit of every
+  // head against the reconstructed key row (maximum = that logit, sum = one weight of 1, accumulator = the reconstructed
+  // value row), which the merge below adds to the wavefronts' records.  All of it stays inside the wavefront.
   if constexpr (kCanAppend) {
-    if (do_append) {                               // uniform over the workgroup
-      if (vw_lo_p) *vw_lo_p = field_insert<VLO_>(vw_lo, tid, sm_vnew, u_new, 0);
-      if constexpr (VHI_ != 0) {
-        if (vw_hi_p) *vw_hi_p = field_insert<VHI_>(vw_hi, tid, sm_vnew, u_new, VLO_);
+    if (app_wave) {                                // uniform
+      if (lane < 32) append_one<BK, BV>(a, PAGED ? 0 : bh, bh, lane, nraw, sm_vnew, t_new, &sm_hat[0][0]);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int d = lane + 64 * t;
+        if (field_owner<VLO_>(d))
+          store_global<uint32_t>(vblk + 4 * (uintptr_t)field_word<VLO_>(d, u_new), field_insert<VLO_>(vw_lo[t], d, sm_vnew, u_new, 0));
+        if constexpr (VHI_ != 0) {
+          if (field_owner<VHI_>(d))
+            store_global<uint32_t>(vblk + 4 * (uintptr_t)(128 * VLO_ + field_word<VHI_>(d, u_new)), field_insert<VHI_>(vw_hi[t], d, sm_vnew, u_new, VLO_));
+        }
       }
-      if (tid < R * 16) {                            // 16 threads per head: 8 channels each, then a sum over the 16
-        const int hh = tid >> 4, lane16 = tid & 15;
-        const u32x4 qv = *reinterpret_cast<const u32x4*>(&sm_q[hh][8 * lane16]);
-        const uint32_t qw[4] = {qv.x, qv.y, qv.z, qv.w};
+#pragma unroll
+      for (int t = 0; t < kQItems; ++t) {          // 16 lanes per head: 8 channels each, then a sum over the 16
+        const int item = lane + 64 * t, o = item & 15;
         float part = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) part = fmaf(widen((uint16_t)(qw[e >> 1] >> (16 * (e & 1)))), sm_hat[0][8 * lane16 + e], part);
+        for (int e = 0; e < 8; ++e) part = fmaf(xq[t][e], sm_hat[0][8 * o + e], part);
 #pragma unroll
         for (int off = 1; off < 16; off <<= 1) part += __shfl_xor(part, off, 16);
-        if (lane16 == 0) sm_mnew[hh] = part * (softmax_scale * kLog2e);
+        if (o == 0 && item < R * 16) sm_mnew[item >> 4] = part * (softmax_scale * kLog2e);
       }
     }
   }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+  for (int k = kEarly; k < kStages; ++k) refill(k, k);       // the second half of the ring's first fill
   // column c of set cs carries head h restricted to key group grp + cs*kSetGroups (zero elsewhere)
-  constexpr int KLO = k_lo<BK>(), KHI = k_hi<BK>();
   u32x4 qb[NCK][4];
   u32x4 qbh[NCK][4];                             // operand of the high run of 3- and 6-bit key codes (else unused)
   float qsum_u[NCK];
-  {
-    uint16_t mych[32];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const u32x4 v = *reinterpret_cast<const u32x4*>(&sm_q[h][k_lane_chan<BK>(L.j, 8 * k)]);
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  for (int cs = 0; cs < NCK; ++cs) {
+    typedef u32x4 __attribute__((may_alias)) u32x4_lds;
+    const int gcs = grp + cs * kSetGroups;
+    const bool act = gcs < g.ng_k;
+    const bool mine = act && (RAW || (32 * L.j) / g.g_k == gcs);          // (unquantized: one group)
+    const uint8_t* zero = reinterpret_cast<const uint8_t*>(sm_zero);
+    const uint8_t* src = mine ? q_lds + h * kOpRow + L.j * 64 : zero;
+    const uint8_t* src_hi = mine && KHI != 0 ? q_lds + h * kOpRow + 256 + L.j * 64 : zero;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) mych[8 * k + e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
-    }
-#pragma unroll
-    for (int cs = 0; cs < NCK; ++cs) {
-      const int gcs = grp + cs * kSetGroups;
-      const bool act = gcs < g.ng_k;
-      const bool mine = act && (RAW || (32 * L.j) / g.g_k == gcs);        // (unquantized: one group)
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        uint32_t w[4] = {0u, 0u, 0u, 0u}, wh[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const uint16_t bits = mych[k_slot_elem<KLO>(m, i)];
-          uint32_t e;                              // unquantized: the query's own 16-bit pattern (same type as the cache)
-          if constexpr (RAW) e = bits;
-          else e = __builtin_bit_cast(uint16_t, (_Float16)(widen(bits) / k_slot_scale<KLO>(i)));
-          if (mine) w[i >> 1] |= e << (16 * (i & 1));
-          if constexpr (KHI != 0) {                // high run: its own slot order, and the codes' factor 2^LO
-            const float qh = widen(mych[k_slot_elem<KHI>(m, i)]) * ((float)(1 << KLO) / k_slot_scale<KHI, k_hi_base<BK>()>(i));
-            if (mine) wh[i >> 1] |= (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)qh) << (16 * (i & 1));
-          }
-        }
-        qb[cs][m] = u32x4{w[0], w[1], w[2], w[3]};
-        qbh[cs][m] = u32x4{wh[0], wh[1], wh[2], wh[3]};
+    for (int m = 0; m < 4; ++m) {
+      if constexpr (!KSEQ) {
+        qb[cs][m] = *reinterpret_cast<const u32x4_lds*>(src + 16 * m);
+        if constexpr (KHI != 0) qbh[cs][m] = *reinterpret_cast<const u32x4_lds*>(src_hi + 16 * m);
       }
-      float qsum = 0.f;
-      if constexpr (!RAW) { if (act) qsum = sm_qsum[h][gcs]; }
-      qsum_u[cs] = qsum * kUnit;
     }
+    float qsum = 0.f;
+    if constexpr (!RAW && !KSEQ) { if (act) qsum = sm_qsum[wave][h][gcs]; }
+    qsum_u[cs] = qsum * kUnit;
   }
   const float kappa = softmax_scale * kLog2e * kInvUnit;
 
@@ -1116,7 +1172,7 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   // ---- main loop, unrolled over the ring: compute a step, then refill its registers with the step kStages
   // ahead, so that kStages-1 steps of loads are always in flight behind the one being computed.
   typename std::conditional<KSEQ, typename std::conditional<k_hi<BK>() != 0, KSeqState2, KSeqState>::type, NoKSeq>::type ks;
-  const float* qrow = &sm_qf[KSEQ ? (grp < 2 ? h : R) : 0][0];   // (column groups 0 and 1 carry the key side)
+  const float* qrow = KSEQ && grp < 2 ? &sm_o[wave][h][0] : sm_zero;      // (column groups 0 and 1 carry the key side)
   // one complete step out of ring slot k (for channel-wise keys an even slot starts a 64-token block, and the query
   // operands are rebuilt there: once per group of 64 tokens, twice per group of 128 -- the second time from the same
   // entries -- and in the odd steps too when a group is one step long)
@@ -1227,61 +1283,37 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   }
   bool wrote_rows = a.rec_splits == 1;               // this workgroup has left normalized rows (rotated values: in sm_o)
   if (a.merge_tag != 0) {                            // uniform: the launch's workgroups merge their records themselves
-    // The workgroup of a (b, h_kv) stream that finishes last combines the stream's records: every workgroup counts
-    // itself in (one device-scope increment, issued after all its record stores have been acknowledged), and the one
-    // that brings the count to n_splits reads all records back.  Nobody waits for anybody.  Records and counter are
-    // device-scope atomic accesses, which go past the caches that are private to a part of the chip; a device-scope
-    // FENCE is not used on purpose: it writes back and invalidates the whole second-level cache of the workgroup's part
-    // of the chip, under the streaming loads of every other workgroup there, and was measured to cost the 8B-layer
-    // step 10 us (the barrier in front of the increment already waits for this workgroup's stores).  The counter word carries the launch's
-    // tag above the count, so that whatever the word held before this launch -- another launch's tag, or the bytes of
-    // a fresh workspace -- counts as zero; the last workgroup leaves the count at zero for a replay of the same launch.
+    // Two records: the workgroup that finishes last combines them.  Every workgroup exchanges the stream's word for this
+    // launch's tag, after its record stores have been performed; the one that finds the tag there is the second, and
+    // leaves a zero for a replay of the same launch.  Nobody waits for anybody.  Records and word are device-scope atomic
+    // accesses, which go past the caches that are private to a part of the chip; a device-scope FENCE is not used on
+    // purpose: it writes back and invalidates the whole second-level cache of the workgroup's part of the chip, under
+    // the streaming loads of every other workgroup there, and was measured to cost the 8B-layer step 10 us.  The order is
+    // carried by the wait below: a store is acknowledged when it has been performed, and a barrier alone does not wait
+    // for it.  Whatever the word held before this launch -- another launch's tag, or the bytes of a fresh workspace --
+    // differs from the tag.
     __shared__ int sm_last;
-    __syncthreads();                                 // (all record stores of this workgroup are performed)
+    __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): this wavefront's record stores are performed
+    __syncthreads();                                 // (and so are the other wavefronts')
     if (tid == 0) {
-      unsigned long long* cnt = reinterpret_cast<unsigned long long*>(ws + (int64_t)g.batch * q_heads * a.rec_splits * kRec) + bh;
-      const unsigned long long tag = a.merge_tag << 16;
-      unsigned long long seen = __hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), want;
-      do {
-        want = ((seen & ~0xFFFFull) == tag ? seen : tag) + 1ull;
-      } while (!__hip_atomic_compare_exchange_strong(cnt, &seen, want, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-      const int last = (int)(want & 0xFFFFull) == a.rec_splits;
-      if (last) __hip_atomic_store(cnt, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      sm_last = last;
+      unsigned long long* word = reinterpret_cast<unsigned long long*>(ws + (int64_t)g.batch * q_heads * a.rec_splits * kRec) + bh;
+      const unsigned long long seen = __hip_atomic_exchange(word, a.merge_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      sm_last = seen == a.merge_tag;
+      if (seen == a.merge_tag) __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
     if (sm_last) {                                   // uniform over the workgroup
-      const int n_rec = a.rec_splits;
       for (int idx = tid; idx < r_act * kHeadDim; idx += 64 * NW) {
         const int hh = idx / kHeadDim, d = idx % kHeadDim;
         const int64_t hq = (int64_t)b * q_heads + hk * r_act + hh;
-        const float* rec = ws + hq * n_rec * kRec;
-        // eight records at a time, all 24 loads of a round in flight together (a record's maximum and sum are the same
-        // words for the 128 threads of a head); rounds are chained by a running maximum as in the main loop
-        float M = kNegBig, o = 0.f, ll = 0.f;
-        for (int s0 = 0; s0 < n_rec; s0 += 8) {
-          float ms[8], ls[8], os[8];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const float* r2 = rec + min(s0 + j, n_rec - 1) * kRec;
-            ms[j] = load_device(r2 + kHeadDim); ls[j] = load_device(r2 + kHeadDim + 1); os[j] = load_device(r2 + d);
-          }
-          float Mc = M;
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            if (s0 + j >= n_rec) { ms[j] = kNegBig; ls[j] = 0.f; os[j] = 0.f; }
-            Mc = fmaxf(Mc, ms[j]);
-          }
-          const float fo = exp2f(M - Mc);
-          o *= fo; ll *= fo;
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const float f = exp2f(ms[j] - Mc);
-            o = fmaf(f, os[j], o);
-            ll = fmaf(f, ls[j], ll);
-          }
-          M = Mc;
-        }
+        const float* r0 = ws + hq * 2 * kRec;
+        const float* r1 = r0 + kRec;
+        // (all loads in flight together; a record's maximum and sum are the same words for the 128 threads of a head)
+        const float m0 = load_device(r0 + kHeadDim), l0 = load_device(r0 + kHeadDim + 1), o0 = load_device(r0 + d);
+        const float m1 = load_device(r1 + kHeadDim), l1 = load_device(r1 + kHeadDim + 1), o1 = load_device(r1 + d);
+        const float M = fmaxf(m0, m1);
+        const float f0 = exp2f(m0 - M), f1 = exp2f(m1 - M);
+        const float o = fmaf(f1, o1, f0 * o0), ll = fmaf(f1, l1, f0 * l0);
         const float val = o / ll;
         if (g.rotate_v) sm_o[0][hh][d] = val;
         else store_out(out, out_dtype, hq * kHeadDim + d, val);
@@ -1444,7 +1476,7 @@ hipError_t launch_sets(const DecodeArgs& a, const DecodePlan& plan, dim3 grid, h
 
 template <int BK, int BV, int R, bool BF = false, bool KSEQ = false>
 hipError_t launch_one(const DecodeArgs& a, const DecodePlan& plan, hipStream_t stream) {
-  dim3 grid(plan.n_splits, a.g.batch * a.g.kv_heads);
+  dim3 grid(plan.n_splits, a.g.kv_heads, a.g.batch);
   hipError_t e;
   e = a.g.page_shift ? launch_sets<BK, BV, R, BF, KSEQ, true>(a, plan, grid, stream)
                      : launch_sets<BK, BV, R, BF, KSEQ, false>(a, plan, grid, stream);

@@ -2079,3 +2079,35 @@ def test_reading_back_in_one_call_and_in_ranges_is_the_same(kvq, kw, dtype):
         alone = kvq.reconstruction_error(L, cache, None, V[:, :, t0:t1], t0, torch.empty_like(whole))
         assert float((alone[..., 1] - one[..., 1]).abs().max()) <= 1e-12 * float(one[..., 1].abs().max()) and not alone[..., 0].any()
     assert float((whole - parts).abs().max()) <= 1e-12 * float(whole.abs().max()) + 1e-300
+
+
+@pytest.mark.parametrize("T", [65536 + 512, 512 * 129 + 33])
+def test_paged_walks_longer_than_the_staged_page_numbers(kvq, T):
+    """More than 512 steps per wavefront (300 streams: 4 wavefronts each, from 65536 tokens): the page numbers behind
+    those come from the table itself.  The table repeats 8 pages of 64 tokens, and a token repeated n times in a softmax
+    weighs what it weighs once, so whole repeats equal attention over the 512 tokens; a partial repeat (33 tokens more)
+    is within its share of the weights of that.  Both sides round weights to binary16 (2^-11 each)."""
+    B, R, P, D = 300, 2, 64, 128
+    n_log = -(-T // P)
+    scale = 1 / math.sqrt(D)
+    L = kvq.Layout(B, 1, n_log * P, page_tokens=P, n_pages=8)
+    one = kvq.Layout(1, 1, 512, page_tokens=P, n_pages=8)
+    K, V, _ = synth.make_kvq(3, 1, 1, R, 512, D, dtype=torch.float16, device="cuda", sigma_k=0.5, outlier_scale=1.0)
+    cache = kvq.Cache(one, fill=0)
+    cache.page_table = torch.tensor([[5, 2, 7, 0, 1, 6, 3, 4]], dtype=torch.int32, device="cuda")
+    kvq.quantize_append(one, cache, K, V, 0)
+    long = kvq.Cache.__new__(kvq.Cache)
+    long.layout, long.planes = L, cache.planes
+    long.v_scale_exp = torch.zeros(B, dtype=torch.int32, device="cuda")
+    long.page_table = cache.page_table.repeat(B, -(-n_log // 8))[:, :n_log].contiguous()
+    q = torch.randn(B, R, D, device="cuda", generator=torch.Generator("cuda").manual_seed(9)).half()
+    out = torch.empty(B, R, D, dtype=torch.float32, device="cuda")
+    assert kvq.decode_workspace_bytes(L, R, T) == 0
+    kvq.decode_attention(L, long, q, T, scale, out, None)
+    want = torch.empty(1, R, D, dtype=torch.float32, device="cuda")
+    ws = torch.empty(max(16, kvq.decode_workspace_bytes(one, R, 512)), dtype=torch.uint8, device="cuda")
+    worst = 0.0
+    for b in range(0, B, 23):
+        kvq.decode_attention(one, cache, q[b:b + 1].contiguous(), 512, scale, want, ws)
+        worst = max(worst, float((out[b] - want[0]).norm() / want.norm()))
+    assert worst < 2e-3 + (33 / T * 20 if T % 512 else 0), worst
