@@ -35,6 +35,7 @@ def _scratch_allowed(kernel_name: str) -> int:
 # (source, object name, extra flags).  The quantizer must round every operation once: no contraction.
 UNITS = [("kvq_api.hip", "kvq_api.o", []),
          ("kvq_quant.hip", "kvq_quant.o", ["-ffp-contract=off"]),
+         ("kvq_seq_append.hip", "kvq_seq_append.o", ["-ffp-contract=off"]),
          ("kvq_readback.hip", "kvq_readback.o", ["-ffp-contract=off"]),
          ("kvq_decode.hip", "kvq_decode.o", [])]
 UNITS += [("kvq_decode.hip", f"kvq_decode_k{bk}v{bv}.o",

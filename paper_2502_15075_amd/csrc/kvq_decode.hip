@@ -767,7 +767,7 @@ __device__ __forceinline__ void append_one(const DecodeArgs& a, int bh, int sbh,
   }
   const float sc = widen16(S, false), zp = widen16(Z, false);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) hat[(is_v ? kHeadDim : 0) + d0 + e] = fmaf((float)codes[e], sc, zp);   // (exact product: one rounding)
+  for (int e = 0; e < 8; ++e) hat[(is_v ? kHeadDim : 0) + d0 + e] = fmaf((float)code_value(codes[e]), sc, zp);   // (exact product: one rounding)
 }
 
 // Second half of the fused append: thread d < 128 inserts channel d's code of the new token into its 32-bit word of
@@ -1200,8 +1200,10 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
     }
   }
 #pragma unroll
-  for (int k = 0; k < kStages - 1; ++k)          // the last few complete steps are already in the ring,
-    if (it + k < n_full) full_step(k, it + k);
+  for (int k = 0; k < kStages - 1; ++k) {        // the last few complete steps are already in the ring,
+    if (it + k >= n_full) break;
+    full_step(k, it + k);
+  }
   if (own_tail) {                                 // and so is the tail, in the slot after them
     const int kt = n_full - it;
 #pragma unroll

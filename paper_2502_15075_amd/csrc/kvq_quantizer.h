@@ -38,17 +38,31 @@ __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
 template <int B> __host__ __device__ constexpr int code_lo_bits() { return B == 3 ? 2 : B == 6 ? 4 : B; }
 template <int B> __host__ __device__ constexpr int code_hi_bits() { return B - code_lo_bits<B>(); }
 
+// How the quantizer hands out a code: as the binary32 pattern of 1.5 * 2^23 + code.  Adding that number is what rounds to the
+// nearest integer (ties to even; the unit in the last place is 1 there) and leaves the code in the lowest 8 bits, so no
+// conversion follows; bits 8 to 21 are zero, those above are kCodeBias.
+constexpr float kCodeMagic = 12582912.0f;
+constexpr uint32_t kCodeBias = 0x4B400000u;
+__device__ __forceinline__ uint32_t code_value(uint32_t code) { return code & 0xFFu; }
+
 // n-bit fields of the 8 codes, first code lowest: bits [shift, shift + N) of every code (MASK: the codes have bits
-// above shift + N; otherwise nothing needs to be cut off)
+// above shift + N that are not kCodeBias's; otherwise only the bias has to go: what it adds up to over the eight shifted
+// terms is one constant, and fields that fill 16 bits or less never meet it)
 template <int N, bool MASK> __device__ __forceinline__ uint32_t pack8(const uint32_t codes[8], int shift) {
-  uint32_t w = 0;
+  if constexpr (MASK) {
+    uint32_t w = 0;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    uint32_t c = codes[e] >> shift;
-    if (MASK) c &= (1u << N) - 1u;
-    w |= c << (N * e);
+    for (int e = 0; e < 8; ++e) w |= ((codes[e] >> shift) & ((1u << N) - 1u)) << (N * e);
+    return w;
+  } else {
+    uint32_t w = codes[7] >> shift, bias = kCodeBias >> shift;
+#pragma unroll
+    for (int e = 6; e >= 0; --e) {
+      w = (w << N) + (codes[e] >> shift);
+      bias = (bias << N) + (kCodeBias >> shift);
+    }
+    return w - bias;
   }
-  return w;
 }
 // NT: a streaming store (the bulk append writes planes that nothing reads back soon; marked so, its stores and loads
 // leave the caches to data that is reused, and the memory system takes the mixed read/write stream about a tenth faster)
@@ -74,8 +88,9 @@ template <int BK, bool NT = false>
 __device__ __forceinline__ void store_key_codes(uint8_t* rowp, int lane16, const uint32_t codes[8]) {
   constexpr int LO = code_lo_bits<BK>(), HI = code_hi_bits<BK>();
   if constexpr (BK == 8) {
-    const uint32_t w0 = codes[0] | (codes[1] << 8) | (codes[2] << 16) | (codes[3] << 24);
-    const uint32_t w1 = codes[4] | (codes[5] << 8) | (codes[6] << 16) | (codes[7] << 24);
+    constexpr uint32_t bias = kCodeBias + (kCodeBias << 8);      // (the shifts by 16 and 24 push it out)
+    const uint32_t w0 = codes[0] + (codes[1] << 8) + (codes[2] << 16) + (codes[3] << 24) - bias;
+    const uint32_t w1 = codes[4] + (codes[5] << 8) + (codes[6] << 16) + (codes[7] << 24) - bias;
     if constexpr (NT) {
       typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
       u32x2 w; w.x = w0; w.y = w1;
@@ -101,11 +116,38 @@ constexpr float kRotScale = 0.08838834764831845f;   // binary32(1/sqrt(128))
 
 // The 8 sign bits of the channels of lane16 (bit e set: channel 8*lane16 + e is negated).
 __device__ __forceinline__ uint32_t rot_sign_bits(const uint32_t signs[4], int lane16) {
-  const int w = lane16 >> 2;
-  const uint32_t word = w == 0 ? signs[0] : w == 1 ? signs[1] : w == 2 ? signs[2] : signs[3];
-  return (word >> (8 * (lane16 & 3))) & 0xFFu;
+  // (two selects by value: a four-way choice becomes branches)
+  const uint32_t lo = (lane16 & 4) ? signs[1] : signs[0], hi = (lane16 & 4) ? signs[3] : signs[2];
+  return (((lane16 & 8) ? hi : lo) >> (8 * (lane16 & 3))) & 0xFFu;
 }
 
+// Value of x in the lane a data-parallel-primitive control word selects (quad permutes, mirrors and rotations of a 16-lane
+// row).  The builtin, not assembly: the compiler then keeps the wait states such an instruction needs.
+template <int CTRL>
+__device__ __forceinline__ float lane_dpp(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
+}
+// x of lane ^ M inside a 16-lane row, M in {1, 2, 4, 8}: one lane-permuted read (folded into the instruction that uses it),
+// two for 4 (lane ^ 7 by the mirror of half rows, then ^ 3 by the reversed quad)
+template <int M> __device__ __forceinline__ float lane_xor(float x) {
+  if (M == 1) return lane_dpp<0xB1>(x);            // quad_perm 1,0,3,2
+  if (M == 2) return lane_dpp<0x4E>(x);            // quad_perm 2,3,0,1
+  if (M == 4) return lane_dpp<0x1B>(lane_dpp<0x141>(x));
+  return lane_dpp<0x128>(x);                       // row_ror 8
+}
+// One butterfly stage across lanes: the lower lane of a pair takes x + o, the upper o - x = o + (-x).
+template <int M> __device__ __forceinline__ void butterfly_lanes(float x[8], int lane16) {
+#pragma clang fp contract(off)
+  const uint32_t flip = (lane16 & M) ? 0x80000000u : 0u;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const float o = lane_xor<M>(x[e]);
+    x[e] = o + __uint_as_float(__float_as_uint(x[e]) ^ flip);
+  }
+}
+
+// (The exchanges between lanes are register permutes.  Through the LDS permute unit, 32 of them per row octet, each followed by
+// its wait, a rotated append of 8 x 8 heads x 8192 tokens (K4V2) took 80.7 us, like this 73.7.)
 __device__ __forceinline__ void hadamard8x16(float x[8], int lane16) {
 #pragma clang fp contract(off)
 #pragma unroll
@@ -118,22 +160,17 @@ __device__ __forceinline__ void hadamard8x16(float x[8], int lane16) {
         x[i + h] = a - b;
       }
   }
-#pragma unroll
-  for (int m = 1; m < 16; m <<= 1) {
-    const bool upper = (lane16 & m) != 0;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float o = __shfl_xor(x[e], m, 16);
-      x[e] = upper ? o - x[e] : x[e] + o;
-    }
-  }
+  butterfly_lanes<1>(x, lane16);
+  butterfly_lanes<2>(x, lane16);
+  butterfly_lanes<4>(x, lane16);
+  butterfly_lanes<8>(x, lane16);
 }
 
 // x <- R x
 __device__ __forceinline__ void rotate8(float x[8], int lane16, uint32_t sign_bits) {
 #pragma clang fp contract(off)
 #pragma unroll
-  for (int e = 0; e < 8; ++e) x[e] = (sign_bits >> e) & 1u ? -x[e] : x[e];
+  for (int e = 0; e < 8; ++e) x[e] = __uint_as_float(__float_as_uint(x[e]) ^ ((sign_bits << (31 - e)) & 0x80000000u));
   hadamard8x16(x, lane16);
 #pragma unroll
   for (int e = 0; e < 8; ++e) x[e] = x[e] * kRotScale;
@@ -146,7 +183,7 @@ __device__ __forceinline__ void unrotate8(float x[8], int lane16, uint32_t sign_
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const float v = x[e] * kRotScale;
-    x[e] = (sign_bits >> e) & 1u ? -v : v;
+    x[e] = __uint_as_float(__float_as_uint(v) ^ ((sign_bits << (31 - e)) & 0x80000000u));
   }
 }
 
@@ -163,13 +200,6 @@ __device__ __forceinline__ float max3f(float a, float b, float c) {
 }
 __device__ __forceinline__ float min2f(float a, float b) { float r; asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b)); return r; }
 __device__ __forceinline__ float max2f(float a, float b) { float r; asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b)); return r; }
-// Value of x in the lane a data-parallel-primitive control word selects (quad permutes and mirrors of a 16-lane
-// row).  The builtin, not assembly: the compiler then keeps the wait states such an instruction needs.
-template <int CTRL>
-__device__ __forceinline__ float lane_dpp(float x) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
-}
-
 // ---- the two divisions of the quantizer, correctly rounded in three operations each ---------------------------------
 // (mx - mn) / levels with levels = 2^b - 1 in {1, 3, 7, 15, 63, 255}: with c = RN(1 / levels), q0 = RN(x c),
 // r = x - levels q0 (one fused multiply-add, exact), q1 = RN(q0 + r c) is the correctly rounded quotient (the classical
@@ -200,7 +230,7 @@ __device__ __forceinline__ float rcp_scale(float s) {
 }
 
 // Quantize 8 consecutive elements held by this lane; the group spans `lanes_per_group`
-// neighbouring lanes (a power of two <= 16, aligned).  Returns the 8 codes, and the stored
+// neighbouring lanes (a power of two <= 16, aligned).  Returns the 8 codes (see kCodeMagic), and the stored
 // scale/zero patterns through S, Z.
 __device__ __forceinline__ void quantize8(const float x[8], int bits, int lanes_per_group, uint32_t codes[8],
                                           uint16_t* S, uint16_t* Z) {
@@ -231,11 +261,10 @@ __device__ __forceinline__ void quantize8(const float x[8], int bits, int lanes_
         "v_min_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n\t"
         "v_max_f32_dpp %1, %1, %1 row_mirror row_mask:0xf bank_mask:0xf"
         : "+v"(mn), "+v"(mx));
-  if (mn == 0.0f) mn = 0.0f;  // -0 -> +0
+  mn = mn + 0.0f;             // -0 -> +0, everything else as it is
   const float levels = (float)((1 << bits) - 1);
   float s32 = div_levels(mx - mn, levels, inv_levels(bits));
-  uint16_t sb = f32_to_f16_bits(s32);
-  if ((sb & 0x7FFFu) == 0) sb = 0;
+  uint16_t sb = f32_to_f16_bits(s32);              // (+0 or positive: a difference of equal numbers is +0, and so is its quotient)
   uint16_t zb = f32_to_f16_bits(mn);
   float s = widen16(sb, false), z = widen16(zb, false);
   *S = sb; *Z = zb;
@@ -245,10 +274,9 @@ __device__ __forceinline__ void quantize8(const float x[8], int bits, int lanes_
   if (s == 0.0f) rcp = 0.0f;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    float t = (x[e] - z) * rcp;
-    float q = rintf(t);
-    q = __builtin_amdgcn_fmed3f(q, 0.0f, levels);     // clip to [0, levels] in one instruction
-    codes[e] = (uint32_t)q;
+    const float t = (x[e] - z) * rcp;
+    // clip to [0, levels] and round: the bounds are integers, so the order does not matter
+    codes[e] = __float_as_uint(__builtin_amdgcn_fmed3f(t, 0.0f, levels) + kCodeMagic);
   }
 }
 
@@ -264,23 +292,18 @@ __device__ __forceinline__ void note_value_scale(int32_t* stream_exp, uint16_t S
 // over tokens): stored scale/zero patterns from the group's minimum and maximum, then one code at a time.
 __device__ __forceinline__ void group_scale_zero(float mn, float mx, int bits, uint16_t* S, uint16_t* Z) {
 #pragma clang fp contract(off)
-  if (mn == 0.0f) mn = 0.0f;  // -0 -> +0
+  mn = mn + 0.0f;             // -0 -> +0, everything else as it is
   const float levels = (float)((1 << bits) - 1);
-  const float s32 = div_levels(mx - mn, levels, inv_levels(bits));
-  uint16_t sb = f32_to_f16_bits(s32);
-  if ((sb & 0x7FFFu) == 0) sb = 0;
-  *S = sb;
+  *S = f32_to_f16_bits(div_levels(mx - mn, levels, inv_levels(bits)));
   *Z = f32_to_f16_bits(mn);
 }
 
-// s, z: the stored scale/zero widened; rcp = 1 / s (unused when s == 0); levels = 2^bits - 1.
-__device__ __forceinline__ uint32_t group_code(float x, float s, float z, float rcp, float levels) {
+// z: the stored zero widened; rcp = 1 / (stored scale), 0 when the scale is 0; levels = 2^bits - 1.  The code as quantize8
+// hands it out.
+__device__ __forceinline__ uint32_t group_code(float x, float z, float rcp, float levels) {
 #pragma clang fp contract(off)
-  if (s == 0.0f) return 0u;
   const float t = (x - z) * rcp;
-  float q = rintf(t);
-  q = fminf(fmaxf(q, 0.0f), levels);
-  return (uint32_t)q;
+  return __float_as_uint(__builtin_amdgcn_fmed3f(t, 0.0f, levels) + kCodeMagic);
 }
 
 }  // namespace kvq
