@@ -716,6 +716,9 @@ __device__ __forceinline__ void compute_step(const StepRegs<BK, BV>& r, const u3
   }
 }
 
+// The upper 48 bits of a counter word behind the records that has been used before (see the merge in decode_kernel).
+constexpr unsigned long long kMergeMark = 0x9E3779B97F4A0000ull;
+
 // Record layout in the workspace: [b][hq][split] x (kHeadDim + 4) floats = acc[128], m, l, 0, 0.
 constexpr int kRec = kHeadDim + 4;
 
@@ -828,6 +831,57 @@ __device__ __forceinline__ void store_unrotated_row(const float* row, int lane16
   }
 }
 
+// ---- sequences of different lengths: which part of which sequence a workgroup takes ------------------------------------
+// A launch planned for the longest sequence cuts every sequence at the same places, and the workgroups behind a short one's
+// end have nothing to do while those of the longest run on.  Instead all workgroups of a kv head (slots 0 .. slots - 1)
+// are dealt out by the lengths: sequence b gets ceil(N_b / q) of them, q steps each, with the smallest q (of 64 evenly
+// spaced ones) for which they are enough.  Every wavefront works that out for itself from the lengths (at most 64, one per
+// lane); the answer depends on nothing else, so all workgroups agree.  Lengths that leave less than a sixteenth of the
+// plan's steps empty keep the plan's q, without the search.
+__device__ __forceinline__ int wave_scan(int v) {  // sum over the lanes up to and including this one
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);     // row_shr 1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);     // row_bcast 15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);     // row_bcast 31 into rows 2 and 3
+  return v;
+}
+struct Share { int b, split, count, q, slot0, len; };   // sequence, part of it, its parts, steps per part, slot of its first part, tokens
+template <int UNIT>                                // q is a multiple of UNIT steps (a workgroup's wavefronts)
+__device__ __forceinline__ Share balanced_share(const int32_t* __restrict__ seq_lens, int offset, int bound, int batch, int splits,
+                                                int q_max, int slot, int lane) {
+  const int len = min(max(seq_lens[min(lane, batch - 1)] + offset, 1), bound);
+  const int n = lane < batch ? (len + 31) >> 5 : 0;           // steps, 2^19 at most
+  const int slots = splits * batch;
+  // parts of q steps; (n + q - 1) / q in binary32: half a unit above the quotient of integers below 2^21 rounds to the right side
+  auto parts = [&](int q) {
+    const float rq = __builtin_amdgcn_rcpf((float)q);
+    return (int)fmaf((float)(n + q - 1), rq, 0.5f * rq);
+  };
+  Share s;
+  s.q = q_max;                                     // (always enough: no sequence is longer than the plan's)
+  const int total = __builtin_amdgcn_readlane(wave_scan(n), 63), full = ((bound + 31) >> 5) * batch;
+  if (total < full - full / 16) {                  // (uniform)
+    int lo = 1, hi = 64;                           // q = q_max i / 64, at least one unit (rounded up twice)
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      const int q = min((int)((((int64_t)q_max * mid + 63) / 64 + UNIT - 1) / UNIT) * UNIT, q_max);
+      const bool enough = __builtin_amdgcn_readlane(wave_scan(parts(q)), 63) <= slots;
+      if (enough) { hi = mid; s.q = q; } else { lo = mid + 1; }
+    }
+  }
+  const int mine = parts(s.q), end = wave_scan(mine);
+  const unsigned long long hit = __ballot(slot >= end - mine && slot < end);       // (one lane, or none)
+  const int l = hit ? __ffsll(hit) - 1 : 0;
+  s.b = hit ? l : -1;
+  s.count = __builtin_amdgcn_readlane(mine, l);
+  s.slot0 = __builtin_amdgcn_readlane(end, l) - s.count;
+  s.split = slot - s.slot0;
+  s.len = __builtin_amdgcn_readlane(len, l);
+  return s;
+}
+
 // KSEQ: channel-wise keys (the caller passes the flushed part of the sequence: seq_len is a multiple of 64, nothing
 // is appended); a wavefront then walks whole 64-token blocks (pairs of steps), rebuilding its query operands per block.
 // PAGED: the planes are pools of pages; a step's data is found through this sequence's row of the page table.
@@ -864,18 +918,32 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   const kvq_cache& cache = a.cache;
   const uint16_t* __restrict__ q = a.q;
   const int q_bf16 = a.q_bf16, q_heads = a.q_heads, out_dtype = a.out_dtype;
-  const int steps_per_split = a.steps_per_split;
   const float softmax_scale = a.softmax_scale;
   float* __restrict__ ws = a.ws;
   void* __restrict__ out = a.out;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int split = blockIdx.x, hk = blockIdx.y, b = blockIdx.z;
+  int split = blockIdx.x, b = blockIdx.z;
+  const int hk = blockIdx.y;
+  int steps_per_split = a.steps_per_split;
+  // this (batch, kv head)'s records: where the first lies and how far apart they are, this workgroup's one, and whether it
+  // is the only one (its result then goes straight to the output)
+  int n_rec = a.rec_splits, slot = 0, slot0 = 0;
+  int seq_len = a.seq_len;
+  bool have_len = a.seq_lens == nullptr;
+  if constexpr (!KSEQ) {
+    if (a.balance) {                               // (uniform)
+      slot = split + a.n_splits * b;
+      const Share sh = balanced_share<NW>(a.seq_lens, a.lens_offset, a.lens_bound, g.batch, a.n_splits, a.steps_per_split, slot, lane);
+      if (sh.b < 0) return;                        // more workgroups than parts
+      b = sh.b; split = sh.split; steps_per_split = sh.q; n_rec = sh.count; slot0 = sh.slot0;
+      seq_len = sh.len; have_len = true;
+    }
+  }
   const int bh = b * g.kv_heads + hk;
   // this sequence's length: its own when the caller gave per-sequence lengths, inside what the launch was planned for
-  int seq_len = a.seq_len;
-  if (a.seq_lens) {
+  if (!have_len) {
     int n = min(max(a.seq_lens[b] + a.lens_offset, 1), a.lens_bound);
     if (a.lens_mode == 1) n &= ~(a.lens_block - 1);         // a residual buffer of lens_block slots: the flushed blocks ...
     else if (a.lens_mode == 2) n &= a.lens_block - 1;       // ... or the tail in the buffer (either may be empty)
@@ -1239,6 +1307,11 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   if (grp == 0 && L.j == 0) { sm_m[wave][h] = st.m + (10.0f - p_shift<BV>()); sm_l[wave][h] = l; }
   __syncthreads();
 
+  // the counter of this (batch, kv head)'s records, read ahead by the thread that counts the workgroup in (see below)
+  unsigned long long* const word = reinterpret_cast<unsigned long long*>(ws + (int64_t)g.batch * q_heads * a.rec_splits * kRec) + bh;
+  unsigned long long seen = 0;
+  if (a.merge_here && tid == 0 && n_rec > 1) seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+
   // ---- merge the wavefronts; write a partial record, or the result when there is one split
   for (int idx = tid; idx < R * kHeadDim; idx += 64 * NW) {
     const int hh = idx / kHeadDim, d = idx % kHeadDim;
@@ -1271,51 +1344,88 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
       o = fmaf(fe, oe, o * f0);
       ll = fmaf(fe, le, ll * f0);
     }
-    if (a.rec_splits == 1) {
+    if (n_rec == 1) {
       const float val = o / ll;
       if (g.rotate_v) { sm_o[0][hh][d] = val; continue; }      // (only this thread touches element (hh, d))
       store_out(out, out_dtype, hq * kHeadDim + d, val);
     } else {
       // (device-scope stores: the record is read by a workgroup on another part of the chip, whose nearest cache is
       // not this one)
-      float* rec = ws + (hq * a.rec_splits + a.rec_base + split) * kRec;
+      float* rec = ws + (a.balance ? ((int64_t)slot * g.kv_heads + hk) * r_act + hh : hq * a.rec_splits + a.rec_base + split) * kRec;
       store_device(rec + d, o);
       if (d == 0) { store_device(rec + kHeadDim, M); store_device(rec + kHeadDim + 1, ll); }
     }
   }
-  bool wrote_rows = a.rec_splits == 1;               // this workgroup has left normalized rows (rotated values: in sm_o)
-  if (a.merge_tag != 0) {                            // uniform: the launch's workgroups merge their records themselves
-    // Two records: the workgroup that finishes last combines them.  Every workgroup exchanges the stream's word for this
-    // launch's tag, after its record stores have been performed; the one that finds the tag there is the second, and
-    // leaves a zero for a replay of the same launch.  Nobody waits for anybody.  Records and word are device-scope atomic
-    // accesses, which go past the caches that are private to a part of the chip; a device-scope FENCE is not used on
-    // purpose: it writes back and invalidates the whole second-level cache of the workgroup's part of the chip, under
-    // the streaming loads of every other workgroup there, and was measured to cost the 8B-layer step 10 us.  The order is
-    // carried by the wait below: a store is acknowledged when it has been performed, and a barrier alone does not wait
-    // for it.  Whatever the word held before this launch -- another launch's tag, or the bytes of a fresh workspace --
-    // differs from the tag.
+  bool wrote_rows = n_rec == 1;               // this workgroup has left normalized rows (rotated values: in sm_o)
+  if (a.merge_here && n_rec > 1) {                   // uniform: the launch's workgroups merge their records themselves
+    // The workgroup of a (batch, kv head) that finishes last combines its records.  Every workgroup counts itself in, after
+    // its record stores have been performed; the one that brings the count to n_rec reads all records back and leaves
+    // the count at zero.  Nobody waits for anybody.  Records and counter are device-scope atomic accesses, which go past
+    // the caches that are private to a part of the chip; a device-scope FENCE is not used on purpose: it writes back and
+    // invalidates the whole second-level cache of the workgroup's part of the chip, under the streaming loads of every
+    // other workgroup there, and was measured to cost the 8B-layer step 10 us.  The order is carried by the wait below: a
+    // store is acknowledged when it has been performed, and a barrier alone does not wait for it.
+    // A counter word is kMergeMark above a 16-bit count.  It may hold anything before the workspace's first launch: a word
+    // without the mark is replaced by "mark, 1" with a compare-and-swap, which one workgroup wins; from then on it has the
+    // mark, and counting in is one addition, whoever else is doing it at the same time.  (The word is read ahead, before the
+    // wavefronts are merged, so that looking at it first costs nothing.)
     __shared__ int sm_last;
     __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): this wavefront's record stores are performed
     __syncthreads();                                 // (and so are the other wavefronts')
     if (tid == 0) {
-      unsigned long long* word = reinterpret_cast<unsigned long long*>(ws + (int64_t)g.batch * q_heads * a.rec_splits * kRec) + bh;
-      const unsigned long long seen = __hip_atomic_exchange(word, a.merge_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      sm_last = seen == a.merge_tag;
-      if (seen == a.merge_tag) __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      unsigned long long before = 0;                 // the count before this workgroup
+      if ((seen & ~0xFFFFull) != kMergeMark &&
+          __hip_atomic_compare_exchange_strong(word, &seen, kMergeMark | 1ull, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+        before = 0;
+      } else {
+        before = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xFFFFull;
+      }
+      const int last = (int)before + 1 == n_rec;
+      if (last) __hip_atomic_store(word, kMergeMark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      sm_last = last;
     }
     __syncthreads();
     if (sm_last) {                                   // uniform over the workgroup
+      // records of this (batch, kv head): the first one's place and the distance to the next, in records
+      const int64_t rec0 = a.balance ? ((int64_t)slot0 * g.kv_heads + hk) * r_act : ((int64_t)b * q_heads + hk * r_act) * n_rec;
+      const int64_t rec_step = a.balance ? q_heads : 1, head_step = a.balance ? 1 : n_rec;
       for (int idx = tid; idx < r_act * kHeadDim; idx += 64 * NW) {
         const int hh = idx / kHeadDim, d = idx % kHeadDim;
         const int64_t hq = (int64_t)b * q_heads + hk * r_act + hh;
-        const float* r0 = ws + hq * 2 * kRec;
-        const float* r1 = r0 + kRec;
-        // (all loads in flight together; a record's maximum and sum are the same words for the 128 threads of a head)
-        const float m0 = load_device(r0 + kHeadDim), l0 = load_device(r0 + kHeadDim + 1), o0 = load_device(r0 + d);
-        const float m1 = load_device(r1 + kHeadDim), l1 = load_device(r1 + kHeadDim + 1), o1 = load_device(r1 + d);
-        const float M = fmaxf(m0, m1);
-        const float f0 = exp2f(m0 - M), f1 = exp2f(m1 - M);
-        const float o = fmaf(f1, o1, f0 * o0), ll = fmaf(f1, l1, f0 * l0);
+        const float* rec = ws + (rec0 + hh * head_step) * kRec;
+        // four records at a time, all 12 loads of a round in flight together (a record's maximum and sum are the same
+        // words for the 128 threads of a head); rounds are chained by a running maximum as in the main loop
+        float M = kNegBig, o = 0.f, ll = 0.f;
+        if (n_rec == 2) {                            // (uniform; the usual number)
+          const float* r1 = rec + rec_step * kRec;
+          const float m0 = load_device(rec + kHeadDim), l0 = load_device(rec + kHeadDim + 1), o0 = load_device(rec + d);
+          const float m1 = load_device(r1 + kHeadDim), l1 = load_device(r1 + kHeadDim + 1), o1 = load_device(r1 + d);
+          M = fmaxf(m0, m1);
+          const float f0 = exp2f(m0 - M), f1 = exp2f(m1 - M);
+          o = fmaf(f1, o1, f0 * o0); ll = fmaf(f1, l1, f0 * l0);
+        } else for (int s0 = 0; s0 < n_rec; s0 += 4) {
+          float ms[4], ls[4], os[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float* r2 = rec + min(s0 + j, n_rec - 1) * rec_step * kRec;
+            ms[j] = load_device(r2 + kHeadDim); ls[j] = load_device(r2 + kHeadDim + 1); os[j] = load_device(r2 + d);
+          }
+          float Mc = M;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            if (s0 + j >= n_rec) { ms[j] = kNegBig; ls[j] = 0.f; os[j] = 0.f; }
+            Mc = fmaxf(Mc, ms[j]);
+          }
+          const float fo = exp2f(M - Mc);
+          o *= fo; ll *= fo;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float f = exp2f(ms[j] - Mc);
+            o = fmaf(f, os[j], o);
+            ll = fmaf(f, ls[j], ll);
+          }
+          M = Mc;
+        }
         const float val = o / ll;
         if (g.rotate_v) sm_o[0][hh][d] = val;
         else store_out(out, out_dtype, hq * kHeadDim + d, val);
@@ -1482,9 +1592,9 @@ hipError_t launch_one(const DecodeArgs& a, const DecodePlan& plan, hipStream_t s
   hipError_t e;
   e = a.g.page_shift ? launch_sets<BK, BV, R, BF, KSEQ, true>(a, plan, grid, stream)
                      : launch_sets<BK, BV, R, BF, KSEQ, false>(a, plan, grid, stream);
-  // the records of this launch are all there is: merge them, in the launch itself where that pays (merge_tag), else
+  // the records of this launch are all there is: merge them, in the launch itself where that pays (merge_here), else
   // here (otherwise the caller adds launches and merges)
-  if (e != hipSuccess || a.rec_splits == 1 || a.rec_splits != plan.n_splits || a.merge_tag != 0) return e;
+  if (e != hipSuccess || a.rec_splits == 1 || a.rec_splits != plan.n_splits || a.merge_here) return e;
   launch_merge(a.ws, a.out, a.out_dtype, a.g.batch * a.q_heads, a.rec_splits, rot_v_of(a.g), stream);
   return hipGetLastError();
 }
@@ -1617,22 +1727,24 @@ DecodePlan plan_decode(const Geom& g, int32_t seq_len) {
   return DecodePlan{splits, sps, nw};
 }
 
-// A number that tells one launch's count of finished workgroups from whatever the counter word held before (48 bits,
-// never 0).  A replayed graph launch carries the same number again: the last workgroup of a launch leaves the count at 0.
-static unsigned long long next_merge_tag() {
-  static std::atomic<unsigned long long> counter{0x9E3779B97F4Aull};
-  unsigned long long t;
-  do { t = counter.fetch_add(0x632BE59BD9B5ull, std::memory_order_relaxed) & 0xFFFFFFFFFFFFull; } while (t == 0);
-  return t;
-}
+// Where the launch's own workgroups merge the records instead of a second launch: up to four of them (the shapes that are
+// bound by their launches).  Counting in, after the wait for the record stores, and reading the records back cost the last
+// workgroup about what a dependent launch costs: two records (1024 tokens of 8 heads) 9.2 us this way, 15.7 with the merge
+// kernel when this was first measured; four (the 8B layer at B=8) 18.5 against 18.8 us at 8192 tokens, 13.5 against 13.9 at
+// 4096; eight (B=4, 8192 tokens) 14.7 against 13.7, and 33 records (B=1, 131071 tokens) 34 against 28 us.
+constexpr int kMergeHereMost = 4;
+static int merge_here_for(int records) { return records >= 2 && records <= kMergeHereMost; }
 
-// Where the launch's own workgroups merge the records (two splits: the shapes that are bound by their launches; the 1 MiB
-// cache of one sequence of 8 heads and 1024 tokens steps in 11.5 us this way and in 15.7 us with the merge kernel).  With
-// four records and more the merge kernel is the faster way: the device-scope accesses of the counting and of reading
-// the records back cost the last workgroup two trips to memory of 1.5 to 2 us each, as many as the second kernel
-// needs, on top of slower record stores (measured: 22.4 against 20.9 us on the 8B layer's four splits, 64 against 30 us
-// with 32 splits, where the workgroups' increments of one counter also queue up behind each other).
-static unsigned long long merge_tag_for(int records) { return records == 2 ? next_merge_tag() : 0ull; }
+// Whether a launch over sequences of different lengths deals its workgroups out by the lengths (balanced_share).  It needs
+// splits to deal out (below 256 streams), and work that outweighs looking at all the lengths first, 0.7 us in every
+// workgroup: 16 sequences of 8 kv heads between 600 and 16001 tokens, K4V4 in 64-token pages, 32.6 us (39.5 without), 12 of
+// 64 heads between 2000 and 30000, K4V2, 47.8 (62.1), 16 between 300 and 4000 15.3 (16.0); all lengths equal, 16 x 8192, 27.8
+// (27.0) and 16 x 16384, 49.4 (48.8).  With four splits it takes longer sequences: 8 between 1000 and 16000 20.7 (23.1), but
+// between 3000 and 8000 17.0 (16.5); with eight it loses (4 sequences up to 8000: 14.4 against 12.3).
+static bool balance_pays(const Geom& g, const DecodePlan& plan) {
+  if (g.batch < 2 || g.batch > 64 || plan.n_splits < 2 || plan.n_splits > 4) return false;
+  return plan.steps_per_split >= (plan.n_splits == 2 ? 6 : 12) * plan.waves_per_wg;
+}
 
 hipError_t launch_decode_attention(const Geom& g, const kvq_cache& c, const void* q, int q_dtype, int32_t q_heads,
                                    int32_t seq_len, float softmax_scale, void* out, int out_dtype, float* workspace,
@@ -1648,7 +1760,7 @@ hipError_t launch_decode_attention(const Geom& g, const kvq_cache& c, const void
   a.ws = workspace; a.out = out; a.out_dtype = out_dtype;
   a.n_splits = plan.n_splits; a.steps_per_split = plan.steps_per_split;
   a.rec_splits = plan.n_splits; a.rec_base = 0;
-  a.merge_tag = 0;
+  a.merge_here = 0;
   if (g.resid) {
     // a residual buffer: flushed blocks from the codes (plan; channel-wise or token-wise keys), the newest tokens from
     // the buffer by the unquantized kernel, all partial records merged at the end
@@ -1666,7 +1778,7 @@ hipError_t launch_decode_attention(const Geom& g, const kvq_cache& c, const void
     hipError_t e = hipSuccess;
     if (n_flushed) {
       a.seq_len = n_flushed; a.rec_splits = records; a.rec_base = 0; a.lens_mode = 1;
-      a.merge_tag = !tail ? merge_tag_for(records) : 0;     // (a launch that writes every record may merge them itself)
+      a.merge_here = !tail && merge_here_for(records);     // (a launch that writes every record may merge them itself)
 #define KVQ_CASE(BK_, BV_) \
       if (g.bits_k == BK_ && g.bits_v == BV_) e = KVQ_CAT(launch_decode_inst_, BK_, BV_)(R, a, plan, stream);
       KVQ_FOR_EACH_PAIR(KVQ_CASE)
@@ -1675,7 +1787,7 @@ hipError_t launch_decode_attention(const Geom& g, const kvq_cache& c, const void
     }
     if (tail) {
       DecodeArgs t = a;
-      t.merge_tag = 0;
+      t.merge_here = 0;
       t.g.axis_k = KVQ_AXIS_HEAD_DIM; t.g.bits_k = t.g.bits_v = 16; t.g.g_k = t.g.g_v = kHeadDim; t.g.ng_k = t.g.ng_v = 1;
       t.g.rotate_k = 0;                                    // (the buffer holds the input rows: their scores take q itself)
       t.g.resid = 0; t.g.seq_g = 0;
@@ -1695,7 +1807,8 @@ hipError_t launch_decode_attention(const Geom& g, const kvq_cache& c, const void
     return e;
   }
   a.lens_mode = 0; a.lens_bound = seq_len; a.lens_block = 1;
-  a.merge_tag = merge_tag_for(a.rec_splits);
+  a.balance = seq_lens != nullptr && balance_pays(g, plan);
+  a.merge_here = a.balance || merge_here_for(a.rec_splits);
   if (app) {
     a.k_new = (const uint16_t*)app->k_new; a.v_new = (const uint16_t*)app->v_new;
     a.in_bf16 = app->in_dtype == KVQ_BF16 ? 1 : 0; a.nsb = app->stride_b; a.nsh = app->stride_h;

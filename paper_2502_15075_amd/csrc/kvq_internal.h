@@ -102,6 +102,9 @@ struct DecodeArgs {
   // into its flushed blocks (lens_mode 1: n rounded down to the buffer's length, possibly 0) or its residual tail (lens_mode 2:
   // n modulo that length, possibly 0); a workgroup with nothing to read writes an empty record.  lens_mode 0: n as it is.
   int32_t lens_mode, lens_bound, lens_block;   // lens_block: the buffer's slots (a power of two)
+  // != 0 (with seq_lens): the launch's n_splits * batch workgroups per kv head are dealt out to the sequences by their
+  // lengths instead of n_splits each; workgroup w of a kv head writes the records of slot w
+  int32_t balance;
   float* ws; void* out; int out_dtype;
   int32_t n_splits, steps_per_split;
   // partial records: a workgroup writes record rec_base + split of rec_splits per (batch, query head); rec_splits == 1
@@ -110,11 +113,10 @@ struct DecodeArgs {
   // != 0 (only with rec_splits == 1): record 0 of extra_splits per (batch, query head) in the workspace, complete
   // before this launch starts, is merged into this launch's result
   int32_t extra_splits;
-  // != 0: this launch writes all rec_splits records of every stream and merges them itself (the workgroup that finishes
-  // a stream last does it; the streams' counters, one 64-bit word per (batch, kv head), follow the records in the
-  // workspace); the number tells this launch's counts from what the words held before.  0: records are merged by
-  // merge_kernel, or there is one record and nothing to merge.
-  unsigned long long merge_tag;
+  // != 0: this launch writes all records of every (batch, kv head) and merges them itself (the workgroup that finishes one
+  // last does it; the counters, one 64-bit word per (batch, kv head), follow the records in the workspace).  0: records are
+  // merged by merge_kernel, or there is one record and nothing to merge.
+  int32_t merge_here;
   // fused decode step: the token at position seq_len-1 is quantized from k_new/v_new ([B][H_kv][D], element strides
   // nsb, nsh) by the workgroup that owns the last step, before it is read.  k_new == nullptr: plain attention.
   const uint16_t* k_new; const uint16_t* v_new; int in_bf16; int64_t nsb, nsh;

@@ -2111,3 +2111,92 @@ def test_paged_walks_longer_than_the_staged_page_numbers(kvq, T):
         kvq.decode_attention(one, cache, q[b:b + 1].contiguous(), 512, scale, want, ws)
         worst = max(worst, float((out[b] - want[0]).norm() / want.norm()))
     assert worst < 2e-3 + (33 / T * 20 if T % 512 else 0), worst
+
+
+@pytest.mark.parametrize("B,H,R,bk,bv,page,rotv,out_dtype", [(16, 8, 4, 4, 2, 0, 0, torch.float32), (16, 8, 1, 4, 4, 64, 0, torch.bfloat16),
+                                                            (64, 2, 2, 2, 4, 0, 1, torch.float32), (8, 8, 8, 4, 2, 256, 0, torch.float32),
+                                                            (2, 40, 5, 8, 8, 0, 0, torch.float32)])
+def test_ragged_batch_dealt_out_by_its_lengths(kvq, B, H, R, bk, bv, page, rotv, out_dtype):
+    """Batches of 64 to 128 streams, whose workgroups go to the sequences by length (two to four splits planned): against
+    attention over each sequence on its own, which takes the other route and is held to the oracle above.  Lengths at the
+    edges of steps and of the bound, all equal, one long among short ones; a workspace full of ones, of the counters'
+    own mark, and as the calls before left it.  Both sides round their weights to binary16: the bar of the oracle tests."""
+    D, scale = 128, 1 / math.sqrt(128)
+    T = 3500 if B * H > 100 else 8200
+    kw = dict(page_tokens=page, n_pages=B * -(-T // page) + 1) if page else {}
+    L = kvq.Layout(B, H, T, D, bk, bv, 64, 64, raw_dtype=kvq.KVQ_BF16, rotate_v=rotv, signs_v=(7, 8, 9, 10) if rotv else (0,) * 4, **kw)
+    one = replace(L, batch=1)
+    K, V, q = synth.make_kvq(31, B, H, H * R, T, D, dtype=torch.bfloat16, device="cuda", sigma_k=1.0)
+    cache = kvq.Cache(L, fill=0)
+    if page:
+        cache.page_table = torch.randperm(L.n_pages, device="cuda")[:L.n_pages - 1].to(torch.int32).view(B, -1).contiguous()
+    kvq.quantize_append(L, cache, K, V, 0)
+    need = kvq.decode_workspace_bytes(L, H * R, T)
+    rng = np.random.RandomState(B)
+    cases = [np.full(B, T), np.r_[T, np.ones(B - 1)], np.r_[np.full(B - 1, 33), T - 1], rng.randint(1, T + 1, B),
+             np.r_[0, T + 9, rng.choice([31, 32, 33, 64, 65, 1000, T], B - 2)], rng.randint(1, T // 3, B)]
+    marks = [0xFF, None, 0, None, 0x5A, None]
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    alone = torch.empty(B, H * R, D, dtype=torch.float32, device="cuda")
+    ws1 = torch.empty(max(16, kvq.decode_workspace_bytes(one, H * R, T)), dtype=torch.uint8, device="cuda")
+    for lens, fill in zip(cases, marks):
+        if fill is not None:
+            ws.fill_(fill)
+        dev = torch.tensor(lens.astype(np.int64), device="cuda").to(torch.int32)
+        got = [kvq.decode_attention_varlen(L, cache, q, dev, T, scale, torch.empty(B, H * R, D, dtype=out_dtype, device="cuda"), ws)
+               for _ in range(3)]
+        assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+        for b in range(B):
+            if page:
+                sub = kvq.Cache.__new__(kvq.Cache)
+                sub.layout, sub.planes, sub.v_scale_exp = one, cache.planes, cache.v_scale_exp.view(B, -1)[b].contiguous()
+                sub.page_table = cache.page_table[b:b + 1].contiguous()
+            else:
+                sub = cache.batch_element(b, one)
+            n = int(min(max(lens[b], 1), T))
+            kvq.decode_attention(one, sub, q[b:b + 1].contiguous(), n, scale, alone[b:b + 1], ws1)
+        err = (got[0].float() - alone).abs().amax(-1) / alone.abs().amax(-1)
+        assert float(err.max()) < 2e-3 + (2.0 ** -8 if out_dtype == torch.bfloat16 else 0), (lens, float(err.max()))
+    # the fused step: the same lengths as positions, planes as sequential appends leave them
+    lens = np.r_[T, rng.randint(1, T + 1, B - 2), 1]
+    pos = torch.tensor(lens - 1, device="cuda").to(torch.int32)
+    kn, vn = (torch.randn(B, H, D, device="cuda").to(torch.bfloat16) for _ in range(2))
+    out = torch.empty(B, H * R, D, dtype=torch.float32, device="cuda")
+    kvq.decode_step_varlen(L, cache, kn, vn, pos, T - 1, q, scale, out, ws)
+    planes = [p.clone() for p in cache.planes[:4]]
+    for b in range(B):
+        if page:
+            sub = kvq.Cache.__new__(kvq.Cache)
+            sub.layout, sub.planes, sub.v_scale_exp = one, cache.planes, cache.v_scale_exp.view(B, -1)[b].contiguous()
+            sub.page_table = cache.page_table[b:b + 1].contiguous()
+        else:
+            sub = cache.batch_element(b, one)
+        kvq.quantize_append(one, sub, kn[b:b + 1, :, None], vn[b:b + 1, :, None], int(lens[b]) - 1)
+        kvq.decode_attention(one, sub, q[b:b + 1].contiguous(), int(lens[b]), scale, alone[b:b + 1], ws1)
+    assert all(torch.equal(a, p) for a, p in zip(planes, cache.planes))
+    err = (out - alone).abs().amax(-1) / alone.abs().amax(-1)
+    assert float(err.max()) < 2e-3, float(err.max())
+
+
+def test_ragged_batch_replayed_from_a_hip_graph(kvq):
+    """The counters behind the records return to where a replay finds them, and the lengths are read at every replay."""
+    B, H, R, T, D = 16, 8, 2, 3500, 128
+    L = kvq.Layout(B, H, T, D, 4, 2)
+    K, V, q = synth.make_kvq(8, B, H, H * R, T, D, dtype=torch.float16, device="cuda", sigma_k=1.0)
+    cache = kvq.Cache(L, fill=0)
+    kvq.quantize_append(L, cache, K, V, 0)
+    ws = torch.full((kvq.decode_workspace_bytes(L, H * R, T),), 0xFF, dtype=torch.uint8, device="cuda")
+    lens = torch.full((B,), T, dtype=torch.int32, device="cuda")
+    out, ref = (torch.empty(B, H * R, D, dtype=torch.float32, device="cuda") for _ in range(2))
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(stream), torch.cuda.graph(graph, stream=stream):
+        kvq.decode_attention_varlen(L, cache, q, lens, T, 0.1, out, ws)
+    ws2 = torch.zeros_like(ws)
+    for seed in range(5):
+        lens.copy_(torch.randint(1, T + 1, (B,), generator=torch.Generator().manual_seed(seed)).to(torch.int32))
+        graph.replay()
+        kvq.decode_attention_varlen(L, cache, q, lens, T, 0.1, ref, ws2)
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref), seed
