@@ -773,6 +773,25 @@ __device__ __forceinline__ void append_one(const DecodeArgs& a, int bh, int sbh,
   for (int e = 0; e < 8; ++e) hat[(is_v ? kHeadDim : 0) + d0 + e] = fmaf((float)code_value(codes[e]), sc, zp);   // (exact product: one rounding)
 }
 
+// The same for the slots of a residual buffer, which hold the rows as they came: 16 bytes per lane of the key row, and the
+// value row's patterns at their places in the token's 32-token block.
+__device__ __forceinline__ void append_patterns(const uint8_t* key_row, uintptr_t vblk, int u, int lane, u32x4 raw, bool bf16, float* hat) {
+  const bool is_v = lane >= 16;
+  const int d0 = 8 * (lane & 15);
+  const uint32_t rw[4] = {raw.x, raw.y, raw.z, raw.w};
+  if (!is_v) {
+    store_global<u32x4>(reinterpret_cast<uintptr_t>(key_row) + 2 * d0, raw);
+  } else {
+    int dw, bit;
+    v_field(u, d0, 16, &dw, &bit);
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      store_global<uint16_t>(vblk + 4 * (uintptr_t)(dw + 4 * e) + (bit >> 3), (uint16_t)(rw[e >> 1] >> (16 * (e & 1))));
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) hat[(is_v ? kHeadDim : 0) + d0 + e] = widen16((uint16_t)(rw[e >> 1] >> (16 * (e & 1))), bf16);
+}
+
 // Second half of the fused append: thread d < 128 inserts channel d's code of the new token into its 32-bit word of
 // the 32-token block (the other fields of the word belong to other tokens of the block and keep their bits).  With
 // 2-bit fields channels d and d+16 share a word (with 1-bit fields d, d+16, d+32 and d+48), so the thread of the first
@@ -980,7 +999,8 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   // ---- what this launch reads.  A fused decode step does not read its new token (position seq_len - 1) back from the
   // cache: the workgroup that owns that position quantizes and stores it, and adds it to the attention as one more
   // partial record, computed from the reconstruction it holds in registers (no store -> load round trip, no fence).
-  constexpr bool kCanAppend = !RAWK && !RAWV && !KSEQ;
+  // (Both tensors unquantized: the kernel that reads residual buffers.  The new token then goes to its slot as it is.)
+  constexpr bool kCanAppend = RAWK == RAWV && !KSEQ;
   const bool fused = kCanAppend && a.k_new != nullptr;
   const int n_att = fused ? seq_len - 1 : seq_len;        // tokens attended through the cache planes
   const int n_steps = (n_att + 31) >> 5;
@@ -1059,6 +1079,7 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
     nraw = load_global<u32x4>(nsrc);
     vblk = reinterpret_cast<uintptr_t>(cache.v_codes) + (uintptr_t)(bh_base * g.vc_stream + (t_new >> 5) * (int64_t)(512 * BV));
     u_new = (int)(t_new & 31);
+    if constexpr (!RAWV)
 #pragma unroll
     for (int t = 0; t < 2; ++t) {                  // channels lane and lane + 64
       const bool own_lo = app_wave && field_owner<VLO_>(lane + 64 * t);
@@ -1114,6 +1135,8 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
       const uint32_t rw[4] = {raw.x, raw.y, raw.z, raw.w};
       if constexpr (RAWK) {
         if (item < R * 16) *reinterpret_cast<u32x4_lds*>(q_lds + hh * 256 + (o & 3) * 64 + (o >> 2) * 16) = raw;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) xq[t][e] = widen16((uint16_t)(rw[e >> 1] >> (16 * (e & 1))), q_is_bf16);   // (a fused step's logit)
       } else {
         float (&x)[8] = xq[t];
 #pragma unroll
@@ -1171,8 +1194,13 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   // value row), which the merge below adds to the wavefronts' records.  All of it stays inside the wavefront.
   if constexpr (kCanAppend) {
     if (app_wave) {                                // uniform
-      if (lane < 32) append_one<BK, BV>(a, PAGED ? 0 : bh, bh, lane, nraw, sm_vnew, t_new, &sm_hat[0][0]);
+      if constexpr (RAWV) {
+        if (lane < 32) append_patterns(L.kc + t_new * (2 * kHeadDim), vblk, u_new, lane, nraw, a.in_bf16 != 0, &sm_hat[0][0]);
+      } else {
+        if (lane < 32) append_one<BK, BV>(a, PAGED ? 0 : bh, bh, lane, nraw, sm_vnew, t_new, &sm_hat[0][0]);
+      }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      if constexpr (!RAWV)
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         const int d = lane + 64 * t;
@@ -1794,6 +1822,10 @@ hipError_t launch_decode_attention(const Geom& g, const kvq_cache& c, const void
       t.g.t_cap = RL; t.g.page_shift = 0; t.cache.page_table = nullptr;     // (the buffers are per sequence, never paged)
       t.g.kc_stream = t.g.vc_stream = (int64_t)RL * kHeadDim * 2; t.g.km_stream = t.g.vm_stream = 0;
       t.cache.k_codes = c.k_resid; t.cache.v_codes = c.v_resid; t.cache.k_meta = t.cache.v_meta = nullptr;
+      if (app) {                                           // (the buffer's newest token comes with this launch)
+        t.k_new = (const uint16_t*)app->k_new; t.v_new = (const uint16_t*)app->v_new;
+        t.in_bf16 = app->in_dtype == KVQ_BF16 ? 1 : 0; t.nsb = app->stride_b; t.nsh = app->stride_h;
+      }
       t.seq_len = tail; t.n_splits = 1; t.steps_per_split = 4; t.lens_mode = 2;
       t.rec_splits = records; t.rec_base = records - 1;
       if (tail_merges) { t.rec_splits = 1; t.rec_base = 0; t.extra_splits = records; }

@@ -116,9 +116,11 @@ constexpr float kRotScale = 0.08838834764831845f;   // binary32(1/sqrt(128))
 
 // The 8 sign bits of the channels of lane16 (bit e set: channel 8*lane16 + e is negated).
 __device__ __forceinline__ uint32_t rot_sign_bits(const uint32_t signs[4], int lane16) {
-  // (two selects by value: a four-way choice becomes branches)
-  const uint32_t lo = (lane16 & 4) ? signs[1] : signs[0], hi = (lane16 & 4) ? signs[3] : signs[2];
-  return (((lane16 & 8) ? hi : lo) >> (8 * (lane16 & 3))) & 0xFFu;
+  // (a four-way choice, which becomes branches: two-way selects between words of the argument block become vector loads
+  // from it, which the compiler moves to the top of the kernel)
+  const int w = lane16 >> 2;
+  const uint32_t word = w == 0 ? signs[0] : w == 1 ? signs[1] : w == 2 ? signs[2] : signs[3];
+  return (word >> (8 * (lane16 & 3))) & 0xFFu;
 }
 
 // Value of x in the lane a data-parallel-primitive control word selects (quad permutes, mirrors and rotations of a 16-lane
