@@ -21,7 +21,7 @@ template <int BK, int BV, bool BF, int SPAN>
 __global__ __launch_bounds__(256) void quantize_append_kernel(Geom g, kvq_cache c, const uint16_t* __restrict__ k_new,
                                                               const uint16_t* __restrict__ v_new, int64_t sb, int64_t sh,
                                                               int64_t st, int32_t pos, int32_t n_new, int32_t chain) {
-  constexpr int kSpan = SPAN;                      // (shadows the 64-token span of the other kernels in this file)
+  constexpr int kSpan = SPAN;                      // (shadows the 64-token span of kvq_stage.h)
   constexpr int NR = SPAN / 16;                    // rows per thread and span
   __shared__ __attribute__((aligned(16))) uint8_t vstage[stage_total<BV, SPAN>()];
   const int tid = threadIdx.x;
@@ -50,6 +50,9 @@ __global__ __launch_bounds__(256) void quantize_append_kernel(Geom g, kvq_cache 
     }
   };
 
+  // (formed once: inside the loop over the spans they cost a bulk append 2 %, also one that does not rotate:
+  // 64 x 8 heads x 2048 tokens K4V2 246.7 us against 242.0)
+  const uint32_t signs_k = rot_sign_bits(g.signs_k, lane16), signs_v = rot_sign_bits(g.signs_v, lane16);
   uint4 kraw[NR], vraw[NR], knext[NR], vnext[NR];
   load_span(blk_first, ~0u, kraw, vraw);
   for (int blk = blk_first; blk < blk_end; ++blk) {
@@ -79,7 +82,7 @@ __global__ __launch_bounds__(256) void quantize_append_kernel(Geom g, kvq_cache 
           float x[8];
 #pragma unroll
           for (int e = 0; e < 8; ++e) x[e] = widen16((uint16_t)(rw[e >> 1] >> (16 * (e & 1))), BF);
-          if (g.rotate_k) rotate8(x, lane16, rot_sign_bits(g.signs_k, lane16));   // whole 16-lane rows are here together
+          if (g.rotate_k) rotate8(x, lane16, signs_k);   // whole 16-lane rows are here together
           uint32_t codes[8];
           uint16_t S, Z;
           quantize8(x, BK, lpg_k, codes, &S, &Z);
@@ -99,7 +102,7 @@ __global__ __launch_bounds__(256) void quantize_append_kernel(Geom g, kvq_cache 
           float x[8];
 #pragma unroll
           for (int e = 0; e < 8; ++e) x[e] = widen16((uint16_t)(rw[e >> 1] >> (16 * (e & 1))), BF);
-          if (g.rotate_v) rotate8(x, lane16, rot_sign_bits(g.signs_v, lane16));
+          if (g.rotate_v) rotate8(x, lane16, signs_v);
           uint16_t S, Z;
           quantize8(x, BV, lpg_v, codes, &S, &Z);
           if ((lane16 & (lpg_v - 1)) == 0) {
