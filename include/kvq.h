@@ -51,7 +51,8 @@
  * combined with it; axis_v stays KVQ_AXIS_HEAD_DIM.  With rotate_k (Sec. 5.3's key-only rotation on this back-end) the
  * buffer keeps the input rows, a flush quantizes R k of every row of the block, and attention scores the flushed tokens
  * with binary16(R q) and the tail with q itself.  Attention needs a query of raw_dtype (KVQ_ERR_UNSUPPORTED otherwise);
- * kvq_decode_step is the append followed by the attention (several launches).  With per-sequence lengths
+ * kvq_decode_step writes the bytes of that append (fused into the launch over the buffer, or launched ahead when the
+ * token completes a block).  With per-sequence lengths
  * (kvq_decode_attention_varlen, kvq_decode_step_varlen) every sequence has its own count of appended tokens, its own
  * flushed blocks and its own tail in its residual buffer; kvq_decode_step_varlen appends sequence b's token at pos[b]
  * (= its count so far; in_dtype = raw_dtype).  kvq_dequantize and
@@ -228,7 +229,8 @@ kvq_status kvq_decode_attention_static(const kvq_layout* layout, const kvq_cache
 /* One autoregressive decode step (Sec. 4: the cache grows by one quantized token per generated token): quantize the new
  * token's K/V row of every (b, h_kv) into position pos -- same bytes as kvq_quantize_append with n_new = 1 -- then
  * attend over tokens [0, pos].  Token-wise keys: the append is fused into the attention kernel (one launch, plus the
- * merge launch when the sequence is split).  Channel-wise keys: the append kernel, then the attention launches.
+ * merge launch when the sequence is split into more parts than the launch merges itself).  With a residual buffer: the
+ * launch that attends to the buffer stores the token there; a token that completes a block is appended by a launch of its own first.
  * A cache with an unquantized tensor (bits == 16 for keys, values or both) has no fused step (KVQ_ERR_UNSUPPORTED):
  * call kvq_quantize_append with n_new = 1, then kvq_decode_attention.
  *   k_new, v_new   [B][H_kv][D] of in_dtype (KVQ_F16 / KVQ_BF16), element strides given, D contiguous.

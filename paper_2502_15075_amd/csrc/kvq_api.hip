@@ -249,8 +249,8 @@ kvq_status kvq_decode_step(const kvq_layout* layout, const kvq_cache* cache, con
   if (kvq::has_residual(*layout)) {
     // The new token goes to the residual buffer.  Short of a full block the launch that attends to the buffer stores it
     // there (8 x 8 heads, 8192 + 37 tokens, rotated keys: 26.5 us with an append launch in front, 24.7 without; 40 tokens of 8
-    // heads 11.4 and 8.2); the token
-    // that completes a block flushes it, in a launch in front of the attention.  Everything is checked before anything runs.
+    // heads 11.4 and 8.2); the token that completes a block flushes it, in a launch in front of the attention.  Everything
+    // is checked before anything runs.
     kvq_status st = decode_check(layout, cache, q, q_dtype, q_heads, pos + 1, softmax_scale, out, out_dtype, workspace,
                                  workspace_bytes, false);
     if (st != KVQ_OK) return st;
@@ -259,8 +259,7 @@ kvq_status kvq_decode_step(const kvq_layout* layout, const kvq_cache* cache, con
       const kvq::AppendOne app{k_new, v_new, (int)in_dtype, stride_b, stride_h};
       return decode_launch(layout, cache, q, q_dtype, q_heads, pos + 1, softmax_scale, out, out_dtype, workspace, &app, stream);
     }
-    st = kvq_quantize_append(layout, cache, k_new, v_new, in_dtype, stride_b, stride_h, layout->head_dim, pos, 1,
-                                        stream);
+    st = kvq_quantize_append(layout, cache, k_new, v_new, in_dtype, stride_b, stride_h, layout->head_dim, pos, 1, stream);
     if (st != KVQ_OK) return st;
     return decode_common(layout, cache, q, q_dtype, q_heads, pos + 1, softmax_scale, out, out_dtype, workspace,
                          workspace_bytes, nullptr, stream);

@@ -149,7 +149,7 @@ template <int M> __device__ __forceinline__ void butterfly_lanes(float x[8], int
 }
 
 // (The exchanges between lanes are register permutes.  Through the LDS permute unit, 32 of them per row octet, each followed by
-// its wait, a rotated append of 8 x 8 heads x 8192 tokens (K4V2) took 80.7 us, like this 73.7.)
+// its wait, a rotated append of 8 x 8 heads x 8192 tokens (K4V2) took 83.3 us, now 70.2 (7 of the 13 by the permutes).)
 __device__ __forceinline__ void hadamard8x16(float x[8], int lane16) {
 #pragma clang fp contract(off)
 #pragma unroll
