@@ -179,7 +179,12 @@ kvq_status kvq_residual_bytes(const kvq_layout* layout, size_t bytes_out[2]);
  * split-sequence pass.  May be 0 (enough (b, h_kv) streams to fill the chip without splitting the sequence); then the
  * workspace pointer may be NULL.  Never shrinks as seq_len grows: a workspace sized once for the longest sequence
  * serves every shorter one.  Touches no device memory; the split plan follows the compute-unit count of the CURRENT
- * device (256 when no device is usable), so size the workspace with the device current that the decode calls run on. */
+ * device (256 when no device is usable), so size the workspace with the device current that the decode calls run on.
+ * What the workspace holds before a call does not matter.  Behind the records lie counters of the workgroups that have
+ * finished; every call numbers itself and takes a counter without its number for zero, so calls that overlap on one
+ * workspace race on it (their results are undefined) and calls after them are right again.  A call captured into a graph
+ * keeps its number: after another call has overlapped with a replay on the same workspace, clear the workspace before the
+ * next replay. */
 kvq_status kvq_decode_workspace_bytes(const kvq_layout* layout, int32_t q_heads, int32_t seq_len,
                                       size_t* bytes_out);
 
@@ -219,8 +224,10 @@ kvq_status kvq_decode_attention(const kvq_layout* layout, const kvq_cache* cache
  *   - a call that needs more than KVQ_STATIC_SCRATCH_BYTES of records (kvq_decode_workspace_bytes tells) returns
  *     KVQ_ERR_STATIC_SCRATCH and launches nothing;
  *   - every call on one GPU shares that GPU's array, whatever its stream: calls that can overlap in time on one GPU
- *     race on it (calls on one stream, or ordered by events, do not).  The array keeps the last call's records; nothing
- *     in it has to start at zero, because every record a call reads is one that the same call wrote. */
+ *     race on it (calls on one stream, or ordered by events, do not), and only they: the array keeps the last call's
+ *     records and counters, but every record a call reads is one that the same call wrote, and a counter without the
+ *     call's own number counts as zero (kvq_decode_workspace_bytes), so nothing in it has to be cleared.  Where that
+ *     would be needed, for graphs whose replays overlap with other calls, use kvq_decode_attention and a workspace. */
 #define KVQ_STATIC_SCRATCH_BYTES ((size_t)4 << 20)
 kvq_status kvq_decode_attention_static(const kvq_layout* layout, const kvq_cache* cache, const void* q,
                                        kvq_dtype q_dtype, int32_t q_heads, int32_t seq_len, float softmax_scale,

@@ -716,9 +716,6 @@ __device__ __forceinline__ void compute_step(const StepRegs<BK, BV>& r, const u3
   }
 }
 
-// The upper 48 bits of a counter word behind the records that has been used before (see the merge in decode_kernel).
-constexpr unsigned long long kMergeMark = 0x9E3779B97F4A0000ull;
-
 // Record layout in the workspace: [b][hq][split] x (kHeadDim + 4) floats = acc[128], m, l, 0, 0.
 constexpr int kRec = kHeadDim + 4;
 
@@ -1335,10 +1332,14 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   if (grp == 0 && L.j == 0) { sm_m[wave][h] = st.m + (10.0f - p_shift<BV>()); sm_l[wave][h] = l; }
   __syncthreads();
 
-  // the counter of this (batch, kv head)'s records, read ahead by the thread that counts the workgroup in (see below)
-  unsigned long long* const word = reinterpret_cast<unsigned long long*>(ws + (int64_t)g.batch * q_heads * a.rec_splits * kRec) + bh;
-  unsigned long long seen = 0;
-  if (a.merge_here && tid == 0 && n_rec > 1) seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // (the ring's last loads, which nothing reads, have come back: said here, or the compiler waits where their registers are used
+  // again, inside the loop below, whose second turn -- more than 4 heads -- would then wait for the first one's record
+  // stores: 10.73 us instead of 10.44 for 1500 tokens of 8 x 8 heads)
+  __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0)
+  // the counter of this (batch, kv head)'s records (kvq_merge_count.h); the maximum is on its way while the wavefronts are merged
+  MergeWord* const word = reinterpret_cast<MergeWord*>(ws + (int64_t)g.batch * q_heads * a.rec_splits * kRec) + bh;
+  if (a.merge_tag != 0 && tid == 0 && n_rec > 1)
+    (void)__hip_atomic_fetch_max(word, a.merge_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
   // ---- merge the wavefronts; write a partial record, or the result when there is one split
   for (int idx = tid; idx < R * kHeadDim; idx += 64 * NW) {
@@ -1385,31 +1386,29 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
     }
   }
   bool wrote_rows = n_rec == 1;               // this workgroup has left normalized rows (rotated values: in sm_o)
-  if (a.merge_here && n_rec > 1) {                   // uniform: the launch's workgroups merge their records themselves
+  if (a.merge_tag != 0 && n_rec > 1) {               // uniform: the launch's workgroups merge their records themselves
     // The workgroup of a (batch, kv head) that finishes last combines its records.  Every workgroup counts itself in, after
-    // its record stores have been performed; the one that brings the count to n_rec reads all records back and leaves
-    // the count at zero.  Nobody waits for anybody.  Records and counter are device-scope atomic accesses, which go past
-    // the caches that are private to a part of the chip; a device-scope FENCE is not used on purpose: it writes back and
-    // invalidates the whole second-level cache of the workgroup's part of the chip, under the streaming loads of every
-    // other workgroup there, and was measured to cost the 8B-layer step 10 us.  The order is carried by the wait below: a
-    // store is acknowledged when it has been performed, and a barrier alone does not wait for it.
-    // A counter word is kMergeMark above a 16-bit count.  It may hold anything before the workspace's first launch: a word
-    // without the mark is replaced by "mark, 1" with a compare-and-swap, which one workgroup wins; from then on it has the
-    // mark, and counting in is one addition, whoever else is doing it at the same time.  (The word is read ahead, before the
-    // wavefronts are merged, so that looking at it first costs nothing.)
+    // its record stores have been performed; the one that brings the count to n_rec reads all records back.  Nobody waits for
+    // anybody.  The counter and its rules: kvq_merge_count.h.
+    // Records and counter are device-scope atomic accesses, which go past the caches that are private to a part of the
+    // chip; a device-scope FENCE is not used on purpose: it writes back and invalidates the whole second-level cache of the
+    // workgroup's part of the chip, under the streaming loads of every other workgroup there, and was measured to cost the
+    // 8B-layer step 10 us.  The order is carried by the wait below: a store is acknowledged when it has been performed, and a
+    // barrier alone does not wait for it.
     __shared__ int sm_last;
     __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): this wavefront's record stores are performed
     __syncthreads();                                 // (and so are the other wavefronts')
     if (tid == 0) {
-      unsigned long long before = 0;                 // the count before this workgroup
-      if ((seen & ~0xFFFFull) != kMergeMark &&
-          __hip_atomic_compare_exchange_strong(word, &seen, kMergeMark | 1ull, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-        before = 0;
-      } else {
-        before = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xFFFFull;
+      MergeWord before = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (merge_unmarked(before, a.merge_tag)) {     // (rare; a swap fails only because another workgroup got on)
+        MergeWord seen = before + 1;
+        while (merge_unmarked(seen, a.merge_tag) &&
+               !__hip_atomic_compare_exchange_strong(word, &seen, a.merge_tag | 1ull, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {}
+        before = merge_unmarked(seen, a.merge_tag) ? a.merge_tag
+                                                   : __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
-      const int last = (int)before + 1 == n_rec;
-      if (last) __hip_atomic_store(word, kMergeMark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const bool last = merge_last(before, n_rec);
+      if (last) __hip_atomic_store(word, a.merge_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       sm_last = last;
     }
     __syncthreads();
@@ -1620,9 +1619,9 @@ hipError_t launch_one(const DecodeArgs& a, const DecodePlan& plan, hipStream_t s
   hipError_t e;
   e = a.g.page_shift ? launch_sets<BK, BV, R, BF, KSEQ, true>(a, plan, grid, stream)
                      : launch_sets<BK, BV, R, BF, KSEQ, false>(a, plan, grid, stream);
-  // the records of this launch are all there is: merge them, in the launch itself where that pays (merge_here), else
+  // the records of this launch are all there is: merge them, in the launch itself where that pays (merge_tag), else
   // here (otherwise the caller adds launches and merges)
-  if (e != hipSuccess || a.rec_splits == 1 || a.rec_splits != plan.n_splits || a.merge_here) return e;
+  if (e != hipSuccess || a.rec_splits == 1 || a.rec_splits != plan.n_splits || a.merge_tag != 0) return e;
   launch_merge(a.ws, a.out, a.out_dtype, a.g.batch * a.q_heads, a.rec_splits, rot_v_of(a.g), stream);
   return hipGetLastError();
 }
@@ -1761,7 +1760,13 @@ DecodePlan plan_decode(const Geom& g, int32_t seq_len) {
 // kernel when this was first measured; four (the 8B layer at B=8) 18.5 against 18.8 us at 8192 tokens, 13.5 against 13.9 at
 // 4096; eight (B=4, 8192 tokens) 14.7 against 13.7, and 33 records (B=1, 131071 tokens) 34 against 28 us.
 constexpr int kMergeHereMost = 4;
-static int merge_here_for(int records) { return records >= 2 && records <= kMergeHereMost; }
+// The number such a launch carries (0: it does not merge): a greater one than all launches before it.  A replayed graph launch
+// carries its number again.
+static MergeWord next_merge_tag() {
+  static std::atomic<MergeWord> launches{0};
+  return merge_tag(launches.fetch_add(1, std::memory_order_relaxed));
+}
+static MergeWord merge_tag_for(int records) { return records >= 2 && records <= kMergeHereMost ? next_merge_tag() : 0; }
 
 // Whether a launch over sequences of different lengths deals its workgroups out by the lengths (balanced_share).  It needs
 // splits to deal out (below 256 streams), and work that outweighs looking at all the lengths first, 0.7 us in every
@@ -1788,7 +1793,7 @@ hipError_t launch_decode_attention(const Geom& g, const kvq_cache& c, const void
   a.ws = workspace; a.out = out; a.out_dtype = out_dtype;
   a.n_splits = plan.n_splits; a.steps_per_split = plan.steps_per_split;
   a.rec_splits = plan.n_splits; a.rec_base = 0;
-  a.merge_here = 0;
+  a.merge_tag = 0;
   if (g.resid) {
     // a residual buffer: flushed blocks from the codes (plan; channel-wise or token-wise keys), the newest tokens from
     // the buffer by the unquantized kernel, all partial records merged at the end
@@ -1806,7 +1811,7 @@ hipError_t launch_decode_attention(const Geom& g, const kvq_cache& c, const void
     hipError_t e = hipSuccess;
     if (n_flushed) {
       a.seq_len = n_flushed; a.rec_splits = records; a.rec_base = 0; a.lens_mode = 1;
-      a.merge_here = !tail && merge_here_for(records);     // (a launch that writes every record may merge them itself)
+      a.merge_tag = !tail ? merge_tag_for(records) : 0;     // (a launch that writes every record may merge them itself)
 #define KVQ_CASE(BK_, BV_) \
       if (g.bits_k == BK_ && g.bits_v == BV_) e = KVQ_CAT(launch_decode_inst_, BK_, BV_)(R, a, plan, stream);
       KVQ_FOR_EACH_PAIR(KVQ_CASE)
@@ -1815,7 +1820,7 @@ hipError_t launch_decode_attention(const Geom& g, const kvq_cache& c, const void
     }
     if (tail) {
       DecodeArgs t = a;
-      t.merge_here = 0;
+      t.merge_tag = 0;
       t.g.axis_k = KVQ_AXIS_HEAD_DIM; t.g.bits_k = t.g.bits_v = 16; t.g.g_k = t.g.g_v = kHeadDim; t.g.ng_k = t.g.ng_v = 1;
       t.g.rotate_k = 0;                                    // (the buffer holds the input rows: their scores take q itself)
       t.g.resid = 0; t.g.seq_g = 0;
@@ -1840,7 +1845,7 @@ hipError_t launch_decode_attention(const Geom& g, const kvq_cache& c, const void
   }
   a.lens_mode = 0; a.lens_bound = seq_len; a.lens_block = 1;
   a.balance = seq_lens != nullptr && balance_pays(g, plan);
-  a.merge_here = a.balance || merge_here_for(a.rec_splits);
+  a.merge_tag = a.balance ? next_merge_tag() : merge_tag_for(a.rec_splits);
   if (app) {
     a.k_new = (const uint16_t*)app->k_new; a.v_new = (const uint16_t*)app->v_new;
     a.in_bf16 = app->in_dtype == KVQ_BF16 ? 1 : 0; a.nsb = app->stride_b; a.nsh = app->stride_h;

@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "kvq.h"
+#include "kvq_merge_count.h"
 
 namespace kvq {
 
@@ -114,9 +115,9 @@ struct DecodeArgs {
   // before this launch starts, is merged into this launch's result
   int32_t extra_splits;
   // != 0: this launch writes all records of every (batch, kv head) and merges them itself (the workgroup that finishes one
-  // last does it; the counters, one 64-bit word per (batch, kv head), follow the records in the workspace).  0: records are
-  // merged by merge_kernel, or there is one record and nothing to merge.
-  int32_t merge_here;
+  // last does it; the counters, one 64-bit word per (batch, kv head), follow the records in the workspace), and this is its
+  // number, in place above the count.  0: records are merged by merge_kernel, or there is one record and nothing to merge.
+  MergeWord merge_tag;
   // fused decode step: the token at position seq_len-1 is quantized from k_new/v_new ([B][H_kv][D], element strides
   // nsb, nsh) by the workgroup that owns the last step, before it is read.  k_new == nullptr: plain attention.
   const uint16_t* k_new; const uint16_t* v_new; int in_bf16; int64_t nsb, nsh;

@@ -2200,3 +2200,54 @@ def test_ragged_batch_replayed_from_a_hip_graph(kvq):
         kvq.decode_attention_varlen(L, cache, q, lens, T, 0.1, ref, ws2)
         torch.cuda.synchronize()
         assert torch.equal(out, ref), seed
+
+
+def _counters(ws, B, Hkv, Hq, records):
+    """The words behind `records` records per query head, one per (batch, kv head): all of them are what a launch that
+    merges its records itself counts on (a launch that does not leaves them alone)."""
+    at = B * Hq * records * (128 + 4) * 4
+    return ws[at:at + 8 * B * Hkv].view(torch.int64)
+
+
+@pytest.mark.parametrize("B,H,R,T,records,ragged", [(1, 8, 2, 1000, 2, False), (1, 8, 8, 1500, 3, False), (8, 8, 4, 3000, 4, False),
+                                                    (16, 8, 2, 3500, 2, True)])
+def test_counts_that_earlier_calls_left_are_ignored(kvq, B, H, R, T, records, ragged):
+    """Launches that merge their records themselves count their workgroups in on words of the workspace.  A wrong count that is
+    left there (calls that overlapped on the workspace), words full of ones, and a replay from a graph after a later
+    call on the same workspace: none of them changes a result."""
+    L = kvq.Layout(B, H, T, 128, 4, 2, raw_dtype=kvq.KVQ_BF16)
+    K, V, q = synth.make_kvq(12, B, H, H * R, T, dtype=torch.bfloat16, device="cuda", sigma_k=1.0)
+    q2 = torch.randn(q.shape, device="cuda", generator=torch.Generator("cuda").manual_seed(2)).to(torch.bfloat16)
+    cache = kvq.Cache(L, fill=0)
+    kvq.quantize_append(L, cache, K, V, 0)
+    lens = torch.randint(T // 2, T + 1, (B,), generator=torch.Generator().manual_seed(3)).to(torch.int32).cuda()
+    ws = torch.zeros(kvq.decode_workspace_bytes(L, H * R, T), dtype=torch.uint8, device="cuda")
+    words = _counters(ws, B, H, H * R, records)
+
+    def call(query, out=None):
+        out = torch.empty(B, H * R, 128, dtype=torch.float32, device="cuda") if out is None else out
+        if ragged:
+            return kvq.decode_attention_varlen(L, cache, query, lens, T, 0.1, out, ws)
+        return kvq.decode_attention(L, cache, query, T, 0.1, out, ws)
+
+    want = call(q2)
+    assert words.ne(0).any() and (ragged or words.ne(0).all())           # (a sequence that is one part counts nothing)
+    for left in (lambda w: w + 1, lambda w: w + 2, lambda w: torch.full_like(w, -1), lambda w: w | 0xFFFF, torch.zeros_like):
+        call(q)
+        words.copy_(left(words))
+        assert torch.equal(call(q2), want)
+        assert torch.equal(call(q2), want)
+    graph, out = torch.cuda.CUDAGraph(), torch.zeros_like(want)
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream), torch.cuda.graph(graph, stream=stream):
+        call(q2, out)
+    for _ in range(3):
+        call(q)
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
