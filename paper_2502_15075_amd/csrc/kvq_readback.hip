@@ -145,7 +145,7 @@ __device__ __forceinline__ void store_rows(void* out, int64_t o, int t, int t0, 
     f32x4* w = reinterpret_cast<f32x4*>(lds);
     w[2 * lane] = a;
     w[2 * lane + 1] = b;
-    __builtin_amdgcn_wave_barrier();               // (LDS is in order within a wavefront; the compiler keeps the order too)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");     // (LDS is in order within a wavefront; this binds the compiler too)
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       const f32x4 v = w[64 * k + lane];
@@ -153,7 +153,7 @@ __device__ __forceinline__ void store_rows(void* out, int64_t o, int t, int t0, 
       if (t + r >= t0 && t + r < t1)
         __builtin_nontemporal_store((f32x4a4)v, reinterpret_cast<f32x4a4*>((float*)out + o + r * kHeadDim + 4 * (lane & 31)));
     }
-    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   } else {
     const int r = lane >> 4;
     if (t + r < t0 || t + r >= t1) return;
