@@ -2251,3 +2251,22 @@ def test_counts_that_earlier_calls_left_are_ignored(kvq, B, H, R, T, records, ra
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("B,H", [(32, 8), (257, 1), (48, 8), (385, 1), (65, 8)])
+def test_reconstruction_error_of_many_streams(kvq, B, H):
+    """512 to 1040 streams and tensors: at the ends of the range where a stream's blocks go to two workgroups, and on both
+    sides of it; 11 blocks, the last one partly filled.  Against binary64 sums over the reconstruction (differences,
+    squares and a thread's sum of 8 are binary32: at most 10 roundings of 2^-24, 6e-7)."""
+    T, D = 339, 128
+    L = kvq.Layout(B, H, T, D, 4, 2, raw_dtype=kvq.KVQ_BF16)
+    K, V, _ = synth.make_kvq(6, B, H, H, T, D, dtype=torch.bfloat16, device="cuda")
+    cache = kvq.Cache(L, fill=0)
+    kvq.quantize_append(L, cache, K, V, 0)
+    k, v = (torch.empty(B, H, T, D, dtype=torch.float32, device="cuda") for _ in range(2))
+    kvq.dequantize(L, cache, 0, T, k, v)
+    want = torch.stack([((x.double() - y.double()) ** 2).sum((-1, -2)) for x, y in ((K, k), (V, v))], dim=-1)
+    got = kvq.reconstruction_error(L, cache, K, V, 0, torch.empty(B, H, 2, dtype=torch.float64, device="cuda"))
+    assert float(((got - want) / want).abs().max()) < 1e-6
+    alone = kvq.reconstruction_error(L, cache, K, None, 0, torch.empty(B, H, 2, dtype=torch.float64, device="cuda"))
+    assert float(((alone - want)[..., 0] / want[..., 0]).abs().max()) < 1e-6 and not alone[..., 1].any()
