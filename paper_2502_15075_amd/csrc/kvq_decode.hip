@@ -1754,19 +1754,23 @@ DecodePlan plan_decode(const Geom& g, int32_t seq_len) {
   return DecodePlan{splits, sps, nw};
 }
 
-// Where the launch's own workgroups merge the records instead of a second launch: up to four of them (the shapes that are
-// bound by their launches).  Counting in, after the wait for the record stores, and reading the records back cost the last
-// workgroup about what a dependent launch costs: two records (1024 tokens of 8 heads) 9.2 us this way, 15.7 with the merge
-// kernel when this was first measured; four (the 8B layer at B=8) 18.5 against 18.8 us at 8192 tokens, 13.5 against 13.9 at
-// 4096; eight (B=4, 8192 tokens) 14.7 against 13.7, and 33 records (B=1, 131071 tokens) 34 against 28 us.
-constexpr int kMergeHereMost = 4;
+// Where the launch's own workgroups merge the records instead of a second launch.  Counting in, after the wait for the
+// record stores, and reading the records back cost the last workgroup about what a dependent launch costs, and more the more
+// it has to read: up to four records of at most 4 heads, two of 8 (a workgroup's threads take 8 heads in two turns).
+// Measured in turn, this way against the merge launch, K4V2, 1 to 10 sequences of 2 to 8 kv heads, 1000 to 12000 tokens:
+// 3 and 4 records of 1 head 2 to 10 % faster this way (4 x 8 heads x 2000 tokens 8.9 against 9.6 us), of 8 heads up to 4 %
+// slower (10.7 against 10.3); 5 to 8 records of 1 head from 2 % faster to 4 % slower, of 4 heads from 3 % faster to 5 %
+// slower, of 8 heads 3 to 14 % slower (4 x 8 heads x 2500 tokens 11.8 against 10.4 us).
+constexpr int kMergeHereMost = 4, kMergeHereMostWide = 2;
 // The number such a launch carries (0: it does not merge): a greater one than all launches before it.  A replayed graph launch
 // carries its number again.
 static MergeWord next_merge_tag() {
   static std::atomic<MergeWord> launches{0};
   return merge_tag(launches.fetch_add(1, std::memory_order_relaxed));
 }
-static MergeWord merge_tag_for(int records) { return records >= 2 && records <= kMergeHereMost ? next_merge_tag() : 0; }
+static MergeWord merge_tag_for(int records, int R) {
+  return records >= 2 && records <= (R > 4 ? kMergeHereMostWide : kMergeHereMost) ? next_merge_tag() : 0;
+}
 
 // Whether a launch over sequences of different lengths deals its workgroups out by the lengths (balanced_share).  It needs
 // splits to deal out (below 256 streams), and work that outweighs looking at all the lengths first, 0.7 us in every
@@ -1811,7 +1815,7 @@ hipError_t launch_decode_attention(const Geom& g, const kvq_cache& c, const void
     hipError_t e = hipSuccess;
     if (n_flushed) {
       a.seq_len = n_flushed; a.rec_splits = records; a.rec_base = 0; a.lens_mode = 1;
-      a.merge_tag = !tail ? merge_tag_for(records) : 0;     // (a launch that writes every record may merge them itself)
+      a.merge_tag = !tail ? merge_tag_for(records, R) : 0;     // (a launch that writes every record may merge them itself)
 #define KVQ_CASE(BK_, BV_) \
       if (g.bits_k == BK_ && g.bits_v == BV_) e = KVQ_CAT(launch_decode_inst_, BK_, BV_)(R, a, plan, stream);
       KVQ_FOR_EACH_PAIR(KVQ_CASE)
@@ -1845,7 +1849,7 @@ hipError_t launch_decode_attention(const Geom& g, const kvq_cache& c, const void
   }
   a.lens_mode = 0; a.lens_bound = seq_len; a.lens_block = 1;
   a.balance = seq_lens != nullptr && balance_pays(g, plan);
-  a.merge_tag = a.balance ? next_merge_tag() : merge_tag_for(a.rec_splits);
+  a.merge_tag = a.balance ? next_merge_tag() : merge_tag_for(a.rec_splits, R);
   if (app) {
     a.k_new = (const uint16_t*)app->k_new; a.v_new = (const uint16_t*)app->v_new;
     a.in_bf16 = app->in_dtype == KVQ_BF16 ? 1 : 0; a.nsb = app->stride_b; a.nsh = app->stride_h;

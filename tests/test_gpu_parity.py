@@ -2209,7 +2209,7 @@ def _counters(ws, B, Hkv, Hq, records):
     return ws[at:at + 8 * B * Hkv].view(torch.int64)
 
 
-@pytest.mark.parametrize("B,H,R,T,records,ragged", [(1, 8, 2, 1000, 2, False), (1, 8, 8, 1500, 3, False), (8, 8, 4, 3000, 4, False),
+@pytest.mark.parametrize("B,H,R,T,records,ragged", [(1, 8, 8, 1000, 2, False), (1, 8, 2, 1500, 3, False), (8, 8, 4, 3000, 4, False),
                                                     (16, 8, 2, 3500, 2, True)])
 def test_counts_that_earlier_calls_left_are_ignored(kvq, B, H, R, T, records, ragged):
     """Launches that merge their records themselves count their workgroups in on words of the workspace.  A wrong count that is
@@ -2270,3 +2270,25 @@ def test_reconstruction_error_of_many_streams(kvq, B, H):
     assert float(((got - want) / want).abs().max()) < 1e-6
     alone = kvq.reconstruction_error(L, cache, K, None, 0, torch.empty(B, H, 2, dtype=torch.float64, device="cuda"))
     assert float(((alone - want)[..., 0] / want[..., 0]).abs().max()) < 1e-6 and not alone[..., 1].any()
+
+
+@pytest.mark.parametrize("R,T,records,merges", [(4, 1500, 3, True), (4, 2000, 4, True), (4, 2500, 5, False), (8, 1000, 2, True),
+                                                (8, 1500, 3, False), (5, 2000, 4, False)])
+def test_which_launches_merge_their_records_themselves(kvq, R, T, records, merges):
+    """Two to four records of up to 4 heads (padded to a power of two), two of 8: a launch that merges them counts on the words
+    behind the records, one that leaves them to a second launch does not touch those.  Against attention over the
+    reconstruction in binary64, to the bar of the oracle tests."""
+    B, H, D, scale = 2, 4, 128, 1 / math.sqrt(128)
+    L = kvq.Layout(B, H, T, D, 4, 2, raw_dtype=kvq.KVQ_BF16)
+    K, V, q = synth.make_kvq(14, B, H, H * R, T, D, dtype=torch.bfloat16, device="cuda", sigma_k=1.0)
+    cache = kvq.Cache(L, fill=0)
+    kvq.quantize_append(L, cache, K, V, 0)
+    ws = torch.zeros(kvq.decode_workspace_bytes(L, H * R, T), dtype=torch.uint8, device="cuda")
+    out = kvq.decode_attention(L, cache, q, T, scale, torch.empty(B, H * R, D, dtype=torch.float32, device="cuda"), ws)
+    words = _counters(ws, B, H, H * R, records)
+    assert words.ne(0).all() if merges else words.eq(0).all()
+    k, v = (torch.empty(B, H, T, D, dtype=torch.float32, device="cuda") for _ in range(2))
+    kvq.dequantize(L, cache, 0, T, k, v)
+    p = torch.softmax(q.double().view(B, H, R, D) @ k.double().transpose(-1, -2).contiguous() * scale, dim=-1)
+    want = (p @ v.double()).view(B, H * R, D)
+    assert _rel_err(out.cpu().numpy(), want.cpu().numpy()) < TOL
