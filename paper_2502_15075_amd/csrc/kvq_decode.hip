@@ -852,8 +852,10 @@ __device__ __forceinline__ void store_unrotated_row(const float* row, int lane16
 // end have nothing to do while those of the longest run on.  Instead all workgroups of a kv head (slots 0 .. slots - 1)
 // are dealt out by the lengths: sequence b gets ceil(N_b / q) of them, q steps each, with the smallest q (of 64 evenly
 // spaced ones) for which they are enough.  Every wavefront works that out for itself from the lengths (at most 64, one per
-// lane); the answer depends on nothing else, so all workgroups agree.  Lengths that leave less than a sixteenth of the
-// plan's steps empty keep the plan's q, without the search.
+// lane); the answer depends on nothing else, so all workgroups agree.  Where the plan's q leaves fewer than an eighth of the
+// workgroups without a part, it stays, without the search: a smaller one would need more parts for the long sequences than
+// there are left, and looking for it costs 0.6 to 0.9 us (16 sequences of 8 kv heads, K4V2, 14000 to 16384 tokens: 45.7 us
+// and 46.4 with the search, 45.5 when nothing is dealt out; 2800 to 4000 tokens 16.2, 17.0 and 16.2).
 __device__ __forceinline__ int wave_scan(int v) {  // sum over the lanes up to and including this one
   v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);     // row_shr 1, 2, 4, 8
   v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
@@ -877,8 +879,8 @@ __device__ __forceinline__ Share balanced_share(const int32_t* __restrict__ seq_
   };
   Share s;
   s.q = q_max;                                     // (always enough: no sequence is longer than the plan's)
-  const int total = __builtin_amdgcn_readlane(wave_scan(n), 63), full = ((bound + 31) >> 5) * batch;
-  if (total < full - full / 16) {                  // (uniform)
+  int mine = parts(q_max), end = wave_scan(mine);
+  if (8 * (slots - __builtin_amdgcn_readlane(end, 63)) >= slots) {        // (uniform)
     int lo = 1, hi = 64;                           // q = q_max i / 64, at least one unit (rounded up twice)
     while (lo < hi) {
       const int mid = (lo + hi) >> 1;
@@ -886,8 +888,8 @@ __device__ __forceinline__ Share balanced_share(const int32_t* __restrict__ seq_
       const bool enough = __builtin_amdgcn_readlane(wave_scan(parts(q)), 63) <= slots;
       if (enough) { hi = mid; s.q = q; } else { lo = mid + 1; }
     }
+    mine = parts(s.q); end = wave_scan(mine);
   }
-  const int mine = parts(s.q), end = wave_scan(mine);
   const unsigned long long hit = __ballot(slot >= end - mine && slot < end);       // (one lane, or none)
   const int l = hit ? __ffsll(hit) - 1 : 0;
   s.b = hit ? l : -1;
@@ -1773,11 +1775,13 @@ static MergeWord merge_tag_for(int records, int R) {
 }
 
 // Whether a launch over sequences of different lengths deals its workgroups out by the lengths (balanced_share).  It needs
-// splits to deal out (below 256 streams), and work that outweighs looking at all the lengths first, 0.7 us in every
-// workgroup: 16 sequences of 8 kv heads between 600 and 16001 tokens, K4V4 in 64-token pages, 32.6 us (39.5 without), 12 of
-// 64 heads between 2000 and 30000, K4V2, 47.8 (62.1), 16 between 300 and 4000 15.3 (16.0); all lengths equal, 16 x 8192, 27.8
-// (27.0) and 16 x 16384, 49.4 (48.8).  With four splits it takes longer sequences: 8 between 1000 and 16000 20.7 (23.1), but
-// between 3000 and 8000 17.0 (16.5); with eight it loses (4 sequences up to 8000: 14.4 against 12.3).
+// splits to deal out (below 256 streams), and work that outweighs looking at all the lengths first.  Both ways in turn,
+// K4V2, 16 sequences of 8 kv heads, dealt out (and not): lengths even between 512 and 8192 tokens 19.9 us (22.8), 1024 and
+// 16384 30.8 (35.9), 250 and 4000 14.5 (15.3), half of them 8192 and half 1024 19.9 (22.4); equal lengths 26.3 (26.2) and
+// 49.1 (49.0).  What still loses are batches in which a sixth to a third of the sequences are short, where the search runs and
+// finds next to nothing: 4 of 16 at 1024 tokens, the others 8192, 23.5 (22.7).  With more than two splits it takes longer
+// sequences: 8 between 1000 and 16000 19.8 (22.5), but between 3000 and 8000 17.0 (16.5 when this was first measured); with
+// eight splits it loses (4 sequences up to 8000: 14.4 against 12.3, then too).
 static bool balance_pays(const Geom& g, const DecodePlan& plan) {
   if (g.batch < 2 || g.batch > 64 || plan.n_splits < 2 || plan.n_splits > 4) return false;
   return plan.steps_per_split >= (plan.n_splits == 2 ? 6 : 12) * plan.waves_per_wg;

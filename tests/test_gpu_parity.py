@@ -2134,8 +2134,9 @@ def test_ragged_batch_dealt_out_by_its_lengths(kvq, B, H, R, bk, bv, page, rotv,
     need = kvq.decode_workspace_bytes(L, H * R, T)
     rng = np.random.RandomState(B)
     cases = [np.full(B, T), np.r_[T, np.ones(B - 1)], np.r_[np.full(B - 1, 33), T - 1], rng.randint(1, T + 1, B),
-             np.r_[0, T + 9, rng.choice([31, 32, 33, 64, 65, 1000, T], B - 2)], rng.randint(1, T // 3, B)]
-    marks = [0xFF, None, 0, None, 0x5A, None]
+             np.r_[0, T + 9, rng.choice([31, 32, 33, 64, 65, 1000, T], B - 2)], rng.randint(1, T // 3, B),
+             np.linspace(T * 0.8, T, B).astype(int)]
+    marks = [0xFF, None, 0, None, 0x5A, None, None]
     ws = torch.empty(need, dtype=torch.uint8, device="cuda")
     alone = torch.empty(B, H * R, D, dtype=torch.float32, device="cuda")
     ws1 = torch.empty(max(16, kvq.decode_workspace_bytes(one, H * R, T)), dtype=torch.uint8, device="cuda")
