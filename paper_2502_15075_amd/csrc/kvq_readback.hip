@@ -364,27 +364,31 @@ hipError_t launch_dequantize(const Geom& g, const kvq_cache& c, int32_t t0, int3
 
 // Reconstruction error.  One round of workgroups, 4 per compute unit, each walking its share of a stream's blocks; at most
 // 32 workgroups per stream and tensor, because they all add to one address (209 of them: 32 us for 6685 tokens of 8
-// heads, 32 of them: 12 us).  Measured, K4V2, 8 x 8 heads x 32768 tokens: 226 us = 5.8 TB/s (3, 5, 6, 7 per unit: 233, 239,
+// heads, 32 of them: 12 us), or one per 16 blocks where that is more, so that a long stream is not walked by few of them
+// (K4V2, one head, 65536 tokens: 60 us with 32, 33, 19 and 16 us with one per 32, 16 and 8 blocks; 4 heads keys alone 48,
+// 29, 23 and 27; 8 heads x 131072 122, and 115 with all three; the first version 56, 105 and 166).  Measured, K4V2, 8 x 8 heads x 32768 tokens: 226 us = 5.8 TB/s (3, 5, 6, 7 per unit: 233, 239,
 // 228, 237; 8 and 16 per unit, more than are resident at once: 251 and 243); 13 x 8 x 2378, K4V1: 36 us (5 to 7 per unit:
 // 33, 33, 35).  Before (one row at a time per thread, 8192 workgroups): 291 us, 40 us for the 6685 tokens, 50 us.
 // The share is rounded down, which leaves up to a third of the round empty, except where it would be one workgroup per
 // stream and tensor and leave a quarter or more empty: two are taken there, up to 6 per unit, all resident at once.  528
 // streams and tensors of 4096 tokens 135 us with two, 166 with one (152 before); 704: 166 and 170; 832: 219 and 212.
 // Rounded to the nearest, 176 to 448 streams and tensors lose up to 9 % (384: 20.4 against 18.7 us).
-constexpr int kErrPerUnit = 4, kErrPerStream = 32;
-constexpr int error_workgroups(int64_t pairs, int64_t round) {     // pairs of stream and tensor; workgroups of one round
+constexpr int kErrPerUnit = 4, kErrPerStream = 32, kErrBlocks = 16;
+constexpr int error_workgroups(int64_t pairs, int64_t round, int64_t blocks) {     // pairs of stream and tensor; workgroups of one round
   int64_t per = round / pairs;
   if (per <= 1) per = 4 * pairs <= 3 * round ? 2 : 1;
-  return (int)(per < kErrPerStream ? per : kErrPerStream);
+  const int64_t most = blocks / kErrBlocks > kErrPerStream ? blocks / kErrBlocks : kErrPerStream;
+  return (int)(per < most ? per : most);
 }
 constexpr bool error_rounds_are_full(int64_t round) {
   for (int64_t pairs = round / kErrPerStream; pairs <= round; ++pairs) {
-    const int64_t n = error_workgroups(pairs, round) * pairs;
+    const int64_t n = error_workgroups(pairs, round, 0) * pairs;
     if (3 * n < 2 * round || 2 * n > 3 * round) return false;
   }
   return true;
 }
 static_assert(error_rounds_are_full(1024) && error_rounds_are_full(4 * 304) && error_rounds_are_full(4 * 32), "two thirds of a round to one and a half");
+static_assert(error_workgroups(2, 1024, 2048) == 128 && error_workgroups(2, 1024, 209) == 32, "long streams take more than 32");
 
 hipError_t launch_reconstruction_error(const Geom& g, const kvq_cache& c, const void* k_ref, const void* v_ref,
                                        int ref_dtype, int64_t sb, int64_t sh, int64_t st, int32_t t0, int32_t t1,
@@ -396,7 +400,7 @@ hipError_t launch_reconstruction_error(const Geom& g, const kvq_cache& c, const 
   if (t1 == t0) return hipGetLastError();
   const int blocks = ((t1 - 1) >> 5) - (t0 >> 5) + 1;
   const int tensors = (k_ref ? 1 : 0) + (v_ref ? 1 : 0);
-  const int per = error_workgroups((int64_t)streams * tensors, (int64_t)kErrPerUnit * device_compute_units());
+  const int per = error_workgroups((int64_t)streams * tensors, (int64_t)kErrPerUnit * device_compute_units(), blocks);
   const int chain = (blocks + per - 1) / per;
   const dim3 grid((blocks + chain - 1) / chain, streams, tensors);
 #define KVQ_ERR_LAUNCH(BK_, BV_, S_)                                                                                     \

@@ -2254,12 +2254,12 @@ def test_counts_that_earlier_calls_left_are_ignored(kvq, B, H, R, T, records, ra
         assert torch.equal(out, want)
 
 
-@pytest.mark.parametrize("B,H", [(32, 8), (257, 1), (48, 8), (385, 1), (65, 8)])
-def test_reconstruction_error_of_many_streams(kvq, B, H):
+@pytest.mark.parametrize("B,H,T", [(32, 8, 339), (257, 1, 339), (48, 8, 339), (385, 1, 339), (65, 8, 339), (1, 1, 16416), (1, 3, 40001)])
+def test_reconstruction_error_of_many_streams_and_of_few(kvq, B, H, T):
     """512 to 1040 streams and tensors: at the ends of the range where a stream's blocks go to two workgroups, and on both
-    sides of it; 11 blocks, the last one partly filled.  Against binary64 sums over the reconstruction (differences,
+    sides of it; 11 blocks, the last one partly filled.  One and three long streams, which take more than 32 workgroups each.  Against binary64 sums over the reconstruction (differences,
     squares and a thread's sum of 8 are binary32: at most 10 roundings of 2^-24, 6e-7)."""
-    T, D = 339, 128
+    D = 128
     L = kvq.Layout(B, H, T, D, 4, 2, raw_dtype=kvq.KVQ_BF16)
     K, V, _ = synth.make_kvq(6, B, H, H, T, D, dtype=torch.bfloat16, device="cuda")
     cache = kvq.Cache(L, fill=0)
