@@ -41,12 +41,12 @@ __device__ __forceinline__ float rows_max(float x) {
 // KTOK: the keys of a flushed block are quantized row by row like the values (a residual buffer in front of token-wise
 // keys); otherwise channel by channel.
 // What bounds it: vector instructions (with rotated keys about 1300 per thread and 64-token block) and memory in about equal
-// parts.  Hence stores stream, rows are compared and rotated by register permutes, and a channel's scale, zero and
+// parts.  Hence stores stream (loads: see launch_sa), rows are compared and rotated by register permutes, and a channel's scale, zero and
 // reciprocal are formed once per workgroup instead of by every thread that holds the channel.  8 x 8 heads x 8229 tokens,
 // K4V2: with rotated keys 111 us before and 78 us now (4.2 TB/s), without 81 and 64 us.  (Several blocks per workgroup with
 // the next one's rows loaded ahead, which pays in quantize_append_kernel, costs this one its occupancy: 210 registers,
 // 115 us with rotated keys at 2 wavefronts per unit's SIMD, 126 at 3.)
-template <int BK, int BV, bool BF, bool KTOK, int RLT>
+template <int BK, int BV, bool BF, bool KTOK, int RLT, bool STREAM_IN>
 __global__ __launch_bounds__(256) void seq_append_kernel(Geom g, kvq_cache c, const uint16_t* __restrict__ k_new,
                                                          const uint16_t* __restrict__ v_new, int64_t sb, int64_t sh,
                                                          int64_t st, int32_t pos, int32_t n_new,
@@ -76,8 +76,13 @@ __global__ __launch_bounds__(256) void seq_append_kernel(Geom g, kvq_cache c, co
   for (int it = 0; it < NIT; ++it) {
     const int row = min(max(rg + 16 * it, lo), hi - 1);
     const int64_t src = (int64_t)b * sb + (int64_t)h * sh + ((int64_t)blk * RLT + row - pos) * st + d0;
-    kraw[it] = load_stream16(k_new + src);
-    vraw[it] = load_stream16(v_new + src);
+    if constexpr (STREAM_IN) {
+      kraw[it] = load_stream16(k_new + src);
+      vraw[it] = load_stream16(v_new + src);
+    } else {
+      kraw[it] = *reinterpret_cast<const uint4*>(k_new + src);
+      vraw[it] = *reinterpret_cast<const uint4*>(v_new + src);
+    }
   }
 #pragma unroll
   for (int it = 0; it < NIT; ++it) {
@@ -226,21 +231,38 @@ __global__ __launch_bounds__(256) void seq_append_kernel(Geom g, kvq_cache c, co
 }  // namespace
 
 namespace {
+// Whether the input rows are read by streaming loads.  An input of up to 256 MiB, the size of the last-level cache, may lie
+// there, where the kernel before left it, and streaming loads do not find it: 16 x 8 heads x 2048 tokens, K4V2 channel-wise, on
+// the same input 83.7 us with them and 70.3 without (on three inputs in turn, which the cache does not hold, 84.3 and
+// 83.9); 48 x 8 x 1000 81.8 and 64.6 (82.3 and 81.4).  Larger inputs gain from them: 8 x 8 x 8229, rotated, 76.8 and 78.5;
+// so do launches of up to two workgroups per unit, which all ask at once: 4 x 8 x 1024 on three inputs in turn 14.5 and
+// 15.1 (on the same one 13.9 and 13.4).
+constexpr int64_t kCacheBytes = (int64_t)256 << 20;
+bool stream_in(const Geom& g, int32_t n_new, dim3 grid) {
+  const int64_t bytes = (int64_t)g.batch * g.kv_heads * n_new * (2 * kHeadDim * 2);
+  return bytes > kCacheBytes || (int64_t)grid.x * grid.y <= 2 * device_compute_units();
+}
 // pos_arr != nullptr: one token per sequence at pos_arr[b] (then pos and n_new are 0 and 1)
+template <int BK, int BV, bool STREAM_IN>
+void launch_sa_in(const Geom& g, const kvq_cache& c, const void* k_new, const void* v_new, int in_dtype, int64_t sb, int64_t sh,
+                  int64_t st, int32_t pos, int32_t n_new, const int32_t* pos_arr, int32_t max_pos, dim3 grid, hipStream_t stream) {
+  const bool bf = in_dtype == KVQ_BF16, ktok = g.axis_k != KVQ_AXIS_SEQ;
+#define KVQ_SA_LAUNCH(BF_, KTOK_, RL_)                                                                                     \
+  hipLaunchKernelGGL((seq_append_kernel<BK, BV, BF_, KTOK_, RL_, STREAM_IN>), grid, dim3(256), 0, stream, g, c,            \
+                     (const uint16_t*)k_new, (const uint16_t*)v_new, sb, sh, st, pos, n_new, pos_arr, max_pos)
+  if (ktok) { if (bf) KVQ_SA_LAUNCH(true, true, 64); else KVQ_SA_LAUNCH(false, true, 64); }
+  else if (g.resid == 128) { if (bf) KVQ_SA_LAUNCH(true, false, 128); else KVQ_SA_LAUNCH(false, false, 128); }
+  else { if (bf) KVQ_SA_LAUNCH(true, false, 64); else KVQ_SA_LAUNCH(false, false, 64); }
+#undef KVQ_SA_LAUNCH
+}
 template <int BK, int BV>
 hipError_t launch_sa(const Geom& g, const kvq_cache& c, const void* k_new, const void* v_new, int in_dtype, int64_t sb,
                      int64_t sh, int64_t st, int32_t pos, int32_t n_new, const int32_t* pos_arr, int32_t max_pos,
                      hipStream_t stream) {
   const int first = pos / g.resid, last = (pos + n_new - 1) / g.resid;
-  dim3 grid(last - first + 1, g.batch * g.kv_heads);
-  const bool bf = in_dtype == KVQ_BF16, ktok = g.axis_k != KVQ_AXIS_SEQ;
-#define KVQ_SA_LAUNCH(BF_, KTOK_, RL_)                                                                                     \
-  hipLaunchKernelGGL((seq_append_kernel<BK, BV, BF_, KTOK_, RL_>), grid, dim3(256), 0, stream, g, c, (const uint16_t*)k_new, \
-                     (const uint16_t*)v_new, sb, sh, st, pos, n_new, pos_arr, max_pos)
-  if (ktok) { if (bf) KVQ_SA_LAUNCH(true, true, 64); else KVQ_SA_LAUNCH(false, true, 64); }
-  else if (g.resid == 128) { if (bf) KVQ_SA_LAUNCH(true, false, 128); else KVQ_SA_LAUNCH(false, false, 128); }
-  else { if (bf) KVQ_SA_LAUNCH(true, false, 64); else KVQ_SA_LAUNCH(false, false, 64); }
-#undef KVQ_SA_LAUNCH
+  const dim3 grid(last - first + 1, g.batch * g.kv_heads);
+  if (stream_in(g, n_new, grid)) launch_sa_in<BK, BV, true>(g, c, k_new, v_new, in_dtype, sb, sh, st, pos, n_new, pos_arr, max_pos, grid, stream);
+  else launch_sa_in<BK, BV, false>(g, c, k_new, v_new, in_dtype, sb, sh, st, pos, n_new, pos_arr, max_pos, grid, stream);
   return hipGetLastError();
 }
 template <int BK>

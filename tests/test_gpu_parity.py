@@ -2293,3 +2293,24 @@ def test_which_launches_merge_their_records_themselves(kvq, R, T, records, merge
     p = torch.softmax(q.double().view(B, H, R, D) @ k.double().transpose(-1, -2).contiguous() * scale, dim=-1)
     want = (p @ v.double()).view(B, H * R, D)
     assert _rel_err(out.cpu().numpy(), want.cpu().numpy()) < TOL
+
+
+@pytest.mark.parametrize("kw", [dict(axis_k=1), dict(resid_len=64), dict(axis_k=1, group_k=128, rotate_k=1, signs_k=SIGNS)])
+def test_buffered_appends_of_all_sizes_store_the_same_bytes(kvq, kw):
+    """Launches of up to two workgroups per compute unit and inputs of more than 256 MiB are read by streaming loads, those
+    between by ordinary ones: one call over a batch, in both of the larger sizes, against one call per sequence, which the
+    tests above hold to the oracle."""
+    for B, T in ((16, 600), (33, 4133)):
+        H = 8
+        L = kvq.Layout(B, H, T, 128, **dict(dict(bits_k=4, bits_v=2, raw_dtype=kvq.KVQ_BF16), **kw))
+        assert B * H * T * 1024 // 2 > 256 << 20 or T == 600
+        one = replace(L, batch=1)
+        g = torch.Generator("cuda").manual_seed(T)
+        K, V = (torch.randn(B, H, T, 128, device="cuda", generator=g, dtype=torch.bfloat16) for _ in range(2))
+        whole, single = kvq.Cache(L, fill=0x3C), kvq.Cache(L, fill=0x3C)
+        kvq.quantize_append(L, whole, K, V, 0)
+        for b in range(0, B, 1 if T == 600 else 4):
+            kvq.quantize_append(one, single.batch_element(b, one), K[b:b + 1], V[b:b + 1], 0)
+        for w, s in zip(whole.planes, single.planes):
+            w, s = w.view(B, -1), s.view(B, -1)
+            assert torch.equal(w[::1 if T == 600 else 4], s[::1 if T == 600 else 4])
