@@ -1398,6 +1398,7 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
     // 8B-layer step 10 us.  The order is carried by the wait below: a store is acknowledged when it has been performed, and a
     // barrier alone does not wait for it.
     __shared__ int sm_last;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");     // (costs nothing: keeps the compiler from moving a store behind the wait)
     __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): this wavefront's record stores are performed
     __syncthreads();                                 // (and so are the other wavefronts')
     if (tid == 0) {
