@@ -206,7 +206,9 @@ __device__ __forceinline__ float max2f(float a, float b) { float r; asm("v_max_f
 // (mx - mn) / levels with levels = 2^b - 1 in {1, 3, 7, 15, 63, 255}: with c = RN(1 / levels), q0 = RN(x c),
 // r = x - levels q0 (one fused multiply-add, exact), q1 = RN(q0 + r c) is the correctly rounded quotient (the classical
 // correction step for a correctly rounded reciprocal; checked against IEEE division for every non-negative finite
-// binary32 x and each of these divisors on a CPU).
+// binary32 x and each of these divisors on a CPU).  For x = -0 the result is +0, where a division would give -0: q0 is -0, r is
+// (-levels q0) + x = +0 + -0 = +0, and q1 = +0 c + -0 = +0.  The callers rest on that: a group of nothing but -0 has the
+// minimum +0 (normalized) and the maximum -0, their difference is -0, and its stored scale has to be +0.
 __device__ __forceinline__ float inv_levels(int bits) {
   return bits == 4 ? 1.0f / 15.0f : bits == 2 ? 1.0f / 3.0f : bits == 8 ? 1.0f / 255.0f
        : bits == 3 ? 1.0f / 7.0f : bits == 6 ? 1.0f / 63.0f : 1.0f;          // (constants: rounded by the compiler)
@@ -266,7 +268,7 @@ __device__ __forceinline__ void quantize8(const float x[8], int bits, int lanes_
   mn = mn + 0.0f;             // -0 -> +0, everything else as it is
   const float levels = (float)((1 << bits) - 1);
   float s32 = div_levels(mx - mn, levels, inv_levels(bits));
-  uint16_t sb = f32_to_f16_bits(s32);              // (+0 or positive: a difference of equal numbers is +0, and so is its quotient)
+  uint16_t sb = f32_to_f16_bits(s32);              // (+0 or positive, also for a difference of -0: see div_levels)
   uint16_t zb = f32_to_f16_bits(mn);
   float s = widen16(sb, false), z = widen16(zb, false);
   *S = sb; *Z = zb;
@@ -296,7 +298,7 @@ __device__ __forceinline__ void group_scale_zero(float mn, float mx, int bits, u
 #pragma clang fp contract(off)
   mn = mn + 0.0f;             // -0 -> +0, everything else as it is
   const float levels = (float)((1 << bits) - 1);
-  *S = f32_to_f16_bits(div_levels(mx - mn, levels, inv_levels(bits)));
+  *S = f32_to_f16_bits(div_levels(mx - mn, levels, inv_levels(bits)));      // (never -0: see div_levels)
   *Z = f32_to_f16_bits(mn);
 }
 

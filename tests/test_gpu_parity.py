@@ -2314,3 +2314,23 @@ def test_buffered_appends_of_all_sizes_store_the_same_bytes(kvq, kw):
         for w, s in zip(whole.planes, single.planes):
             w, s = w.view(B, -1), s.view(B, -1)
             assert torch.equal(w[::1 if T == 600 else 4], s[::1 if T == 600 else 4])
+
+
+@pytest.mark.parametrize("bk", [1, 2, 4, 8])
+def test_channelwise_groups_of_negative_zeros(kvq, oracle, bk):
+    """Channels of nothing but -0, of -0 and +0, and one with a negative minimum: scale and zero of the first two are stored
+    as +0, as the oracle has them."""
+    B, H, T = 1, 1, 64
+    x = np.zeros((B, H, T, 128), dtype=np.float32)
+    x[..., :40] = -0.0
+    x[:, :, ::2, 40:80] = -0.0
+    x[..., 80:] = np.random.default_rng(3).standard_normal((B, H, T, 48))
+    K = torch.from_numpy(x).to(torch.float16)
+    Lg = kvq.Layout(B, H, T, 128, bk, 4, axis_k=kvq.AXIS_SEQ)
+    Lo = oracle.Layout(B, H, T, 128, bk, 4, 64, 64, axis_k=1)
+    cache = kvq.Cache(Lg, fill=0x3C)
+    kvq.quantize_append(Lg, cache, K.cuda(), K.cuda(), 0)
+    planes = oracle.new_seq_planes(Lo, fill=0x3C)
+    oracle.seq_append(Lo, planes, synth.to_numpy_bits(K), synth.to_numpy_bits(K), 0, bf16=False)
+    torch.cuda.synchronize()
+    _assert_seq_planes_equal(cache, planes)
