@@ -17,7 +17,8 @@
 // once.  Each wavefront keeps a ring of steps in registers: after a step is computed its registers
 // are refilled with the step one ring length ahead, so several steps of streaming loads are always
 // in flight per wavefront.  Wavefronts merge through LDS, workgroups through a workspace of
-// (max, sum, acc) records and a small second kernel.
+// (max, sum, acc) records: a few are merged by the workgroup that finishes last, more by a small
+// second kernel (merge_tag_for says how many).
 //
 // Variants of the same kernel (template parameters): unquantized rows as operands (bits = 16), key
 // codes of 3 and 6 bits as a low and a high run with a query operand each, two column sets (8 heads
@@ -69,9 +70,9 @@ __device__ __forceinline__ float sum_over_groups(float x) {
 // ---- key codes: one lane holds 32 consecutive channels of one token (BK dwords) -------------
 // (Channels 32j .. 32j+31 in the lanes of row quarter j.  A row of 16-bit patterns is 256 bytes, of which a lane would hold
 // 4 neighbouring 16-byte pieces: every load instruction would touch every line of the tile and use a quarter of each.
-// There a lane's pieces lie 64 bytes apart instead, so that the 4 lanes of a row read 64 bytes in one piece
-// (k_lane_chan; any assignment of channels to slots is as good as another for the matrix product, as long as the query
-// operand follows it): the unquantized 8B layer at B=8, T=32768 takes 159 us = 6.74 TB/s where it took 201.  The same
+// There a lane's pieces lie 64 bytes apart instead, so that the 4 lanes of a row read 64 bytes in one piece: element x (0..31)
+// of row quarter j is channel 32 (x / 8) + 8 j + x % 8 (any assignment of channels to slots is as good as another for the
+// matrix product, as long as the query operand follows it): the unquantized 8B layer at B=8, T=32768 takes 159 us = 6.74 TB/s where it took 201.  The same
 // for the two pieces of 8-bit rows changes nothing (86.4 against 86.1 us for K8V8 there): lines are halves, not quarters.)
 // Matrix step m (0..3) consumes 8 of them; slot i of that step is channel k_slot_elem(m,i) of the
 // lane's 32, left at bit k of its 16-bit lane, i.e. read as code * 2^k * 2^-24, so the query operand of the slot is
@@ -97,10 +98,7 @@ template <int BK> __device__ __forceinline__ constexpr int k_slot_elem(int m, in
   return 16 * (m >> 1) + 4 * (m & 1) + v + 8 * x;  // BK == 2
 }
 template <int BK> constexpr int k_piece_stride() { return BK == 16 ? 64 : 16; }
-// Row channel of element x (0..31) of the lanes of row quarter j, and bytes from the row's start to their first piece.
-template <int BK> __device__ __forceinline__ constexpr int k_lane_chan(int j, int x) {
-  return BK == 16 ? 32 * (x >> 3) + 8 * j + (x & 7) : 32 * j + x;
-}
+// Bytes from the row's start to the first piece of the lanes of row quarter j.
 template <int BK> __device__ __forceinline__ constexpr int k_lane_offset(int j) { return j * (BK == 16 ? 16 : 4 * BK); }
 template <int BK> constexpr int k_default_base() { return BK == 2 ? 4 : BK == 1 ? 3 : 0; }
 template <int BK, int BASE = k_default_base<BK>()> __device__ __forceinline__ constexpr float k_slot_scale(int i) {
@@ -1156,7 +1154,7 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
             dst[1] = float4v{y[4], y[5], y[6], y[7]};
           }
         } else {
-          auto stage = [&](auto run, uint8_t* row) {           // the operand of one run of the codes: see stage_slot
+          auto stage = [&](auto run, uint8_t* row) {           // the operand of one run of the codes: see k_octet_offset
             constexpr int B = decltype(run)::bits, BASE = decltype(run)::base;
             uint16_t y[8];
 #pragma unroll
@@ -1532,7 +1530,8 @@ inline RotV rot_v_of(const Geom& g) {
   return r;
 }
 
-// The same merge for up to 8 records (the plans of the short shapes: 2 to 8 splits): one wavefront pair per head, every
+// The same merge for up to 8 records (5 to 8 splits, 3 to 8 with 8 heads, and those of caches with a residual buffer, which
+// come from two launches): one wavefront pair per head, every
 // record's maximum, sum and element loaded at once -- 24 independent loads, one memory latency -- and no step through
 // LDS (the kernel above spends two latencies and two barriers, which is most of its 3.9 us at 4 records).
 constexpr int kMergeFew = 8;

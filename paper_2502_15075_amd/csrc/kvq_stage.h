@@ -13,8 +13,6 @@ constexpr int kSpan = 64;                // tokens one workgroup covers (two 32-
 // of an output word adjacent (so a word is assembled from one wide LDS read).  (Padding the area against the bank
 // conflicts of the strided byte writes was measured: its address arithmetic costs more than the conflicts, 3 %.)
 
-// Pack the codes held one per byte in w (first code in the lowest byte) into adjacent b-bit fields.
-// (Bytes of tokens that were not staged hold garbage: they are masked to b bits so that they stay inside their field.)
 // 16 bytes read once / written once: streaming accesses (see store_bytes)
 __device__ __forceinline__ uint4 load_stream16(const void* p) {
   typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
@@ -27,6 +25,8 @@ __device__ __forceinline__ void store_stream16(void* p, uint4 w) {
   __builtin_nontemporal_store(v, reinterpret_cast<u32x4v*>(p));
 }
 
+// Pack the codes held one per byte in w (first code in the lowest byte) into adjacent b-bit fields.
+// (Bytes of tokens that were not staged hold garbage: they are masked to b bits so that they stay inside their field.)
 template <int B> __device__ __forceinline__ uint32_t pack_bytes(uint32_t w) {
   if (B == 1) { w &= 0x01010101u; return (w | (w >> 7) | (w >> 14) | (w >> 21)) & 0xFu; }
   if (B == 2) { w &= 0x03030303u; return (w | (w >> 6) | (w >> 12) | (w >> 18)) & 0xFFu; }
@@ -55,9 +55,7 @@ __device__ __forceinline__ void stage_value_codes(uint8_t* vstage, int row, int 
   }
 }
 
-// One thread per 32-bit word of the span (two blocks of 128*BV words, BW words apart in the plane: a block of 3- or
-// 6-bit codes is a block of low parts followed by a block of high parts): assemble the word from the staged codes and
-// store it; when the span is only partly covered by the new tokens [lo, hi), keep the fields of the other tokens.
+// Assemble a 32-bit word of the span from its staged codes.
 template <int BV> __device__ __forceinline__ uint32_t staged_word(const uint8_t* sp) {
   if (BV == 1) {
     const uint4 r0 = *reinterpret_cast<const uint4*>(sp), r1 = *reinterpret_cast<const uint4*>(sp + 16);
@@ -72,6 +70,9 @@ template <int BV> __device__ __forceinline__ uint32_t staged_word(const uint8_t*
   }
   return *reinterpret_cast<const uint32_t*>(sp);              // 8-bit: four codes; 16-bit: two patterns
 }
+// One thread per 32-bit word of the span (two blocks of 128*BV words, BW words apart in the plane: a block of 3- or
+// 6-bit codes is a block of low parts followed by a block of high parts): assemble the word from the staged codes and
+// store it; when the span is only partly covered by the new tokens [lo, hi), keep the fields of the other tokens.
 template <int BV, int BW = 128 * BV, int SPAN = kSpan, bool NT = false>
 __device__ __forceinline__ void store_value_words(uint32_t* vcp, const uint8_t* vstage, int tid, int lo, int hi) {
   constexpr int F = 32 / BV, P = 16 / BV, ES = BV == 16 ? 2 : 1, W = 128 * BV, N = SPAN / 32 * W;
