@@ -2121,14 +2121,17 @@ def test_paged_walks_longer_than_the_staged_page_numbers(kvq, T):
 
 @pytest.mark.parametrize("B,H,R,bk,bv,page,rotv,out_dtype", [(16, 8, 4, 4, 2, 0, 0, torch.float32), (16, 8, 1, 4, 4, 64, 0, torch.bfloat16),
                                                             (64, 2, 2, 2, 4, 0, 1, torch.float32), (8, 8, 8, 4, 2, 256, 0, torch.float32),
-                                                            (2, 40, 5, 8, 8, 0, 0, torch.float32)])
+                                                            (2, 40, 5, 8, 8, 0, 0, torch.float32), (2, 32, 4, 4, 2, 0, 0, torch.float32)])
 def test_ragged_batch_dealt_out_by_its_lengths(kvq, B, H, R, bk, bv, page, rotv, out_dtype):
     """Batches of 64 to 128 streams, whose workgroups go to the sequences by length (two to four splits planned): against
     attention over each sequence on its own, which takes the other route and is held to the oracle above.  Lengths at the
-    edges of steps and of the bound, all equal, one long among short ones; a workspace full of ones, of the counters'
-    own mark, and as the calls before left it.  Both sides round their weights to binary16: the bar of the oracle tests."""
+    edges of steps and of the bound, all equal, one long among short ones; a workspace full of ones, of other bytes, and as
+    the calls before left it.  Both sides round their weights to binary16: the bar of the oracle tests.
+    That it is this route that runs shows in the counters behind the records: a sequence that is a single part counts
+    nothing, where a launch that cuts every sequence into the plan's parts counts all of them."""
     D, scale = 128, 1 / math.sqrt(128)
-    T = 3500 if B * H > 100 else 8200
+    splits = {128: 2, 80: 3, 64: 4}[B * H]                    # (on 256 compute units)
+    T = {2: 3500, 3: 9300, 4: 12300}[splits]
     kw = dict(page_tokens=page, n_pages=B * -(-T // page) + 1) if page else {}
     L = kvq.Layout(B, H, T, D, bk, bv, 64, 64, raw_dtype=kvq.KVQ_BF16, rotate_v=rotv, signs_v=(7, 8, 9, 10) if rotv else (0,) * 4, **kw)
     one = replace(L, batch=1)
@@ -2144,6 +2147,12 @@ def test_ragged_batch_dealt_out_by_its_lengths(kvq, B, H, R, bk, bv, page, rotv,
              np.linspace(T * 0.8, T, B).astype(int)]
     marks = [0xFF, None, 0, None, 0x5A, None, None]
     ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    ws.zero_()
+    few = torch.ones(B, dtype=torch.int32, device="cuda")
+    few[0] = T
+    kvq.decode_attention_varlen(L, cache, q, few, T, scale, torch.empty(B, H * R, D, dtype=out_dtype, device="cuda"), ws)
+    words = _counters(ws, B, H, H * R, splits).view(B, H)
+    assert words[0].ne(0).all() and words[1:].eq(0).all()
     alone = torch.empty(B, H * R, D, dtype=torch.float32, device="cuda")
     ws1 = torch.empty(max(16, kvq.decode_workspace_bytes(one, H * R, T)), dtype=torch.uint8, device="cuda")
     for lens, fill in zip(cases, marks):
