@@ -1530,7 +1530,7 @@ inline RotV rot_v_of(const Geom& g) {
   return r;
 }
 
-// The same merge for up to 8 records (5 to 8 splits, 3 to 8 with 8 heads, and those of caches with a residual buffer, which
+// The same merge for up to 8 records (5 to 8 splits, 3 to 8 for attention alone over 7 or 8 heads, and those of caches with a residual buffer, which
 // come from two launches): one wavefront pair per head, every
 // record's maximum, sum and element loaded at once -- 24 independent loads, one memory latency -- and no step through
 // LDS (the kernel above spends two latencies and two barriers, which is most of its 3.9 us at 4 records).
@@ -1758,20 +1758,22 @@ DecodePlan plan_decode(const Geom& g, int32_t seq_len) {
 
 // Where the launch's own workgroups merge the records instead of a second launch.  Counting in, after the wait for the
 // record stores, and reading the records back cost the last workgroup about what a dependent launch costs, and more the more
-// it has to read: up to four records of at most 4 heads, two of 8 (a workgroup's threads take 8 heads in two turns).
-// Measured in turn, this way against the merge launch, K4V2, 1 to 10 sequences of 2 to 8 kv heads, 1000 to 12000 tokens:
-// 3 and 4 records of 1 head 2 to 10 % faster this way (4 x 8 heads x 2000 tokens 8.9 against 9.6 us), of 8 heads up to 4 %
-// slower (10.7 against 10.3); 5 to 8 records of 1 head from 2 % faster to 4 % slower, of 4 heads from 3 % faster to 5 %
-// slower, of 8 heads 3 to 14 % slower (4 x 8 heads x 2500 tokens 11.8 against 10.4 us).
-constexpr int kMergeHereMost = 4, kMergeHereMostWide = 2;
+// it has to read (a workgroup's threads take more than 4 heads in two turns): up to four records, except that attention
+// alone over 7 or 8 heads leaves three and four to the second launch.  Measured in turn, K4V2 and K4V4, 1 to 10 sequences of 2 to 8
+// kv heads, 700 to 12000 tokens, the launch's own merge against the merge launch: three and four records of 1 head, attention,
+// 2 to 10 % faster (4 x 8 heads x 2000 tokens 8.9 against 9.6 us), of 5 and 6 heads from 2.6 % faster to 2.3 % slower, of 7
+// and 8 from 1 % faster to 4 % slower (4 x 8 x 8 heads x 2000 tokens 10.7 against 10.3); with the fused append, of 5 to 8
+// heads, up to 3.5 % faster.  Five to eight records of 1 head from 2 % faster to 4 % slower, of 4 heads from 3 % faster to
+// 5 % slower, of 8 heads 3 to 14 % slower (4 x 8 x 8 heads x 2500 tokens 11.8 against 10.4 us).
+constexpr int kMergeHereMost = 4, kMergeHereMostAlone = 2, kAloneHeads = 6;
 // The number such a launch carries (0: it does not merge): a greater one than all launches before it.  A replayed graph launch
 // carries its number again.
 static MergeWord next_merge_tag() {
   static std::atomic<MergeWord> launches{0};
   return merge_tag(launches.fetch_add(1, std::memory_order_relaxed));
 }
-static MergeWord merge_tag_for(int records, int R) {
-  return records >= 2 && records <= (R > 4 ? kMergeHereMostWide : kMergeHereMost) ? next_merge_tag() : 0;
+static MergeWord merge_tag_for(int records, int most = kMergeHereMost) {
+  return records >= 2 && records <= most ? next_merge_tag() : 0;
 }
 
 // Whether a launch over sequences of different lengths deals its workgroups out by the lengths (balanced_share).  It needs
@@ -1819,7 +1821,7 @@ hipError_t launch_decode_attention(const Geom& g, const kvq_cache& c, const void
     hipError_t e = hipSuccess;
     if (n_flushed) {
       a.seq_len = n_flushed; a.rec_splits = records; a.rec_base = 0; a.lens_mode = 1;
-      a.merge_tag = !tail ? merge_tag_for(records, R) : 0;     // (a launch that writes every record may merge them itself)
+      a.merge_tag = !tail ? merge_tag_for(records) : 0;     // (a launch that writes every record may merge them itself)
 #define KVQ_CASE(BK_, BV_) \
       if (g.bits_k == BK_ && g.bits_v == BV_) e = KVQ_CAT(launch_decode_inst_, BK_, BV_)(R, a, plan, stream);
       KVQ_FOR_EACH_PAIR(KVQ_CASE)
@@ -1853,7 +1855,8 @@ hipError_t launch_decode_attention(const Geom& g, const kvq_cache& c, const void
   }
   a.lens_mode = 0; a.lens_bound = seq_len; a.lens_block = 1;
   a.balance = seq_lens != nullptr && balance_pays(g, plan);
-  a.merge_tag = a.balance ? next_merge_tag() : merge_tag_for(a.rec_splits, R);
+  a.merge_tag = a.balance ? next_merge_tag()
+                          : merge_tag_for(a.rec_splits, !app && a.heads_per_kv > kAloneHeads ? kMergeHereMostAlone : kMergeHereMost);
   if (app) {
     a.k_new = (const uint16_t*)app->k_new; a.v_new = (const uint16_t*)app->v_new;
     a.in_bf16 = app->in_dtype == KVQ_BF16 ? 1 : 0; a.nsb = app->stride_b; a.nsh = app->stride_h;

@@ -2289,11 +2289,12 @@ def test_reconstruction_error_of_many_streams_and_of_few(kvq, B, H, T):
 
 
 @pytest.mark.parametrize("R,T,records,merges", [(4, 1500, 3, True), (4, 2000, 4, True), (4, 2500, 5, False), (8, 1000, 2, True),
-                                                (8, 1500, 3, False), (5, 2000, 4, False)])
+                                                (8, 1500, 3, False), (7, 2000, 4, False), (6, 2000, 4, True)])
 def test_which_launches_merge_their_records_themselves(kvq, R, T, records, merges):
-    """Two to four records of up to 4 heads (padded to a power of two), two of 8: a launch that merges them counts on the words
-    behind the records, one that leaves them to a second launch does not touch those.  Against attention over the
-    reconstruction in binary64, to the bar of the oracle tests."""
+    """Two to four records, for attention alone over 7 or 8 heads two: a launch that merges them counts on the words behind the
+    records, one that leaves them to a second launch does not touch those.  Attention over the same tokens with the last one
+    appended by the call (up to four whatever the heads) and without, against attention over the reconstruction in
+    binary64, to the bar of the oracle tests."""
     B, H, D, scale = 2, 4, 128, 1 / math.sqrt(128)
     L = kvq.Layout(B, H, T, D, 4, 2, raw_dtype=kvq.KVQ_BF16)
     K, V, q = synth.make_kvq(14, B, H, H * R, T, D, dtype=torch.bfloat16, device="cuda", sigma_k=1.0)
@@ -2307,6 +2308,10 @@ def test_which_launches_merge_their_records_themselves(kvq, R, T, records, merge
     kvq.dequantize(L, cache, 0, T, k, v)
     p = torch.softmax(q.double().view(B, H, R, D) @ k.double().transpose(-1, -2).contiguous() * scale, dim=-1)
     want = (p @ v.double()).view(B, H * R, D)
+    assert _rel_err(out.cpu().numpy(), want.cpu().numpy()) < TOL
+    ws.zero_()
+    kvq.decode_step(L, cache, K[:, :, T - 1].contiguous(), V[:, :, T - 1].contiguous(), T - 1, q, scale, out.zero_(), ws)
+    assert words.ne(0).all() if records <= 4 else words.eq(0).all()
     assert _rel_err(out.cpu().numpy(), want.cpu().numpy()) < TOL
 
 
