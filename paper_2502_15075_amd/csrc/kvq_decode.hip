@@ -787,6 +787,57 @@ __device__ __forceinline__ void append_patterns(const uint8_t* key_row, uintptr_
   for (int e = 0; e < 8; ++e) hat[(is_v ? kHeadDim : 0) + d0 + e] = widen16((uint16_t)(rw[e >> 1] >> (16 * (e & 1))), bf16);
 }
 
+// ---- the tokens still in the residual buffer of a cache with channel-wise keys ------------------------------------------
+// One wavefront takes 32 of them (tile 0 .. RL/32 - 1) as one masked step over the buffer's patterns, behind its own part of the
+// flushed tokens, into a (maximum, sum, accumulator) record in LDS that the final merge adds to the wavefronts' own.  What
+// the step loads comes straight from memory in operand order, the query (as it is: the buffer holds unrotated rows) too.
+// It is one memory latency and some 150 vector instructions, for the most part beside wavefronts that still walk the flushed
+// tokens.  A launch of its own over the buffer (and one to merge) cost 5 to 6 us: K4V2, rotated keys, a fused step with 37 tokens
+// in the buffer, 8 x 8 heads x 8192 tokens of 4 query heads 23.8 us so, 18.1 now (16.9 without a buffer); of 8 query heads
+// 26.1 and 20.6; 32 x 8 heads x 8192 tokens 60.9 and 54.6; 8 heads x 2048 tokens 15.0 and 9.4.  (8 tokens per wavefront
+// in vector arithmetic in front of the walk: 20.4 us and, for 8 query heads, 25.4.)
+//   n    tokens in the buffer (slots 0 .. n - 1), more than 32 tile
+//   q    this kv head's r_act query rows
+template <int R, bool BF>
+__device__ __forceinline__ void buffer_step(const uint8_t* k_resid, const uint8_t* v_resid, const uint16_t* q, int r_act, int n,
+                                            int tile, const LaneCtx& L, float kappa, float (&rec)[R][kHeadDim], float (&rec_m)[R],
+                                            float (&rec_l)[R]) {
+  const int h = L.c % R;
+  const bool head_lane = L.c < R;                  // (one column per head; the others carry nothing)
+  u32x4 qb[1][4];
+  StepRegs<16, 16> r;
+  const uintptr_t qp = reinterpret_cast<uintptr_t>(q) + (head_lane && h < r_act ? h * (2 * kHeadDim) : 0) + 16 * L.j;
+  const uintptr_t kp = reinterpret_cast<uintptr_t>(k_resid) + (32 * tile + L.c) * (2 * kHeadDim) + k_lane_offset<16>(L.j);
+  const uintptr_t vp = reinterpret_cast<uintptr_t>(v_resid) + tile * (512 * 16) + 16 * L.lane;
+#pragma unroll
+  for (int m = 0; m < 4; ++m) qb[0][m] = load_global<u32x4>(qp + 64 * m);
+#pragma unroll
+  for (int x4 = 0; x4 < 2; ++x4)
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+      *reinterpret_cast<u32x4*>(r.kc[x4] + 4 * m) = load_global<u32x4>(kp + 16 * x4 * (2 * kHeadDim) + k_piece_stride<16>() * m);
+#pragma unroll
+  for (int k = 0; k < 8; ++k) *reinterpret_cast<u32x4*>(r.vc + 4 * k) = load_global<u32x4>(vp + 1024 * k);
+#pragma unroll
+  for (int m = 0; m < 4; ++m) qb[0][m] = head_lane && h < r_act ? qb[0][m] : u32x4{0u, 0u, 0u, 0u};
+  WaveState<1> st;
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt) st.acc[dt] = float4v{0.f, 0.f, 0.f, 0.f};
+  st.m = kNegBig; st.headroom = 0.f;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) { st.l[v] = 0.f; st.noff[v] = 0.f; st.zacc[0][v] = 0.f; }
+  const float qsum[1] = {0.f};
+  NoKSeq none;
+  compute_step<16, 16, R, BF, 1, 1, true>(r, qb, qb, qsum, kappa, st, L, tile, n, none);
+  float l = (st.l[0] + st.l[1]) + (st.l[2] + st.l[3]);
+  l += __shfl_xor(l, 16); l += __shfl_xor(l, 32);
+  if (head_lane) {
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) *reinterpret_cast<float4v*>(&rec[h][16 * dt + 4 * L.j]) = st.acc[dt];
+    if (L.j == 0) { rec_m[h] = st.m; rec_l[h] = l; }
+  }
+}
+
 // Second half of the fused append: thread d < 128 inserts channel d's code of the new token into its 32-bit word of
 // the 32-token block (the other fields of the word belong to other tokens of the block and keep their bits).  With
 // 2-bit fields channels d and d+16 share a word (with 1-bit fields d, d+16, d+32 and d+48), so the thread of the first
@@ -898,8 +949,8 @@ __device__ __forceinline__ Share balanced_share(const int32_t* __restrict__ seq_
   return s;
 }
 
-// KSEQ: channel-wise keys (the caller passes the flushed part of the sequence: seq_len is a multiple of 64, nothing
-// is appended); a wavefront then walks whole 64-token blocks (pairs of steps), rebuilding its query operands per block.
+// KSEQ: channel-wise keys (the caller passes the flushed part of the sequence: seq_len is a multiple of 64; the tokens in
+// the residual buffer come on top, see buffer_step, and a fused step's token goes there); a wavefront then walks whole 64-token blocks (pairs of steps), rebuilding its query operands per block.
 // PAGED: the planes are pools of pages; a step's data is found through this sequence's row of the page table.
 // ROTV: the values are stored rotated (quantized caches with token-wise keys; compute_step then corrects its weights).
 template <int BK, int BV, int R, int NW, bool BF, int NCK, int NCV, bool KSEQ = false, bool PAGED = false, bool ROTV = false>
@@ -930,6 +981,9 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   __shared__ float sm_hat[2][kHeadDim];           // its reconstructed key and value rows,
   __shared__ float sm_mnew[R];                    // and its logit per head in log2 units
   __shared__ float sm_qsum[NW][R][4];
+  // channel-wise keys: the records of the tokens still in the residual buffer (buffer_step: at most 128 of them)
+  __shared__ __attribute__((aligned(16))) float sm_buf[KSEQ ? 4 : 1][R][kHeadDim];
+  __shared__ float sm_bufm[KSEQ ? 4 : 1][R], sm_bufl[KSEQ ? 4 : 1][R];
   const Geom& g = a.g;
   const kvq_cache& cache = a.cache;
   const uint16_t* __restrict__ q = a.q;
@@ -947,6 +1001,7 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   // is the only one (its result then goes straight to the output)
   int n_rec = a.rec_splits, slot = 0, slot0 = 0;
   int seq_len = a.seq_len;
+  int n_buf = a.buf_len;                           // channel-wise keys: this sequence's tokens in the residual buffer
   bool have_len = a.seq_lens == nullptr;
   if constexpr (!KSEQ) {
     if (a.balance) {                               // (uniform)
@@ -961,6 +1016,7 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   // this sequence's length: its own when the caller gave per-sequence lengths, inside what the launch was planned for
   if (!have_len) {
     int n = min(max(a.seq_lens[b] + a.lens_offset, 1), a.lens_bound);
+    n_buf = n & (a.lens_block - 1);
     if (a.lens_mode == 1) n &= ~(a.lens_block - 1);         // a residual buffer of lens_block slots: the flushed blocks ...
     else if (a.lens_mode == 2) n &= a.lens_block - 1;       // ... or the tail in the buffer (either may be empty)
     seq_len = min(n, a.seq_len);
@@ -997,13 +1053,16 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   // cache: the workgroup that owns that position quantizes and stores it, and adds it to the attention as one more
   // partial record, computed from the reconstruction it holds in registers (no store -> load round trip, no fence).
   // (Both tensors unquantized: the kernel that reads residual buffers.  The new token then goes to its slot as it is.)
-  constexpr bool kCanAppend = RAWK == RAWV && !KSEQ;
+  // (Channel-wise keys: the sequence's last workgroup takes the tokens in the residual buffer as well, n_buf of them, and the
+  // new token goes there as it is.)
+  constexpr bool kCanAppend = RAWK == RAWV;
   const bool fused = kCanAppend && a.k_new != nullptr;
-  const int n_att = fused ? seq_len - 1 : seq_len;        // tokens attended through the cache planes
+  const int n_att = fused && !KSEQ ? seq_len - 1 : seq_len;        // tokens attended through the cache planes
   const int n_steps = (n_att + 31) >> 5;
   const int step_begin = split * steps_per_split;
   const int step_end = min(step_begin + steps_per_split, n_steps);
-  const bool do_append = fused && split == ((seq_len + 31) / 32 - 1) / steps_per_split;   // uniform over the workgroup
+  const bool last_split = KSEQ ? split == a.n_splits - 1 : split == ((seq_len + 31) / 32 - 1) / steps_per_split;
+  const bool do_append = fused && last_split;             // uniform over the workgroup
   // this wavefront's steps: step_begin + wave, + NW, ...; the last one may be the ragged tail of the sequence
   const int first = step_begin + SPB * wave;
   auto step_of = [&](int i) { return KSEQ ? first + 2 * NW * (i >> 1) + (i & 1) : first + NW * i; };
@@ -1060,7 +1119,9 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   int u_new = 0;                                   // its place in that block
   if constexpr (kCanAppend) {
     // (paged: the new token's row number in plane order, with the stream index 0)
-    if constexpr (PAGED) {
+    if constexpr (KSEQ) {
+      t_new = n_buf - 1;                           // its slot in the buffer
+    } else if constexpr (PAGED) {
       const int64_t pg = my_pages[app_wave ? (seq_len - 1) >> g.page_shift : safe_step >> step_shift];
       t_new = ((pg * g.kv_heads + hk) << g.page_shift) + ((seq_len - 1) & ((1 << g.page_shift) - 1));
     } else {
@@ -1074,9 +1135,12 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
                     vp = reinterpret_cast<uintptr_t>(a.v_new);
     const uintptr_t nsrc = qp + (new_lane ? (kp - qp) + (lane >= 16 ? vp - kp : (uintptr_t)0) + (uintptr_t)row_off : (uintptr_t)0);
     nraw = load_global<u32x4>(nsrc);
-    vblk = reinterpret_cast<uintptr_t>(cache.v_codes) + (uintptr_t)(bh_base * g.vc_stream + (t_new >> 5) * (int64_t)(512 * BV));
+    if constexpr (KSEQ)
+      vblk = reinterpret_cast<uintptr_t>(cache.v_resid) + (uintptr_t)((int64_t)bh * g.resid * (2 * kHeadDim) + (t_new >> 5) * (int64_t)(512 * 16));
+    else
+      vblk = reinterpret_cast<uintptr_t>(cache.v_codes) + (uintptr_t)(bh_base * g.vc_stream + (t_new >> 5) * (int64_t)(512 * BV));
     u_new = (int)(t_new & 31);
-    if constexpr (!RAWV)
+    if constexpr (!RAWV && !KSEQ)
 #pragma unroll
     for (int t = 0; t < 2; ++t) {                  // channels lane and lane + 64
       const bool own_lo = app_wave && field_owner<VLO_>(lane + 64 * t);
@@ -1135,9 +1199,10 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
 #pragma unroll
         for (int e = 0; e < 8; ++e) xq[t][e] = widen16((uint16_t)(rw[e >> 1] >> (16 * (e & 1))), q_is_bf16);   // (a fused step's logit)
       } else {
-        float (&x)[8] = xq[t];
+        float xk[8];
+        float (&x)[8] = *(KSEQ ? &xk : &xq[t]);    // (the residual buffer holds rows as they came: their scores take the query as it is)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = widen16((uint16_t)(rw[e >> 1] >> (16 * (e & 1))), q_is_bf16);
+        for (int e = 0; e < 8; ++e) xq[t][e] = x[e] = widen16((uint16_t)(rw[e >> 1] >> (16 * (e & 1))), q_is_bf16);
         if (g.rotate_k) {
           // rotated keys: the scores need R q, rounded once to binary16 (16 lanes hold one query row, 8 channels each)
           rotate8(x, o, rot_sign_bits(g.signs_k, o));
@@ -1191,13 +1256,16 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   // value row), which the merge below adds to the wavefronts' records.  All of it stays inside the wavefront.
   if constexpr (kCanAppend) {
     if (app_wave) {                                // uniform
-      if constexpr (RAWV) {
+      if constexpr (KSEQ) {
+        const uint8_t* row = reinterpret_cast<const uint8_t*>(cache.k_resid) + ((int64_t)bh * g.resid + t_new) * (2 * kHeadDim);
+        if (lane < 32) append_patterns(row, vblk, u_new, lane, nraw, a.in_bf16 != 0, &sm_hat[0][0]);
+      } else if constexpr (RAWV) {
         if (lane < 32) append_patterns(L.kc + t_new * (2 * kHeadDim), vblk, u_new, lane, nraw, a.in_bf16 != 0, &sm_hat[0][0]);
       } else {
         if (lane < 32) append_one<BK, BV>(a, PAGED ? 0 : bh, bh, lane, nraw, sm_vnew, t_new, &sm_hat[0][0]);
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      if constexpr (!RAWV)
+      if constexpr (!RAWV && !KSEQ)
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         const int d = lane + 64 * t;
@@ -1304,6 +1372,8 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
       if (kt == k) tail_step(k);
   }
 
+  // ---- channel-wise keys, the sequence's last workgroup: the tokens in the residual buffer, behind the totals below
+  const int n_old = KSEQ && last_split ? n_buf - (fused ? 1 : 0) : 0;
   // ---- wavefront totals: l and zacc over register classes and the 4 lane groups j; then this lane's output rows
   float l = 0.f;
 #pragma unroll
@@ -1330,6 +1400,16 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   // (records of kernels that carry their weights times different powers of two meet in one merge when channel-wise keys
   // add the residual tail: the difference to 2^10 goes into the record's maximum)
   if (grp == 0 && L.j == 0) { sm_m[wave][h] = st.m + (10.0f - p_shift<BV>()); sm_l[wave][h] = l; }
+  if constexpr (KSEQ) {
+    if (32 * wave < n_old) {                       // (uniform: at most 4 wavefronts)
+      const int64_t at = (int64_t)bh * g.resid * (2 * kHeadDim);
+      const uint8_t* kb = reinterpret_cast<const uint8_t*>(cache.k_resid) + at;
+      const uint8_t* vb = reinterpret_cast<const uint8_t*>(cache.v_resid) + at;
+      const float kp = softmax_scale * kLog2e;
+      if (g.raw_dtype == KVQ_BF16) buffer_step<R, true>(kb, vb, qbase, r_act, n_old, wave, L, kp, sm_buf[wave], sm_bufm[wave], sm_bufl[wave]);
+      else buffer_step<R, false>(kb, vb, qbase, r_act, n_old, wave, L, kp, sm_buf[wave], sm_bufm[wave], sm_bufl[wave]);
+    }
+  }
   __syncthreads();
 
   // (the ring's last loads, which nothing reads, have come back: said here, or the compiler waits where their registers are used
@@ -1348,6 +1428,9 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
 #pragma unroll
     for (int w = 1; w < NW; ++w) M = fmaxf(M, sm_m[w][hh]);
     if (do_append) M = fmaxf(M, sm_mnew[hh]);
+    const int buf_recs = KSEQ ? (n_old + 31) >> 5 : 0;
+    if constexpr (KSEQ)
+      for (int w = 0; w < buf_recs; ++w) M = fmaxf(M, sm_bufm[w][hh]);
     float o = 0.f, ll = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
@@ -1360,6 +1443,12 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
       o = fmaf(f, sm_hat[1][d], o);
       ll += f;
     }
+    if constexpr (KSEQ)
+      for (int w = 0; w < buf_recs; ++w) {
+        const float f = exp2f(sm_bufm[w][hh] - M);
+        o = fmaf(f, sm_buf[w][hh][d], o);
+        ll = fmaf(f, sm_bufl[w][hh], ll);
+      }
     if (hh >= r_act) continue;
     const int64_t hq = (int64_t)b * q_heads + hk * r_act + hh;
     if (a.extra_splits != 0) {
@@ -1530,8 +1619,8 @@ inline RotV rot_v_of(const Geom& g) {
   return r;
 }
 
-// The same merge for up to 8 records (5 to 8 splits, 3 to 8 for attention alone over 7 or 8 heads, and those of caches with a residual buffer, which
-// come from two launches): one wavefront pair per head, every
+// The same merge for up to 8 records (5 to 8 splits, 3 to 8 for attention alone over 7 or 8 heads, and those of token-wise keys behind a
+// residual buffer, which come from two launches): one wavefront pair per head, every
 // record's maximum, sum and element loaded at once -- 24 independent loads, one memory latency -- and no step through
 // LDS (the kernel above spends two latencies and two barriers, which is most of its 3.9 us at 4 records).
 constexpr int kMergeFew = 8;
@@ -1806,13 +1895,29 @@ hipError_t launch_decode_attention(const Geom& g, const kvq_cache& c, const void
   a.merge_tag = 0;
   if (g.resid) {
     // a residual buffer: flushed blocks from the codes (plan; channel-wise or token-wise keys), the newest tokens from
-    // the buffer by the unquantized kernel, all partial records merged at the end
+    // the buffer: by the same launch where the keys are channel-wise, else (and where nothing is flushed yet) by the unquantized
+    // kernel, all partial records merged at the end
     // (per-sequence lengths: seq_len is their bound; every sequence's own flushed part and tail are cut out on the
     // device, the tail launch always runs, and a sequence without one of the parts gets empty records for it)
     const bool varlen = seq_lens != nullptr;
     const int32_t RL = g.resid;
     const int32_t n_flushed = seq_len / RL * RL;
     const int32_t tail = varlen ? (n_flushed ? RL - 1 : seq_len) : seq_len - n_flushed;
+    if (g.axis_k == KVQ_AXIS_SEQ && n_flushed) {
+      // channel-wise keys: the flushed blocks' launch takes the buffer's tokens along (buffer_step)
+      a.seq_len = n_flushed; a.lens_mode = 1; a.lens_bound = seq_len; a.lens_block = RL;
+      a.buf_len = seq_len - n_flushed;
+      if (app) {
+        a.k_new = (const uint16_t*)app->k_new; a.v_new = (const uint16_t*)app->v_new;
+        a.in_bf16 = app->in_dtype == KVQ_BF16 ? 1 : 0; a.nsb = app->stride_b; a.nsh = app->stride_h;
+      }
+      a.merge_tag = merge_tag_for(a.rec_splits);
+#define KVQ_CASE(BK_, BV_) \
+      if (g.bits_k == BK_ && g.bits_v == BV_) return KVQ_CAT(launch_decode_inst_, BK_, BV_)(R, a, plan, stream);
+      KVQ_FOR_EACH_PAIR(KVQ_CASE)
+#undef KVQ_CASE
+      return hipErrorInvalidValue;
+    }
     const int32_t records = plan.n_splits + (tail ? 1 : 0);
     // one split of flushed blocks and a tail: the tail's launch, which comes second, takes the first one's record in and
     // writes the result (one launch less than with the merge kernel)

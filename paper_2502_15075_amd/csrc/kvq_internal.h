@@ -103,6 +103,7 @@ struct DecodeArgs {
   // into its flushed blocks (lens_mode 1: n rounded down to the buffer's length, possibly 0) or its residual tail (lens_mode 2:
   // n modulo that length, possibly 0); a workgroup with nothing to read writes an empty record.  lens_mode 0: n as it is.
   int32_t lens_mode, lens_bound, lens_block;   // lens_block: the buffer's slots (a power of two)
+  int32_t buf_len;            // channel-wise keys: tokens in the residual buffer (uniform lengths; the new one of a fused step counts)
   // != 0 (with seq_lens): the launch's n_splits * batch workgroups per kv head are dealt out to the sequences by their
   // lengths instead of n_splits each; workgroup w of a kv head writes the records of slot w
   int32_t balance;

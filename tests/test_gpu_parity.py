@@ -887,6 +887,39 @@ def test_channelwise_attention_fp16_long_multi_split(kvq, oracle):
         assert _rel_err(out.cpu().numpy(), ref) < TOL
 
 
+@pytest.mark.parametrize("R", [1, 3, 8])
+@pytest.mark.parametrize("rl,blocks,dtype", [(64, 1, torch.float16), (64, 40, torch.bfloat16), (128, 1, torch.bfloat16), (128, 9, torch.float16)])
+def test_channelwise_tokens_in_the_buffer(kvq, oracle, R, rl, blocks, dtype):
+    """The flushed tokens' launch takes the residual buffer's tokens in steps of 32: 1 token, one below, at and above every
+    step's edge, a full buffer but one; one and several splits, 4 and 8 wavefronts.  The slots behind the last token hold
+    NaN patterns, for keys and values, and must not be seen.  Attention alone and the fused step."""
+    B, H = 1, 2
+    raw = 1 if dtype == torch.bfloat16 else 0
+    lens = [n for n in (1, 2, 31, 32, 33, 63, 64, 65, 96, 97, 127) if n < rl]
+    K, V, q = synth.make_kvq(230 + R + rl, B, H, H * R, (blocks + 1) * rl, dtype=dtype)
+    qn = synth.to_numpy_bits(q) if raw else q.numpy()
+    Lg = kvq.Layout(B, H, (blocks + 1) * rl, 128, 4, 2, 64, 64, axis_k=kvq.AXIS_SEQ, raw_dtype=raw, resid_len=rl)
+    Lo = oracle.Layout(B, H, (blocks + 1) * rl, 128, 4, 2, 64, 64, axis_k=1, raw_dtype=raw, resid_len=rl)
+    for n in lens:
+        T = blocks * rl + n
+        cache, planes = _seq_fill_both(kvq, oracle, Lg, Lo, K[:, :, :blocks * rl], V[:, :, :blocks * rl], [(0, blocks * rl)])
+        for side in (cache.planes, planes):                # every slot: NaN of either type
+            for p in side[4:6]:
+                p[:] = 0xFF
+        oracle.seq_append(Lo, planes, np.ascontiguousarray(synth.to_numpy_bits(K[:, :, blocks * rl:T])),
+                          np.ascontiguousarray(synth.to_numpy_bits(V[:, :, blocks * rl:T])), blocks * rl, bf16=bool(raw))
+        Kd, Vd = K.cuda(), V.cuda()
+        if n > 1:
+            kvq.quantize_append(Lg, cache, Kd[:, :, blocks * rl:T - 1], Vd[:, :, blocks * rl:T - 1], blocks * rl)
+        out = torch.empty(B, H * R, 128, dtype=torch.float32, device="cuda")
+        ws = torch.empty(max(16, kvq.decode_workspace_bytes(Lg, H * R, T)), dtype=torch.uint8, device="cuda")
+        kvq.decode_step(Lg, cache, Kd[:, :, T - 1], Vd[:, :, T - 1], T - 1, q.cuda(), 1 / math.sqrt(128), out, ws)
+        _assert_seq_planes_equal(cache, planes)
+        ref = oracle.seq_decode_attention(Lo, planes, qn, T, 1 / math.sqrt(128), bf16=bool(raw))
+        assert _rel_err(out.cpu().numpy(), ref) < TOL, n
+        assert _rel_err(_decode(kvq, Lg, cache, q, T).cpu().numpy(), ref) < TOL, n
+
+
 def test_channelwise_decode_steps_cross_a_flush(kvq, oracle):
     """kvq_decode_step on a cache with channel-wise keys: positions 60..69 include the token that completes block 0
     (position 63: the buffer is flushed) and the first tokens of the next block."""
