@@ -981,6 +981,7 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   __shared__ float sm_hat[2][kHeadDim];           // its reconstructed key and value rows,
   __shared__ float sm_mnew[R];                    // and its logit per head in log2 units
   __shared__ float sm_qsum[NW][R][4];
+  __shared__ int sm_turn[NW];                      // how far each wavefront has come (see the main loop)
   // channel-wise keys: the records of the tokens still in the residual buffer (buffer_step: at most 128 of them)
   __shared__ __attribute__((aligned(16))) float sm_buf[KSEQ ? 4 : 1][R][kHeadDim];
   __shared__ float sm_bufm[KSEQ ? 4 : 1][R], sm_bufl[KSEQ ? 4 : 1][R];
@@ -1352,10 +1353,42 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
     if constexpr (!KSEQ)
       compute_step<BK, BV, R, BF, NCK, NCV, true>(buf[k], qb, qbh, qsum_u, kappa, st, L, n_steps - 1, n_att, ks);
   };
+  // Two wavefronts share a SIMD (w and w + 4 of a workgroup of 8; of 4, two workgroups), and at equal priority it serves the
+  // older one first: wavefronts 0-3 of the 70B layer's step were done after 103 us and 4-7 after 136, those of 8 x 8 heads x 8192
+  // tokens after 9.0 and 12.3, and what a wavefront walks alone comes at half the rate.  So whoever is behind goes first.  Short
+  // walks give their turns (kStages steps) falling priorities; from 4 turns on a wavefront notes each turn in LDS and goes
+  // last where its partner has not come as far (a stale or early look costs a turn at the wrong priority, nothing else); a
+  // workgroup of 4 does not know its partner and takes a priority per quarter of its walk.  In turn, K4V2, before and with it:
+  // 70B step 148.3 and 143.3 us, 8 x 8 heads x 32768 tokens 47.7 and 44.4, x 16384 26.1 and 25.3, x 8192 17.1 and 16.7, 32 x 8 x 8 heads x
+  // 4096 tokens 25.9 and 24.9, 40 x 8 x 8 heads x 2000 tokens 22.2 and 21.3.  (Falling quarters for all 145.6, 45.6, 25.4, 16.8, 24.9; by the partner
+  // for all 143.6, 44.3, 25.3, 17.3, 25.1; steps drawn from a counter in LDS 146.1, 44.2, 25.9, 17.4, 25.8: a wavefront draws
+  // a ring ahead of what it computes, so the last steps still meet at the slow ones.)
+  // Not where memory alone binds (K8V8, 8 x 8 heads x 32768 tokens: 85.5 us before, 86.6 with it; K8V4 71.4 and 71.0), nor over
+  // channel-wise keys by 8 wavefronts (K4V2, 8 x 8 heads x 8229 tokens 17.25 and 17.44 us, K4V4 19.5 and 20.1; by 4, 40 x 8 heads x 3000
+  // tokens, 33.3 and 32.3).
+  constexpr bool kPairs = NW == 8, kYield = BK + BV <= 12 && !(KSEQ && kPairs);
+  const bool by_partner = kYield && kPairs && n_full >= 4 * kStages;
+  const int q1 = kPairs ? kStages : n_full >> 2, q2 = kPairs ? 2 * kStages : n_full >> 1, q3 = q1 + q2;
+  int partner = 0;                                 // the turn that the other wavefront of this SIMD has reached, in steps
+  if constexpr (kYield && kPairs) __hip_atomic_store(&sm_turn[wave], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  if constexpr (kYield) __builtin_amdgcn_s_setprio(3);
   int it = 0;
   for (; it + kStages <= n_full; it += kStages) {
+    if constexpr (kYield) {                        // (uniform, all of this)
+      if (by_partner) {
+        if (partner < it) __builtin_amdgcn_s_setprio(0); else __builtin_amdgcn_s_setprio(3);
+      } else {
+        if (it >= q3) __builtin_amdgcn_s_setprio(0);
+        else if (it >= q2) __builtin_amdgcn_s_setprio(1);
+        else if (it >= q1) __builtin_amdgcn_s_setprio(2);
+      }
+    }
 #pragma unroll
     for (int k = 0; k < kStages; ++k) {
+      if (kYield && kPairs && k == kStages - 1) {
+        __hip_atomic_store(&sm_turn[wave], it + kStages, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        partner = __builtin_amdgcn_readfirstlane(__hip_atomic_load(&sm_turn[wave ^ (NW / 2)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+      }
       full_step(k, it + k);
       refill(k, it + k + kStages);
     }
@@ -1372,6 +1405,7 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
       if (kt == k) tail_step(k);
   }
 
+  if constexpr (kYield) __builtin_amdgcn_s_setprio(0);
   // ---- channel-wise keys, the sequence's last workgroup: the tokens in the residual buffer, behind the totals below
   const int n_old = KSEQ && last_split ? n_buf - (fused ? 1 : 0) : 0;
   // ---- wavefront totals: l and zacc over register classes and the 4 lane groups j; then this lane's output rows
