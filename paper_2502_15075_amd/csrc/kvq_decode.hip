@@ -1110,9 +1110,13 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
     const int item = lane + 64 * t;
     qraw[t] = *reinterpret_cast<const u32x4*>(qbase + (item < R * 16 && (item >> 4) < r_act ? item * 8 : 0));
   }
-  // the fused append is one wavefront's work, the last one's: where the steps do not divide evenly it has one less
+  // The fused append is one wavefront's work: of 8 the fourth's.  Wavefronts 0-3 are a microsecond ahead of 4-7, which share their SIMDs,
+  // when the first step's data comes; the last one, which had it before (it has a step less where the steps do not divide
+  // evenly), brought that and the append to the final barrier.  Fused steps with the last and with the fourth wavefront's append, in turn, K4V2:
+  // 8 heads x 1024 tokens, 1 query head, 8.88 and 8.48 us, 4 query heads 9.02 and 8.50; 8 x 8 heads x 2048 tokens 10.27
+  // and 9.47 (9.27 without an append), x 8192 16.75 and 16.64; 32 x 8 x 8 heads x 1024 tokens 12.44 and 11.91.
   constexpr int VLO_ = v_lo<BV>(), VHI_ = v_hi<BV>();
-  const bool app_wave = do_append && wave == NW - 1;
+  const bool app_wave = do_append && wave == (NW == 8 ? 3 : NW - 1);
   u32x4 nraw = u32x4{0u, 0u, 0u, 0u};
   uint32_t vw_lo[2] = {0u, 0u}, vw_hi[2] = {0u, 0u};
   uintptr_t vblk = 0;                              // the new token's 32-token block of value codes
