@@ -67,6 +67,30 @@ __device__ __forceinline__ float sum_over_groups(float x) {
   return x;
 }
 
+// Sum (maximum) over the four 16-lane rows of a wavefront, in every lane: a swap of rows (of halves) leaves the two values to
+// combine in the two registers.  Register permutes: through the LDS unit the same exchanges are a latency each in the chain
+// that bounds a short launch.
+__device__ __forceinline__ float rows_sum(float x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  const float s = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+__device__ __forceinline__ float rows_max(float x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  const float m = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+// Sum over groups of n = 4, 8 or 16 neighbouring lanes (uniform), in every lane.
+__device__ __forceinline__ float lanes_sum(float x, int n) {
+  x += dpp_f32<0xB1>(x);                // quad permutes: lane ^ 1, lane ^ 2
+  x += dpp_f32<0x4E>(x);
+  if (n > 4) x += dpp_f32<0x141>(x);    // row_half_mirror: the other quad's total
+  if (n > 8) x += dpp_f32<0x140>(x);    // row_mirror: the other half's
+  return x;
+}
+
 // ---- key codes: one lane holds 32 consecutive channels of one token (BK dwords) -------------
 // (Channels 32j .. 32j+31 in the lanes of row quarter j.  A row of 16-bit patterns is 256 bytes, of which a lane would hold
 // 4 neighbouring 16-byte pieces: every load instruction would touch every line of the tile and use a quarter of each.
@@ -465,8 +489,7 @@ __device__ __forceinline__ void kseq_rebuild(KSeqState& ks, const LaneCtx& L, co
   float zq = 0.f;
 #pragma unroll
   for (int c = 0; c < NC; ++c) zq = fmaf(zc[c], k_chan_scale<BK>(c), zq);
-  zq += __shfl_xor(zq, 16);
-  zq += __shfl_xor(zq, 32);
+  zq = rows_sum(zq);
   ks.zq_u = zq * (kCodeUnit - kCodeUnit * low_part);          // (only the high part's column adds the constant)
 }
 
@@ -514,8 +537,7 @@ __device__ __forceinline__ void kseq_rebuild_runs(KS& ks, const LaneCtx& L, cons
       ks.qoph[m] = u32x4{op[0], op[1], op[2], op[3]};
     }
   }
-  zq += __shfl_xor(zq, 16);
-  zq += __shfl_xor(zq, 32);
+  zq = rows_sum(zq);
   ks.zq_u = zq * (kCodeUnit - kCodeUnit * low_part);
 }
 
@@ -617,9 +639,7 @@ __device__ __forceinline__ void compute_step(const StepRegs<BK, BV>& r, const u3
   float lmax = fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])), fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7])));
   float lx = fmaf(lmax, kappa, st.headroom);
   if (__any(lx > st.m)) {
-    lx = fmaxf(lx, __shfl_xor(lx, 16));
-    lx = fmaxf(lx, __shfl_xor(lx, 32));
-    const float m_new = fmaxf(st.m, lx);
+    const float m_new = fmaxf(st.m, rows_max(lx));
     const float f = __builtin_amdgcn_exp2f(st.m - m_new);
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) st.acc[dt] *= f;
@@ -830,7 +850,7 @@ __device__ __forceinline__ void buffer_step(const uint8_t* k_resid, const uint8_
   NoKSeq none;
   compute_step<16, 16, R, BF, 1, 1, true>(r, qb, qb, qsum, kappa, st, L, tile, n, none);
   float l = (st.l[0] + st.l[1]) + (st.l[2] + st.l[3]);
-  l += __shfl_xor(l, 16); l += __shfl_xor(l, 32);
+  l = rows_sum(l);
   if (head_lane) {
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) *reinterpret_cast<float4v*>(&rec[h][16 * dt + 4 * L.j]) = st.acc[dt];
@@ -1249,7 +1269,7 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
 #pragma unroll
           for (int e = 0; e < 8; ++e) part += x[e];
           const int lpg = g.g_k >> 3;              // lanes per key group: 4, 8 or 16
-          for (int off = 1; off < lpg; off <<= 1) part += __shfl_xor(part, off, 16);
+          part = lanes_sum(part, lpg);
           if (item < R * 16 && (o & (lpg - 1)) == 0) sm_qsum[wave][hh][o >> lpg_shift(lpg)] = part;
         }
       }
@@ -1287,8 +1307,7 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
         float part = 0.f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) part = fmaf(xq[t][e], sm_hat[0][8 * o + e], part);
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) part += __shfl_xor(part, off, 16);
+        part = lanes_sum(part, 16);
         if (o == 0 && item < R * 16) sm_mnew[item >> 4] = part * (softmax_scale * kLog2e);
       }
     }
@@ -1416,13 +1435,13 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   float l = 0.f;
 #pragma unroll
   for (int v = 0; v < 4; ++v) l = fmaf(st.l[v], (float)(1 << v_slot_shift<BV>(v)), l);
-  l += __shfl_xor(l, 16); l += __shfl_xor(l, 32);
+  l = rows_sum(l);
 #pragma unroll
   for (int cs = 0; cs < NCV; ++cs) {
     float z = 0.f;
 #pragma unroll
     for (int v = 0; v < 4; ++v) z = fmaf(st.zacc[cs][v], (float)(1 << v_slot_shift<BV>(v)), z);
-    z += __shfl_xor(z, 16); z += __shfl_xor(z, 32);
+    z = rows_sum(z);
     const int gcs = grp + cs * kSetGroups;                     // the value group this lane's column carries in set cs
     if (gcs < g.ng_v) {
       const int dtg = 8 / g.ng_v;                              // d-tiles per value group
