@@ -1634,45 +1634,57 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
 }
 
 // Combine the split records of one (b, hq): log-sum-exp merge, then normalize (and take rotated values back).
-// 512 threads: four groups of 128 channels, group k takes the records s = k, k+4, ...  Every load is independent of
-// the ones before it (the maxima first, by one thread per record; then the weighted sums with the loop unrolled), so
-// the kernel costs a few memory latencies rather than one per record.
+// 512 threads: four groups of 128 channels, group k takes the records s = k, k+4, ..., eight at a time with all their loads
+// (maximum, sum, element) in flight together, under a running maximum of its own; one step through LDS adds the groups.  So
+// up to 32 records cost one memory latency, which is what bounds the kernel (with a pass over the maxima in front of the sums
+// it had two: whole steps, K4V2, before and now, 8 heads x 131071 tokens, 32 records, 27.1 and 26.6 us, x 8192, 16 records,
+// 12.0 and 11.2; 2 x 8 x 8 heads x 16384 tokens, 16 records, 15.5 and 14.7; 4 x 7 heads x 131071, 64 records, 20.05 and 19.85).
 struct RotV { int32_t on; uint32_t signs[4]; };
-constexpr int kMergeGroups = 4;
+constexpr int kMergeGroups = 4, kMergeDeep = 8;
 __global__ __launch_bounds__(128 * kMergeGroups) void merge_kernel(const float* __restrict__ ws, void* __restrict__ out,
                                                                    int out_dtype, int32_t n_splits, RotV rot) {
   __shared__ float row[kHeadDim];
-  __shared__ float s_part[kMergeGroups][kHeadDim + 1];     // partial sums of o (128) and l (1) per group
-  __shared__ float s_max[128 * kMergeGroups / 64];
+  __shared__ float s_o[kMergeGroups][kHeadDim], s_m[kMergeGroups], s_l[kMergeGroups];
   const int64_t hq = blockIdx.x;
   const int tid = threadIdx.x, d = tid & (kHeadDim - 1), grp = tid >> 7;
   const float* rec = ws + hq * n_splits * kRec;
-  // maximum over the records
-  float M = kNegBig;
-  for (int s = tid; s < n_splits; s += 128 * kMergeGroups) M = fmaxf(M, rec[s * kRec + kHeadDim]);
+  float M = kNegBig, o = 0.f, l = 0.f;
+  for (int s0 = grp; s0 < n_splits; s0 += kMergeGroups * kMergeDeep) {
+    float ms[kMergeDeep], ls[kMergeDeep], os[kMergeDeep];
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
-  if ((tid & 63) == 0) s_max[tid >> 6] = M;
-  __syncthreads();
+    for (int j = 0; j < kMergeDeep; ++j) {         // (records past the last repeat it and count nothing)
+      const float* r = rec + min(s0 + kMergeGroups * j, n_splits - 1) * kRec;
+      ms[j] = r[kHeadDim]; ls[j] = r[kHeadDim + 1]; os[j] = r[d];
+    }
+    float Mc = M;
 #pragma unroll
-  for (int w = 0; w < 128 * kMergeGroups / 64; ++w) M = fmaxf(M, s_max[w]);
-  // weighted sums of this group's records
-  float o = 0.f, l = 0.f;
-#pragma unroll 8
-  for (int s = grp; s < n_splits; s += kMergeGroups) {
-    const float f = __builtin_amdgcn_exp2f(rec[s * kRec + kHeadDim] - M);
-    o = fmaf(f, rec[s * kRec + d], o);
-    l = fmaf(f, rec[s * kRec + kHeadDim + 1], l);
+    for (int j = 0; j < kMergeDeep; ++j) Mc = fmaxf(Mc, ms[j]);
+    const float fo = __builtin_amdgcn_exp2f(M - Mc);
+    o *= fo; l *= fo;
+#pragma unroll
+    for (int j = 0; j < kMergeDeep; ++j) {
+      const float f = s0 + kMergeGroups * j < n_splits ? __builtin_amdgcn_exp2f(ms[j] - Mc) : 0.f;
+      o = fmaf(f, os[j], o);
+      l = fmaf(f, ls[j], l);
+    }
+    M = Mc;
   }
-  s_part[grp][d] = o;
-  if (d == 0) s_part[grp][kHeadDim] = l;
+  s_o[grp][d] = o;
+  if (d == 0) { s_m[grp] = M; s_l[grp] = l; }
   __syncthreads();
   if (grp != 0) {
     if (!rot.on) return;
   } else {
+    M = s_m[0];
+#pragma unroll
+    for (int k = 1; k < kMergeGroups; ++k) M = fmaxf(M, s_m[k]);
     o = 0.f; l = 0.f;
 #pragma unroll
-    for (int k = 0; k < kMergeGroups; ++k) { o += s_part[k][d]; l += s_part[k][kHeadDim]; }
+    for (int k = 0; k < kMergeGroups; ++k) {
+      const float f = __builtin_amdgcn_exp2f(s_m[k] - M);
+      o = fmaf(f, s_o[k][d], o);
+      l = fmaf(f, s_l[k], l);
+    }
   }
   const float val = o / l;
   if (rot.on) {                                      // uniform
@@ -1681,12 +1693,7 @@ __global__ __launch_bounds__(128 * kMergeGroups) void merge_kernel(const float* 
     if (tid < 16) store_unrotated_row(row, tid, rot.signs, out, out_dtype, hq);
     return;
   }
-  if (out_dtype == KVQ_F32) ((float*)out)[hq * kHeadDim + d] = val;
-  else if (out_dtype == KVQ_F16) ((_Float16*)out)[hq * kHeadDim + d] = (_Float16)val;
-  else {
-    uint32_t u = __float_as_uint(val);
-    ((uint16_t*)out)[hq * kHeadDim + d] = (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
-  }
+  store_out(out, out_dtype, hq * kHeadDim + d, val);
 }
 
 inline RotV rot_v_of(const Geom& g) {
@@ -1697,7 +1704,7 @@ inline RotV rot_v_of(const Geom& g) {
 // The same merge for up to 8 records (5 to 8 splits, 3 to 8 for attention alone over 7 or 8 heads, and those of token-wise keys behind a
 // residual buffer, which come from two launches): one wavefront pair per head, every
 // record's maximum, sum and element loaded at once -- 24 independent loads, one memory latency -- and no step through
-// LDS (the kernel above spends two latencies and two barriers, which is most of its 3.9 us at 4 records).
+// LDS.
 constexpr int kMergeFew = 8;
 __global__ __launch_bounds__(kHeadDim) void merge_few_kernel(const float* __restrict__ ws, void* __restrict__ out,
                                                              int out_dtype, int32_t n_splits, RotV rot) {
