@@ -178,7 +178,8 @@ kvq_status kvq_residual_bytes(const kvq_layout* layout, size_t bytes_out[2]);
 /* Bytes of scratch kvq_decode_attention needs for (q_heads, seq_len): the partial (max, sum, accumulator) records of its
  * split-sequence pass.  May be 0 (enough (b, h_kv) streams to fill the chip without splitting the sequence); then the
  * workspace pointer may be NULL.  Never shrinks as seq_len grows: a workspace sized once for the longest sequence
- * serves every shorter one.  Touches no device memory; the split plan follows the compute-unit count of the CURRENT
+ * serves every shorter one.  (A call also accepts fewer bytes, down to the records of a plan of at least two steps of 32 tokens
+ * per wavefront -- none for short sequences -- and then cuts the sequence into fewer parts.)  Touches no device memory; the split plan follows the compute-unit count of the CURRENT
  * device (256 when no device is usable), so size the workspace with the device current that the decode calls run on.
  * What the workspace holds before a call does not matter.  Behind the records lie counters of the workgroups that have
  * finished; every call numbers itself and takes a counter without its number for zero, so calls that overlap on one

@@ -64,6 +64,14 @@ kvq_status check_cache(const kvq_layout* L, const kvq_cache* c) {
   return KVQ_OK;
 }
 
+// One record of (head_dim + 2) floats per (batch, query head, split), padded to 16 bytes; behind them one 64-bit counter of
+// finished workgroups per (batch, kv head).
+size_t record_bytes(const kvq_layout* L, int32_t q_heads) { return (size_t)L->batch * q_heads * (kvq::kHeadDim + 4) * sizeof(float); }
+size_t counter_bytes(const kvq_layout* L) { return ((size_t)L->batch * L->kv_heads * 8 + 15) & ~(size_t)15; }
+size_t records_bytes(const kvq_layout* L, int32_t q_heads, int32_t records) {
+  return records == 1 ? 0 : records * record_bytes(L, q_heads) + counter_bytes(L);
+}
+
 }  // namespace
 
 extern "C" {
@@ -98,12 +106,8 @@ kvq_status kvq_decode_workspace_bytes(const kvq_layout* layout, int32_t q_heads,
   if (!bytes_out || q_heads <= 0 || q_heads % layout->kv_heads || seq_len <= 0) return KVQ_ERR_INVALID_ARG;
   if (seq_len > layout->max_seq) return KVQ_ERR_CAPACITY;
   const kvq::Geom g = kvq::make_geom(*layout);
-  // one record of (head_dim + 2) floats per (batch, query head, split), padded to 16 bytes; sized for the most records
-  // any length up to seq_len writes, so that the figure never shrinks as seq_len grows
-  const int32_t records = kvq::decode_records_bound(g, seq_len);
-  // ... followed by one 64-bit counter of finished workgroups per (batch, kv head)
-  *bytes_out = records == 1 ? 0 : (size_t)layout->batch * q_heads * records * (kvq::kHeadDim + 4) * sizeof(float) +
-                                      (((size_t)layout->batch * layout->kv_heads * 8 + 15) & ~(size_t)15);
+  // sized for the most records any length up to seq_len writes, so that the figure never shrinks as seq_len grows
+  *bytes_out = records_bytes(layout, q_heads, kvq::decode_records_bound(g, seq_len));
   return KVQ_OK;
 }
 
@@ -155,9 +159,8 @@ kvq_status decode_check(const kvq_layout* layout, const kvq_cache* cache, const 
   if (kvq::has_residual(*layout) && (int)q_dtype != layout->raw_dtype) return KVQ_ERR_UNSUPPORTED;   // residual tail: as unquantized
   if (layout->bits_k == 16 && (int)q_dtype != layout->raw_dtype) return KVQ_ERR_UNSUPPORTED;   // matrix operands share a type
   if ((layout->bits_k == 16 || layout->bits_v == 16) && fused_append) return KVQ_ERR_UNSUPPORTED; // fused append: both tensors quantized
-  size_t need = 0;
-  st = kvq_decode_workspace_bytes(layout, q_heads, seq_len, &need);
-  if (st != KVQ_OK) return st;
+  // (what the coarse plan needs: with less than kvq_decode_workspace_bytes the sequence is cut into fewer parts)
+  const size_t need = records_bytes(layout, q_heads, kvq::decode_records_bound(g, seq_len, true));
   if (need && (!workspace || workspace_bytes < need || !aligned16(workspace))) return KVQ_ERR_WORKSPACE;
   return KVQ_OK;
 }
@@ -165,9 +168,12 @@ kvq_status decode_check(const kvq_layout* layout, const kvq_cache* cache, const 
 // The launches of a call that decode_check has passed.
 kvq_status decode_launch(const kvq_layout* layout, const kvq_cache* cache, const void* q, kvq_dtype q_dtype, int32_t q_heads,
                          int32_t seq_len, float softmax_scale, void* out, kvq_dtype out_dtype, void* workspace,
-                         const kvq::AppendOne* app, void* stream, const int32_t* seq_lens = nullptr, int32_t lens_offset = 0) {
+                         size_t workspace_bytes, const kvq::AppendOne* app, void* stream, const int32_t* seq_lens = nullptr, int32_t lens_offset = 0) {
   const kvq::Geom g = kvq::make_geom(*layout);
-  const kvq::DecodePlan plan = kvq::plan_decode(g, seq_len);
+  const size_t counters = counter_bytes(layout);
+  const bool usable = workspace && aligned16(workspace) && workspace_bytes > counters;
+  const int64_t room = usable ? (int64_t)((workspace_bytes - counters) / record_bytes(layout, q_heads)) : 0;
+  const kvq::DecodePlan plan = kvq::plan_decode(g, seq_len, q_heads / layout->kv_heads, room);
   hipError_t e = kvq::launch_decode_attention(g, *cache, q, q_dtype, q_heads, seq_len, softmax_scale, out, out_dtype,
                                               (float*)workspace, plan, app, (hipStream_t)stream, seq_lens, lens_offset);
   return e == hipSuccess ? KVQ_OK : KVQ_ERR_DEVICE;
@@ -181,8 +187,8 @@ kvq_status decode_common(const kvq_layout* layout, const kvq_cache* cache, const
   kvq_status st = decode_check(layout, cache, q, q_dtype, q_heads, seq_len, softmax_scale, out, out_dtype, workspace,
                                workspace_bytes, app != nullptr);
   if (st != KVQ_OK) return st;
-  return decode_launch(layout, cache, q, q_dtype, q_heads, seq_len, softmax_scale, out, out_dtype, workspace, app, stream,
-                       seq_lens, lens_offset);
+  return decode_launch(layout, cache, q, q_dtype, q_heads, seq_len, softmax_scale, out, out_dtype, workspace, workspace_bytes, app,
+                       stream, seq_lens, lens_offset);
 }
 }  // namespace
 
@@ -257,7 +263,8 @@ kvq_status kvq_decode_step(const kvq_layout* layout, const kvq_cache* cache, con
     if ((int)in_dtype != layout->raw_dtype) return KVQ_ERR_INVALID_ARG;     // the buffer keeps patterns of raw_dtype
     if ((pos + 1) % kvq::residual_slots(*layout) != 0) {
       const kvq::AppendOne app{k_new, v_new, (int)in_dtype, stride_b, stride_h};
-      return decode_launch(layout, cache, q, q_dtype, q_heads, pos + 1, softmax_scale, out, out_dtype, workspace, &app, stream);
+      return decode_launch(layout, cache, q, q_dtype, q_heads, pos + 1, softmax_scale, out, out_dtype, workspace, workspace_bytes, &app,
+                           stream);
     }
     st = kvq_quantize_append(layout, cache, k_new, v_new, in_dtype, stride_b, stride_h, layout->head_dim, pos, 1, stream);
     if (st != KVQ_OK) return st;

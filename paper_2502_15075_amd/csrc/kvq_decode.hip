@@ -1898,19 +1898,9 @@ int plan_steps(const Geom& g, int32_t seq_len) {
 }
 }  // namespace
 
-// Upper bound, over every length up to seq_len, of the partial records per (batch, query head) that one decode call
-// writes (with a residual buffer: one per split of the flushed blocks plus one for the tail in the buffer): the number of splits
-// before the steps are dealt out never shrinks as the sequence grows, and dealing them out in whole multiples of the
-// workgroup's wavefronts only ever lowers it.  The workspace is sized for this bound, so a workspace sized once for the longest sequence serves every
-// shorter one (the exact count is not monotone in the length).
-int32_t decode_records_bound(const Geom& g, int32_t seq_len) {
-  const int n_steps = plan_steps(g, seq_len);
-  if (n_steps == 0) return 1;
-  const int splits = wave_budget(g, n_steps).splits;
-  return g.resid ? splits + 1 : splits;
-}
-
-DecodePlan plan_decode(const Geom& g, int32_t seq_len) {
+namespace {
+// The plan for every layout: fill the chip exactly once, at least two steps per wavefront.
+DecodePlan plan_coarse(const Geom& g, int32_t seq_len) {
   // Fill the chip exactly once: compute units x 4 SIMDs x KVQ_WAVES_PER_SIMD wavefronts, spread over the (b,h) streams.
   // Workgroups of 8 wavefronts halve the number of sequence splits (none at all from 256 streams up, where the
   // merge kernel and the workspace traffic disappear); each wavefront should still own a few steps.
@@ -1925,6 +1915,78 @@ DecodePlan plan_decode(const Geom& g, int32_t seq_len) {
   sps = (sps + nw * unit - 1) / (nw * unit) * (nw * unit);
   const int splits = (n_steps + sps - 1) / sps;
   return DecodePlan{splits, sps, nw};
+}
+
+// Sequences without a residual buffer (whose plan takes whole blocks as it is) are cut with their parts' size in view.  n8: steps per
+// wavefront if one workgroup of 8 took the sequence; most: workgroups per sequence that fill the chip.
+//   - n8 <= 3: one workgroup and nothing to merge.
+//   - n8 == 4: four parts of one step per wavefront, which the launch merges itself, where the chip has room for them and there are up to 4
+//     heads to merge (more: one part up to 30 steps, then two).
+//   - above that up to 8 parts of two or three steps per wavefront.  Up to 4 heads leave this to the coarse plan: a few parts more, and with
+//     them the second launch, gain 0.5 us on the device and lose 1 where the host paces.
+//   - where more than three steps per wavefront are left, as few as all the parts allow: from 9 records on a larger merge launch costs a
+//     microsecond more.
+// Fused steps, K4V2, 4 query heads unless said, before (the coarse plan) and so, captured in a graph: 8 heads x 800 tokens 7.07 and 6.44 us,
+// x 1024 7.43 and 6.85 (1 query head 7.38 and 6.84), x 7000 10.73 and 9.93, x 8192 10.12 and 9.28, x 10000 11.12 and 10.51; 8 x 8
+// heads x 1024 8.23 and 7.90; 4 x 8 heads x 3000, 8 query heads, back to back 10.32 and 9.45.  On the other side of the lines: 8 heads x 640 tokens in
+// one part 6.49, in three 6.94; 8 heads x 800, 8 query heads, in one part 8.01, in four 8.12; 16 x 8 heads x 800 in one part 7.89, in two
+// 8.10; 8 heads x 3000 in 4 parts 8.93, back to back 8.52, in 6 parts 8.45 and 9.57; 8 heads x 4096 in 8 parts 8.49, in 16 9.53, x
+// 6000 in 8 parts 9.12, in 24 9.73; x 8192 in 8 parts 10.46, in 16 10.17, in 32 9.28.
+struct FinePlan { int splits, steps; };            // steps per wavefront; splits = 0: the coarse plan
+FinePlan fine_plan(int n_steps, int most, int heads) {
+  const int n8 = (n_steps + 7) / 8;
+  if (n8 == 4 && most >= 4 && heads <= 4) return FinePlan{4, 1};
+  if (most <= 1 || n8 <= 3 || n_steps < 31) return FinePlan{1, n8};
+  const int few = most < 8 ? most : 8;
+  int steps;
+  if (n8 <= 3 * few) {
+    if (heads <= 4) return FinePlan{0, 0};
+    steps = (n8 + few - 1) / few;
+    if (steps < 2) steps = 2;
+  } else {
+    steps = (n8 + most - 1) / most;
+  }
+  return FinePlan{(n8 + steps - 1) / steps, steps};
+}
+// No length up to n_steps takes more parts.
+int fine_bound(int n_steps, int most) {
+  const int n8 = (n_steps + 7) / 8;
+  if (most <= 1 || n8 <= 3) return 1;
+  const int few = most < 8 ? most : 8, two = (n8 + 1) / 2 > 4 ? (n8 + 1) / 2 : 4;
+  if (n8 <= 3 * few) return two < few ? two : few;
+  return n8 < most ? n8 : most;
+}
+// Workgroups of 8 wavefronts per sequence that fill the chip; 0 where there are too many sequences for one each.
+int fine_most(const Geom& g) {
+  const int streams = g.batch * g.kv_heads, waves = device_compute_units() * 4 * KVQ_WAVES_PER_SIMD;
+  return g.resid ? 0 : (waves + streams - 1) / streams / 8;
+}
+}  // namespace
+
+// Upper bound, over every length up to seq_len, of the partial records per (batch, query head) that one decode call
+// writes (with a residual buffer: one per split of the flushed blocks plus one for the tail in the buffer): the number of splits
+// before the steps are dealt out never shrinks as the sequence grows, and dealing them out in whole multiples of the
+// workgroup's wavefronts only ever lowers it.  The workspace is sized for this bound, so a workspace sized once for the longest sequence serves every
+// shorter one (the exact count is not monotone in the length).  coarse: of the coarse plan alone, which is what a call must
+// bring; with less than the full bound it falls back on that plan.
+int32_t decode_records_bound(const Geom& g, int32_t seq_len, bool coarse) {
+  const int n_steps = plan_steps(g, seq_len);
+  if (n_steps == 0) return 1;
+  const int splits = wave_budget(g, n_steps).splits;
+  if (g.resid) return splits + 1;
+  const int fine = coarse ? 0 : fine_bound(n_steps, fine_most(g));
+  return fine > splits ? fine : splits;
+}
+
+// heads: query heads per kv head; room: records per query head that the workspace holds.
+DecodePlan plan_decode(const Geom& g, int32_t seq_len, int heads, int64_t room) {
+  const int n_steps = plan_steps(g, seq_len), most = n_steps ? fine_most(g) : 0;
+  if (most < 1) return plan_coarse(g, seq_len);
+  const FinePlan f = fine_plan(n_steps, most, heads);
+  if (f.splits == 0 || (f.splits > 1 && f.splits > room)) return plan_coarse(g, seq_len);
+  // (fewer than 8 steps and one or two heads: four wavefronts have less to merge.  7 steps, 4 and 8 wavefronts, 1 head 5.02 and 5.10 us,
+  // 2 heads 5.10 and 5.20, 3 heads 5.56 and 5.14, 8 heads 6.62 and 6.23; 8 steps, 1 head 5.63 and 5.29, 8 heads 7.26 and 6.45)
+  return DecodePlan{f.splits, 8 * f.steps, n_steps < 8 && heads < 3 ? 4 : 8};
 }
 
 // Where the launch's own workgroups merge the records instead of a second launch.  Counting in, after the wait for the

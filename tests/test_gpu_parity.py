@@ -887,6 +887,42 @@ def test_channelwise_attention_fp16_long_multi_split(kvq, oracle):
         assert _rel_err(out.cpu().numpy(), ref) < TOL
 
 
+@pytest.mark.parametrize("R", [1, 2, 4, 8])
+@pytest.mark.parametrize("B,H", [(1, 2), (1, 32), (12, 8)])
+def test_plans_of_short_sequences(kvq, oracle, B, H, R):
+    """The lengths at which the split of a short sequence changes (7, 8, 24, 25, 31, 64, 65, 192, 193 and more steps of 32 tokens; few,
+    32 and 96 (batch, kv head) pairs): the fused step and attention alone with the workspace that the library asks for, with
+    none or too little of it for all the parts (then fewer are made), against the oracle."""
+    few = H == 2
+    for T in (193, 224, 255, 256, 480, 768, 769, 991, 992, 1025) + ((1500, 2049, 3000, 6145, 6400, 8192) if few and R in (1, 4) else ()):
+        K, V, q = synth.make_kvq(T + R, B, H, H * R, T, dtype=torch.bfloat16, sigma_k=1.0)
+        Lg, Lo = _layouts(kvq, oracle, B, H, T, 4, 2, 64, 64, raw=1)
+        planes = oracle.new_planes(Lo)
+        oracle.quantize_append(Lo, planes, synth.to_numpy_bits(K), synth.to_numpy_bits(V), 0, bf16=True)
+        ref = oracle.decode_attention(Lo, planes, synth.to_numpy_bits(q), T, 1 / math.sqrt(128), bf16=True)
+        cache = kvq.Cache(Lg, fill=0)
+        Kd, Vd, qd = K.cuda(), V.cuda(), q.cuda()
+        kvq.quantize_append(Lg, cache, Kd[:, :, :T - 1], Vd[:, :, :T - 1], 0)
+        need = kvq.decode_workspace_bytes(Lg, H * R, T)
+        out = torch.empty(q.shape, dtype=torch.float32, device="cuda")
+        kvq.decode_step(Lg, cache, Kd[:, :, T - 1], Vd[:, :, T - 1], T - 1, qd, 1 / math.sqrt(128), out,
+                        torch.full((max(16, need),), 0xFF, dtype=torch.uint8, device="cuda"))
+        assert _rel_err(out.cpu().numpy(), ref) < TOL, T
+        accepted = 0
+        for room in (need, need - 16, need // 2, 16, 0):
+            guard = torch.full((max(room, 0) + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+            out.fill_(float("nan"))
+            try:
+                kvq.decode_attention(Lg, cache, qd, T, 1 / math.sqrt(128), out, guard[:max(room, 0)] if room > 0 else torch.empty(0, dtype=torch.uint8, device="cuda"))
+            except kvq.KvqError as e:
+                assert e.status == kvq.ERR_WORKSPACE and room < need
+                continue
+            accepted += 1
+            assert _rel_err(out.cpu().numpy(), ref) < TOL, (T, room)
+            assert guard[max(room, 0):].eq(0x5A).all(), (T, room)             # nothing behind what was handed over
+        assert accepted >= (5 if need == 0 or T < 960 else 1)    # (a sequence of up to 30 steps never asked for any)
+
+
 @pytest.mark.parametrize("R", [1, 3, 8])
 @pytest.mark.parametrize("rl,blocks,dtype", [(64, 1, torch.float16), (64, 40, torch.bfloat16), (128, 1, torch.bfloat16), (128, 9, torch.float16)])
 def test_channelwise_tokens_in_the_buffer(kvq, oracle, R, rl, blocks, dtype):
