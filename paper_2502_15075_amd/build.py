@@ -12,6 +12,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libkvq.so")
+BINDING = os.path.join(HERE, "_kvq_binding.so")    # the hot calls of kvq.py as C functions (host code only)
 
 COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
           # packed-FP32 VALU forms are kept out of the generated code
@@ -61,9 +62,28 @@ def _compile(item):
     return objname, r.returncode, log, obj
 
 
+def _build_binding():
+    """The extension module, against this interpreter and its torch."""
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    inc = [os.path.join(ROOT, "include")] + cpp_extension.include_paths(device_type="cuda") + [sysconfig.get_paths()["include"]]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", os.path.join(CSRC, "kvq_binding.cpp"), "-o", BINDING]
+    for d in inc:
+        cmd += ["-isystem", d]
+    cmd += ["-L", os.path.join(os.path.dirname(torch.__file__), "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        if os.path.exists(BINDING):
+            os.remove(BINDING)
+        raise RuntimeError(f"binding failed:\n{r.stdout}{r.stderr}")
+
+
 def build_lib(verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=8) as ex:
+        binding = ex.submit(_build_binding)
         results = list(ex.map(_compile, UNITS))
     objs, failed = [], []
     for src, rc, log, obj in results:
@@ -76,6 +96,7 @@ def build_lib(verbose: bool = False) -> str:
         if os.path.exists(LIB):                    # nothing may load a library that the sources no longer produce
             os.remove(LIB)
         raise RuntimeError("hipcc failed on " + "\n".join(failed))
+    binding.result()
     r = subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}{r.stderr}")

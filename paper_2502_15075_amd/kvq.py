@@ -43,11 +43,32 @@ class _CCache(C.Structure):
 
 
 _lib = None
+# The extension module with the hot calls (csrc/kvq_binding.cpp).  Its functions take what the functions below take and return the
+# library's status, or None for a case that they leave to the code here.
+_fast = None
+
+
+def _bind(lib) -> None:
+    """Hands the library's entry points to the extension module; raises if that is not there."""
+    global _fast
+    if _fast is None:
+        try:
+            from . import _kvq_binding
+        except ModuleNotFoundError as e:
+            raise ImportError("the extension module _kvq_binding is missing: run `python -m paper_2502_15075_amd.build`") from e
+        _fast = _kvq_binding
+    _fast.bind(*[C.cast(f, C.c_void_p).value for f in (lib.kvq_quantize_append, lib.kvq_decode_attention, lib.kvq_decode_attention_varlen,
+                                                         lib.kvq_decode_step, lib.kvq_decode_step_varlen)])
+
+
+def _not_loaded(*args):
+    """In the extension functions' place until the library has been loaded."""
+    return None
 
 
 def load():
     """Loads libkvq.so (built by `paper_2502_15075_amd.build`); raises if it is not there."""
-    global _lib
+    global _lib, _fast_append, _fast_attention, _fast_attention_varlen, _fast_step, _fast_step_varlen
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError(f"{LIB_PATH} is missing: run `python -m paper_2502_15075_amd.build` (there is no fallback path)")
@@ -81,8 +102,14 @@ def load():
                   "kvq_decode_step", "kvq_dequantize", "kvq_reconstruction_error", "kvq_decode_attention_varlen",
                   "kvq_decode_step_varlen", "kvq_selftest_quantizer", "kvq_decode_attention_static"):
             getattr(lib, f).restype = C.c_int
+        _bind(lib)
+        _fast_append, _fast_attention, _fast_attention_varlen = _fast.quantize_append, _fast.decode_attention, _fast.decode_attention_varlen
+        _fast_step, _fast_step_varlen = _fast.decode_step, _fast.decode_step_varlen
         _lib = lib
     return _lib
+
+
+_fast_append = _fast_attention = _fast_attention_varlen = _fast_step = _fast_step_varlen = _not_loaded
 
 
 def status_string(status: int) -> str:
@@ -133,14 +160,16 @@ def _check(status: int, where: str) -> None:
 
 
 # What a call costs here is object building: attribute reads of tensors (0.1 to 0.3 us each) and ctypes temporaries (0.1 us
-# each).  Numbers are passed as numbers (the declared argument types convert them), and a tensor attribute is read
-# once.  Back to back, where the host paces: a 2048-token append of one sequence 7.1 us before and 6.0 now, a fused step over
-# 33 tokens 7.9 and 6.5.
+# each).  The five calls of a decode loop therefore go to the extension module first; what it leaves comes by the statements
+# below, where numbers are passed as numbers (the declared argument types convert them) and a tensor attribute is read once.
 
 def _stream_ptr() -> int:
     # (the raw handle of torch's current stream: the same value as torch.cuda.current_stream().cuda_stream, without
     # building a Stream object per call; current_device() stays for its check that this is no forked child)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    device = torch.cuda.current_device()
+    if _fast is not None:
+        _fast.ready()                                        # (torch's device runtime is up in this process)
+    return torch._C._cuda_getCurrentRawStream(device)
 
 
 def _p(t) -> int:
@@ -220,6 +249,11 @@ class Cache:
 
 def quantize_append(layout: Layout, cache: Cache, k_new: torch.Tensor, v_new: torch.Tensor, pos: int) -> None:
     """k_new, v_new: [B, H_kv, n_new, D] fp16/bf16 device tensors, last axis contiguous."""
+    st = _fast_append(layout, cache, k_new, v_new, pos)
+    if st is not None:
+        if st:
+            _check(st, "kvq_quantize_append")
+        return
     shape, strides, dtype = k_new.shape, k_new.stride(), k_new.dtype
     assert shape == v_new.shape and dtype == v_new.dtype and len(shape) == 4
     assert strides == v_new.stride() and strides[3] == 1
@@ -231,6 +265,11 @@ def quantize_append(layout: Layout, cache: Cache, k_new: torch.Tensor, v_new: to
 def decode_attention(layout: Layout, cache: Cache, q: torch.Tensor, seq_len: int, softmax_scale: float,
                      out: torch.Tensor, workspace: torch.Tensor) -> torch.Tensor:
     """q: [B, H_q, D] contiguous fp16/bf16; out: [B, H_q, D] contiguous fp32/fp16/bf16; workspace: uint8 device tensor."""
+    st = _fast_attention(layout, cache, q, seq_len, softmax_scale, out, workspace)
+    if st is not None:
+        if st:
+            _check(st, "kvq_decode_attention")
+        return out
     assert q.is_contiguous() and out.is_contiguous() and q.dim() == 3 and out.shape == q.shape
     st = load().kvq_decode_attention(layout.c(), cache.c(), _p(q), _DTYPES[q.dtype], q.size(1), seq_len,
                                      softmax_scale, _p(out), _DTYPES[out.dtype], _p(workspace),
@@ -254,6 +293,11 @@ def decode_step(layout: Layout, cache: Cache, k_new: torch.Tensor, v_new: torch.
                 softmax_scale: float, out: torch.Tensor, workspace) -> torch.Tensor:
     """Fused step: quantize the new token (k_new, v_new: [B, H_kv, D] or [B, H_kv, 1, D]) into position pos, then attend
     over [0, pos].  q, out, workspace as in decode_attention (workspace may be None when no bytes are needed)."""
+    st = _fast_step(layout, cache, k_new, v_new, pos, q, softmax_scale, out, workspace)
+    if st is not None:
+        if st:
+            _check(st, "kvq_decode_step")
+        return out
     if k_new.dim() == 4:
         k_new, v_new = k_new[:, :, 0], v_new[:, :, 0]
     strides, dtype, q_shape = k_new.stride(), k_new.dtype, q.shape
@@ -301,6 +345,11 @@ def decode_attention_varlen(layout: Layout, cache: Cache, q: torch.Tensor, seq_l
                             softmax_scale: float, out: torch.Tensor, workspace) -> torch.Tensor:
     """As decode_attention with one length per batch element: seq_lens is an int32 device tensor [B], max_seq_len an
     upper bound of its values (the workspace is sized for it)."""
+    st = _fast_attention_varlen(layout, cache, q, seq_lens, max_seq_len, softmax_scale, out, workspace)
+    if st is not None:
+        if st:
+            _check(st, "kvq_decode_attention_varlen")
+        return out
     assert q.is_contiguous() and out.is_contiguous() and q.dim() == 3 and out.shape == q.shape
     assert seq_lens.dtype == torch.int32 and seq_lens.is_contiguous() and seq_lens.numel() == layout.batch
     st = load().kvq_decode_attention_varlen(layout.c(), cache.c(), _p(q), _DTYPES[q.dtype], q.size(1), _p(seq_lens),
@@ -314,6 +363,11 @@ def decode_attention_varlen(layout: Layout, cache: Cache, q: torch.Tensor, seq_l
 def decode_step_varlen(layout: Layout, cache: Cache, k_new: torch.Tensor, v_new: torch.Tensor, pos: torch.Tensor,
                        max_pos: int, q: torch.Tensor, softmax_scale: float, out: torch.Tensor, workspace) -> torch.Tensor:
     """As decode_step with one position per batch element: pos is an int32 device tensor [B], max_pos its upper bound."""
+    st = _fast_step_varlen(layout, cache, k_new, v_new, pos, max_pos, q, softmax_scale, out, workspace)
+    if st is not None:
+        if st:
+            _check(st, "kvq_decode_step_varlen")
+        return out
     if k_new.dim() == 4:
         assert k_new.shape[2] == 1
         k_new, v_new = k_new[:, :, 0], v_new[:, :, 0]

@@ -278,3 +278,14 @@ def test_workspace_never_shrinks_as_the_sequence_grows(kvq):
         assert all(a <= b for a, b in zip(sizes, sizes[1:])), (B, H, axis)
         counters = (B * H * 8 + 15) // 16 * 16
         assert sizes[-1] > counters and (sizes[-1] - counters) % (132 * 4 * B * Hq) == 0
+
+
+def test_extension_module_leaves_what_is_not_plain(kvq):
+    """The extension module's functions do nothing and return None before a call has brought torch's device runtime up, and for
+    arguments of any other number or kind; they never raise."""
+    kvq.load()
+    f = kvq._fast
+    for fn, n in ((f.quantize_append, 5), (f.decode_attention, 7), (f.decode_attention_varlen, 8), (f.decode_step, 9), (f.decode_step_varlen, 10)):
+        for count in (0, 1, n - 1, n, n + 1):
+            for arg in (None, 1, 1.5, "x", object()):
+                assert fn(*[arg] * count) is None

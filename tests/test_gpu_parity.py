@@ -2423,3 +2423,91 @@ def test_channelwise_groups_of_negative_zeros(kvq, oracle, bk):
     oracle.seq_append(Lo, planes, synth.to_numpy_bits(K), synth.to_numpy_bits(K), 0, bf16=False)
     torch.cuda.synchronize()
     _assert_seq_planes_equal(cache, planes)
+
+
+def test_binding_routes_agree(kvq, monkeypatch):
+    """The hot calls go through the extension module where their arguments are plain, through the Python statements otherwise.  Both
+    take and refuse the same things with the same results: rows of both ranks and odd strides, missing, short and misaligned workspaces,
+    other dtypes, shapes and number types, a tensor subclass, a call on another stream."""
+    B, H, R, T, D, scale = 2, 2, 4, 1100, 128, 1 / math.sqrt(128)
+    L = kvq.Layout(B, H, T, D, 4, 2, raw_dtype=kvq.KVQ_BF16)
+    K, V, q = synth.make_kvq(41, B, H, H * R, T, D, dtype=torch.bfloat16, device="cuda", sigma_k=1.0)
+    Kt = K.transpose(1, 2).contiguous().transpose(1, 2)                       # the same rows with other strides
+    Vt = V.transpose(1, 2).contiguous().transpose(1, 2)
+    need = kvq.decode_workspace_bytes(L, H * R, T)
+    ws = torch.zeros(need + 16, dtype=torch.uint8, device="cuda")
+    lens = torch.tensor([T, 700], dtype=torch.int32, device="cuda")
+
+    class Sub(torch.Tensor):
+        pass
+
+    sub = q.as_subclass(Sub)
+    k3, v3, kt4, vt4 = K[:, :, -1].contiguous(), V[:, :, -1].contiguous(), Kt[:, :, -1:], Vt[:, :, -1:]
+    calls = [
+        ("append", lambda c, o: kvq.quantize_append(L, c, K, V, 0), True),
+        ("append strided", lambda c, o: kvq.quantize_append(L, c, Kt, Vt, 0), True),
+        ("append strides differ", lambda c, o: kvq.quantize_append(L, c, K, Vt, 0), False),
+        ("append fp32", lambda c, o: kvq.quantize_append(L, c, K.float(), V.float(), 0), True),
+        ("append int64", lambda c, o: kvq.quantize_append(L, c, K.view(torch.int16), V.view(torch.int16), 0), False),
+        ("append beyond", lambda c, o: kvq.quantize_append(L, c, K, V, 1), True),
+        ("append far beyond", lambda c, o: kvq.quantize_append(L, c, K, V, 1 << 40), False),
+        ("append numpy pos", lambda c, o: kvq.quantize_append(L, c, K, V, np.int64(0)), False),
+        ("attention", lambda c, o: kvq.decode_attention(L, c, q, T, scale, o, ws), True),
+        ("attention bf16", lambda c, o: kvq.decode_attention(L, c, q, T, scale, o.bfloat16(), ws), True),
+        ("attention int scale", lambda c, o: kvq.decode_attention(L, c, q, T, 1, o, ws), False),
+        ("attention zero scale", lambda c, o: kvq.decode_attention(L, c, q, T, 0.0, o, ws), True),
+        ("attention subclass", lambda c, o: kvq.decode_attention(L, c, sub, T, scale, o, ws), False),
+        ("attention strided q", lambda c, o: kvq.decode_attention(L, c, q.transpose(1, 2).contiguous().transpose(1, 2), T, scale, o, ws), False),
+        ("attention other shape", lambda c, o: kvq.decode_attention(L, c, q, T, scale, o[:, :4].contiguous(), ws), False),
+        ("attention double", lambda c, o: kvq.decode_attention(L, c, q, T, scale, o.double(), ws), False),
+        ("attention no workspace", lambda c, o: kvq.decode_attention(L, c, q, T, scale, o, None), True),
+        ("attention short workspace", lambda c, o: kvq.decode_attention(L, c, q, T, scale, o, ws[:64]), True),
+        ("attention odd workspace", lambda c, o: kvq.decode_attention(L, c, q, T, scale, o, ws[8:]), True),
+        ("step", lambda c, o: kvq.decode_step(L, c, k3, v3, T - 1, q, scale, o, ws), True),
+        ("step rank 4", lambda c, o: kvq.decode_step(L, c, kt4, vt4, T - 1, q, scale, o, ws), True),
+        ("step many rows", lambda c, o: kvq.decode_step(L, c, K[:, :, 5:9], V[:, :, 5:9], T - 1, q, scale, o, ws), False),
+        ("step negative", lambda c, o: kvq.decode_step(L, c, k3, v3, -1, q, scale, o, ws), True),
+        ("varlen", lambda c, o: kvq.decode_attention_varlen(L, c, q, lens, T, scale, o, ws), True),
+        ("varlen int64", lambda c, o: kvq.decode_attention_varlen(L, c, q, lens.long(), T, scale, o, ws), False),
+        ("varlen too many", lambda c, o: kvq.decode_attention_varlen(L, c, q, lens.repeat(2), T, scale, o, ws), False),
+        ("step varlen", lambda c, o: kvq.decode_step_varlen(L, c, k3, v3, lens - 1, T - 1, q, scale, o, ws), True),
+        ("step varlen rank 4", lambda c, o: kvq.decode_step_varlen(L, c, kt4, vt4, lens - 1, T - 1, q, scale, o, ws), True),
+    ]
+    names = ("_fast_append", "_fast_attention", "_fast_attention_varlen", "_fast_step", "_fast_step_varlen")
+    kvq.quantize_append(L, kvq.Cache(L, fill=0), K, V, 0)                       # (the module takes calls after the first one)
+    taken = []
+
+    def run(call, route, stream):
+        for n in names:
+            real = getattr(kvq._fast, {"_fast_append": "quantize_append", "_fast_attention": "decode_attention", "_fast_step": "decode_step",
+                                       "_fast_attention_varlen": "decode_attention_varlen", "_fast_step_varlen": "decode_step_varlen"}[n])
+
+            def counted(*a, real=real):
+                st = real(*a)
+                taken.append(st is not None)
+                return st
+            monkeypatch.setattr(kvq, n, counted if route else kvq._not_loaded)
+        cache = kvq.Cache(L, fill=0)
+        kvq.load().kvq_quantize_append(L.c(), cache.c(), Kt.data_ptr(), Vt.data_ptr(), 1, *Kt.stride()[:3], 0, T, kvq._stream_ptr())
+        o = torch.full((B, H * R, D), 7.0, dtype=torch.float32, device="cuda")
+        torch.cuda.synchronize()
+        try:
+            with torch.cuda.stream(stream):
+                res = call(cache, o)
+            what = "ok" if res is None else tuple(res.shape)
+        except kvq.KvqError as e:
+            what = ("kvq", e.status, str(e))
+        except Exception as e:                                                # noqa: BLE001
+            what = (type(e), str(e)[:60])
+        torch.cuda.synchronize()
+        return what, [p.clone() for p in cache.planes if p is not None] + [o]
+
+    for stream in (torch.cuda.current_stream(), torch.cuda.Stream()):
+        for name, call, fast in calls:
+            want, state = run(call, False, stream)
+            taken.clear()
+            got, new = run(call, True, stream)
+            assert got == want, name
+            assert taken == [fast], name
+            for a, b in zip(state, new):
+                assert torch.equal(a, b), name
