@@ -6,8 +6,9 @@
 //   - keys and values are separate workgroups (blockIdx.z), so that each body is compiled for one tensor's width alone;
 //   - the unit is a 32-token block: a thread owns 8 channels of the tokens u and u + 16 of it, whose value codes share
 //     their 32-bit words (for widths up to 4), so one set of 8 loads serves two rows;
-//   - a workgroup takes several blocks in a row and loads the next one (codes, scale/zero, reference rows) before it
-//     computes the current one, no load behind a branch;
+//   - a workgroup takes several blocks in a row, one or two in registers (codes, scale/zero, reference rows), which are loaded
+//     again, no load behind a branch, as soon as a block is done.  (A "next" that is copied to a "current" is waited for in
+//     whole at the copy: nothing is in flight from there to the next load, and the copy has registers of its own);
 //   - positions come from the grid and a running block number: no division per thread.
 // Figures: at the launchers.
 #include "kvq_internal.h"
@@ -187,19 +188,29 @@ __device__ __forceinline__ void dequantize_body(const Geom& g, const kvq_cache& 
     v_field(L.row, L.d0, code_lo_bits<B>(), &dw, &vs_lo);
     if constexpr (code_hi_bits<B>() != 0) v_field(L.row, L.d0, code_hi_bits<B>(), &dw, &vs_hi);
   }
-  Packed<B, IS_V, KSEQ> cur, next;
-  load_packed(cur, g, c, virtual_token(g, c.page_table, b, h, (int64_t)first * 32), L);
-  for (int blk = first; blk < end; ++blk) {
-    if constexpr (CHAIN) load_packed(next, g, c, virtual_token(g, c.page_table, b, h, (int64_t)min(blk + 1, end - 1) * 32), L);
+  constexpr int kDepth = CHAIN ? 2 : 1;
+  Packed<B, IS_V, KSEQ> packed[kDepth];
+  auto load_slot = [&](int k, int blk) {                         // (past the end the last block once more)
+    load_packed(packed[k], g, c, virtual_token(g, c.page_table, b, h, (int64_t)min(blk, end - 1) * 32), L);
+  };
 #pragma unroll
-    for (int x4 = 0; x4 < 2; ++x4) {
-      float val[8];
-      reconstruct<B, IS_V, KSEQ>(cur, x4, vs_lo, vs_hi, raw_bf16, val);
-      if (rotated) unrotate8(val, L.lane16, signs);            // (uniform; the 16 threads of a row are all here)
-      const int t = blk * 32 + 4 * wave + 16 * x4;             // the wavefront's first row
-      store_rows<OUT>(out, ((int64_t)bh * (t1 - t0) + (t - t0)) * kHeadDim, t, t0, t1, lane, val, lds + 512 * wave);
+  for (int k = 0; k < kDepth; ++k) load_slot(k, first + k);
+  for (int blk0 = first; blk0 < end; blk0 += kDepth) {
+#pragma unroll
+    for (int k = 0; k < kDepth; ++k) {
+      const int blk = blk0 + k;
+      if (blk < end) {                                           // (uniform)
+#pragma unroll
+        for (int x4 = 0; x4 < 2; ++x4) {
+          float val[8];
+          reconstruct<B, IS_V, KSEQ>(packed[k], x4, vs_lo, vs_hi, raw_bf16, val);
+          if (rotated) unrotate8(val, L.lane16, signs);          // (uniform; the 16 threads of a row are all here)
+          const int t = blk * 32 + 4 * wave + 16 * x4;           // the wavefront's first row
+          store_rows<OUT>(out, ((int64_t)bh * (t1 - t0) + (t - t0)) * kHeadDim, t, t0, t1, lane, val, lds + 512 * wave);
+        }
+      }
+      if constexpr (CHAIN) load_slot(k, blk + kDepth);
     }
-    if constexpr (CHAIN) cur = next;
   }
 }
 
@@ -335,24 +346,27 @@ __global__ __launch_bounds__(256) void zero_f64_kernel(double* p, int64_t n) {
 
 }  // namespace
 
-// Dequantize.  Blocks per workgroup: one for calls of fewer than 24576 blocks (both tensors counted), which need their
-// workgroups side by side, four in a row above that, the next one loaded ahead.  Measured, K4V2, both tensors: 8 x 8 heads
-// x 8192 tokens to bf16 (32768 blocks) 63 us with one, 57 with two, 52 to 55 with four or eight (6.2 TB/s); 29 x 8 heads
-// x 1181 tokens (17168 blocks) 28.0 us with one, 28.6 with four, 31.1 with eight; 562 tokens of 24 heads 5.7 us with one,
-// 8.3 with eight.  Before (one thread per row octet with two 64-bit divisions, widths switched per row): 181, 97.6, 6.7 us.
+// Dequantize, bound by its stores.  Blocks per workgroup: one for calls of fewer than 16384 blocks (both tensors counted), which need
+// their workgroups side by side, and for binary32 rows; above that eight in a row, dealt out evenly, two of them in registers.
+// In turn, K4V2, both tensors, to bf16: 8 x 8 heads x 8192 tokens (32768 blocks) 61.7 us with one, 55.9 with four, 52.1 with eight (6.3 TB/s), 53.5 with
+// sixteen, 54.1 with one in registers and 55.8 with four in a row, the next copied to the current (the version before); x 5000 (20096 blocks) 38.3 with
+// one, 33.0 with eight; 29 x 8 x 1181 (17632) 31.5 and 30.8; 40 x 8 x 800 (16000) 29.1 and 31.1; 6 x 8 x 4000 (12000) 17.0 and 20.3;
+// both tensors unquantized, 8 x 8 x 8192, 180 with four, 164 with eight.  To binary32, whose workgroups write twice the bytes: 8 x 8 x
+// 8192 85.5 us with one, 99.4 with eight, 101 with four; x 5000 56.4 and 63.6; 20 x 8 x 3000 87.3, 93 with four.
 // Streaming stores: 16-bit rows 52 us with them, 87 without.
-constexpr int kDeqChain = 4, kDeqChainFrom = 24576;
+constexpr int kDeqChain = 8, kDeqChainFrom = 16384;
 hipError_t launch_dequantize(const Geom& g, const kvq_cache& c, int32_t t0, int32_t t1, void* k_out, void* v_out,
                              int out_dtype, hipStream_t stream) {
   if (t1 == t0) return hipSuccess;
   const int streams = g.batch * g.kv_heads, blocks = ((t1 - 1) >> 5) - (t0 >> 5) + 1;
   const int tensors = (k_out ? 1 : 0) + (v_out ? 1 : 0);
   const uint32_t which_v = k_out ? 1u : 0u;
-  const int chain = (int64_t)blocks * streams * tensors >= kDeqChainFrom ? kDeqChain : 1;
+  const bool chained = out_dtype != KVQ_F32 && (int64_t)blocks * streams * tensors >= kDeqChainFrom;
+  const int per = chained ? (blocks + kDeqChain - 1) / kDeqChain : blocks, chain = (blocks + per - 1) / per;
   const dim3 grid((blocks + chain - 1) / chain, streams, tensors);
 #define KVQ_DEQ_LAUNCH(OUT_)                                                                                              \
-  if (chain > 1)                                                                                                         \
-    hipLaunchKernelGGL((dequantize_kernel<OUT_, true>), grid, dim3(256), 0, stream, g, c, t0, t1, k_out, v_out, chain, which_v); \
+  if (OUT_ != KVQ_F32 && chained)                                                                                        \
+    hipLaunchKernelGGL((dequantize_kernel<OUT_, OUT_ != KVQ_F32>), grid, dim3(256), 0, stream, g, c, t0, t1, k_out, v_out, chain, which_v); \
   else                                                                                                                   \
     hipLaunchKernelGGL((dequantize_kernel<OUT_, false>), grid, dim3(256), 0, stream, g, c, t0, t1, k_out, v_out, chain, which_v)
   if (out_dtype == KVQ_F32) { KVQ_DEQ_LAUNCH(KVQ_F32); }

@@ -165,6 +165,31 @@ def test_dequantize_is_bit_identical(kvq, oracle, bk, bv, g):
     assert torch.equal(kh.cpu(), torch.from_numpy(kd).to(torch.bfloat16))
 
 
+@pytest.mark.parametrize("T", [8192, 8225, 8415])
+@pytest.mark.parametrize("bk,bv,page,axis_seq,rotate", [(4, 2, 0, False, False), (3, 16, 0, False, False), (4, 2, 64, False, True), (2, 4, 0, True, False)])
+def test_dequantize_to_16_bits_of_many_blocks(kvq, T, bk, bv, page, axis_seq, rotate):
+    """Calls on both sides of 16384 blocks (32 heads x 256 and more blocks of two tensors), above which a workgroup takes up to eight
+    in a row: whole shares, one block over, uneven shares, first and last block partly asked for.  binary32 rows come by one
+    block per workgroup; rounding those once gives the 16-bit ones."""
+    B, H, D = 4, 8, 128
+    cap = (T + 63) // 64 * 64
+    pages = B * (cap // page) + 3 if page else 0
+    L = kvq.Layout(B, H, cap, D, bk, bv, 64, 64, axis_k=kvq.AXIS_SEQ if axis_seq else kvq.AXIS_HEAD_DIM, raw_dtype=kvq.KVQ_BF16,
+                   rotate_k=int(rotate), signs_k=(0x9E3779B9, 1, 2, 3) if rotate else (0, 0, 0, 0), page_tokens=page, n_pages=pages)
+    cache = kvq.Cache(L, fill=0)
+    if page:
+        cache.page_table = torch.randperm(pages, generator=torch.Generator().manual_seed(3))[:pages - 3].to(torch.int32).view(B, -1).contiguous().cuda()
+    K, V, _ = synth.make_kvq(8, B, H, H, cap, D, dtype=torch.bfloat16, device="cuda")
+    kvq.quantize_append(L, cache, K, V, 0)
+    for t0, t1 in ((0, T), (37, T), (0, T - 37)):
+        want = [torch.empty(B, H, t1 - t0, D, dtype=torch.float32, device="cuda") for _ in range(2)]
+        kvq.dequantize(L, cache, t0, t1, *want)
+        for dtype in (torch.bfloat16, torch.float16):
+            got = [torch.full((B, H, t1 - t0, D), float("nan"), dtype=dtype, device="cuda") for _ in range(2)]
+            kvq.dequantize(L, cache, t0, t1, *got)
+            assert torch.equal(got[0], want[0].to(dtype)) and torch.equal(got[1], want[1].to(dtype)), (t0, t1, dtype)
+
+
 # --------------------------------------------------------------------------- decode attention
 
 def test_config0_attention(kvq, oracle):
