@@ -287,20 +287,17 @@ __device__ __forceinline__ void sq_error_body(const Geom& g, const kvq_cache& c,
       r[x4] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ref + base + (int64_t)(t - t0) * st));
     }
   };
-  Packed<B, IS_V, KSEQ> cur, next;
-  u32x4 rcur[2], rnext[2];
+  u32x4 rows[2];
+  Packed<B, IS_V, KSEQ> packed;
+  load_ref(rows, first);
+  load_packed(packed, g, c, virtual_token(g, c.page_table, b, h, (int64_t)first * 32), L);
   double acc = 0.0;
-  load_ref(rcur, first);
-  load_packed(cur, g, c, virtual_token(g, c.page_table, b, h, (int64_t)first * 32), L);
   for (int blk = first; blk < end; ++blk) {
-    const int nb = min(blk + 1, end - 1);
-    load_ref(rnext, nb);
-    load_packed(next, g, c, virtual_token(g, c.page_table, b, h, (int64_t)nb * 32), L);
 #pragma unroll
     for (int x4 = 0; x4 < 2; ++x4) {
       float val[8], x[8];
-      reconstruct<B, IS_V, KSEQ>(cur, x4, vs_lo, vs_hi, raw_bf16, val);
-      const uint32_t rw[4] = {rcur[x4].x, rcur[x4].y, rcur[x4].z, rcur[x4].w};
+      reconstruct<B, IS_V, KSEQ>(packed, x4, vs_lo, vs_hi, raw_bf16, val);
+      const uint32_t rw[4] = {rows[x4].x, rows[x4].y, rows[x4].z, rows[x4].w};
 #pragma unroll
       for (int e = 0; e < 8; ++e) x[e] = widen16((uint16_t)(rw[e >> 1] >> (16 * (e & 1))), ref_bf16);
       // rotated rows are compared in the rotated basis: ||R x - y||_2 = ||x - R^T y||_2
@@ -314,8 +311,11 @@ __device__ __forceinline__ void sq_error_body(const Geom& g, const kvq_cache& c,
       const int t = blk * 32 + L.row + 16 * x4;
       if (t >= t0 && t < t1) acc += (double)sq;                // (what lies outside may hold anything)
     }
-    cur = next;
-    rcur[0] = rnext[0]; rcur[1] = rnext[1];
+    // the next block into the same registers, the loads moved up by the compiler to where each is used for the last time (past
+    // the end the last block once more, so that none is behind a branch)
+    const int nb = min(blk + 1, end - 1);
+    load_ref(rows, nb);
+    load_packed(packed, g, c, virtual_token(g, c.page_table, b, h, (int64_t)nb * 32), L);
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o);
@@ -380,9 +380,14 @@ hipError_t launch_dequantize(const Geom& g, const kvq_cache& c, int32_t t0, int3
 // 32 workgroups per stream and tensor, because they all add to one address (209 of them: 32 us for 6685 tokens of 8
 // heads, 32 of them: 12 us), or one per 16 blocks where that is more, so that a long stream is not walked by few of them
 // (K4V2, one head, 65536 tokens: 60 us with 32, 33, 19 and 16 us with one per 32, 16 and 8 blocks; 4 heads keys alone 48,
-// 29, 23 and 27; 8 heads x 131072 122, and 115 with all three; the first version 56, 105 and 166).  Measured, K4V2, 8 x 8 heads x 32768 tokens: 226 us = 5.8 TB/s (3, 5, 6, 7 per unit: 233, 239,
+// 29, 23 and 27; 8 heads x 131072 122, and 115 with all three; the first version 56, 105 and 166).  Measured, K4V2, 8 x 8 heads x 32768 tokens, with the copied block: 226 us = 5.8 TB/s (3, 5, 6, 7 per unit: 233, 239,
 // 228, 237; 8 and 16 per unit, more than are resident at once: 251 and 243); 13 x 8 x 2378, K4V1: 36 us (5 to 7 per unit:
 // 33, 33, 35).  Before (one row at a time per thread, 8192 workgroups): 291 us, 40 us for the 6685 tokens, 50 us.
+// One block in registers, loaded again in place, in turn with a next block that is copied to the current one: 8 x 8 heads x 32768 tokens 216 and 203 us
+// (228 and 216 on another card: 5.8 and 6.1 TB/s); 8 x 8 x 8192 K3V2 64.5 and 60.2, K8V4 64.2 and 62.2, K4V6 81 and 74, rotated keys 78 and 74; 48 x
+// 8 x 2000, K8V8, 111 and 95; one head of 65536 tokens 18.6 and 16.7; 33 x 8 x 4096 135 and 131; 44 x 8 x 4096 160 and 154.  Two blocks so: 8 x 8 x
+// 32768 205, but 94 registers instead of 67 leave five workgroups per unit where six or seven were resident: 44 x 8 x 4096 163, 43 x 8 x 2000, K8V4, 99
+// (93 copied, 90.5 with one).  Loaded at the head of the loop instead: 3 x 8 x 30000, K2V2, 95 (80 and 75), one head of 65536 21.3.
 // The share is rounded down, which leaves up to a third of the round empty, except where it would be one workgroup per
 // stream and tensor and leave a quarter or more empty: two are taken there, up to 6 per unit, all resident at once.  528
 // streams and tensors of 4096 tokens 135 us with two, 166 with one (152 before); 704: 166 and 170; 832: 219 and 212.
