@@ -948,6 +948,17 @@ def test_plans_of_short_sequences(kvq, oracle, B, H, R):
         assert accepted >= (5 if need == 0 or T < 960 else 1)    # (a sequence of up to 30 steps never asked for any)
 
 
+@pytest.mark.parametrize("T,records", [(8192, 32), (8200, 33), (16500, 65)])
+def test_merge_launch_of_many_records(kvq, oracle, T, records):
+    """The merge launch takes 32 records in one pass: a full pass, one record in a second one, two passes and one record."""
+    K, V, q = synth.make_kvq(T, 1, 1, 3, T, dtype=torch.bfloat16, sigma_k=1.0)
+    Lg, Lo = _layouts(kvq, oracle, 1, 1, T, 4, 2, 64, 64, raw=1)
+    cache, planes = _fill_both(kvq, oracle, Lg, Lo, K, V, [(0, T)])
+    assert kvq.decode_workspace_bytes(Lg, 3, T) >= records * 3 * 132 * 4
+    ref = oracle.decode_attention(Lo, planes, synth.to_numpy_bits(q), T, 1 / math.sqrt(128), bf16=True)
+    assert _rel_err(_decode(kvq, Lg, cache, q, T).cpu().numpy(), ref) < TOL
+
+
 @pytest.mark.parametrize("R", [1, 3, 8])
 @pytest.mark.parametrize("rl,blocks,dtype", [(64, 1, torch.float16), (64, 40, torch.bfloat16), (128, 1, torch.bfloat16), (128, 9, torch.float16)])
 def test_channelwise_tokens_in_the_buffer(kvq, oracle, R, rl, blocks, dtype):
