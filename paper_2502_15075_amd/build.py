@@ -62,18 +62,21 @@ def _compile(item):
     return objname, r.returncode, log, obj
 
 
-def _build_binding():
-    """The extension module, against this interpreter and its torch."""
+def binding_command(out: str, *extra: str):
+    """The compiler call that makes the extension module, against this interpreter and its torch."""
     import sysconfig
     import torch
     from torch.utils import cpp_extension
     inc = [os.path.join(ROOT, "include")] + cpp_extension.include_paths(device_type="cuda") + [sysconfig.get_paths()["include"]]
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", os.path.join(CSRC, "kvq_binding.cpp"), "-o", BINDING]
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *extra, os.path.join(CSRC, "kvq_binding.cpp"), "-o", out]
     for d in inc:
         cmd += ["-isystem", d]
-    cmd += ["-L", os.path.join(os.path.dirname(torch.__file__), "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
-    r = subprocess.run(cmd, capture_output=True, text=True)
+    return cmd + ["-L", os.path.join(os.path.dirname(torch.__file__), "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+
+
+def _build_binding():
+    r = subprocess.run(binding_command(BINDING), capture_output=True, text=True)
     if r.returncode != 0:
         if os.path.exists(BINDING):
             os.remove(BINDING)

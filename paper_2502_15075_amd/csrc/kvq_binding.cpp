@@ -9,6 +9,7 @@
 // Host time per call through kvq.py, without and with it: a 2048-token append of one sequence 5.6 and 3.9 us (4.0 of them the
 // library and the launch, by ctypes with everything at hand), a fused step 6.7 and 4.1; back to back that append takes 5.7 and 4.5 us.
 #include <Python.h>
+#include <string.h>
 #include <unistd.h>
 
 #include <ATen/PythonTorchFunctionTLS.h>
@@ -16,6 +17,11 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "kvq.h"
+
+// torch's current stream (a build that runs without a device names another source)
+#ifndef KVQ_CURRENT_STREAM
+#define KVQ_CURRENT_STREAM() c10::hip::getCurrentHIPStream().stream()
+#endif
 
 namespace {
 
@@ -31,34 +37,34 @@ pid_t g_pid = 0;
 PyObject* g_layout_attr = nullptr;                 // "_c", "_struct": where kvq.py's objects keep their C structs
 PyObject* g_cache_attr = nullptr;
 
-// The C struct that `obj` keeps under `attr`, or nullptr.
-template <typename T> const T* kept_struct(PyObject* obj, PyObject* attr) {
+// Copies the C struct that `obj` keeps under `attr` to `to`; false where there is none.  A copy, made with the interpreter's lock held:
+// `obj` may drop its struct (a new page table does) while the library, which runs without the lock, still reads it.
+template <typename T> bool copy_struct(PyObject* obj, PyObject* attr, T* to) {
   PyObject* s = PyObject_GetAttr(obj, attr);
-  if (!s) { PyErr_Clear(); return nullptr; }
+  if (!s) { PyErr_Clear(); return false; }
   Py_buffer view;
-  const T* p = nullptr;
+  bool copied = false;
   if (s != Py_None && PyObject_GetBuffer(s, &view, PyBUF_SIMPLE) == 0) {
-    if (view.len == (Py_ssize_t)sizeof(T)) p = static_cast<const T*>(view.buf);
+    copied = view.len == (Py_ssize_t)sizeof(T);
+    if (copied) memcpy(to, view.buf, sizeof(T));
     PyBuffer_Release(&view);
   } else {
     PyErr_Clear();
   }
-  Py_DECREF(s);                                    // (obj keeps it alive, and the caller obj)
-  return p;
+  Py_DECREF(s);
+  return copied;
 }
 
 // Reads the arguments of one call; `ok` turns false at the first that is not plain.
 struct Reader {
   bool ok = true;
-  const kvq_layout* layout = nullptr;
-  const kvq_cache* cache = nullptr;
+  kvq_layout layout;
+  kvq_cache cache;
   void* stream = nullptr;
 
   Reader(bool right_form, PyObject* l, PyObject* c) {
     if (!need(right_form && g_pid != 0 && getpid() == g_pid && !at::impl::torch_function_mode_enabled())) return;
-    layout = kept_struct<kvq_layout>(l, g_layout_attr);
-    cache = kept_struct<kvq_cache>(c, g_cache_attr);
-    if (need(layout && cache)) stream = c10::hip::getCurrentHIPStream().stream();
+    if (need(copy_struct(l, g_layout_attr, &layout) && copy_struct(c, g_cache_attr, &cache))) stream = KVQ_CURRENT_STREAM();
   }
   bool need(bool holds) { ok = ok && holds; return ok; }
   const at::Tensor* tensor(PyObject* o) { return need(THPVariable_CheckExact(o)) ? &THPVariable_Unpack(o) : nullptr; }
@@ -114,7 +120,7 @@ struct Attention {
 };
 const int32_t* lengths(Reader& r, PyObject* o) {
   const at::Tensor* t = r.tensor(o);
-  if (!r.ok || !r.need(t->scalar_type() == at::kInt && t->is_contiguous() && t->numel() == r.layout->batch)) return nullptr;
+  if (!r.ok || !r.need(t->scalar_type() == at::kInt && t->is_contiguous() && t->numel() == r.layout.batch)) return nullptr;
   return static_cast<const int32_t*>(t->data_ptr());
 }
 
@@ -146,7 +152,7 @@ PyObject* quantize_append(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const Rows w(r, a[2], a[3], true);
     const int32_t pos = r.int32(a[4]);
     if (!r.ok) return -1;
-    return released([&] { return g_append(r.layout, r.cache, w.k, w.v, w.type, w.sb, w.sh, w.st, pos, (int32_t)w.n, r.stream); });
+    return released([&] { return g_append(&r.layout, &r.cache, w.k, w.v, w.type, w.sb, w.sh, w.st, pos, (int32_t)w.n, r.stream); });
   });
 }
 
@@ -160,7 +166,7 @@ PyObject* decode_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int32_t len = r.int32(a[3]);
     if (!r.ok) return -1;
     return released([&] {
-      return g_attention(r.layout, r.cache, t.q, t.q_type, t.heads, len, t.scale, t.out, t.out_type, t.ws, t.ws_bytes, r.stream);
+      return g_attention(&r.layout, &r.cache, t.q, t.q_type, t.heads, len, t.scale, t.out, t.out_type, t.ws, t.ws_bytes, r.stream);
     });
   });
 }
@@ -176,7 +182,7 @@ PyObject* decode_attention_varlen(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int32_t bound = r.int32(a[4]);
     if (!r.ok) return -1;
     return released([&] {
-      return g_attention_varlen(r.layout, r.cache, t.q, t.q_type, t.heads, lens, bound, t.scale, t.out, t.out_type, t.ws, t.ws_bytes,
+      return g_attention_varlen(&r.layout, &r.cache, t.q, t.q_type, t.heads, lens, bound, t.scale, t.out, t.out_type, t.ws, t.ws_bytes,
                                 r.stream);
     });
   });
@@ -193,7 +199,7 @@ PyObject* decode_step(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int32_t pos = r.int32(a[4]);
     if (!r.ok) return -1;
     return released([&] {
-      return g_step(r.layout, r.cache, w.k, w.v, w.type, w.sb, w.sh, pos, t.q, t.q_type, t.heads, t.scale, t.out, t.out_type, t.ws,
+      return g_step(&r.layout, &r.cache, w.k, w.v, w.type, w.sb, w.sh, pos, t.q, t.q_type, t.heads, t.scale, t.out, t.out_type, t.ws,
                     t.ws_bytes, r.stream);
     });
   });
@@ -211,7 +217,7 @@ PyObject* decode_step_varlen(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int32_t bound = r.int32(a[5]);
     if (!r.ok) return -1;
     return released([&] {
-      return g_step_varlen(r.layout, r.cache, w.k, w.v, w.type, w.sb, w.sh, pos, bound, t.q, t.q_type, t.heads, t.scale, t.out,
+      return g_step_varlen(&r.layout, &r.cache, w.k, w.v, w.type, w.sb, w.sh, pos, bound, t.q, t.q_type, t.heads, t.scale, t.out,
                            t.out_type, t.ws, t.ws_bytes, r.stream);
     });
   });

@@ -1,0 +1,93 @@
+"""The extension module of the Python binding on the host: a build of it that takes the null stream, with callbacks in the
+library's place.  Nothing is launched and no device is needed."""
+import ctypes as C
+import importlib.util
+import subprocess
+
+import pytest
+import torch
+
+from paper_2502_15075_amd import build, kvq
+
+P, I32, I64, F, SZ = C.c_void_p, C.c_int32, C.c_int64, C.c_float, C.c_size_t
+# the five entry points, in the order in which bind() takes them
+SIGNATURES = {
+    "quantize_append": (P, P, P, P, C.c_int, I64, I64, I64, I32, I32, P),
+    "decode_attention": (P, P, P, C.c_int, I32, I32, F, P, C.c_int, P, SZ, P),
+    "decode_attention_varlen": (P, P, P, C.c_int, I32, P, I32, F, P, C.c_int, P, SZ, P),
+    "decode_step": (P, P, P, P, C.c_int, I64, I64, I32, P, C.c_int, I32, F, P, C.c_int, P, SZ, P),
+    "decode_step_varlen": (P, P, P, P, C.c_int, I64, I64, P, I32, P, C.c_int, I32, F, P, C.c_int, P, SZ, P),
+}
+
+
+@pytest.fixture(scope="module")
+def binding(tmp_path_factory):
+    """A module of its own: its entry points and its process are not those of the module that kvq.py has loaded."""
+    so = str(tmp_path_factory.mktemp("binding") / "_kvq_binding.so")
+    r = subprocess.run(build.binding_command(so, "-DKVQ_CURRENT_STREAM()=nullptr"), capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    spec = importlib.util.spec_from_file_location("_kvq_binding", so)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    return module
+
+
+class Library:
+    """Callbacks in the library's place: calls are noted with their arguments, and `body` (if any) runs inside of each."""
+
+    def __init__(self, binding):
+        self.calls, self.body = [], None
+        self.functions = [C.CFUNCTYPE(C.c_int, *sig)(self._entry(name)) for name, sig in SIGNATURES.items()]
+        binding.bind(*[C.cast(f, C.c_void_p).value for f in self.functions])
+        binding.ready()
+
+    def _entry(self, name):
+        def call(*args):
+            self.calls.append((name, args))
+            if self.body is not None:
+                self.body(*args)
+            return 0
+        return call
+
+
+def host_cache(layout, cls=kvq.Cache):
+    """A cache in host memory (its addresses go nowhere but to the callbacks)."""
+    return cls(layout, device="cpu", fill=0)
+
+
+def plain_arguments(layout, cache):
+    """For each function arguments that it takes."""
+    B, H, Hq = layout.batch, layout.kv_heads, 2 * layout.kv_heads
+    rows, one = torch.zeros(B, H, 3, 128, dtype=torch.float16), torch.zeros(B, H, 128, dtype=torch.float16)
+    q, out = torch.zeros(B, Hq, 128, dtype=torch.float16), torch.zeros(B, Hq, 128)
+    ws, lens = torch.zeros(64, dtype=torch.uint8), torch.ones(B, dtype=torch.int32)
+    return {
+        "quantize_append": [layout, cache, rows, rows.clone(), 5],
+        "decode_attention": [layout, cache, q, 7, 0.5, out, ws],
+        "decode_attention_varlen": [layout, cache, q, lens, 7, 0.5, out, ws],
+        "decode_step": [layout, cache, one, one.clone(), 6, q, 0.5, out, ws],
+        "decode_step_varlen": [layout, cache, one, one.clone(), lens, 6, q, 0.5, out, ws],
+    }
+
+
+@pytest.mark.parametrize("name", SIGNATURES)
+def test_structs_of_a_call_outlive_a_new_page_table(binding, name):
+    """While a call is inside the library the interpreter's lock is free: what another thread does to the cache, here a new page
+    table, must not change or free what the call reads."""
+    lib = Library(binding)
+    L = kvq.Layout(2, 2, 256, page_tokens=64, n_pages=8)
+    cache = host_cache(L)
+    cache.page_table = torch.zeros(2, 4, dtype=torch.int32)
+    want_layout, want_cache = bytes(L.c()), bytes(cache.c())
+    seen = []
+
+    def body(layout, planes, *_):
+        cache.page_table = torch.ones(2, 4, dtype=torch.int32)          # drops the struct that was kept ...
+        held = [(C.c_uint64 * (len(want_cache) // 8))(*[0x11] * (len(want_cache) // 8)) for _ in range(2000)]   # ... and takes its place
+        seen.append((C.string_at(layout, len(want_layout)), C.string_at(planes, len(want_cache)), len(held)))
+
+    lib.body = body
+    assert getattr(binding, name)(*plain_arguments(L, cache)[name]) == 0
+    assert len(seen) == 1
+    assert seen[0][0] == want_layout
+    assert seen[0][1] == want_cache
