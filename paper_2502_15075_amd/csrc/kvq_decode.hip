@@ -1652,18 +1652,21 @@ __global__ __launch_bounds__(128 * kMergeGroups) void merge_kernel(const float* 
   for (int s0 = grp; s0 < n_splits; s0 += kMergeGroups * kMergeDeep) {
     float ms[kMergeDeep], ls[kMergeDeep], os[kMergeDeep];
 #pragma unroll
-    for (int j = 0; j < kMergeDeep; ++j) {         // (records past the last repeat it and count nothing)
+    for (int j = 0; j < kMergeDeep; ++j) {         // (past the last record its cache lines once more, cleared below)
       const float* r = rec + min(s0 + kMergeGroups * j, n_splits - 1) * kRec;
       ms[j] = r[kHeadDim]; ls[j] = r[kHeadDim + 1]; os[j] = r[d];
     }
     float Mc = M;
 #pragma unroll
-    for (int j = 0; j < kMergeDeep; ++j) Mc = fmaxf(Mc, ms[j]);
+    for (int j = 0; j < kMergeDeep; ++j) {         // (cleared, not weighted by 0: an infinite value of an unquantized cache stays one)
+      if (s0 + kMergeGroups * j >= n_splits) { ms[j] = kNegBig; ls[j] = 0.f; os[j] = 0.f; }
+      Mc = fmaxf(Mc, ms[j]);
+    }
     const float fo = __builtin_amdgcn_exp2f(M - Mc);
     o *= fo; l *= fo;
 #pragma unroll
     for (int j = 0; j < kMergeDeep; ++j) {
-      const float f = s0 + kMergeGroups * j < n_splits ? __builtin_amdgcn_exp2f(ms[j] - Mc) : 0.f;
+      const float f = __builtin_amdgcn_exp2f(ms[j] - Mc);
       o = fmaf(f, os[j], o);
       l = fmaf(f, ls[j], l);
     }
@@ -1715,16 +1718,19 @@ __global__ __launch_bounds__(kHeadDim) void merge_few_kernel(const float* __rest
   float m[kMergeFew], l[kMergeFew], o[kMergeFew];
 #pragma unroll
   for (int j = 0; j < kMergeFew; ++j) {
-    const float* r = rec + min(j, n_splits - 1) * kRec;       // (records past the last repeat it: same cache lines)
+    const float* r = rec + min(j, n_splits - 1) * kRec;       // (past the last record its cache lines once more, cleared below)
     m[j] = r[kHeadDim]; l[j] = r[kHeadDim + 1]; o[j] = r[d];
   }
   float M = m[0];
 #pragma unroll
-  for (int j = 1; j < kMergeFew; ++j) M = fmaxf(M, m[j]);
+  for (int j = 1; j < kMergeFew; ++j) {
+    if (j >= n_splits) { m[j] = kNegBig; l[j] = 0.f; o[j] = 0.f; }
+    M = fmaxf(M, m[j]);
+  }
   float os = 0.f, ls = 0.f;
 #pragma unroll
   for (int j = 0; j < kMergeFew; ++j) {
-    const float f = j < n_splits ? __builtin_amdgcn_exp2f(m[j] - M) : 0.f;
+    const float f = __builtin_amdgcn_exp2f(m[j] - M);
     os = fmaf(f, o[j], os);
     ls = fmaf(f, l[j], ls);
   }

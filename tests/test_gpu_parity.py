@@ -959,6 +959,28 @@ def test_merge_launch_of_many_records(kvq, oracle, T, records):
     assert _rel_err(_decode(kvq, Lg, cache, q, T).cpu().numpy(), ref) < TOL
 
 
+@pytest.mark.parametrize("T,records", [(2000, 4), (2500, 5), (4000, 7), (4620, 9), (8192, 32), (8200, 33), (10000, 40)])
+def test_infinite_values_survive_every_merge(kvq, T, records):
+    """Values of an unquantized cache are whatever they are: an infinite one makes its channel's result infinite, of its sign, wherever the
+    record that holds it stands among the others and whichever way they are merged (in the launch, up to 8 at once, up to 32 per
+    pass); the other channels are what they are without it."""
+    R, D = 4, 128
+    K, V, q = synth.make_kvq(T + 1, 1, 1, R, T, D, dtype=torch.float16, sigma_k=0.1)
+    L = kvq.Layout(1, 1, T, D, 16, 16, raw_dtype=kvq.KVQ_F16)
+    if records > 1:
+        assert kvq.decode_workspace_bytes(L, R, T) >= records * R * 132 * 4
+    for token in (0, T // 2, T - 1):
+        Vi = V.clone()
+        Vi[0, 0, token, 3], Vi[0, 0, token, 70] = float("inf"), float("-inf")
+        cache = kvq.Cache(L, fill=0)
+        kvq.quantize_append(L, cache, K.cuda(), Vi.cuda(), 0)
+        out = _decode(kvq, L, cache, q, T).cpu()
+        assert (out[..., 3] == float("inf")).all() and (out[..., 70] == float("-inf")).all(), token
+        want = torch.softmax(q[0].double() @ K[0, 0].double().T / math.sqrt(D), dim=-1) @ V[0, 0].double()
+        rest = [d for d in range(D) if d not in (3, 70)]
+        assert _rel_err(out[0][:, rest].numpy(), want[:, rest].numpy()) < TOL, token
+
+
 @pytest.mark.parametrize("R", [1, 3, 8])
 @pytest.mark.parametrize("rl,blocks,dtype", [(64, 1, torch.float16), (64, 40, torch.bfloat16), (128, 1, torch.bfloat16), (128, 9, torch.float16)])
 def test_channelwise_tokens_in_the_buffer(kvq, oracle, R, rl, blocks, dtype):
