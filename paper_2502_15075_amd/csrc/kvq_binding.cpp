@@ -36,15 +36,25 @@ pid_t g_pid = 0;
 
 PyObject* g_layout_attr = nullptr;                 // "_c", "_struct": where kvq.py's objects keep their C structs
 PyObject* g_cache_attr = nullptr;
+PyObject* g_c = nullptr;                           // "c": the method that builds them
+PyObject* g_layout_class = nullptr;                // kvq.py's Layout and Cache (bind)
+PyObject* g_cache_class = nullptr;
 
-// Copies the C struct that `obj` keeps under `attr` to `to`; false where there is none.  A copy, made with the interpreter's lock held:
-// `obj` may drop its struct (a new page table does) while the library, which runs without the lock, still reads it.
-template <typename T> bool copy_struct(PyObject* obj, PyObject* attr, T* to) {
-  PyObject* s = PyObject_GetAttr(obj, attr);
-  if (!s) { PyErr_Clear(); return false; }
+// Copies the C struct of `obj` to `to`; false where there is none.  An object of kvq.py's own class keeps its struct under `attr`; where
+// nothing is kept yet, and for any other class, which may build it in its own way, it is what obj.c() returns.  A copy, made with
+// the interpreter's lock held: `obj` may drop its struct (a new page table does) while the library, which runs without the lock,
+// still reads it.
+template <typename T> bool copy_struct(PyObject* obj, PyObject* own, PyObject* attr, T* to) {
+  PyObject* s = (PyObject*)Py_TYPE(obj) == own ? PyObject_GetAttr(obj, attr) : nullptr;
+  if (!s || s == Py_None) {
+    PyErr_Clear();
+    Py_XDECREF(s);
+    s = PyObject_CallMethodNoArgs(obj, g_c);
+    if (!s) return false;
+  }
   Py_buffer view;
   bool copied = false;
-  if (s != Py_None && PyObject_GetBuffer(s, &view, PyBUF_SIMPLE) == 0) {
+  if (PyObject_GetBuffer(s, &view, PyBUF_SIMPLE) == 0) {
     copied = view.len == (Py_ssize_t)sizeof(T);
     if (copied) memcpy(to, view.buf, sizeof(T));
     PyBuffer_Release(&view);
@@ -64,7 +74,7 @@ struct Reader {
 
   Reader(bool right_form, PyObject* l, PyObject* c) {
     if (!need(right_form && g_pid != 0 && getpid() == g_pid && !at::impl::torch_function_mode_enabled())) return;
-    if (need(copy_struct(l, g_layout_attr, &layout) && copy_struct(c, g_cache_attr, &cache))) stream = KVQ_CURRENT_STREAM();
+    if (need(copy_struct(l, g_layout_class, g_layout_attr, &layout) && copy_struct(c, g_cache_class, g_cache_attr, &cache))) stream = KVQ_CURRENT_STREAM();
   }
   bool need(bool holds) { ok = ok && holds; return ok; }
   const at::Tensor* tensor(PyObject* o) { return need(THPVariable_CheckExact(o)) ? &THPVariable_Unpack(o) : nullptr; }
@@ -132,7 +142,11 @@ template <typename F> PyObject* plain(F body) {
   } catch (...) {                                  // (whatever a tensor without plain storage or strides raises)
     status = -1;
   }
-  if (status < 0) { PyErr_Clear(); Py_RETURN_NONE; }
+  if (status < 0) {                                // (an object's own c() may have raised: kvq.py meets that again, an interrupt goes on)
+    if (PyErr_Occurred() && !PyErr_ExceptionMatches(PyExc_Exception)) return nullptr;
+    PyErr_Clear();
+    Py_RETURN_NONE;
+  }
   return PyLong_FromLong(status);
 }
 // The library's call itself, other threads running.
@@ -223,15 +237,19 @@ PyObject* decode_step_varlen(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
-// (five addresses, in the order of the pointers above): the entry points of the library that kvq.py has loaded
+// (five addresses, in the order of the pointers above: the entry points of the library that kvq.py has loaded; then its classes
+// Layout and Cache)
 PyObject* bind(PyObject*, PyObject* args) {
   unsigned long long p[5];
-  if (!PyArg_ParseTuple(args, "KKKKK", &p[0], &p[1], &p[2], &p[3], &p[4])) return nullptr;
+  PyObject *layout, *cache;
+  if (!PyArg_ParseTuple(args, "KKKKKOO", &p[0], &p[1], &p[2], &p[3], &p[4], &layout, &cache)) return nullptr;
   g_append = reinterpret_cast<decltype(g_append)>(p[0]);
   g_attention = reinterpret_cast<decltype(g_attention)>(p[1]);
   g_attention_varlen = reinterpret_cast<decltype(g_attention_varlen)>(p[2]);
   g_step = reinterpret_cast<decltype(g_step)>(p[3]);
   g_step_varlen = reinterpret_cast<decltype(g_step_varlen)>(p[4]);
+  Py_INCREF(layout); Py_XSETREF(g_layout_class, layout);
+  Py_INCREF(cache); Py_XSETREF(g_cache_class, cache);
   Py_RETURN_NONE;
 }
 // torch's device runtime is up in this process (kvq.py says so after a call that went its own way).
@@ -251,6 +269,7 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_kvq_binding", nullptr, -1, method
 PyMODINIT_FUNC PyInit__kvq_binding(void) {
   g_layout_attr = PyUnicode_InternFromString("_c");
   g_cache_attr = PyUnicode_InternFromString("_struct");
-  if (!g_layout_attr || !g_cache_attr) return nullptr;
+  g_c = PyUnicode_InternFromString("c");
+  if (!g_layout_attr || !g_cache_attr || !g_c) return nullptr;
   return PyModule_Create(&module);
 }

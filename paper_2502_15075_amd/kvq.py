@@ -58,7 +58,7 @@ def _bind(lib) -> None:
             raise ImportError("the extension module _kvq_binding is missing: run `python -m paper_2502_15075_amd.build`") from e
         _fast = _kvq_binding
     _fast.bind(*[C.cast(f, C.c_void_p).value for f in (lib.kvq_quantize_append, lib.kvq_decode_attention, lib.kvq_decode_attention_varlen,
-                                                         lib.kvq_decode_step, lib.kvq_decode_step_varlen)])
+                                                         lib.kvq_decode_step, lib.kvq_decode_step_varlen)], Layout, Cache)
 
 
 def _not_loaded(*args):
@@ -138,6 +138,8 @@ class Layout:
     n_pages: int = 0
     resid_len: int = 0
 
+    _c = None                                                # (no field: the C struct, once c() has built it)
+
     def c(self) -> _CLayout:
         st = self.__dict__.get("_c")                         # (kept on the object: hashing 18 fields per call costs 1.5 us)
         if st is None:
@@ -204,6 +206,8 @@ def decode_workspace_bytes(layout: Layout, q_heads: int, seq_len: int) -> int:
 class Cache:
     """The caller-owned device planes (torch uint8 tensors) of one layer: codes and scale/zero of keys and values,
     then the two residual buffers of channel-wise keys (None otherwise)."""
+
+    _struct = None                                           # the C struct, once c() has built it
 
     def __init__(self, layout: Layout, device="cuda", fill=None):
         self.layout = layout

@@ -3,6 +3,7 @@ library's place.  Nothing is launched and no device is needed."""
 import ctypes as C
 import importlib.util
 import subprocess
+from dataclasses import replace
 
 import pytest
 import torch
@@ -38,7 +39,7 @@ class Library:
     def __init__(self, binding):
         self.calls, self.body = [], None
         self.functions = [C.CFUNCTYPE(C.c_int, *sig)(self._entry(name)) for name, sig in SIGNATURES.items()]
-        binding.bind(*[C.cast(f, C.c_void_p).value for f in self.functions])
+        binding.bind(*[C.cast(f, C.c_void_p).value for f in self.functions], kvq.Layout, kvq.Cache)
         binding.ready()
 
     def _entry(self, name):
@@ -91,3 +92,71 @@ def test_structs_of_a_call_outlive_a_new_page_table(binding, name):
     assert len(seen) == 1
     assert seen[0][0] == want_layout
     assert seen[0][1] == want_cache
+
+
+@pytest.mark.parametrize("name", SIGNATURES)
+def test_a_new_layout_and_cache_are_taken_at_once(binding, name):
+    """The first call that a layout and a cache are handed to is taken like any other: nobody has built their structs before."""
+    lib = Library(binding)
+    L = kvq.Layout(2, 2, 256 + 64 * list(SIGNATURES).index(name))
+    cache = host_cache(replace(L))
+    seen = []
+    lib.body = lambda layout, planes, *_: seen.append((C.string_at(layout, C.sizeof(kvq._CLayout)), C.string_at(planes, C.sizeof(kvq._CCache))))
+    assert L._c is None and cache._struct is None
+    assert getattr(binding, name)(*plain_arguments(L, cache)[name]) == 0
+    assert seen == [(bytes(L.c()), bytes(cache.c()))]
+
+
+@pytest.mark.parametrize("name", SIGNATURES)
+def test_a_class_that_builds_its_own_struct_is_asked_for_it(binding, name):
+    """A subclass with a c() of its own, and any other object that has one, is asked on every call, whatever has been kept."""
+    class Moving(kvq.Cache):
+        shift = 0
+
+        def c(self):
+            st = kvq._CCache.from_buffer_copy(kvq.Cache.c(self))
+            st.k_codes += self.shift
+            return st
+
+    class Longer(kvq.Layout):
+        def c(self):
+            st = kvq._CLayout.from_buffer_copy(kvq.Layout.c(self))
+            st.max_seq += 1
+            return st
+
+    class Other:                                             # no Cache at all
+        def __init__(self, cache):
+            self.cache = cache
+
+        def c(self):
+            return self.cache.c()
+
+    lib = Library(binding)
+    seen = []
+    lib.body = lambda layout, planes, *_: seen.append((kvq._CLayout.from_address(layout).max_seq, kvq._CCache.from_address(planes).k_codes))
+    L, cache = Longer(2, 2, 256), host_cache(kvq.Layout(2, 2, 256), Moving)
+    base = kvq.Cache.c(cache).k_codes                        # (kept now)
+    for shift in (0, 64, 128):
+        cache.shift = shift
+        assert getattr(binding, name)(*plain_arguments(L, cache)[name]) == 0
+        assert getattr(binding, name)(*plain_arguments(L, Other(cache))[name]) == 0
+        assert seen[-2:] == [(257, base + shift)] * 2
+
+
+def test_a_struct_that_cannot_be_built_is_left_to_the_caller(binding):
+    """An error in c() is none of the module's, an interrupt is passed on."""
+    class Broken(kvq.Cache):
+        error = ValueError
+
+        def c(self):
+            raise self.error
+
+    lib = Library(binding)
+    L = kvq.Layout(2, 2, 256)
+    cache = host_cache(L, Broken)
+    args = plain_arguments(L, cache)["quantize_append"]
+    assert binding.quantize_append(*args) is None
+    cache.error = KeyboardInterrupt
+    with pytest.raises(KeyboardInterrupt):
+        binding.quantize_append(*args)
+    assert lib.calls == []
