@@ -5,6 +5,7 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -12,7 +13,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libkvq.so")
-BINDING = os.path.join(HERE, "_kvq_binding.so")    # the hot calls of kvq.py as C functions (host code only)
+# the hot calls of kvq.py as C functions (host code only), for one interpreter: the suffix says which
+BINDING = os.path.join(HERE, "_kvq_binding" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
           # packed-FP32 VALU forms are kept out of the generated code
@@ -64,23 +66,26 @@ def _compile(item):
 
 def binding_command(out: str, *extra: str):
     """The compiler call that makes the extension module, against this interpreter and its torch."""
-    import sysconfig
     import torch
     from torch.utils import cpp_extension
     inc = [os.path.join(ROOT, "include")] + cpp_extension.include_paths(device_type="cuda") + [sysconfig.get_paths()["include"]]
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *extra, os.path.join(CSRC, "kvq_binding.cpp"), "-o", out]
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DKVQ_TORCH_VERSION="{torch.__version__}"', *extra, os.path.join(CSRC, "kvq_binding.cpp"), "-o", out]
     for d in inc:
         cmd += ["-isystem", d]
     return cmd + ["-L", os.path.join(os.path.dirname(torch.__file__), "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
 
 
-def _build_binding():
-    r = subprocess.run(binding_command(BINDING), capture_output=True, text=True)
-    if r.returncode != 0:
-        if os.path.exists(BINDING):
-            os.remove(BINDING)
-        raise RuntimeError(f"binding failed:\n{r.stdout}{r.stderr}")
+def _build_binding() -> str:
+    """Builds the extension module; returns what went wrong, "" if nothing did.  kvq.py works without it (the calls are slower)."""
+    for old in (BINDING, os.path.join(HERE, "_kvq_binding.so")):     # (the second: its name before it said the interpreter)
+        if os.path.exists(old):
+            os.remove(old)
+    try:
+        r = subprocess.run(binding_command(BINDING), capture_output=True, text=True)
+    except Exception as e:                          # no torch, no torch headers, no compiler
+        return f"{type(e).__name__}: {e}"
+    return "" if r.returncode == 0 else f"{r.stdout}{r.stderr}" or "the compiler failed"
 
 
 def build_lib(verbose: bool = False) -> str:
@@ -99,7 +104,8 @@ def build_lib(verbose: bool = False) -> str:
         if os.path.exists(LIB):                    # nothing may load a library that the sources no longer produce
             os.remove(LIB)
         raise RuntimeError("hipcc failed on " + "\n".join(failed))
-    binding.result()
+    if binding.result():
+        print(f"the extension module was not built, calls will go through ctypes:\n{binding.result()}", file=sys.stderr)
     r = subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}{r.stderr}")

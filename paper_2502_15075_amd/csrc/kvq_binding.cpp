@@ -271,5 +271,7 @@ PyMODINIT_FUNC PyInit__kvq_binding(void) {
   g_cache_attr = PyUnicode_InternFromString("_struct");
   g_c = PyUnicode_InternFromString("c");
   if (!g_layout_attr || !g_cache_attr || !g_c) return nullptr;
-  return PyModule_Create(&module);
+  PyObject* m = PyModule_Create(&module);
+  if (m && PyModule_AddStringConstant(m, "torch_version", KVQ_TORCH_VERSION) != 0) Py_CLEAR(m);   // (whose structures it reads)
+  return m;
 }

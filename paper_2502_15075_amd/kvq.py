@@ -9,6 +9,7 @@ from __future__ import annotations
 import ctypes as C
 import functools
 import os
+import warnings
 from dataclasses import dataclass
 
 import torch
@@ -48,27 +49,42 @@ _lib = None
 _fast = None
 
 
+def _extension():
+    """The extension module, or None where there is none for this interpreter and this torch, whose tensors it reads."""
+    try:
+        from . import _kvq_binding as module
+        built_for = getattr(module, "torch_version", "another torch")
+        if built_for == torch.__version__:
+            return module
+        reason = f"_kvq_binding is for torch {built_for}, this is {torch.__version__}"
+    except ImportError as e:
+        reason = str(e)
+    warnings.warn(f"the calls of a decode loop take about 2 us more host time each, by ctypes: {reason} "
+                  "(`python -m paper_2502_15075_amd.build` builds the extension module)", RuntimeWarning, stacklevel=4)
+    return None
+
+
 def _bind(lib) -> None:
-    """Hands the library's entry points to the extension module; raises if that is not there."""
-    global _fast
+    """Hands the library's entry points to the extension module, if there is one."""
+    global _fast, _fast_append, _fast_attention, _fast_attention_varlen, _fast_step, _fast_step_varlen
     if _fast is None:
-        try:
-            from . import _kvq_binding
-        except ModuleNotFoundError as e:
-            raise ImportError("the extension module _kvq_binding is missing: run `python -m paper_2502_15075_amd.build`") from e
-        _fast = _kvq_binding
+        _fast = _extension()
+    if _fast is None:
+        return
     _fast.bind(*[C.cast(f, C.c_void_p).value for f in (lib.kvq_quantize_append, lib.kvq_decode_attention, lib.kvq_decode_attention_varlen,
                                                          lib.kvq_decode_step, lib.kvq_decode_step_varlen)], Layout, Cache)
+    _fast_append, _fast_attention, _fast_attention_varlen = _fast.quantize_append, _fast.decode_attention, _fast.decode_attention_varlen
+    _fast_step, _fast_step_varlen = _fast.decode_step, _fast.decode_step_varlen
 
 
 def _not_loaded(*args):
-    """In the extension functions' place until the library has been loaded."""
+    """In the extension functions' place until the library has been loaded, and for good where there is no extension module."""
     return None
 
 
 def load():
     """Loads libkvq.so (built by `paper_2502_15075_amd.build`); raises if it is not there."""
-    global _lib, _fast_append, _fast_attention, _fast_attention_varlen, _fast_step, _fast_step_varlen
+    global _lib
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError(f"{LIB_PATH} is missing: run `python -m paper_2502_15075_amd.build` (there is no fallback path)")
@@ -103,8 +119,6 @@ def load():
                   "kvq_decode_step_varlen", "kvq_selftest_quantizer", "kvq_decode_attention_static"):
             getattr(lib, f).restype = C.c_int
         _bind(lib)
-        _fast_append, _fast_attention, _fast_attention_varlen = _fast.quantize_append, _fast.decode_attention, _fast.decode_attention_varlen
-        _fast_step, _fast_step_varlen = _fast.decode_step, _fast.decode_step_varlen
         _lib = lib
     return _lib
 

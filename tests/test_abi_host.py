@@ -12,9 +12,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 @pytest.fixture(scope="module")
 def kvq():
-    from paper_2502_15075_amd import kvq as m
-    if not os.path.exists(m.LIB_PATH):
-        from paper_2502_15075_amd import build
+    from paper_2502_15075_amd import build, kvq as m
+    if not os.path.exists(m.LIB_PATH) or not os.path.exists(build.BINDING):
         build.build_lib()
     m.load()
     return m

@@ -1,8 +1,13 @@
 """The extension module of the Python binding on the host: a build of it that takes the null stream, with callbacks in the
 library's place.  Nothing is launched and no device is needed."""
 import ctypes as C
+import importlib
 import importlib.util
+import os
 import subprocess
+import sys
+import sysconfig
+import types
 from dataclasses import replace
 
 import pytest
@@ -160,3 +165,52 @@ def test_a_struct_that_cannot_be_built_is_left_to_the_caller(binding):
     with pytest.raises(KeyboardInterrupt):
         binding.quantize_append(*args)
     assert lib.calls == []
+
+
+def test_the_module_that_is_built_is_the_one_that_is_loaded():
+    """Named for this interpreter, made for this torch, and what the calls go through."""
+    kvq.load()
+    assert os.path.samefile(kvq._fast.__file__, build.BINDING) and build.BINDING.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    assert kvq._fast.torch_version == torch.__version__
+    assert kvq._fast_append is kvq._fast.quantize_append and kvq._fast_step_varlen is kvq._fast.decode_step_varlen
+
+
+@pytest.mark.parametrize("there", [None, types.SimpleNamespace(), types.SimpleNamespace(torch_version="0.1")])
+def test_the_library_works_without_the_module(monkeypatch, there):
+    """None that can be imported, one from before it said what it was made for, one for another torch: load() says so and the
+    Python statements serve every call."""
+    name = "_kvq_binding"
+    package = importlib.import_module("paper_2502_15075_amd")
+    monkeypatch.setitem(sys.modules, f"{package.__name__}.{name}", there)
+    monkeypatch.delattr(package, name, raising=False)
+    if there is not None:
+        monkeypatch.setattr(package, name, there, raising=False)
+    for fast in ("_fast_append", "_fast_attention", "_fast_attention_varlen", "_fast_step", "_fast_step_varlen"):
+        monkeypatch.setattr(kvq, fast, kvq._not_loaded)
+    monkeypatch.setattr(kvq, "_fast", None)
+    monkeypatch.setattr(kvq, "_lib", None)
+    with pytest.warns(RuntimeWarning, match="ctypes"):
+        kvq.load()
+    assert kvq._fast is None and kvq._fast_append is kvq._not_loaded and kvq._fast_step is kvq._not_loaded
+    L = kvq.Layout(2, 2, 64)
+    assert kvq.cache_bytes(L) == [4 * 64 * 64, 4 * 64 * 8, 4 * 64 * 32, 4 * 64 * 8]
+    cache, rows = host_cache(L), torch.zeros(2, 2, 4, 128, dtype=torch.float16)
+    monkeypatch.setattr(kvq, "_stream_ptr", lambda: 0)       # (no device: what the library refuses before it launches anything)
+    with pytest.raises(kvq.KvqError) as e:
+        kvq.quantize_append(L, cache, rows, rows, 61)
+    assert e.value.status == kvq.ERR_CAPACITY
+
+
+@pytest.mark.parametrize("command", [["false"], ["/nonexistent/compiler"], None])
+def test_a_build_without_the_modules_compiler_goes_on(monkeypatch, tmp_path, command):
+    """A compiler that fails or is not there, torch headers that are not: said, and the module of an earlier build goes."""
+    def make(out, *extra):
+        if command is None:
+            raise ImportError("no torch headers")
+        return command
+    old = tmp_path / "_kvq_binding.so"
+    old.write_bytes(b"")
+    monkeypatch.setattr(build, "BINDING", str(old))
+    monkeypatch.setattr(build, "HERE", str(tmp_path))
+    monkeypatch.setattr(build, "binding_command", make)
+    assert build._build_binding() != "" and not old.exists()
