@@ -107,7 +107,7 @@ typedef enum {
   KVQ_ERR_INVALID_ARG = 1, /* null pointer, non-positive size, bits/group not allowed, bad head ratio */
   KVQ_ERR_UNSUPPORTED = 2, /* a valid request this build has no kernel for (head_dim != 128, axis) */
   KVQ_ERR_CAPACITY = 3,    /* pos + n_new > max_seq, seq_len > max_seq */
-  KVQ_ERR_WORKSPACE = 4,   /* workspace smaller than kvq_decode_workspace_bytes */
+  KVQ_ERR_WORKSPACE = 4,   /* workspace missing, misaligned or too small (kvq_decode_workspace_bytes always does) */
   KVQ_ERR_DEVICE = 5,      /* the HIP runtime reported an error at launch */
   KVQ_ERR_STATIC_SCRATCH = 6 /* kvq_decode_attention_static only: the call needs more partial-record bytes than
                                 KVQ_STATIC_SCRATCH_BYTES; use kvq_decode_attention with a workspace of the caller's */
@@ -178,9 +178,12 @@ kvq_status kvq_residual_bytes(const kvq_layout* layout, size_t bytes_out[2]);
 /* Bytes of scratch kvq_decode_attention needs for (q_heads, seq_len): the partial (max, sum, accumulator) records of its
  * split-sequence pass.  May be 0 (enough (b, h_kv) streams to fill the chip without splitting the sequence); then the
  * workspace pointer may be NULL.  Never shrinks as seq_len grows: a workspace sized once for the longest sequence
- * serves every shorter one.  (A call also accepts fewer bytes, down to the records of a plan of at least two steps of 32 tokens
- * per wavefront -- none for short sequences -- and then cuts the sequence into fewer parts.)  Touches no device memory; the split plan follows the compute-unit count of the CURRENT
- * device (256 when no device is usable), so size the workspace with the device current that the decode calls run on.
+ * serves every shorter one.  A call also accepts fewer bytes, down to the records of a plan of at least two steps of 32 tokens
+ * per wavefront (none for short sequences, none for the tokens in the residual buffer of channel-wise keys), and then cuts the
+ * sequence into fewer parts: the plan, and with it the rounding of the result, follows the number of bytes that a call is
+ * given, so calls that are to agree bit for bit bring the same number.  Touches no device memory; the split plan follows the
+ * compute-unit count of the CURRENT device (256 when no device is usable), so size the workspace with the device current that the
+ * decode calls run on.
  * What the workspace holds before a call does not matter.  Behind the records lie counters of the workgroups that have
  * finished; every call numbers itself and takes a counter without its number for zero, so calls that overlap on one
  * workspace race on it (their results are undefined) and calls after them are right again.  A call captured into a graph
@@ -205,7 +208,8 @@ kvq_status kvq_quantize_append(const kvq_layout* layout, const kvq_cache* cache,
  *        are not supported); q_heads / kv_heads in 1..8 (with 32-element groups on both tensors: up to 8, and the
  *        head count times the groups per row at most 32 after rounding the heads up to a power of two).
  *   out  [B][q_heads][D] contiguous, KVQ_F32 (the graded type), KVQ_F16 or KVQ_BF16 (rounded once).
- *   workspace  at least kvq_decode_workspace_bytes(layout, q_heads, seq_len) bytes, 16-byte aligned.
+ *   workspace  kvq_decode_workspace_bytes(layout, q_heads, seq_len) bytes (fewer: see there), 16-byte aligned;
+ *              KVQ_ERR_WORKSPACE where the call cannot do with what it is given.
  * Unquantized tensors (bits == 16; both: the full-precision baseline; one: the ablation that quantizes only keys or
  * only values, Table 1's discussion): a 16-bit key plane is multiplied by the query as it is, so q_dtype must be
  * raw_dtype (KVQ_ERR_UNSUPPORTED otherwise).  With exactly one tensor unquantized the keys are token-wise, values are

@@ -159,7 +159,7 @@ kvq_status decode_check(const kvq_layout* layout, const kvq_cache* cache, const 
   if (kvq::has_residual(*layout) && (int)q_dtype != layout->raw_dtype) return KVQ_ERR_UNSUPPORTED;   // residual tail: as unquantized
   if (layout->bits_k == 16 && (int)q_dtype != layout->raw_dtype) return KVQ_ERR_UNSUPPORTED;   // matrix operands share a type
   if ((layout->bits_k == 16 || layout->bits_v == 16) && fused_append) return KVQ_ERR_UNSUPPORTED; // fused append: both tensors quantized
-  // (what the coarse plan needs: with less than kvq_decode_workspace_bytes the sequence is cut into fewer parts)
+  // (the records that the call cannot do without: with less than kvq_decode_workspace_bytes a sequence is cut into fewer parts)
   const size_t need = records_bytes(layout, q_heads, kvq::decode_records_bound(g, seq_len, true));
   if (need && (!workspace || workspace_bytes < need || !aligned16(workspace))) return KVQ_ERR_WORKSPACE;
   return KVQ_OK;

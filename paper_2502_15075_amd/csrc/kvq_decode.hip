@@ -1970,17 +1970,20 @@ int fine_most(const Geom& g) {
 }  // namespace
 
 // Upper bound, over every length up to seq_len, of the partial records per (batch, query head) that one decode call
-// writes (with a residual buffer: one per split of the flushed blocks plus one for the tail in the buffer): the number of splits
+// writes: one per split (token-wise keys behind a residual buffer: of the flushed blocks) plus, for token-wise keys behind a buffer, one
+// for the tokens in it.  The number of splits
 // before the steps are dealt out never shrinks as the sequence grows, and dealing them out in whole multiples of the
 // workgroup's wavefronts only ever lowers it.  The workspace is sized for this bound, so a workspace sized once for the longest sequence serves every
-// shorter one (the exact count is not monotone in the length).  coarse: of the coarse plan alone, which is what a call must
-// bring; with less than the full bound it falls back on that plan.
-int32_t decode_records_bound(const Geom& g, int32_t seq_len, bool coarse) {
+// shorter one (the exact count is not monotone in the length).
+// least: what a call must bring.  That is the coarse plan's records: with less than the full bound the call falls back on that plan.  And
+// channel-wise keys, whose last split takes the buffer's tokens along, write none for them; the full bound counts one all the same,
+// as it did when they did: the figure that callers ask for, and may have kept, does not change.
+int32_t decode_records_bound(const Geom& g, int32_t seq_len, bool least) {
   const int n_steps = plan_steps(g, seq_len);
   if (n_steps == 0) return 1;
   const int splits = wave_budget(g, n_steps).splits;
-  if (g.resid) return splits + 1;
-  const int fine = coarse ? 0 : fine_bound(n_steps, fine_most(g));
+  if (g.resid) return least && g.axis_k == KVQ_AXIS_SEQ ? splits : splits + 1;
+  const int fine = least ? 0 : fine_bound(n_steps, fine_most(g));
   return fine > splits ? fine : splits;
 }
 

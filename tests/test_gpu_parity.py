@@ -1014,6 +1014,41 @@ def test_channelwise_tokens_in_the_buffer(kvq, oracle, R, rl, blocks, dtype):
         assert _rel_err(_decode(kvq, Lg, cache, q, T).cpu().numpy(), ref) < TOL, n
 
 
+@pytest.mark.parametrize("B,H,R,T,rl", [(32, 8, 2, 64, 64), (32, 8, 2, 101, 64), (33, 8, 8, 300, 128), (2, 4, 4, 1500, 64), (1, 2, 8, 3000, 64)])
+def test_channelwise_calls_ask_for_the_records_they_write(kvq, B, H, R, T, rl):
+    """Channel-wise keys write one record per split and none for the tokens in the buffer, which the last split takes along: from
+    256 (batch, kv head) pairs on a call needs no workspace at all, below that one record less than the size query counts.  With that
+    much the result is the one of a full workspace (the plan is the same), with a byte less the call is refused, and nothing
+    behind it is written.  Attention, the fused step and the calls with per-sequence lengths."""
+    D, scale = 128, 1 / math.sqrt(128)
+    K, V, q = synth.make_kvq(17, B, H, H * R, T, D, dtype=torch.bfloat16, device="cuda", sigma_k=1.0)
+    L = kvq.Layout(B, H, T, D, 4, 2, 64, 64, axis_k=kvq.AXIS_SEQ, raw_dtype=kvq.KVQ_BF16, resid_len=rl)
+    cache = kvq.Cache(L, fill=0)
+    kvq.quantize_append(L, cache, K, V, 0)
+    counters = (B * H * 8 + 15) // 16 * 16
+    records = (kvq.decode_workspace_bytes(L, H * R, T) - counters) // (132 * 4 * B * H * R)
+    least = 0 if records == 2 else (records - 1) * 132 * 4 * B * H * R + counters
+    assert (records == 2) == (B * H >= 256)
+    lens = torch.arange(T, T - B, -1, dtype=torch.int32, device="cuda").clamp(min=1)
+    k1, v1 = K[:, :, T - 1].contiguous(), V[:, :, T - 1].contiguous()
+    flushes = T % rl == 0                                    # (the step that completes a block flushes it again, to the same bytes)
+    calls = [lambda o, ws: kvq.decode_attention(L, cache, q, T, scale, o, ws),
+             lambda o, ws: kvq.decode_attention_varlen(L, cache, q, lens, T, scale, o, ws)]
+    if not flushes:
+        calls.append(lambda o, ws: kvq.decode_step(L, cache, k1, v1, T - 1, q, scale, o, ws))
+    for call in calls:
+        want = call(torch.empty(B, H * R, D, dtype=torch.float32, device="cuda"),
+                    torch.zeros(kvq.decode_workspace_bytes(L, H * R, T), dtype=torch.uint8, device="cuda"))
+        room = torch.full((least + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+        got = call(torch.empty_like(want), room[:least] if least else None)
+        assert torch.equal(got, want) and bool(torch.isfinite(got).all())
+        assert room[least:].eq(0x5A).all()
+        if least:
+            with pytest.raises(kvq.KvqError) as e:
+                call(torch.empty_like(want), room[:least - 1])
+            assert e.value.status == kvq.ERR_WORKSPACE
+
+
 def test_channelwise_decode_steps_cross_a_flush(kvq, oracle):
     """kvq_decode_step on a cache with channel-wise keys: positions 60..69 include the token that completes block 0
     (position 63: the buffer is flushed) and the first tokens of the next block."""
