@@ -1402,10 +1402,17 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   // 4096 tokens 25.9 and 24.9, 40 x 8 x 8 heads x 2000 tokens 22.2 and 21.3.  (Falling quarters for all 145.6, 45.6, 25.4, 16.8, 24.9; by the partner
   // for all 143.6, 44.3, 25.3, 17.3, 25.1; steps drawn from a counter in LDS 146.1, 44.2, 25.9, 17.4, 25.8: a wavefront draws
   // a ring ahead of what it computes, so the last steps still meet at the slow ones.)
-  // Not where memory alone binds (K8V8, 8 x 8 heads x 32768 tokens: 85.5 us before, 86.6 with it; K8V4 71.4 and 71.0), nor over
-  // channel-wise keys by 8 wavefronts (K4V2, 8 x 8 heads x 8229 tokens 17.25 and 17.44 us, K4V4 19.5 and 20.1; by 4, 40 x 8 heads x 3000
-  // tokens, 33.3 and 32.3).
-  constexpr bool kPairs = NW == 8, kYield = BK + BV <= 12 && !(KSEQ && kPairs);
+  // Not where memory alone binds: the sum of the widths, and 8-bit keys with values of one run (K8V8, 8 x 8 heads x 32768 tokens: 85.5 us
+  // before, 86.6 with it).  Equal priorities and these, 32 x 8 x 8 heads, in turn, means over eight placements of the planes (a call's time
+  // differs by up to 8 % between them, above all where sequences lie powers of two apart): K8V2 x 24576 tokens 185.9 and 192.5,
+  // x 36000 256.8 and 253.7, x 40960 299.7 and 321.8; K8V1 x 40960 287.0 and 305.4, K8V4 335.2 and 353.7, x 65536 522.4 and 519.9; 8 x
+  // 8 heads x 8192 tokens K8V4 22.4 and 22.4, K8V3 22.1 and 21.8.  On this side of the line: 6-bit keys gain 1 to 4 % (K6V1 x 36000
+  // 205.6 and 197.5, K6V6 308.7 and 304.9), except at 65536 and 81920 tokens, where they lose up to 2 (K6V2 x 65536 405.9 and 407.6, K6V4
+  // 473.3 and 480.8; x 70000 429.6 and 417.3, 497.6 and 492.1); narrower ones gain 1 to 5 (K4V2 x 65536 304.6 and 292.4, K4V4 377.6 and 362.5,
+  // K4V8 539.2 and 532.0, K1V8 412.9 and 402.4).
+  // Nor over channel-wise keys by 8 wavefronts (K4V2, 8 x 8 heads x 8229 tokens 17.25 and 17.44 us, K4V4 19.5 and 20.1; by 4, 40 x 8
+  // heads x 3000 tokens, 33.3 and 32.3).
+  constexpr bool kPairs = NW == 8, kYield = BK + BV <= 12 && !(BK == 8 && v_hi<BV>() == 0) && !(KSEQ && kPairs);
   const bool by_partner = kYield && kPairs && n_full >= 4 * kStages;
   const int q1 = kPairs ? kStages : n_full >> 2, q2 = kPairs ? 2 * kStages : n_full >> 1, q3 = q1 + q2;
   int partner = 0;                                 // the turn that the other wavefront of this SIMD has reached, in steps
