@@ -188,28 +188,45 @@ __device__ __forceinline__ void dequantize_body(const Geom& g, const kvq_cache& 
     v_field(L.row, L.d0, code_lo_bits<B>(), &dw, &vs_lo);
     if constexpr (code_hi_bits<B>() != 0) v_field(L.row, L.d0, code_hi_bits<B>(), &dw, &vs_hi);
   }
-  constexpr int kDepth = CHAIN ? 2 : 1;
-  Packed<B, IS_V, KSEQ> packed[kDepth];
-  auto load_slot = [&](int k, int blk) {                         // (past the end the last block once more)
-    load_packed(packed[k], g, c, virtual_token(g, c.page_table, b, h, (int64_t)min(blk, end - 1) * 32), L);
-  };
+  if constexpr (!CHAIN) {
+    // (a loop of its own, though it has one turn: as the ring below with a depth of one, or with the rows in a function of both, the
+    // compiler forms the addresses and orders the rotation otherwise, 2-bit values 1 to 4 % slower, rotated rows up to 10)
+    Packed<B, IS_V, KSEQ> cur;
+    load_packed(cur, g, c, virtual_token(g, c.page_table, b, h, (int64_t)first * 32), L);
+    for (int blk = first; blk < end; ++blk) {
 #pragma unroll
-  for (int k = 0; k < kDepth; ++k) load_slot(k, first + k);
-  for (int blk0 = first; blk0 < end; blk0 += kDepth) {
-#pragma unroll
-    for (int k = 0; k < kDepth; ++k) {
-      const int blk = blk0 + k;
-      if (blk < end) {                                           // (uniform)
-#pragma unroll
-        for (int x4 = 0; x4 < 2; ++x4) {
-          float val[8];
-          reconstruct<B, IS_V, KSEQ>(packed[k], x4, vs_lo, vs_hi, raw_bf16, val);
-          if (rotated) unrotate8(val, L.lane16, signs);          // (uniform; the 16 threads of a row are all here)
-          const int t = blk * 32 + 4 * wave + 16 * x4;           // the wavefront's first row
-          store_rows<OUT>(out, ((int64_t)bh * (t1 - t0) + (t - t0)) * kHeadDim, t, t0, t1, lane, val, lds + 512 * wave);
-        }
+      for (int x4 = 0; x4 < 2; ++x4) {
+        float val[8];
+        reconstruct<B, IS_V, KSEQ>(cur, x4, vs_lo, vs_hi, raw_bf16, val);
+        if (rotated) unrotate8(val, L.lane16, signs);            // (uniform; the 16 threads of a row are all here)
+        const int t = blk * 32 + 4 * wave + 16 * x4;             // the wavefront's first row
+        store_rows<OUT>(out, ((int64_t)bh * (t1 - t0) + (t - t0)) * kHeadDim, t, t0, t1, lane, val, lds + 512 * wave);
       }
-      if constexpr (CHAIN) load_slot(k, blk + kDepth);
+    }
+  } else {
+    constexpr int kDepth = 2;
+    Packed<B, IS_V, KSEQ> packed[kDepth];
+    auto load_slot = [&](int k, int blk) {                       // (past the end the last block once more)
+      load_packed(packed[k], g, c, virtual_token(g, c.page_table, b, h, (int64_t)min(blk, end - 1) * 32), L);
+    };
+#pragma unroll
+    for (int k = 0; k < kDepth; ++k) load_slot(k, first + k);
+    for (int blk0 = first; blk0 < end; blk0 += kDepth) {
+#pragma unroll
+      for (int k = 0; k < kDepth; ++k) {
+        const int blk = blk0 + k;
+        if (blk < end) {                                         // (uniform)
+#pragma unroll
+          for (int x4 = 0; x4 < 2; ++x4) {
+            float val[8];
+            reconstruct<B, IS_V, KSEQ>(packed[k], x4, vs_lo, vs_hi, raw_bf16, val);
+            if (rotated) unrotate8(val, L.lane16, signs);
+            const int t = blk * 32 + 4 * wave + 16 * x4;
+            store_rows<OUT>(out, ((int64_t)bh * (t1 - t0) + (t - t0)) * kHeadDim, t, t0, t1, lane, val, lds + 512 * wave);
+          }
+        }
+        load_slot(k, blk + kDepth);
+      }
     }
   }
 }
