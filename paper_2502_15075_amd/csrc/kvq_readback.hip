@@ -363,23 +363,52 @@ __global__ __launch_bounds__(256) void zero_f64_kernel(double* p, int64_t n) {
 
 }  // namespace
 
-// Dequantize, bound by its stores.  Blocks per workgroup: one for calls of fewer than 16384 blocks (both tensors counted), which need
-// their workgroups side by side, and for binary32 rows; above that eight in a row, dealt out evenly, two of them in registers.
-// In turn, K4V2, both tensors, to bf16: 8 x 8 heads x 8192 tokens (32768 blocks) 61.7 us with one, 55.9 with four, 52.1 with eight (6.3 TB/s), 53.5 with
-// sixteen, 54.1 with one in registers and 55.8 with four in a row, the next copied to the current (the version before); x 5000 (20096 blocks) 38.3 with
-// one, 33.0 with eight; 29 x 8 x 1181 (17632) 31.5 and 30.8; 40 x 8 x 800 (16000) 29.1 and 31.1; 6 x 8 x 4000 (12000) 17.0 and 20.3;
-// both tensors unquantized, 8 x 8 x 8192, 180 with four, 164 with eight.  To binary32, whose workgroups write twice the bytes: 8 x 8 x
-// 8192 85.5 us with one, 99.4 with eight, 101 with four; x 5000 56.4 and 63.6; 20 x 8 x 3000 87.3, 93 with four.
-// Streaming stores: 16-bit rows 52 us with them, 87 without.
-constexpr int kDeqChain = 8, kDeqChainFrom = 16384;
+// Dequantize, bound by its stores.  Blocks per workgroup: one for binary32 rows and for calls of fewer than 24576 blocks (both tensors
+// counted), which need their workgroups side by side; above that eight in a row, four of some keys alone (deq_in_a_row), dealt out evenly,
+// two of them in registers.  From 16384 blocks on already where one round of workgroups less pays: narrow tensors, and middling ones in
+// long sequences, whose uneven last share is a small part.
+// In turn, to bf16, us with one / four / eight in a row (and with the version before: four, the next copied to the current, from 24576 on).
+// Both tensors:
+//   8 x 8 heads x 8192 tokens (32768 blocks)  K4V2 60.4 / 53.5 / 50.7 (54.0)  K8V8 67.4 / 71.0 / 68.4 (72.7)  unquantized 156.0 / 179.2 / 164.0 (179.9)
+//   8 x 8 x 32768 (131072)                    K4V2 228.6 / 204.8 / 191.0 (204.7)
+//   8 x 8 x 5000 (20096)                      K4V2 37.1 / 33.3 / 32.5  paged 39.1 / 37.5 / 36.4  K4V4 42.2 / 41.4 / 41.0  K8V8 42.2 / 44.9 / 43.5
+//                                             unquantized 96.9 / 112.3 / 103.1
+//   40 x 8 x 900 (18560)                      K4V2 33.6 / 32.6 / 33.1  paged 35.8 / 37.2 / 38.3  rotated keys 40.1 / 41.8 / 42.5
+//                                             K4V4 38.4 / 40.4 / 39.1  K8V8 39.1 / 45.3 / 43.3  unquantized 89.9 / 112.5 / 103.5
+// Keys alone:
+//   16384 blocks   K4 29.8 / 25.7 / 27.7  K8 30.8 / 32.2 / 32.9
+//   32768          K4 57.8 / 49.2 / 51.3 (50.4)  K2 57.3 / 47.4 / 45.4 (49.5)  unquantized 80.7 / 78.3 / 80.5 (79.0)
+//   65536          K4 115.9 / 97.8 / 96.4 (97.9)  K2 113.8 / 94.8 / 91.6 (97.9)  unquantized 177.1 / 180.1 / 195.4 (187.1)
+// Values alone:
+//   16384          V2 29.2 / 28.2 / 27.3  V8 39.6 / 42.7 / 39.8
+//   32768          V2 59.3 / 53.8 / 51.4 (55.8)
+// To binary32, whose workgroups write twice the bytes: 8 x 8 x 8192 85.5 us with one, 99.4 with eight, 101 with four; x 5000 56.4 and 63.6;
+// 20 x 8 x 3000 87.3, 93 with four.  Streaming stores: 16-bit rows 52 us with them, 87 without.
+constexpr int kDeqChain = 8, kDeqChainKeys = 4, kDeqChainFrom = 24576, kDeqChainFromNarrow = 16384, kDeqLong = 64, kDeqManyKeys = 49152;
+// Whether several in a row pay from the smaller number of blocks on (blocks: of one sequence).
+inline bool deq_chains_early(const Geom& g, bool keys, bool values, int blocks) {
+  if (!values) return g.bits_k <= 6 && !g.rotate_k;
+  if (!keys) return g.bits_v <= 2;
+  if (g.bits_k <= 4 && g.bits_v <= 2 && !g.rotate_k && !g.rotate_v && g.page_shift == 0) return true;
+  return blocks >= kDeqLong && (g.bits_v <= 4 || (g.bits_v == 8 && g.bits_k <= 4));
+}
+// How many at most (blocks: of the call).
+inline int deq_in_a_row(const Geom& g, bool values, int64_t blocks) {
+  if (values) return kDeqChain;
+  if (g.bits_k >= 8 || g.rotate_k) return kDeqChainKeys;
+  return g.bits_k >= 4 && g.axis_k != KVQ_AXIS_SEQ && g.page_shift == 0 && blocks < kDeqManyKeys ? kDeqChainKeys : kDeqChain;
+}
 hipError_t launch_dequantize(const Geom& g, const kvq_cache& c, int32_t t0, int32_t t1, void* k_out, void* v_out,
                              int out_dtype, hipStream_t stream) {
   if (t1 == t0) return hipSuccess;
   const int streams = g.batch * g.kv_heads, blocks = ((t1 - 1) >> 5) - (t0 >> 5) + 1;
   const int tensors = (k_out ? 1 : 0) + (v_out ? 1 : 0);
   const uint32_t which_v = k_out ? 1u : 0u;
-  const bool chained = out_dtype != KVQ_F32 && (int64_t)blocks * streams * tensors >= kDeqChainFrom;
-  const int per = chained ? (blocks + kDeqChain - 1) / kDeqChain : blocks, chain = (blocks + per - 1) / per;
+  const int64_t all = (int64_t)blocks * streams * tensors;
+  const bool early = deq_chains_early(g, k_out != nullptr, v_out != nullptr, blocks);
+  const bool chained = out_dtype != KVQ_F32 && all >= (early ? kDeqChainFromNarrow : kDeqChainFrom);
+  const int most = deq_in_a_row(g, v_out != nullptr, all);
+  const int per = chained ? (blocks + most - 1) / most : blocks, chain = (blocks + per - 1) / per;
   const dim3 grid((blocks + chain - 1) / chain, streams, tensors);
 #define KVQ_DEQ_LAUNCH(OUT_)                                                                                              \
   if (OUT_ != KVQ_F32 && chained)                                                                                        \

@@ -190,6 +190,37 @@ def test_dequantize_to_16_bits_of_many_blocks(kvq, T, bk, bv, page, axis_seq, ro
             assert torch.equal(got[0], want[0].to(dtype)) and torch.equal(got[1], want[1].to(dtype)), (t0, t1, dtype)
 
 
+@pytest.mark.parametrize("which", ["both", "keys", "values"])
+@pytest.mark.parametrize("B,T,bk,bv,page,rotate", [(6, 8192, 3, 16, 0, False), (6, 8161, 16, 2, 0, False), (6, 8225, 4, 2, 64, True), (8, 8192, 4, 2, 0, False),
+                                                   (8, 8161, 2, 1, 0, False), (12, 8192, 8, 4, 0, False), (12, 8415, 4, 2, 0, True), (40, 900, 8, 8, 0, False),
+                                                   (16, 2048, 4, 4, 0, False), (17, 2016, 4, 4, 64, False)])
+def test_dequantize_where_the_blocks_per_workgroup_change(kvq, B, T, bk, bv, page, rotate, which):
+    """16384 and 24576 blocks, one block less and more, sequences of 63 and 64 blocks: narrow, wide, rotated and paged tensors, both and either
+    alone, which take one, four or eight blocks per workgroup.  16-bit rows are the binary32 ones (one block per workgroup) rounded once, and nothing
+    outside the range that is asked for is written."""
+    H, D = 8, 128
+    cap = (T + 63) // 64 * 64
+    pages = B * (cap // page) + 3 if page else 0
+    signs = (0x9E3779B9, 1, 2, 3) if rotate else (0, 0, 0, 0)
+    L = kvq.Layout(B, H, cap, D, bk, bv, 64, 64, raw_dtype=kvq.KVQ_BF16, rotate_k=int(rotate), signs_k=signs, page_tokens=page, n_pages=pages)
+    cache = kvq.Cache(L, fill=0)
+    if page:
+        cache.page_table = torch.randperm(pages, generator=torch.Generator().manual_seed(3))[:pages - 3].to(torch.int32).view(B, -1).contiguous().cuda()
+    K, V, _ = synth.make_kvq(9, B, H, H, cap, D, dtype=torch.bfloat16, device="cuda")
+    kvq.quantize_append(L, cache, K, V, 0)
+    for t0, t1 in ((0, T), (37, T - 5)):
+        n = B * H * (t1 - t0) * D
+        want, got = torch.empty(n, dtype=torch.float32, device="cuda"), torch.full((n + 4096,), 7.0, dtype=torch.bfloat16, device="cuda")
+        want2, got2 = torch.empty_like(want), got.clone()
+        row = (B, H, t1 - t0, D)
+        ask = lambda k, v: (k if which != "values" else None, v if which != "keys" else None)
+        kvq.dequantize(L, cache, t0, t1, *ask(want.view(row), want2.view(row)))
+        kvq.dequantize(L, cache, t0, t1, *ask(got[:n].view(row), got2[:n].view(row)))
+        for asked, g, w in ((which != "values", got, want), (which != "keys", got2, want2)):
+            assert torch.equal(g[:n], w.bfloat16()) if asked else g.eq(7.0).all()
+            assert g[n:].eq(7.0).all()
+
+
 # --------------------------------------------------------------------------- decode attention
 
 def test_config0_attention(kvq, oracle):
