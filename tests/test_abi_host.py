@@ -68,7 +68,8 @@ def test_cache_bytes_closed_forms(kvq):
     Lp = kvq.Layout(2, 3, 1000, 128, 4, 2, 64, 32, axis_k=kvq.AXIS_SEQ, page_tokens=128, n_pages=20)
     assert kvq.cache_bytes(Lp) == [20 * 3 * 128 * 64, 20 * 3 * 2 * 512, 20 * 3 * 128 * 32, 20 * 3 * 128 * 16]
     assert kvq.residual_bytes(Lp) == [6 * 64 * 256, 6 * 64 * 256]
-    # the workspace of a channel-wise cache always counts the record of the residual tail once there are flushed blocks
+    # the size query for a channel-wise cache counts a record for the tokens in the buffer once there are flushed blocks (the calls
+    # themselves ask for none: tests/test_gpu_parity.py)
     assert kvq.decode_workspace_bytes(Ls, 12, 63) == 0
     assert kvq.decode_workspace_bytes(Ls, 12, 64) == kvq.decode_workspace_bytes(Ls, 12, 100) > 0
     assert kvq.residual_bytes(kvq.Layout(2, 3, 100)) == [0, 0]
@@ -280,8 +281,8 @@ def test_workspace_never_shrinks_as_the_sequence_grows(kvq):
 
 
 def test_extension_module_leaves_what_is_not_plain(kvq):
-    """The extension module's functions do nothing and return None before a call has brought torch's device runtime up, and for
-    arguments of any other number or kind; they never raise."""
+    """The extension module's functions do nothing and return None before a call has brought torch's device runtime up, whatever they are
+    given; they never raise.  (What they make of each argument after that: tests/test_binding_host.py.)"""
     kvq.load()
     f = kvq._fast
     for fn, n in ((f.quantize_append, 5), (f.decode_attention, 7), (f.decode_attention_varlen, 8), (f.decode_step, 9), (f.decode_step_varlen, 10)):

@@ -214,3 +214,77 @@ def test_a_build_without_the_modules_compiler_goes_on(monkeypatch, tmp_path, com
     monkeypatch.setattr(build, "HERE", str(tmp_path))
     monkeypatch.setattr(build, "binding_command", make)
     assert build._build_binding() != "" and not old.exists()
+
+
+class Wrapped(torch.Tensor):
+    """A tensor subclass: what its attributes say is its own business."""
+
+
+# what takes the place of one argument: other kinds of object, numbers of other types and beyond 32 bits, tensors that are not plain
+JUNK = {
+    "None": None, "text": "x", "object": object(), "int": 3, "big int": 1 << 40, "negative big int": -(1 << 31) - 1, "bool": True, "float": 2.5,
+    "list": [1], "scalar tensor": torch.tensor(1.0), "double": torch.zeros(2, 2, 128, dtype=torch.float64), "int64": torch.zeros(2, dtype=torch.int64),
+    "sparse": torch.zeros(2, 2, 3, 128).to_sparse(), "subclass": torch.zeros(2, 2, 3, 128).as_subclass(Wrapped),
+    "strided": torch.zeros(2, 2, 128, 3, dtype=torch.float16).transpose(2, 3), "rank 5": torch.zeros(1, 2, 2, 3, 128, dtype=torch.float16),
+    "strided lengths": torch.ones(2, 2, dtype=torch.int32)[:, 0], "lengths of other batch": torch.ones(3, dtype=torch.int32),
+}
+# the arguments after layout and cache: R rows, Q query, O output, W workspace, L lengths, I integer, S scale
+SLOTS = {"quantize_append": "RRI", "decode_attention": "QISOW", "decode_attention_varlen": "QLISOW", "decode_step": "RRIQSOW",
+         "decode_step_varlen": "RRLIQSOW"}
+PLAIN = {"I": ("int",), "S": ("float",), "L": (),
+         # the library looks at the bytes of a workspace, the binding at nothing but its being a plain tensor or None
+         "W": ("None", "scalar tensor", "double", "int64", "strided", "rank 5", "strided lengths", "lengths of other batch")}
+
+
+@pytest.mark.parametrize("name", SIGNATURES)
+def test_an_argument_that_is_not_plain_leaves_the_call_to_the_caller(binding, name):
+    """Each argument in turn replaced by something else, all others plain: None comes back, nothing is raised and the library is not
+    called.  (Where the replacement is plain too, it is.)"""
+    lib = Library(binding)
+    L = kvq.Layout(2, 2, 256)
+    cache = host_cache(L)
+    args = plain_arguments(L, cache)[name]
+    assert getattr(binding, name)(*args) == 0 and len(lib.calls) == 1
+    for slot in range(len(args)):
+        for what, junk in JUNK.items():
+            lib.calls.clear()
+            kind = "LC"[slot] if slot < 2 else SLOTS[name][slot - 2]
+            taken = slot >= 2 and what in PLAIN.get(kind, ())
+            got = getattr(binding, name)(*args[:slot], junk, *args[slot + 1:])
+            assert got == (0 if taken else None), (slot, what)
+            assert len(lib.calls) == (1 if taken else 0), (slot, what)
+    for wrong in (args[:-1], args + [None]):
+        assert getattr(binding, name)(*wrong) is None
+    assert getattr(binding, name)(cache, L, *args[2:]) is None                # (each where the other belongs)
+    with torch.device("cpu"):                                                 # a function mode: torch's own calls may mean something else
+        assert getattr(binding, name)(*args) is None
+
+
+def test_the_library_gets_what_the_arguments_say(binding):
+    """Addresses, types, strides, sizes and numbers as the C functions take them."""
+    lib = Library(binding)
+    L = kvq.Layout(2, 2, 256)
+    a = plain_arguments(L, host_cache(L))
+    big = torch.zeros(2, 5, 2, 256, dtype=torch.bfloat16)
+    k, v = big.transpose(1, 2)[:, :, 1:4, :128], big.transpose(1, 2)[:, :, 2:5, 128:]
+    assert binding.quantize_append(*a["quantize_append"][:2], k, v, 9) == 0
+    assert lib.calls[-1][1][2:] == (k.data_ptr(), v.data_ptr(), kvq.KVQ_BF16, 5 * 2 * 256, 256, 2 * 256, 9, 3, None)
+    args = a["decode_attention"]
+    assert binding.decode_attention(*args) == 0
+    q, n, scale, out, ws = args[2:]
+    assert lib.calls[-1][1][2:] == (q.data_ptr(), kvq.KVQ_F16, 4, n, scale, out.data_ptr(), kvq.KVQ_F32, ws.data_ptr(), 64, None)
+    args = a["decode_attention_varlen"]
+    assert binding.decode_attention_varlen(*args[:-1], None) == 0
+    q, lens, n, scale, out, _ = args[2:]
+    assert lib.calls[-1][1][2:] == (q.data_ptr(), kvq.KVQ_F16, 4, lens.data_ptr(), n, scale, out.data_ptr(), kvq.KVQ_F32, None, 0, None)
+    args = a["decode_step"]
+    k4, v4 = torch.zeros(2, 2, 1, 256, dtype=torch.float16)[..., :128], torch.ones(2, 2, 1, 256, dtype=torch.float16)[..., :128]
+    assert binding.decode_step(*args[:2], k4, v4, *args[4:]) == 0
+    pos, q, scale, out, ws = args[4:]
+    assert lib.calls[-1][1][2:] == (k4.data_ptr(), v4.data_ptr(), kvq.KVQ_F16, 512, 256, pos, q.data_ptr(), kvq.KVQ_F16, 4, scale,
+                                    out.data_ptr(), kvq.KVQ_F32, ws.data_ptr(), 64, None)
+    args = a["decode_step_varlen"]
+    assert binding.decode_step_varlen(*args) == 0
+    k, v, pos, most, q, scale, out, ws = args[2:]
+    assert lib.calls[-1][1][2:] == (k.data_ptr(), v.data_ptr(), kvq.KVQ_F16, 256, 128, pos.data_ptr(), most, q.data_ptr(), kvq.KVQ_F16, 4,
+                                    scale, out.data_ptr(), kvq.KVQ_F32, ws.data_ptr(), 64, None)

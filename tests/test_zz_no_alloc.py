@@ -54,8 +54,8 @@ def test_static_scratch_matches_the_workspace_call_twice_in_a_row(kvq, oracle):
 
 def test_static_scratch_rejects_what_does_not_fit(kvq):
     """Token-wise caches never need more than about 1 MiB of records (the plan splits a sequence only while there are
-    fewer than 256 streams).  Channel-wise keys add one record per query head for the residual tail whatever the batch:
-    1024 sequences of 8 heads need 2 x 8192 records = 8.25 MiB, more than the array holds."""
+    fewer than 256 streams).  For a cache with a residual buffer the size query, which this entry point goes by, counts one more
+    record per query head whatever the batch: for 1024 sequences of 8 heads 2 x 8192 records = 8.25 MiB, more than the array holds."""
     B, Hq, T = 1024, 8, 100
     L = kvq.Layout(B, 1, T, 128, 4, 2, 64, 64, axis_k=kvq.AXIS_SEQ)
     assert kvq.decode_workspace_bytes(L, Hq, T) > kvq.STATIC_SCRATCH_BYTES
