@@ -254,8 +254,8 @@ kvq_status kvq_decode_step(const kvq_layout* layout, const kvq_cache* cache, con
   if (!aligned16(k_new) || !aligned16(v_new) || stride_b % 8 || stride_h % 8) return KVQ_ERR_INVALID_ARG;
   if (kvq::has_residual(*layout)) {
     // The new token goes to the residual buffer.  Short of a full block the launch that attends to the buffer stores it
-    // there (8 x 8 heads, 8192 + 37 tokens, rotated keys: 26.5 us with an append launch in front, 24.7 without; 40 tokens of 8
-    // heads 11.4 and 8.2); the token that completes a block flushes it, in a launch in front of the attention.  Everything
+    // there (with an append launch in front and without: 8 x 8 heads, 8192 + 37 tokens, rotated channel-wise keys 26.5 and 24.7 us while the buffer
+    // still had a launch of its own, 18.0 now; 40 tokens of 8 heads 11.4 and 8.2); the token that completes a block flushes it, in a launch in front of the attention.  Everything
     // is checked before anything runs.
     kvq_status st = decode_check(layout, cache, q, q_dtype, q_heads, pos + 1, softmax_scale, out, out_dtype, workspace,
                                  workspace_bytes, false);

@@ -1504,6 +1504,7 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
     (void)__hip_atomic_fetch_max(word, a.merge_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
   // ---- merge the wavefronts; write a partial record, or the result when there is one split
+  // (plain exponentials here and in the merges below: a weight under 2^-126 comes out as 0, far under a binary32 rounding of any sum it enters)
   for (int idx = tid; idx < R * kHeadDim; idx += 64 * NW) {
     const int hh = idx / kHeadDim, d = idx % kHeadDim;
     float M = sm_m[0][hh];
@@ -1918,7 +1919,8 @@ DecodePlan plan_coarse(const Geom& g, int32_t seq_len) {
   // Workgroups of 8 wavefronts halve the number of sequence splits (none at all from 256 streams up, where the
   // merge kernel and the workspace traffic disappear); each wavefront should still own a few steps.
   // Channel-wise keys: the plan covers the flushed tokens only (whole 64-token blocks, two steps each, taken in pairs);
-  // n_splits = 0 when nothing is flushed yet.  The residual tail is a launch of its own.
+  // n_splits = 0 when nothing is flushed yet.  The tokens in the buffer come with the last split (token-wise keys behind a buffer, and
+  // nothing flushed yet: a launch of their own).
   const int unit = g.axis_k == KVQ_AXIS_SEQ ? 2 : 1;
   const int n_steps = plan_steps(g, seq_len);
   if (n_steps == 0) return DecodePlan{0, 0, 4};
@@ -1939,6 +1941,10 @@ DecodePlan plan_coarse(const Geom& g, int32_t seq_len) {
 //     them the second launch, gain 0.5 us on the device and lose 1 where the host paces.
 //   - where more than three steps per wavefront are left, as few as all the parts allow: from 9 records on a larger merge launch costs a
 //     microsecond more.
+// The lines were drawn on K4V2.  Wider rows, captured in a graph, against the coarse plan: with more than four heads and in long sequences within 1 %
+// (K8V8 and unquantized, 8 to 352 sequences, 500 to 16384 tokens); unquantized sequences of 40 and 100 tokens would take four wavefronts 2 to 6 %
+// faster (8 x 8 heads x 100, 8 query heads, 6.35 and 6.69 us, 4 query heads 5.46 and 5.56), K8V8 and unquantized ones of 300 tokens and one query
+// head too (8 x 8 heads 6.34 and 6.49, 7.50 and 7.68).
 // Fused steps, K4V2, 4 query heads unless said, before (the coarse plan) and so, captured in a graph: 8 heads x 800 tokens 7.07 and 6.44 us,
 // x 1024 7.43 and 6.85 (1 query head 7.38 and 6.84), x 7000 10.73 and 9.93, x 8192 10.12 and 9.28, x 10000 11.12 and 10.51; 8 x 8
 // heads x 1024 8.23 and 7.90; 4 x 8 heads x 3000, 8 query heads, back to back 10.32 and 9.45.  On the other side of the lines: 8 heads x 640 tokens in
