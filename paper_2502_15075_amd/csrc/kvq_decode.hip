@@ -1406,15 +1406,19 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   // before, 86.6 with it).  Equal priorities and these, 32 x 8 x 8 heads, in turn, means over eight placements of the planes (a call's time
   // differs by up to 8 % between them, above all where sequences lie powers of two apart): K8V2 x 24576 tokens 185.9 and 192.5,
   // x 36000 256.8 and 253.7, x 40960 299.7 and 321.8; K8V1 x 40960 287.0 and 305.4, K8V4 335.2 and 353.7, x 65536 522.4 and 519.9; 8 x
-  // 8 heads x 8192 tokens K8V4 22.4 and 22.4, K8V3 22.1 and 21.8.  On this side of the line: 6-bit keys gain 1 to 4 % (K6V1 x 36000
-  // 205.6 and 197.5, K6V6 308.7 and 304.9), except at 65536 and 81920 tokens, where they lose up to 2 (K6V2 x 65536 405.9 and 407.6, K6V4
-  // 473.3 and 480.8; x 70000 429.6 and 417.3, 497.6 and 492.1); narrower ones gain 1 to 5 (K4V2 x 65536 304.6 and 292.4, K4V4 377.6 and 362.5,
-  // K4V8 539.2 and 532.0, K1V8 412.9 and 402.4).
+  // 8 heads x 8192 tokens K8V4 22.4 and 22.4, K8V3 22.1 and 21.8.  On this side of the line keys of up to 4 bits gain 1 to 6 % (K4V2 x 65536
+  // 304.6 and 292.4, K4V4 377.6 and 362.5, K4V8 539.2 and 532.0, K1V8 395.6 and 384.8, K3V6 463.7 and 443.5).
+  // 6-bit keys gain 1 to 4 % (K6V1 x 36000 205.6 and 197.5, K6V6 308.7 and 304.9; K6V3 anywhere, x 65536 469.6 and 452.4), except in long walks
+  // over sequences that lie a power of two from 32768 tokens on apart, as they do in a cache of that capacity, whatever they are filled to:
+  // there all turns have one priority.  Capacity 32768, 22937 tokens, K6V1 132.3 and 134.5, K6V6 192.2 and 196.4; capacity 65536, 13107 tokens (51
+  // steps) K6V2 84.6 and 85.7, 29491 K6V2 177.8 and 186.3, K6V4 210.1 and 216.2; 16 x 8 sequences of 131072, 91750 tokens K6V1 263.7 and 281.7.
+  // Not with a capacity of 16384 (K6V1 95.8 and 94.5) nor in shorter walks (8 x 8 sequences of 32768, 32 steps, K6V2 54.7 and 53.7).
   // Nor over channel-wise keys by 8 wavefronts (K4V2, 8 x 8 heads x 8229 tokens 17.25 and 17.44 us, K4V4 19.5 and 20.1; by 4, 40 x 8
   // heads x 3000 tokens, 33.3 and 32.3).
   constexpr bool kPairs = NW == 8, kYield = BK + BV <= 12 && !(BK == 8 && v_hi<BV>() == 0) && !(KSEQ && kPairs);
-  const bool by_partner = kYield && kPairs && n_full >= 4 * kStages;
-  const int q1 = kPairs ? kStages : n_full >> 2, q2 = kPairs ? 2 * kStages : n_full >> 1, q3 = q1 + q2;
+  const bool level = BK == 6 && BV != 3 && kPairs && !PAGED && n_full >= 48 && g.t_cap >= 32768 && (g.t_cap & (g.t_cap - 1)) == 0;
+  const bool by_partner = kYield && kPairs && n_full >= 4 * kStages && !level;
+  const int q1 = level ? n_full : kPairs ? kStages : n_full >> 2, q2 = level ? n_full : kPairs ? 2 * kStages : n_full >> 1, q3 = q1 + q2;
   int partner = 0;                                 // the turn that the other wavefront of this SIMD has reached, in steps
   if constexpr (kYield && kPairs) __hip_atomic_store(&sm_turn[wave], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   if constexpr (kYield) __builtin_amdgcn_s_setprio(3);

@@ -620,6 +620,12 @@ def test_full_size_70b_layer_sampled_streams(kvq, oracle):
     _check_sampled_streams(kvq, oracle, 32, 64, 8, 32768, 1000, 3.3, [(0, 0), (13, 5), (31, 7)])
 
 
+@pytest.mark.parametrize("bk,bv", [(6, 2), (6, 3), (6, 6), (8, 2)])
+def test_full_size_70b_layer_wide_keys_sampled_streams(kvq, oracle, bk, bv):
+    """Long walks of 6- and 8-bit keys over sequences a power of two apart: the wavefronts' priorities are others there."""
+    _check_sampled_streams(kvq, oracle, 32, 64, 8, 32768, 1001, 3.3, [(7, 3), (31, 7)], bk=bk, bv=bv)
+
+
 def test_full_size_8b_layer_sampled_streams(kvq, oracle):
     """The 8B-layer workload (B=8, 32 query / 8 KV heads, context 8192): 4 sequence splits and the merge kernel."""
     _check_sampled_streams(kvq, oracle, 8, 32, 8, 8192, 1, 4.0, [(0, 0), (3, 6), (7, 7)])
