@@ -82,6 +82,17 @@ __device__ __forceinline__ float rows_max(float x) {
   const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
   return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
+// The same sum where channel-wise keys of BK bits rebuild their query operands, once per block in the main loop.  Keys of 1 and 2 bits, whose loop
+// vector instructions bound, take it through the LDS permute unit, which saves 16 of 690 in a pair of steps; wider ones by
+// register permutes.  In turn, register and LDS permutes (and before either was looked at), everything flushed: 32 x 8 x 8 heads x 32768 tokens
+// K2V2 157.3 and 153.5 us (153.8), rotated keys 158.9 and 154.4 (155.7), K4V4 185.7 and 187.8 (188.5), K4V2 164.6 and 164.2; K1V4 2 % less, K2V8
+// 8 x 8 x 32768 4 % less, K3V2 and K3V3 from 2 % less to 2 % more, K8V8 339.8 and 338.4.
+template <int BK> __device__ __forceinline__ float kseq_rows_sum(float x) {
+  if constexpr (BK > 2) return rows_sum(x);
+  x += __shfl_xor(x, 16);
+  x += __shfl_xor(x, 32);
+  return x;
+}
 // Sum over groups of n = 4, 8 or 16 neighbouring lanes (uniform), in every lane.
 __device__ __forceinline__ float lanes_sum(float x, int n) {
   x += dpp_f32<0xB1>(x);                // quad permutes: lane ^ 1, lane ^ 2
@@ -489,7 +500,7 @@ __device__ __forceinline__ void kseq_rebuild(KSeqState& ks, const LaneCtx& L, co
   float zq = 0.f;
 #pragma unroll
   for (int c = 0; c < NC; ++c) zq = fmaf(zc[c], k_chan_scale<BK>(c), zq);
-  zq = rows_sum(zq);
+  zq = kseq_rows_sum<BK>(zq);
   ks.zq_u = zq * (kCodeUnit - kCodeUnit * low_part);          // (only the high part's column adds the constant)
 }
 
@@ -537,7 +548,7 @@ __device__ __forceinline__ void kseq_rebuild_runs(KS& ks, const LaneCtx& L, cons
       ks.qoph[m] = u32x4{op[0], op[1], op[2], op[3]};
     }
   }
-  zq = rows_sum(zq);
+  zq = kseq_rows_sum<BK>(zq);
   ks.zq_u = zq * (kCodeUnit - kCodeUnit * low_part);
 }
 
