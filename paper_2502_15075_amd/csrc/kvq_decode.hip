@@ -67,6 +67,29 @@ __device__ __forceinline__ float sum_over_groups(float x) {
   return x;
 }
 
+// ---- two tiles side by side ------------------------------------------------------------------------------------------------
+// Where a kv head's columns (heads times groups) fill no more than 8 of a tile's 16, the two 16-token tiles of a step lie side by
+// side: lanes 0-7 of every row carry the columns for the step's first tile, lanes 8-15 the same columns for its second.  Both
+// tiles are multiplied by the same query operand in all 16 columns, and each half keeps the product it is responsible for, so that a
+// lane has 4 scores of its step instead of 8: half the scale and zero terms, exponentials, sums and weights (of 160 vector
+// instructions a step of K4V2 40 fewer, and 4 of its 8 exponentials), and no sums over empty columns.  What it gives is issue time, which
+// bounds every walk that does not bring the memory system to its rate.  8 and 4 scores, before the ring was cut to two
+// steps, 4 query heads: 8 x 8 heads x 8192 tokens K4V2 15.8 and 15.0 us, channel-wise rotated keys 18.1 and 17.2, 16 x 8 x 16000
+// K2V2 33.3 and 30.9, 16 sequences of 600 to 16001 tokens in pages 29.1 and 26.4, 32 x 8 x 32768 140.7 and 139.1.  The
+// packed weights of the second tile come over by a rotation of the row (halves_swap) when the values are multiplied.  Column
+// c & 7 of a half carries group (c & 7) % (8 / R) of head (c & 7) / (8 / R): groups next to each other, so that their sums are quad
+// permutes, which stay inside the half.
+template <int R>
+__device__ __forceinline__ float sum_over_groups_half(float x) {
+  if (R <= 4) x += dpp_f32<0xB1>(x);    // quad permutes: lane ^ 1, lane ^ 2
+  if (R <= 2) x += dpp_f32<0x4E>(x);
+  if (R <= 1) x += dpp_f32<0x141>(x);   // row_half_mirror: the other quad's total
+  return x;
+}
+__device__ __forceinline__ uint32_t halves_swap(uint32_t x) {      // lane ^ 8's value (row_ror:8)
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xF, 0xF, false);
+}
+
 // Sum (maximum) over the four 16-lane rows of a wavefront, in every lane: a swap of rows (of halves) leaves the two values to
 // combine in the two registers.  Register permutes: through the LDS unit the same exchanges are a latency each in the chain
 // that bounds a short launch.
@@ -264,24 +287,28 @@ template <int BV> __device__ __forceinline__ u32x4 unpack_v(const uint32_t* w, i
 }
 
 #ifndef KVQ_STAGES
-#define KVQ_STAGES 4           // 32-token steps resident or in flight per wavefront (register ring)
+#define KVQ_STAGES 2           // 32-token steps resident or in flight per wavefront (register ring)
 #endif
 #ifndef KVQ_WAVES_PER_SIMD
 #define KVQ_WAVES_PER_SIMD 2   // occupancy the register allocation is held to
 #endif
 
-// Ring depth per instantiation: a step costs 2 b_K + 2 b_V + 4 registers per lane (and the scheduler wants room to
-// start a refill before the old contents are dead); deeper rings for the narrow formats, two steps for the wide ones.
-template <int BK, int BV, int NCK = 1, int NCV = 1, bool ROTV = false>
+// Ring depth per instantiation: two steps, one where the registers of a step (2 b_K + 2 b_V + 4 per lane) leave no room for a second.
+// Eight wavefronts with one step each in flight, 28 KB of K4V2 per unit, keep the memory system busy; a deeper ring only makes the
+// first fill, which every wavefront asks for at once, and the code longer.  With 6, 4, 3, 2 and 1 steps, K4V2: 8 x 8 heads x 8192 tokens
+// 16.7, 15.2, 14.4, 14.1 and 15.4 us, 8 heads x 131071 26.9, 25.4, 24.4, 24.1 and 26.3, 32 x 8 x 8 heads x 32768 143.3, 141.7, 142.0, 140.6 and
+// 164.1; K4V4 with 3, 2 and 1: 8 x 8 x 8192 17.1, 16.7 and 17.1, 40 x 8 x 3000 30.8, 29.6 and 33.4; K2V2 with 4, 3, 2: 13.4, 12.6, 12.5.
+template <int BK, int BV, int NCK = 1, int NCV = 1, bool ROTV = false, bool HALF = false>
 constexpr int ring_stages() {
+  if (HALF) return KVQ_STAGES;
   constexpr int regs = 2 * BK + 2 * BV + 4;
-  constexpr int base = regs <= 16 ? KVQ_STAGES : regs <= 20 ? 3 : 2;
+  constexpr int base = regs <= 16 ? 4 : regs <= 20 ? 3 : 2;
   constexpr int less = (NCK == 2 ? 2 : 0) + (NCV == 2 ? 1 : 0)    // a second column set costs registers (query operand,
                        + (code_hi_bits<BK>() ? 1 : 0)              // scale/zero entries, weights), so does a high run
                        + (code_hi_bits<BV>() ? 1 : 0)              // of keys or a high part of values (its weights)
                        + (ROTV ? 1 : 0)                            // (rotated values: the unrounded weights stay live)
                        + (BK == 2 && regs >= 16 ? 1 : 0);         // (moved 2-bit fields: two shifted copies of a word live)
-  return base - less >= 1 ? base - less : 1;
+  return base - less >= KVQ_STAGES ? KVQ_STAGES : base - less >= 1 ? base - less : 1;
 }
 
 // Everything one lane loads for one 32-token step (two 16-token tiles).
@@ -387,13 +414,14 @@ __device__ __forceinline__ void load_step(StepRegs<BK, BV>& r, const LaneCtx& L,
 __device__ __forceinline__ float meta_scale(uint32_t m) { return (float)__builtin_bit_cast(_Float16, (uint16_t)(m & 0xFFFFu)); }
 __device__ __forceinline__ float meta_zero(uint32_t m) { return (float)__builtin_bit_cast(_Float16, (uint16_t)(m >> 16)); }
 
-template <int NCV>
+template <int NCV, bool HALF = false>
 struct WaveState {
+  static constexpr int kClasses = HALF ? 2 : 4;  // register classes of a lane's scores (HALF: v or v + 2, by the lane's tile)
   float4v acc[8];       // out^T tile dt: rows d = 16*dt + 4*j + r, column c
   float m;              // running max of this lane's head, in log2 units
-  float noff[4];        // p_shift - m - v_slot_shift(v): exponent offset of the slots in operand register v
-  float l[4];           // per register class v: this lane's share of sum_t p * 2^(p_shift - shift(v))
-  float zacc[NCV][4];   // same, weighted by zV[t, g] for this lane's value group of each column set
+  float noff[kClasses]; // p_shift - m - v_slot_shift(v): exponent offset of the slots in operand register v
+  float l[kClasses];    // per register class v: this lane's share of sum_t p * 2^(p_shift - shift(v))
+  float zacc[NCV][kClasses];   // same, weighted by zV[t, g] for this lane's value group of each column set
   float headroom;       // the running maximum is kept this far (in log2 units) above the largest logit seen, which holds
                         // every weight below 2^-headroom of its usual size (see weight_headroom); wave-uniform
 };
@@ -558,11 +586,12 @@ __device__ __forceinline__ void kseq_rebuild_runs(KS& ks, const LaneCtx& L, cons
 // (8 heads with 32-channel groups) the groups are spread over two column sets: set cs carries group grp + cs*(16/R).
 // KS: KSeqState for channel-wise keys (then NEWBLK marks the first step of a 64-token block: the query operands are
 // rebuilt from that block's scale/zero entries), NoKSeq otherwise.
-template <int BK, int BV, int R, bool BF, int NCK, int NCV, bool MASKED, bool NEWBLK = false, typename KS = NoKSeq,
+// HALF: the two tiles side by side (quantized tensors, one column set).
+template <int BK, int BV, int R, bool BF, int NCK, int NCV, bool MASKED, bool NEWBLK = false, bool HALF = false, typename KS = NoKSeq,
           typename LC = LaneCtx>
 __device__ __forceinline__ void compute_step(const StepRegs<BK, BV>& r, const u32x4 (&qb)[NCK][4],
                                              const u32x4 (&qbh)[NCK][4], const float (&qsum_u)[NCK],
-                                             float kappa, WaveState<NCV>& st, const LC& L, int step, int seq_len,
+                                             float kappa, WaveState<NCV, HALF>& st, const LC& L, int step, int seq_len,
                                              KS& ks, const float* qrow = nullptr, float kseq_low = 0.f,
                                              bool rebuild = true) {
   // a tensor of bits = 16 is stored as its 16-bit patterns (BF: bfloat16) and multiplied as it is, no scale/zero
@@ -570,8 +599,11 @@ __device__ __forceinline__ void compute_step(const StepRegs<BK, BV>& r, const u3
   constexpr bool BFK = RAWK && BF, BFV = RAWV && BF;
   constexpr int KLO = k_lo<BK>(), KHI = k_hi<BK>();   // qbh: the query operand of the high run (3- and 6-bit keys)
   constexpr bool KSEQ = !__is_same(KS, NoKSeq);
+  static_assert(!HALF || (!RAWK && !RAWV && NCK == 1 && NCV == 1), "two tiles side by side: quantized tensors, one column set");
+  constexpr int NS = HALF ? 4 : 8;               // scores of this lane: slot i of tile i / 4 (HALF: of its half's tile)
+  const bool upper = HALF && (L.c & 8);
   constexpr int kSetStride = (16 / R) * 64;      // bytes between the scale/zero entries of a lane's groups in two sets
-  uint32_t kmeta[NCK][8], vmeta[NCV][8];
+  uint32_t kmeta[NCK][NS], vmeta[NCV][NS];
   if constexpr (!RAWK || !RAWV) {
     // scale/zero bytes: plane order -> LDS -> the entries this lane needs (tokens 4j..4j+3 of both tiles, own groups)
     *reinterpret_cast<u32x4*>(L.meta_lds + L.lane * 16) = r.meta;     // (lanes beyond the bytes fill slots nobody reads)
@@ -582,7 +614,7 @@ __device__ __forceinline__ void compute_step(const StepRegs<BK, BV>& r, const u3
       }
     }
 #pragma unroll
-    for (int x4 = 0; x4 < 2; ++x4) {
+    for (int x4 = 0; x4 < (HALF ? 1 : 2); ++x4) {
 #pragma unroll
       for (int cs = 0; cs < NCK; ++cs) {
         if constexpr (KSEQ || RAWK) continue;
@@ -598,10 +630,11 @@ __device__ __forceinline__ void compute_step(const StepRegs<BK, BV>& r, const u3
     }
   }
 
-  // ---- scores: slot i = token 16*(i/4) + 4*j + i%4 of this step
-  float s[8];
+  // ---- scores: slot i = token 16*(i/4) + 4*j + i%4 of this step (HALF: token 16*tile + 4*j + i)
+  float s[NS];
   {
-    float part[8];
+    float part[NS];
+    auto own = [&](const float4v& d0, const float4v& d1, int i) { return HALF ? (upper ? d1[i & 3] : d0[i & 3]) : i < 4 ? d0[i & 3] : d1[i & 3]; };
     if constexpr (KSEQ) {
       float4v d0 = {0.f, 0.f, 0.f, 0.f}, d1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -614,7 +647,7 @@ __device__ __forceinline__ void compute_step(const StepRegs<BK, BV>& r, const u3
         }
       }
 #pragma unroll
-      for (int i = 0; i < 8; ++i) part[i] = (i < 4 ? d0[i & 3] : d1[i & 3]) + ks.zq_u;
+      for (int i = 0; i < NS; ++i) part[i] = own(d0, d1, i) + ks.zq_u;
     }
 #pragma unroll
     for (int cs = 0; cs < NCK; ++cs) {
@@ -630,36 +663,38 @@ __device__ __forceinline__ void compute_step(const StepRegs<BK, BV>& r, const u3
         }
       }
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float d = i < 4 ? d0[i & 3] : d1[i & 3];
+      for (int i = 0; i < NS; ++i) {
+        const float d = own(d0, d1, i);
         float pt = d;
         if constexpr (!RAWK) pt = fmaf(d, meta_scale(kmeta[cs][i]), fmaf(meta_zero(kmeta[cs][i]), qsum_u[cs], 0.0f));
         part[i] = cs == 0 ? pt : part[i] + pt;
       }
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) s[i] = sum_over_groups<R>(part[i]);
+    for (int i = 0; i < NS; ++i) s[i] = HALF ? sum_over_groups_half<R>(part[i]) : sum_over_groups<R>(part[i]);
   }
-  bool valid[8];
+  bool valid[NS];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    valid[i] = !MASKED || (step * 32 + 16 * (i >> 2) + 4 * L.j + (i & 3) < seq_len);
+  for (int i = 0; i < NS; ++i) {
+    valid[i] = !MASKED || (step * 32 + 16 * (HALF ? (L.c >> 3) : i >> 2) + 4 * L.j + (i & 3) < seq_len);
     if (MASKED && !valid[i]) s[i] = kNegBig;
   }
   // ---- running max (kept st.headroom above the logits): only when some lane sees a larger logit than its current max
-  float lmax = fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])), fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7])));
+  float lmax = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+  if constexpr (!HALF) lmax = fmaxf(lmax, fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7])));
   float lx = fmaf(lmax, kappa, st.headroom);
   if (__any(lx > st.m)) {
+    if constexpr (HALF) lx = fmaxf(lx, __uint_as_float(halves_swap(__float_as_uint(lx))));      // (both halves of a head share its maximum)
     const float m_new = fmaxf(st.m, rows_max(lx));
     const float f = __builtin_amdgcn_exp2f(st.m - m_new);
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) st.acc[dt] *= f;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
+    for (int v = 0; v < st.kClasses; ++v) {
       st.l[v] *= f;
 #pragma unroll
       for (int cs = 0; cs < NCV; ++cs) st.zacc[cs][v] *= f;
-      st.noff[v] = p_shift<BV>() - (float)v_slot_shift<BV>(v) - m_new;
+      st.noff[v] = p_shift<BV>() - (float)(upper ? v_slot_shift<BV>(v + 2) : v_slot_shift<BV>(v)) - m_new;
     }
     st.m = m_new;
   }
@@ -668,9 +703,11 @@ __device__ __forceinline__ void compute_step(const StepRegs<BK, BV>& r, const u3
   uint32_t pw[NCV][4], pl[4];                    // pl: low-order bfloat16 part of the weights (bfloat16 cache only)
   uint32_t pwh[NCV][4];                          // weights of the high parts of 3- and 6-bit value codes
   constexpr bool ROTV = !RAWK && !RAWV && !KSEQ && LC::kRotV;   // (rotation is not combined with channel-wise keys)
-  float pv[ROTV ? 8 : 1];
+  float pv[ROTV ? NS : 1];
+  // (the high part's factor of class v, and what it is divided by again: the lane's own class)
+  auto hi_factor = [&](int v) { return upper ? v_hi_factor<BV>(v + 2) : v_hi_factor<BV>(v); };
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < NS; ++i) {
     const int v = i >> 1;
     float p = __builtin_amdgcn_exp2f(fmaf(s[i], kappa, st.noff[v]));
     if (MASKED && !valid[i]) p = 0.f;
@@ -684,7 +721,7 @@ __device__ __forceinline__ void compute_step(const StepRegs<BK, BV>& r, const u3
         st.zacc[cs][v] = fmaf(p, meta_zero(vm), st.zacc[cs][v]);
         if (i & 1) mix_hi(pw[cs][v], p, vm); else mix_lo(pw[cs][v], p, vm);
         if constexpr (VHI != 0) {
-          const float ph = p * v_hi_factor<BV>(v);
+          const float ph = p * hi_factor(v);
           if (i & 1) mix_hi(pwh[cs][v], ph, vm); else mix_lo(pwh[cs][v], ph, vm);
         }
       }
@@ -705,7 +742,7 @@ __device__ __forceinline__ void compute_step(const StepRegs<BK, BV>& r, const u3
     // rounding error times the codes' distance from the middle, which has no common part to gather.
     constexpr float kMidLo = 0.5f * (float)((1 << VLO) - 1);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < NS; ++i) {
       const int v = i >> 1;
 #pragma unroll
       for (int cs = 0; cs < NCV; ++cs) {
@@ -715,11 +752,18 @@ __device__ __forceinline__ void compute_step(const StepRegs<BK, BV>& r, const u3
         st.zacc[cs][v] = fmaf(kMidLo, fmaf(pv[i], meta_scale(vm), -back), st.zacc[cs][v]);
         if constexpr (VHI != 0) {
           constexpr float kMidHi = 0.5f * (float)((1 << VHI) - 1) * (float)(1 << VLO);
-          const float f = v_hi_factor<BV>(v);
+          const float f = hi_factor(v);
           const float backh = (float)__builtin_bit_cast(_Float16, (uint16_t)((i & 1) ? pwh[cs][v] >> 16 : pwh[cs][v] & 0xFFFFu));
-          st.zacc[cs][v] = fmaf(kMidHi / f, fmaf(pv[i] * f, meta_scale(vm), -backh), st.zacc[cs][v]);
+          st.zacc[cs][v] = fmaf(upper ? kMidHi / v_hi_factor<BV>(v + 2) : kMidHi / v_hi_factor<BV>(v), fmaf(pv[i] * f, meta_scale(vm), -backh), st.zacc[cs][v]);
         }
       }
+    }
+  }
+  if constexpr (HALF) {                          // the other tile's weights, of the same head and value group (lanes 0-7 need them)
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      pw[0][v + 2] = halves_swap(pw[0][v]);
+      if constexpr (VHI != 0) pwh[0][v + 2] = halves_swap(pwh[0][v]);
     }
   }
   // (Nothing is scheduled across this point.  The matrix instructions below cannot start before the weights are
@@ -984,14 +1028,15 @@ __device__ __forceinline__ Share balanced_share(const int32_t* __restrict__ seq_
 // the residual buffer come on top, see buffer_step, and a fused step's token goes there); a wavefront then walks whole 64-token blocks (pairs of steps), rebuilding its query operands per block.
 // PAGED: the planes are pools of pages; a step's data is found through this sequence's row of the page table.
 // ROTV: the values are stored rotated (quantized caches with token-wise keys; compute_step then corrects its weights).
-template <int BK, int BV, int R, int NW, bool BF, int NCK, int NCV, bool KSEQ = false, bool PAGED = false, bool ROTV = false>
+// HALF: at most 8 columns, two tiles side by side (sum_over_groups_half).
+template <int BK, int BV, int R, int NW, bool BF, int NCK, int NCV, bool KSEQ = false, bool PAGED = false, bool ROTV = false, bool HALF = false>
 __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(const DecodeArgs a) {
   constexpr int kSetGroups = 16 / R;             // groups per column set
   constexpr bool RAWK = BK == 16, RAWV = BV == 16;     // a tensor kept as its 16-bit patterns (either one, or both)
   constexpr bool RAW = RAWK;                          // (what the key side and the query staging ask)
   static_assert(!KSEQ || (!RAWK && !RAWV && NCK == 1), "channel-wise keys: quantized, one key column per head");
   static_assert(!ROTV || (!RAWK && !RAWV), "rotated values: both tensors quantized");
-  constexpr int kRing = ring_stages<BK, BV, NCK, NCV, ROTV>();
+  constexpr int kRing = ring_stages<BK, BV, NCK, NCV, ROTV, HALF>();
 #ifndef KVQ_KSEQ_STAGES
 #define KVQ_KSEQ_STAGES 2
 #endif
@@ -1070,7 +1115,8 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   std::conditional_t<ROTV, LaneCtxRotV, LaneCtx> L;
   L.lane = lane; L.c = lane & 15; L.j = lane >> 4;
   L.ngk = g.ng_k; L.ngv = g.ng_v;
-  const int h = L.c % R, grp = L.c / R;
+  constexpr int kHalfGroups = 8 / R;
+  const int h = HALF ? (L.c & 7) / kHalfGroups : L.c % R, grp = HALF ? (L.c & 7) % kHalfGroups : L.c / R;
   const bool act_k = grp < g.ng_k, act_v = grp < g.ng_v;
   L.gk = act_k ? grp : 0; L.gv = act_v ? grp : 0;
   const int64_t bh_base = PAGED ? 0 : bh;           // paged: rows are numbered from the plane base (virtual_token)
@@ -1091,6 +1137,10 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
     L.meta_step_mask = (KSEQ && is_k) ? ~(uint32_t)((g.seq_g >> 5) - 1) : ~0u;
     L.km_rd = (L.gk * 16 + 4 * L.j) * 4;                       // key bytes come first in the LDS copy
     L.vm_rd = 16 * nk + (L.gv * 16 + 4 * L.j) * 4;
+    if constexpr (HALF) {                                      // (this half's tile)
+      L.km_rd += (L.c >> 3) * 64 * L.ngk;
+      L.vm_rd += (L.c >> 3) * 64 * L.ngv;
+    }
     L.meta_lds = &sm_meta[wave][0];
   }
 
@@ -1374,14 +1424,14 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   }
   const float kappa = softmax_scale * kLog2e * kInvUnit;
 
-  WaveState<NCV> st;
+  WaveState<NCV, HALF> st;
 #pragma unroll
   for (int dt = 0; dt < 8; ++dt) st.acc[dt] = float4v{0.f, 0.f, 0.f, 0.f};
   st.m = kNegBig;
   st.headroom = 0.f;
   if constexpr (!RAWV) st.headroom = weight_headroom<BV>(stream_scale_exp);
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
+  for (int v = 0; v < st.kClasses; ++v) {
     st.l[v] = 0.f; st.noff[v] = 0.f;
 #pragma unroll
     for (int cs = 0; cs < NCV; ++cs) st.zacc[cs][v] = 0.f;
@@ -1398,16 +1448,16 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   auto full_step = [&](int k, int i) {
     if constexpr (KSEQ) {                        // an even step of this wavefront's sequence starts a block (uniform;
       const int odd = kStages % 2 == 0 ? (k & 1) : (i & 1);      // with an even ring it is the ring slot's parity)
-      compute_step<BK, BV, R, BF, NCK, NCV, false, true>(buf[k], qb, qbh, qsum_u, kappa, st, L, step_of(i), n_att, ks, qrow,
+      compute_step<BK, BV, R, BF, NCK, NCV, false, true, HALF>(buf[k], qb, qbh, qsum_u, kappa, st, L, step_of(i), n_att, ks, qrow,
                                                          grp == 1 ? 1.0f : 0.0f, !odd || rebuild_every_step);
     } else {
-      compute_step<BK, BV, R, BF, NCK, NCV, false>(buf[k], qb, qbh, qsum_u, kappa, st, L, step_of(i), n_att, ks);
+      compute_step<BK, BV, R, BF, NCK, NCV, false, false, HALF>(buf[k], qb, qbh, qsum_u, kappa, st, L, step_of(i), n_att, ks);
     }
   };
   // the ragged tail of the sequence out of ring slot k (it came through the ring like every other step): masked
   auto tail_step = [&](int k) {
     if constexpr (!KSEQ)
-      compute_step<BK, BV, R, BF, NCK, NCV, true>(buf[k], qb, qbh, qsum_u, kappa, st, L, n_steps - 1, n_att, ks);
+      compute_step<BK, BV, R, BF, NCK, NCV, true, false, HALF>(buf[k], qb, qbh, qsum_u, kappa, st, L, n_steps - 1, n_att, ks);
   };
   // Two wavefronts share a SIMD (w and w + 4 of a workgroup of 8; of 4, two workgroups), and at equal priority it serves the
   // older one first: wavefronts 0-3 of the 70B layer's step were done after 103 us and 4-7 after 136, those of 8 x 8 heads x 8192
@@ -1477,17 +1527,21 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   const int n_old = KSEQ && last_split ? n_buf - (fused ? 1 : 0) : 0;
   // ---- wavefront totals: l and zacc over register classes and the 4 lane groups j; then this lane's output rows
   float l = 0.f;
+  const bool upper = HALF && (L.c & 8);
+  // (of the lane's class: the halves' classes are two apart; then over both halves)
+  auto class_factor = [&](int v) { return upper ? (float)(1 << v_slot_shift<BV>((v + 2) & 3)) : (float)(1 << v_slot_shift<BV>(v)); };
+  auto both_halves = [&](float x) { return HALF ? x + __uint_as_float(halves_swap(__float_as_uint(x))) : x; };
 #pragma unroll
-  for (int v = 0; v < 4; ++v) l = fmaf(st.l[v], (float)(1 << v_slot_shift<BV>(v)), l);
-  l = rows_sum(l);
+  for (int v = 0; v < st.kClasses; ++v) l = fmaf(st.l[v], class_factor(v), l);
+  l = both_halves(rows_sum(l));
 #pragma unroll
   for (int cs = 0; cs < NCV; ++cs) {
     float z = 0.f;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) z = fmaf(st.zacc[cs][v], (float)(1 << v_slot_shift<BV>(v)), z);
-    z = rows_sum(z);
+    for (int v = 0; v < st.kClasses; ++v) z = fmaf(st.zacc[cs][v], class_factor(v), z);
+    z = both_halves(rows_sum(z));
     const int gcs = grp + cs * kSetGroups;                     // the value group this lane's column carries in set cs
-    if (gcs < g.ng_v) {
+    if (gcs < g.ng_v && !upper) {
       // (a shift: group counts are powers of two, and eight divisions by them, with a group's tokens and the last step's owner in
       // the prologue, took 0.2 to 0.6 us of a launch: 8 heads x 1024 tokens 7.83 us with them, 7.21 without)
       const int dt_shift = 3 - __builtin_ctz(g.ng_v);          // log2 of the d-tiles per value group
@@ -1502,7 +1556,7 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   }
   // (records of kernels that carry their weights times different powers of two meet in one merge when channel-wise keys
   // add the residual tail: the difference to 2^10 goes into the record's maximum)
-  if (grp == 0 && L.j == 0) { sm_m[wave][h] = st.m + (10.0f - p_shift<BV>()); sm_l[wave][h] = l; }
+  if (grp == 0 && L.j == 0 && !upper) { sm_m[wave][h] = st.m + (10.0f - p_shift<BV>()); sm_l[wave][h] = l; }
   if constexpr (KSEQ) {
     if (32 * wave < n_old) {                       // (uniform: at most 4 wavefronts)
       const int64_t at = (int64_t)bh * g.resid * (2 * kHeadDim);
@@ -1782,21 +1836,39 @@ inline void launch_merge(const float* ws, void* out, int out_dtype, int32_t head
 }
 
 
-template <int BK, int BV, int R, bool BF, int NCK, int NCV, bool KSEQ, bool PAGED>
+template <int BK, int BV, int R, bool BF, int NCK, int NCV, bool KSEQ, bool PAGED, bool HALF = false>
 void launch_nw(const DecodeArgs& a, const DecodePlan& plan, dim3 grid, hipStream_t stream) {
   if constexpr (BK != 16 && BV != 16 && !KSEQ) {
     if (a.g.rotate_v) {
       if (plan.waves_per_wg == 8)
-        hipLaunchKernelGGL((decode_kernel<BK, BV, R, 8, BF, NCK, NCV, KSEQ, PAGED, true>), grid, dim3(512), 0, stream, a);
+        hipLaunchKernelGGL((decode_kernel<BK, BV, R, 8, BF, NCK, NCV, KSEQ, PAGED, true, HALF>), grid, dim3(512), 0, stream, a);
       else
-        hipLaunchKernelGGL((decode_kernel<BK, BV, R, 4, BF, NCK, NCV, KSEQ, PAGED, true>), grid, dim3(256), 0, stream, a);
+        hipLaunchKernelGGL((decode_kernel<BK, BV, R, 4, BF, NCK, NCV, KSEQ, PAGED, true, HALF>), grid, dim3(256), 0, stream, a);
       return;
     }
   }
   if (plan.waves_per_wg == 8)
-    hipLaunchKernelGGL((decode_kernel<BK, BV, R, 8, BF, NCK, NCV, KSEQ, PAGED>), grid, dim3(512), 0, stream, a);
+    hipLaunchKernelGGL((decode_kernel<BK, BV, R, 8, BF, NCK, NCV, KSEQ, PAGED, false, HALF>), grid, dim3(512), 0, stream, a);
   else
-    hipLaunchKernelGGL((decode_kernel<BK, BV, R, 4, BF, NCK, NCV, KSEQ, PAGED>), grid, dim3(256), 0, stream, a);
+    hipLaunchKernelGGL((decode_kernel<BK, BV, R, 4, BF, NCK, NCV, KSEQ, PAGED, false, HALF>), grid, dim3(256), 0, stream, a);
+}
+
+// One column set: at most 8 columns on either side take two tiles side by side (channel-wise keys: two columns a head).  Always
+// so up to two heads, never for channel-wise keys of 8; unquantized tensors, whose step is bound by its bytes, keep one tile after the other.
+template <int BK, int BV, int R, bool BF, bool KSEQ, bool PAGED>
+void launch_columns(const DecodeArgs& a, const DecodePlan& plan, dim3 grid, hipStream_t stream) {
+  constexpr bool kMay = BK != 16 && BV != 16 && !(KSEQ && R == 8), kMust = kMay && R <= 2;
+  if constexpr (kMust) {
+    launch_nw<BK, BV, R, BF, 1, 1, KSEQ, PAGED, true>(a, plan, grid, stream);
+  } else {
+    if constexpr (kMay) {
+      if (R * (KSEQ ? 2 : a.g.ng_k) <= 8 && R * a.g.ng_v <= 8) {
+        launch_nw<BK, BV, R, BF, 1, 1, KSEQ, PAGED, true>(a, plan, grid, stream);
+        return;
+      }
+    }
+    launch_nw<BK, BV, R, BF, 1, 1, KSEQ, PAGED>(a, plan, grid, stream);
+  }
 }
 
 // column sets: two only where 8 heads meet four groups (32 columns); quantized caches only
@@ -1807,16 +1879,16 @@ hipError_t launch_sets(const DecodeArgs& a, const DecodePlan& plan, dim3 grid, h
     if constexpr (KSEQ) {
       if (k2) return hipErrorInvalidValue;
       if (v2) launch_nw<BK, BV, R, BF, 1, 2, true, PAGED>(a, plan, grid, stream);
-      else launch_nw<BK, BV, R, BF, 1, 1, true, PAGED>(a, plan, grid, stream);
+      else launch_columns<BK, BV, R, BF, true, PAGED>(a, plan, grid, stream);
     } else {
       if (k2 && v2) launch_nw<BK, BV, R, BF, 2, 2, false, PAGED>(a, plan, grid, stream);
       else if (k2) launch_nw<BK, BV, R, BF, 2, 1, false, PAGED>(a, plan, grid, stream);
       else if (v2) launch_nw<BK, BV, R, BF, 1, 2, false, PAGED>(a, plan, grid, stream);
-      else launch_nw<BK, BV, R, BF, 1, 1, false, PAGED>(a, plan, grid, stream);
+      else launch_columns<BK, BV, R, BF, false, PAGED>(a, plan, grid, stream);
     }
   } else {
     if (k2 || v2) return hipErrorInvalidValue;
-    launch_nw<BK, BV, R, BF, 1, 1, KSEQ, PAGED>(a, plan, grid, stream);
+    launch_columns<BK, BV, R, BF, KSEQ, PAGED>(a, plan, grid, stream);
   }
   return hipGetLastError();
 }

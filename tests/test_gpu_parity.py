@@ -262,6 +262,25 @@ def test_eight_heads_with_32_channel_groups(kvq, oracle, gk, gv):
         assert np.isfinite(out).all() and _rel_err(out, ref) < TOL, seq_len
 
 
+@pytest.mark.parametrize("R,gk,gv", [(1, 32, 32), (1, 128, 64), (2, 32, 128), (3, 64, 64), (4, 64, 128), (4, 128, 32), (4, 32, 64), (7, 128, 128),
+                                     (8, 128, 128), (8, 64, 128), (8, 128, 64)])
+@pytest.mark.parametrize("bk,bv,rotv", [(4, 2, 0), (2, 1, 0), (3, 3, 0), (6, 6, 1), (8, 8, 1), (1, 4, 0)])
+def test_tiles_side_by_side_and_one_after_the_other(kvq, oracle, R, gk, gv, bk, bv, rotv):
+    """Heads times groups on both sides of 8 columns: at most 8, and a step's two 16-token tiles lie side by side in the matrix
+    columns.  Lengths that end in the first tile, on its last token and in the second; the largest logits sit in either tile in
+    turn, so that the running maximum comes from both; value widths whose weights are scaled by the tile."""
+    B, H, T = 1, 2, 337
+    K, V, q = synth.make_kvq(900 + R + bk, B, H, H * R, T, dtype=torch.float16)
+    K[:, :, 20::96] *= 3.0                                  # (token 20 of a step: its second tile; 84 = 64 + 20 mod 32 too)
+    K[:, :, 100::128] *= 4.0                                # (token 4 of a step: its first)
+    Lg, Lo = _layouts(kvq, oracle, B, H, T, bk, bv, gk, gv, rotv=rotv)
+    cache, planes = _fill_both(kvq, oracle, Lg, Lo, K, V, [(0, T)], fill=0xFF)
+    for seq_len in (1, 16, 17, 31, 80, T):
+        out = _decode(kvq, Lg, cache, q, seq_len).cpu().numpy()
+        ref = oracle.decode_attention(Lo, planes, q.numpy(), seq_len, 1 / math.sqrt(128))
+        assert np.isfinite(out).all() and _rel_err(out, ref) < TOL, seq_len
+
+
 def test_small_groups_and_multi_split(kvq, oracle):
     """32-channel groups with 4 query heads per KV head, long enough for several sequence splits."""
     B, H, R, T = 1, 2, 4, 2100
