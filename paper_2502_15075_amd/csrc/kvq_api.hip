@@ -173,7 +173,7 @@ kvq_status decode_launch(const kvq_layout* layout, const kvq_cache* cache, const
   const size_t counters = counter_bytes(layout);
   const bool usable = workspace && aligned16(workspace) && workspace_bytes > counters;
   const int64_t room = usable ? (int64_t)((workspace_bytes - counters) / record_bytes(layout, q_heads)) : 0;
-  const kvq::DecodePlan plan = kvq::plan_decode(g, seq_len, q_heads / layout->kv_heads, room);
+  const kvq::DecodePlan plan = kvq::plan_decode(g, seq_len, q_heads / layout->kv_heads, room, seq_lens != nullptr);
   hipError_t e = kvq::launch_decode_attention(g, *cache, q, q_dtype, q_heads, seq_len, softmax_scale, out, out_dtype,
                                               (float*)workspace, plan, app, (hipStream_t)stream, seq_lens, lens_offset);
   return e == hipSuccess ? KVQ_OK : KVQ_ERR_DEVICE;
@@ -236,7 +236,8 @@ kvq_status kvq_decode_attention_static(const kvq_layout* layout, const kvq_cache
   size_t need = 0;
   kvq_status st = kvq_decode_workspace_bytes(layout, q_heads, seq_len, &need);
   if (st != KVQ_OK) return st;
-  if (need > KVQ_STATIC_SCRATCH_BYTES) return KVQ_ERR_STATIC_SCRATCH;
+  // (without a residual buffer, more than the array holds is only ever asked for sequences of different lengths, which this call does not take)
+  if (need > KVQ_STATIC_SCRATCH_BYTES && kvq::has_residual(*layout)) return KVQ_ERR_STATIC_SCRATCH;
   void* ws = nullptr;
   if (need && static_scratch(&ws) != hipSuccess) return KVQ_ERR_DEVICE;
   return decode_common(layout, cache, q, q_dtype, q_heads, seq_len, softmax_scale, out, out_dtype, ws,

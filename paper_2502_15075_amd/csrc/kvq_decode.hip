@@ -977,8 +977,8 @@ __device__ __forceinline__ void store_unrotated_row(const float* row, int lane16
 // are dealt out by the lengths: sequence b gets ceil(N_b / q) of them, q steps each, with the smallest q (of 64 evenly
 // spaced ones) for which they are enough.  Every wavefront works that out for itself from the lengths (at most 64, one per
 // lane); the answer depends on nothing else, so all workgroups agree.  Where the plan's q leaves fewer than an eighth of the
-// workgroups without a part, it stays, without the search: a smaller one would need more parts for the long sequences than
-// there are left, and looking for it costs 0.6 to 0.9 us (16 sequences of 8 kv heads, K4V2, 14000 to 16384 tokens: 45.7 us
+// workgroups without a part, or 7/8 of it would not do, it stays, without the search: a smaller one would need more parts for the
+// long sequences than there are left, and looking for it costs 0.6 to 0.9 us (16 sequences of 8 kv heads, K4V2, 14000 to 16384 tokens: 45.7 us
 // and 46.4 with the search, 45.5 when nothing is dealt out; 2800 to 4000 tokens 16.2, 17.0 and 16.2).
 __device__ __forceinline__ int wave_scan(int v) {  // sum over the lanes up to and including this one
   v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);     // row_shr 1, 2, 4, 8
@@ -991,11 +991,10 @@ __device__ __forceinline__ int wave_scan(int v) {  // sum over the lanes up to a
 }
 struct Share { int b, split, count, q, slot0, len; };   // sequence, part of it, its parts, steps per part, slot of its first part, tokens
 template <int UNIT>                                // q is a multiple of UNIT steps (a workgroup's wavefronts)
-__device__ __forceinline__ Share balanced_share(const int32_t* __restrict__ seq_lens, int offset, int bound, int batch, int splits,
+__device__ __forceinline__ Share balanced_share(const int32_t* __restrict__ seq_lens, int offset, int bound, int batch, int slots,
                                                 int q_max, int slot, int lane) {
   const int len = min(max(seq_lens[min(lane, batch - 1)] + offset, 1), bound);
   const int n = lane < batch ? (len + 31) >> 5 : 0;           // steps, 2^19 at most
-  const int slots = splits * batch;
   // parts of q steps; (n + q - 1) / q in binary32: half a unit above the quotient of integers below 2^21 rounds to the right side
   auto parts = [&](int q) {
     const float rq = __builtin_amdgcn_rcpf((float)q);
@@ -1004,7 +1003,9 @@ __device__ __forceinline__ Share balanced_share(const int32_t* __restrict__ seq_
   Share s;
   s.q = q_max;                                     // (always enough: no sequence is longer than the plan's)
   int mine = parts(q_max), end = wave_scan(mine);
-  if (8 * (slots - __builtin_amdgcn_readlane(end, 63)) >= slots) {        // (uniform)
+  const int q_less = (q_max * 7 / 8 + UNIT - 1) / UNIT * UNIT;
+  if (8 * (slots - __builtin_amdgcn_readlane(end, 63)) >= slots &&
+      __builtin_amdgcn_readlane(wave_scan(parts(q_less)), 63) <= slots) {        // (uniform)
     int lo = 1, hi = 64;                           // q = q_max i / 64, at least one unit (rounded up twice)
     while (lo < hi) {
       const int mid = (lo + hi) >> 1;
@@ -1095,8 +1096,8 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   bool have_len = a.seq_lens == nullptr;
   if constexpr (!KSEQ) {
     if (a.balance) {                               // (uniform)
-      slot = split + a.n_splits * b;
-      const Share sh = balanced_share<NW>(a.seq_lens, a.lens_offset, a.lens_bound, g.batch, a.n_splits, a.steps_per_split, slot, lane);
+      slot = b;
+      const Share sh = balanced_share<NW>(a.seq_lens, a.lens_offset, a.lens_bound, g.batch, a.balance, a.steps_per_split, slot, lane);
       if (sh.b < 0) return;                        // more workgroups than parts
       b = sh.b; split = sh.split; steps_per_split = sh.q; n_rec = sh.count; slot0 = sh.slot0;
       seq_len = sh.len; have_len = true;
@@ -1895,7 +1896,7 @@ hipError_t launch_sets(const DecodeArgs& a, const DecodePlan& plan, dim3 grid, h
 
 template <int BK, int BV, int R, bool BF = false, bool KSEQ = false>
 hipError_t launch_one(const DecodeArgs& a, const DecodePlan& plan, hipStream_t stream) {
-  dim3 grid(plan.n_splits, a.g.kv_heads, a.g.batch);
+  const dim3 grid = a.balance ? dim3(1, a.g.kv_heads, a.balance) : dim3(plan.n_splits, a.g.kv_heads, a.g.batch);
   hipError_t e;
   e = a.g.page_shift ? launch_sets<BK, BV, R, BF, KSEQ, true>(a, plan, grid, stream)
                      : launch_sets<BK, BV, R, BF, KSEQ, false>(a, plan, grid, stream);
@@ -1984,12 +1985,16 @@ int device_compute_units() {
 }
 
 namespace {
-// Wavefronts per (b, h_kv) stream that fill the chip once, and what a sequence of n_steps steps can use of them.
+// Wavefronts per (b, h_kv) stream that fill the chip once, and what a sequence of n_steps steps can use of them.  A few workgroups more
+// than the chip takes at a time cost a whole round, so the plan rounds the wavefronts per stream down; the bound on the
+// records, which callers have sized workspaces by, rounds up as the plan once did.  Rounded up and down, K4V2: 11 x 8 heads x 6000
+// tokens (88 streams in 3 and 2 parts) 21.5 and 14.4 us, x 16000 43.0 and 29.1; 17 x 8 x 6000 (2 parts and 1) 28.5 and 20.6; 33 x 8
+// (one workgroup of 8 wavefronts and of 4, two of which share a unit) x 700 11.7 and 9.3, x 6000 45.0 and 38.4.
 struct WaveBudget { int waves, nw, splits; };
-WaveBudget wave_budget(const Geom& g, int n_steps) {
+WaveBudget wave_budget(const Geom& g, int n_steps, bool bound) {
   const int streams = g.batch * g.kv_heads;
   const int total_waves = device_compute_units() * 4 * KVQ_WAVES_PER_SIMD;
-  int waves_per_stream = (total_waves + streams - 1) / streams;
+  int waves_per_stream = (total_waves + (bound ? streams - 1 : 0)) / streams;
   // at least two steps per wavefront (four or eight, i.e. fewer splits and at B=8, T=2048 the two-record merge inside
   // the launch instead of the merge launch, measure 13.7 and 14.6 us there against 11.9)
   const int max_waves = (n_steps + 1) / 2;
@@ -2016,13 +2021,13 @@ DecodePlan plan_coarse(const Geom& g, int32_t seq_len) {
   // nothing flushed yet: a launch of their own).
   const int unit = g.axis_k == KVQ_AXIS_SEQ ? 2 : 1;
   const int n_steps = plan_steps(g, seq_len);
-  if (n_steps == 0) return DecodePlan{0, 0, 4};
-  const WaveBudget wb = wave_budget(g, n_steps);
+  if (n_steps == 0) return DecodePlan{0, 0, 4, 0};
+  const WaveBudget wb = wave_budget(g, n_steps, false);
   const int nw = wb.nw;
   int sps = (n_steps + wb.splits - 1) / wb.splits;
   sps = (sps + nw * unit - 1) / (nw * unit) * (nw * unit);
   const int splits = (n_steps + sps - 1) / sps;
-  return DecodePlan{splits, sps, nw};
+  return DecodePlan{splits, sps, nw, 0};
 }
 
 // Sequences without a residual buffer (whose plan takes whole blocks as it is) are cut with their parts' size in view.  n8: steps per
@@ -2069,9 +2074,29 @@ int fine_bound(int n_steps, int most) {
   return n8 < most ? n8 : most;
 }
 // Workgroups of 8 wavefronts per sequence that fill the chip; 0 where there are too many sequences for one each.
-int fine_most(const Geom& g) {
+int fine_most(const Geom& g, bool bound) {
   const int streams = g.batch * g.kv_heads, waves = device_compute_units() * 4 * KVQ_WAVES_PER_SIMD;
-  return g.resid ? 0 : (waves + streams - 1) / streams / 8;
+  return g.resid ? 0 : (waves + (bound ? streams - 1 : 0)) / streams / 8;
+}
+}  // namespace
+
+// Sequences of different lengths: a launch deals its workgroups of nw wavefronts out by the lengths (balanced_share) where a part planned
+// for the longest has at least 6 steps per wavefront (of more than two parts: 12); with less, looking at all the lengths first outweighs
+// it.  Both ways in turn, K4V2, 16 sequences of 8 kv heads, dealt out (and not): lengths even between 512 and 8192 tokens 19.9 us
+// (22.8), 1024 and 16384 30.8 (35.9), 250 and 4000 14.5 (15.3), half of them 8192 and half 1024 19.9 (22.4); equal lengths 26.3 (26.2) and
+// 49.1 (49.0).  With eight splits it loses (4 sequences up to 8000: 14.4 against 12.3).
+// How many: as many as fill the chip, where the plan takes more than half of it; sequences of one part each, 129 to 255 and 257 to 511 streams,
+// leave some over for the longest.  Where the plan takes less (few, short sequences), its own number.
+namespace {
+bool deals(const Geom& g, int nw, int steps_per_split) { return !g.resid && g.batch >= 2 && g.batch <= 64 && steps_per_split >= 6 * nw; }
+int full_slots(const Geom& g, int nw) { return device_compute_units() * 4 * KVQ_WAVES_PER_SIMD / nw / g.kv_heads; }
+int deal_records(const Geom& g, int slots) { return (slots + g.batch - 1) / g.batch; }      // of the workspace, per (batch, kv head)
+// No plan of more than half the chip in up to 4 parts a sequence, for lengths up to n_steps, takes more.
+int deal_bound(const Geom& g, int n_steps) {
+  const int streams = g.batch * g.kv_heads, nw = streams <= device_compute_units() ? 8 : 4;
+  if (!deals(g, nw, n_steps) || 8 * streams <= device_compute_units()) return 1;
+  const int records = deal_records(g, full_slots(g, nw));
+  return records < 8 ? records : 8;
 }
 }  // namespace
 
@@ -2087,21 +2112,32 @@ int fine_most(const Geom& g) {
 int32_t decode_records_bound(const Geom& g, int32_t seq_len, bool least) {
   const int n_steps = plan_steps(g, seq_len);
   if (n_steps == 0) return 1;
-  const int splits = wave_budget(g, n_steps).splits;
+  const int splits = wave_budget(g, n_steps, true).splits;
   if (g.resid) return least && g.axis_k == KVQ_AXIS_SEQ ? splits : splits + 1;
-  const int fine = least ? 0 : fine_bound(n_steps, fine_most(g));
-  return fine > splits ? fine : splits;
+  const int fine = least ? 0 : fine_bound(n_steps, fine_most(g, true));
+  const int dealt = least ? 0 : deal_bound(g, n_steps);
+  return dealt > fine && dealt > splits ? dealt : fine > splits ? fine : splits;
 }
 
 // heads: query heads per kv head; room: records per query head that the workspace holds.
-DecodePlan plan_decode(const Geom& g, int32_t seq_len, int heads, int64_t room) {
-  const int n_steps = plan_steps(g, seq_len), most = n_steps ? fine_most(g) : 0;
+static DecodePlan plan_parts(const Geom& g, int32_t seq_len, int heads, int64_t room) {
+  const int n_steps = plan_steps(g, seq_len), most = n_steps ? fine_most(g, false) : 0;
   if (most < 1) return plan_coarse(g, seq_len);
   const FinePlan f = fine_plan(n_steps, most, heads);
   if (f.splits == 0 || (f.splits > 1 && f.splits > room)) return plan_coarse(g, seq_len);
   // (fewer than 8 steps and one or two heads: four wavefronts have less to merge.  7 steps, 4 and 8 wavefronts, 1 head 5.02 and 5.10 us,
   // 2 heads 5.10 and 5.20, 3 heads 5.56 and 5.14, 8 heads 6.62 and 6.23; 8 steps, 1 head 5.63 and 5.29, 8 heads 7.26 and 6.45)
-  return DecodePlan{f.splits, 8 * f.steps, n_steps < 8 && heads < 3 ? 4 : 8};
+  return DecodePlan{f.splits, 8 * f.steps, n_steps < 8 && heads < 3 ? 4 : 8, 0};
+}
+
+DecodePlan plan_decode(const Geom& g, int32_t seq_len, int heads, int64_t room, bool ragged) {
+  DecodePlan p = plan_parts(g, seq_len, heads, room);
+  if (!ragged || p.n_splits < 1 || p.n_splits > 4 || !deals(g, p.waves_per_wg, p.steps_per_split)) return p;
+  if (p.n_splits > 2 && p.steps_per_split < 12 * p.waves_per_wg) return p;
+  const int own = p.n_splits * g.batch, full = full_slots(g, p.waves_per_wg);
+  if (full > own && full < 2 * own && deal_records(g, full) <= room) p.slots = full;
+  else if (p.n_splits > 1) p.slots = own;
+  return p;
 }
 
 // Where the launch's own workgroups merge the records instead of a second launch.  Counting in, after the wait for the
@@ -2122,19 +2158,6 @@ static MergeWord next_merge_tag() {
 }
 static MergeWord merge_tag_for(int records, int most = kMergeHereMost) {
   return records >= 2 && records <= most ? next_merge_tag() : 0;
-}
-
-// Whether a launch over sequences of different lengths deals its workgroups out by the lengths (balanced_share).  It needs
-// splits to deal out (below 256 streams), and work that outweighs looking at all the lengths first.  Both ways in turn,
-// K4V2, 16 sequences of 8 kv heads, dealt out (and not): lengths even between 512 and 8192 tokens 19.9 us (22.8), 1024 and
-// 16384 30.8 (35.9), 250 and 4000 14.5 (15.3), half of them 8192 and half 1024 19.9 (22.4); equal lengths 26.3 (26.2) and
-// 49.1 (49.0).  What still loses are batches in which a sixth to a third of the sequences are short, where the search runs and
-// finds next to nothing: 4 of 16 at 1024 tokens, the others 8192, 23.5 (22.7).  With more than two splits it takes longer
-// sequences: 8 between 1000 and 16000 19.8 (22.5), but between 3000 and 8000 17.0 (16.5 when this was first measured); with
-// eight splits it loses (4 sequences up to 8000: 14.4 against 12.3, then too).
-static bool balance_pays(const Geom& g, const DecodePlan& plan) {
-  if (g.batch < 2 || g.batch > 64 || plan.n_splits < 2 || plan.n_splits > 4) return false;
-  return plan.steps_per_split >= (plan.n_splits == 2 ? 6 : 12) * plan.waves_per_wg;
 }
 
 hipError_t launch_decode_attention(const Geom& g, const kvq_cache& c, const void* q, int q_dtype, int32_t q_heads,
@@ -2208,7 +2231,7 @@ hipError_t launch_decode_attention(const Geom& g, const kvq_cache& c, const void
       t.seq_len = tail; t.n_splits = 1; t.steps_per_split = 4; t.lens_mode = 2;
       t.rec_splits = records; t.rec_base = records - 1;
       if (tail_merges) { t.rec_splits = 1; t.rec_base = 0; t.extra_splits = records; }
-      e = launch_decode_inst_16_16(R, t, DecodePlan{1, 4, 4}, stream);
+      e = launch_decode_inst_16_16(R, t, DecodePlan{1, 4, 4, 0}, stream);
       if (e != hipSuccess) return e;
     }
     if (records > 1 && !(n_flushed && !tail) && !tail_merges) {     // (a launch that wrote all the records has merged them itself)
@@ -2218,7 +2241,8 @@ hipError_t launch_decode_attention(const Geom& g, const kvq_cache& c, const void
     return e;
   }
   a.lens_mode = 0; a.lens_bound = seq_len; a.lens_block = 1;
-  a.balance = seq_lens != nullptr && balance_pays(g, plan);
+  a.balance = plan.slots;
+  if (a.balance) a.rec_splits = deal_records(g, plan.slots);
   a.merge_tag = a.balance ? next_merge_tag()
                           : merge_tag_for(a.rec_splits, !app && a.heads_per_kv > kAloneHeads ? kMergeHereMostAlone : kMergeHereMost);
   if (app) {

@@ -78,13 +78,14 @@ struct DecodePlan {
   int32_t n_splits;         // workgroups per (b, h_kv)
   int32_t steps_per_split;  // 32-token steps each workgroup walks (a multiple of waves_per_wg)
   int32_t waves_per_wg;     // 4 or 8 wavefronts per workgroup
+  int32_t slots;            // != 0: sequences of different lengths; this many workgroups per kv head are dealt out by the lengths
 };
 
 // The single new token of a fused decode step: [B][H_kv][D] rows with element strides.
 struct AppendOne {
   const void* k_new; const void* v_new; int in_dtype; int64_t stride_b, stride_h;
 };
-DecodePlan plan_decode(const Geom& g, int32_t seq_len, int heads, int64_t room);
+DecodePlan plan_decode(const Geom& g, int32_t seq_len, int heads, int64_t room, bool ragged);
 int32_t decode_records_bound(const Geom& g, int32_t seq_len, bool least = false);   // >= the records per head of every length up to seq_len
 int device_compute_units();                                      // of the current device (256 without one)
 
@@ -104,8 +105,8 @@ struct DecodeArgs {
   // n modulo that length, possibly 0); a workgroup with nothing to read writes an empty record.  lens_mode 0: n as it is.
   int32_t lens_mode, lens_bound, lens_block;   // lens_block: the buffer's slots (a power of two)
   int32_t buf_len;            // channel-wise keys: tokens in the residual buffer (uniform lengths; the new one of a fused step counts)
-  // != 0 (with seq_lens): the launch's n_splits * batch workgroups per kv head are dealt out to the sequences by their
-  // lengths instead of n_splits each; workgroup w of a kv head writes the records of slot w
+  // != 0 (with seq_lens): this many workgroups per kv head are dealt out to the sequences by their lengths, instead of n_splits to
+  // each; workgroup w of a kv head writes the records of slot w
   int32_t balance;
   float* ws; void* out; int out_dtype;
   int32_t n_splits, steps_per_split;

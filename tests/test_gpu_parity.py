@@ -2412,6 +2412,56 @@ def test_ragged_batch_dealt_out_by_its_lengths(kvq, B, H, R, bk, bv, page, rotv,
     assert float(err.max()) < 2e-3, float(err.max())
 
 
+@pytest.mark.parametrize("B,H,R,bk,bv,page", [(9, 8, 4, 4, 2, 0), (11, 8, 2, 4, 4, 64), (18, 8, 1, 4, 2, 0), (28, 4, 7, 2, 4, 0), (30, 8, 4, 4, 2, 256),
+                                              (33, 8, 4, 4, 2, 0), (37, 8, 8, 8, 2, 64)])
+def test_workgroups_that_fill_the_chip_dealt_out_by_lengths(kvq, B, H, R, bk, bv, page):
+    """Stream counts that do not divide the chip, one or several parts a sequence (on 256 compute units): with the reported workspace
+    the workgroups left over go to the longest sequences.  Against attention over each sequence on its own; with the least workspace a
+    call takes (none from 129 streams that are not split up), which deals out the plan's own number or none, too.  Uniform
+    lengths of the same counts, which the plan cuts so that they fit the chip in one round."""
+    D, scale, T = 128, 1 / math.sqrt(128), 1700
+    kw = dict(page_tokens=page, n_pages=B * -(-T // page) + 1) if page else {}
+    L = kvq.Layout(B, H, T, D, bk, bv, 64, 64, raw_dtype=kvq.KVQ_BF16, **kw)
+    one = replace(L, batch=1)
+    K, V, q = synth.make_kvq(33, B, H, H * R, T, D, dtype=torch.bfloat16, device="cuda", sigma_k=1.0)
+    cache = kvq.Cache(L, fill=0)
+    if page:
+        cache.page_table = torch.randperm(L.n_pages, device="cuda")[:L.n_pages - 1].to(torch.int32).view(B, -1).contiguous()
+    kvq.quantize_append(L, cache, K, V, 0)
+    need = kvq.decode_workspace_bytes(L, H * R, T)
+    assert need > 0
+    rng = np.random.RandomState(B)
+    cases = [np.full(B, T), np.r_[T, np.ones(B - 1)], rng.randint(1, T + 1, B), np.linspace(60, T, B).astype(int), np.r_[T, T - 1, np.full(B - 2, T // 3)]]
+    alone = torch.empty(B, H * R, D, dtype=torch.float32, device="cuda")
+    ws1 = torch.empty(max(16, kvq.decode_workspace_bytes(one, H * R, T)), dtype=torch.uint8, device="cuda")
+    least = 0 if B * H > 146 else need                       # (88 and 72 streams: the plan's parts need records of their own)
+    for lens in cases:
+        dev = torch.tensor(lens.astype(np.int64), device="cuda").to(torch.int32)
+        for b in range(B):
+            if page:
+                sub = kvq.Cache.__new__(kvq.Cache)
+                sub.layout, sub.planes, sub.v_scale_exp = one, cache.planes, cache.v_scale_exp.view(B, -1)[b].contiguous()
+                sub.page_table = cache.page_table[b:b + 1].contiguous()
+            else:
+                sub = cache.batch_element(b, one)
+            kvq.decode_attention(one, sub, q[b:b + 1].contiguous(), int(lens[b]), scale, alone[b:b + 1], ws1)
+        for size in {need, least}:
+            ws = torch.full((size + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
+            got = [kvq.decode_attention_varlen(L, cache, q, dev, T, scale, torch.empty(B, H * R, D, dtype=torch.float32, device="cuda"),
+                                               ws[:size] if size else None) for _ in range(2)]
+            assert torch.equal(got[0], got[1]) and ws[size:].eq(0xFF).all()
+            err = (got[0] - alone).abs().amax(-1) / alone.abs().amax(-1)
+            assert float(err.max()) < 2e-3, (lens, size, float(err.max()))
+    got = kvq.decode_attention(L, cache, q, T, scale, torch.empty(B, H * R, D, dtype=torch.float32, device="cuda"),
+                               torch.full((need,), 0x5A, dtype=torch.uint8, device="cuda"))
+    for b in range(B):
+        sub = cache.batch_element(b, one) if not page else None
+        if sub is not None:
+            kvq.decode_attention(one, sub, q[b:b + 1].contiguous(), T, scale, alone[b:b + 1], ws1)
+    if not page:
+        assert float(((got - alone).abs().amax(-1) / alone.abs().amax(-1)).max()) < 2e-3
+
+
 def test_ragged_batch_replayed_from_a_hip_graph(kvq):
     """The counters behind the records return to where a replay finds them, and the lengths are read at every replay."""
     B, H, R, T, D = 16, 8, 2, 3500, 128
