@@ -31,6 +31,34 @@ __device__ __forceinline__ float rows_max(float x) {
   return max2f(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
+// Value patterns of four neighbouring tokens into the residual buffer's block of 32 (v_field's order for 16-bit patterns: a channel's
+// 8 tokens 4 j .. 4 j + 3 of both 16-token tiles are 16 bytes).  A wavefront's four rows of lanes hold the four tokens, 8 channels
+// a lane; a transposition of 4 x 4 words by two swaps of rows and two of halves leaves every lane with two channels of all four,
+// which go out as 16 bytes each, or 8 where only one tile's tokens are there.  As 16-bit stores 16 bytes apart they were one
+// request of the second-level cache each, 8192 a block and sequence: 43 x 8 heads x 2036 tokens, where the last blocks of all
+// sequences fall to one of the 8 parts of the chip, 174 us and 90 so, 35 x 8 x 776 36.5 and 31.4, 11 x 8 x 1921 25.3 and 23.6.  Every lane takes part.
+//   a, b  this lane's rows of the two tiles; put_a, put_b: whether all four tokens of the tile are stored (uniform)
+__device__ __forceinline__ void store_value_quads(uint8_t* block, int j, int lane16, int r, const uint4& a, const uint4& b, bool put_a, bool put_b) {
+  auto pairs = [](const uint4& x, uint2 (&ch)[2]) {
+    const auto s0 = __builtin_amdgcn_permlane16_swap(x.x, x.y, false, false), s1 = __builtin_amdgcn_permlane16_swap(x.z, x.w, false, false);
+    const auto e = __builtin_amdgcn_permlane32_swap(s0[0], s1[0], false, false), o = __builtin_amdgcn_permlane32_swap(s0[1], s1[1], false, false);
+    // e[0], o[0], e[1], o[1]: word r of tokens 0 .. 3
+    ch[0] = make_uint2((e[0] & 0xFFFFu) | (o[0] << 16), (e[1] & 0xFFFFu) | (o[1] << 16));
+    ch[1] = make_uint2((e[0] >> 16) | (o[0] & 0xFFFF0000u), (e[1] >> 16) | (o[1] & 0xFFFF0000u));
+  };
+  uint2 ca[2], cb[2];
+  pairs(a, ca);
+  pairs(b, cb);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int c = 8 * lane16 + 2 * r + k;
+    uint32_t* dst = reinterpret_cast<uint32_t*>(block) + (c >> 4) * 256 + (16 * j + (c & 15)) * 4;
+    if (put_a && put_b) *reinterpret_cast<uint4*>(dst) = make_uint4(ca[k].x, ca[k].y, cb[k].x, cb[k].y);
+    else if (put_a) *reinterpret_cast<uint2*>(dst) = ca[k];
+    else *reinterpret_cast<uint2*>(dst + 2) = cb[k];
+  }
+}
+
 // Channel-wise keys (Sec. 4 "Downstream Task Accuracy": the per-column back-end with its residual buffer).
 // One workgroup = one block of RLT tokens (the residual buffer's length: 64 or 128) of one (b,h) stream, restricted to
 // the new tokens [lo, hi) in it.  New tokens that no later token of this call overwrites go to their residual slot as
@@ -61,7 +89,15 @@ __global__ __launch_bounds__(256) void seq_append_kernel(Geom g, kvq_cache c, co
   const int bh = blockIdx.y;
   const int b = bh / g.kv_heads, h = bh % g.kv_heads;
   if (pos_arr) pos = min(max(pos_arr[b], 0), max_pos);     // one token per sequence at its own position (n_new == 1)
-  const int blk = pos / RLT + blockIdx.x;
+  // Where the blocks of a sequence are a multiple of 8, its last two, which fill the buffer, would fall to the same part of the chip for all
+  // sequences: they begin at another one each there (43 x 8 heads x 2036 tokens 89.7 us without, 83.0; 128-token buffers, 10 x 8 x 1937, 31.9
+  // and 26.5).  Elsewhere the parts share them anyway, and the order costs (8 x 8 x 8229 61.9 and 64.3).
+  int turn = blockIdx.x;
+  if ((gridDim.x & 7) == 0) {                              // (uniform)
+    turn += blockIdx.y & 7;
+    if (turn >= (int)gridDim.x) turn -= gridDim.x;
+  }
+  const int blk = pos / RLT + turn;
   const int lo = max(pos, blk * RLT) - blk * RLT;
   const int hi = min(pos + n_new, (blk + 1) * RLT) - blk * RLT;
   const bool complete = hi == RLT;                         // this call brings the block's last token
@@ -84,19 +120,30 @@ __global__ __launch_bounds__(256) void seq_append_kernel(Geom g, kvq_cache c, co
       vraw[it] = *reinterpret_cast<const uint4*>(v_new + src);
     }
   }
+  // the rows [keep, hi) are the last tokens of this call that land in their slots
+  const int keep = max(lo, pos + n_new - RLT - blk * RLT);
+  const int quad = 4 * __builtin_amdgcn_readfirstlane(tid >> 6);           // a wavefront's rows: 16 it + quad .. + 3
+  if (keep < hi) {                                         // (uniform)
+#pragma unroll
+    for (int it = 0; it < NIT; it += 2) {
+      const bool full0 = 16 * it + quad >= keep && 16 * it + quad + 4 <= hi, full1 = 16 * it + quad + 16 >= keep && 16 * it + quad + 20 <= hi;
+      if (full0 || full1) store_value_quads(vr + (it >> 1) * (512 * 16), quad >> 2, lane16, rg & 3, vraw[it], vraw[it + 1], full0, full1);
+    }
+  }
 #pragma unroll
   for (int it = 0; it < NIT; ++it) {
     const int row = rg + 16 * it;
-    const int64_t t = (int64_t)blk * RLT + row;
     if (row >= lo && row < hi) {
-      if (t + RLT >= (int64_t)pos + n_new) {               // the last token of this call that lands in slot `row`
+      if (row >= keep) {
         *reinterpret_cast<uint4*>(kr + row * (kHeadDim * 2) + d0 * 2) = kraw[it];
-        const uint32_t rw[4] = {vraw[it].x, vraw[it].y, vraw[it].z, vraw[it].w};
-        int dw, bit;
-        v_field(row & 31, d0, 16, &dw, &bit);
-        uint16_t* blk16 = reinterpret_cast<uint16_t*>(vr + (row >> 5) * (512 * 16));
+        if (16 * it + quad < keep || 16 * it + quad + 4 > hi) {            // (uniform: a quad at an end of the rows that stay)
+          const uint32_t rw[4] = {vraw[it].x, vraw[it].y, vraw[it].z, vraw[it].w};
+          int dw, bit;
+          v_field(row & 31, d0, 16, &dw, &bit);
+          uint16_t* blk16 = reinterpret_cast<uint16_t*>(vr + (row >> 5) * (512 * 16));
 #pragma unroll
-        for (int e = 0; e < 8; ++e) blk16[(dw + 4 * e) * 2 + (bit >> 4)] = (uint16_t)(rw[e >> 1] >> (16 * (e & 1)));
+          for (int e = 0; e < 8; ++e) blk16[(dw + 4 * e) * 2 + (bit >> 4)] = (uint16_t)(rw[e >> 1] >> (16 * (e & 1)));
+        }
       }
     } else if (complete && row < lo) {                     // older tokens of the block being flushed
       kraw[it] = *reinterpret_cast<const uint4*>(kr + row * (kHeadDim * 2) + d0 * 2);

@@ -911,6 +911,21 @@ def _assert_seq_planes_equal(cache, planes):
         assert bad.size == 0, f"{name}: {bad.size} bytes differ, first at {bad[:5]}"
 
 
+@pytest.mark.parametrize("axis,gk,rl", [(1, 64, 0), (1, 128, 128), (1, 32, 64), (0, 64, 64)])
+def test_buffered_values_at_the_edges_of_four_tokens(kvq, oracle, axis, gk, rl):
+    """The buffer's value patterns are stored four tokens at a time: calls that begin and end on every remainder of four, inside one
+    16-token tile, across tiles, across 32-token blocks and across flushed blocks, with tokens that a later one of the call replaces."""
+    B, H, cap = 2, 5, 640
+    slots = rl or gk
+    K, V, _ = synth.make_kvq(77 + gk, B, H, H, cap, dtype=torch.bfloat16)
+    kw = dict(axis_k=axis, raw_dtype=1, resid_len=rl)
+    Lg, Lo = kvq.Layout(B, H, cap, 128, 4, 2, gk, 64, **kw), oracle.Layout(B, H, cap, 128, 4, 2, gk, 64, **kw)
+    for a, b in ((0, 3), (1, 4), (2, 9), (3, 16), (5, 23), (4, 20), (12, 37), (15, 60), (slots - 3, slots + 6), (0, slots + 21), (7, 2 * slots + 18),
+                 (0, 4 * slots + 37), (0, 4 * slots - 2)):
+        cache, planes = _seq_fill_both(kvq, oracle, Lg, Lo, K, V, ([(0, a)] if a else []) + [(a, b)])
+        _assert_seq_planes_equal(cache, planes)
+
+
 @pytest.mark.parametrize("bk,bv,gv", [(4, 2, 64), (2, 4, 128), (8, 8, 32), (4, 4, 64), (4, 1, 64), (8, 6, 128), (2, 3, 32),
                                       (6, 2, 64), (3, 3, 128), (1, 4, 32)])
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
