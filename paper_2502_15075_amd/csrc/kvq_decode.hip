@@ -2040,7 +2040,7 @@ DecodePlan plan_coarse(const Geom& g, int32_t seq_len) {
 //   - where more than three steps per wavefront are left, as few as all the parts allow: from 9 records on a larger merge launch costs a
 //     microsecond more.
 // The lines were drawn on K4V2.  Wider rows, captured in a graph, against the coarse plan: with more than four heads and in long sequences within 1 %
-// (K8V8 and unquantized, 8 to 352 sequences, 500 to 16384 tokens); unquantized sequences of 40 and 100 tokens would take four wavefronts 2 to 6 %
+// (K8V8, 8 to 352 sequences, 500 to 16384 tokens; unquantized rows: below); unquantized sequences of 40 and 100 tokens would take four wavefronts 2 to 6 %
 // faster (8 x 8 heads x 100, 8 query heads, 6.35 and 6.69 us, 4 query heads 5.46 and 5.56), K8V8 and unquantized ones of 300 tokens and one query
 // head too (8 x 8 heads 6.34 and 6.49, 7.50 and 7.68).
 // Fused steps, K4V2, 4 query heads unless said, before (the coarse plan) and so, captured in a graph: 8 heads x 800 tokens 7.07 and 6.44 us,
@@ -2050,8 +2050,15 @@ DecodePlan plan_coarse(const Geom& g, int32_t seq_len) {
 // 8.10; 8 heads x 3000 in 4 parts 8.93, back to back 8.52, in 6 parts 8.45 and 9.57; 8 heads x 4096 in 8 parts 8.49, in 16 9.53, x
 // 6000 in 8 parts 9.12, in 24 9.73; x 8192 in 8 parts 10.46, in 16 10.17, in 32 9.28.
 struct FinePlan { int splits, steps; };            // steps per wavefront; splits = 0: the coarse plan
-FinePlan fine_plan(int n_steps, int most, int heads) {
+// Rows of 512 bytes (wide: both tensors unquantized; K8V8 takes half) are the other way round: one step of eight wavefronts is 128 KB, so the parts
+// are as many as fill the chip down to one step per wavefront, from 14 steps on (13: 8 query heads, 8 x 8 heads 11.5 and 10.4 us, 2 x 8 9.1 and 9.3).  Attention, with the lines above and so: 2 x 8 heads x 700 tokens, 4 query
+// heads, 12.4 and 8.8 us; 17 x 4 heads x 907, 7 query heads, 18.0 and 15.0, x 500 12.3 and 10.4; 4 x 8 x 2000 14.1 and 10.9; K8V8 2 x 8 x 700 8.6 and 7.8.
+FinePlan fine_plan(int n_steps, int most, int heads, bool wide) {
   const int n8 = (n_steps + 7) / 8;
+  if (wide && most > 1 && n_steps >= 14) {
+    const int steps = (n8 + most - 1) / most;
+    return FinePlan{(n8 + steps - 1) / steps, steps};
+  }
   if (n8 == 4 && most >= 4 && heads <= 4) return FinePlan{4, 1};
   if (most <= 1 || n8 <= 3 || n_steps < 31) return FinePlan{1, n8};
   const int few = most < 8 ? most : 8;
@@ -2066,13 +2073,15 @@ FinePlan fine_plan(int n_steps, int most, int heads) {
   return FinePlan{(n8 + steps - 1) / steps, steps};
 }
 // No length up to n_steps takes more parts.
-int fine_bound(int n_steps, int most) {
+int fine_bound(int n_steps, int most, bool wide) {
   const int n8 = (n_steps + 7) / 8;
+  if (wide) return most <= 1 || n_steps < 14 ? 1 : n8 < most ? n8 : most;
   if (most <= 1 || n8 <= 3) return 1;
   const int few = most < 8 ? most : 8, two = (n8 + 1) / 2 > 4 ? (n8 + 1) / 2 : 4;
   if (n8 <= 3 * few) return two < few ? two : few;
   return n8 < most ? n8 : most;
 }
+bool wide_rows(const Geom& g) { return g.bits_k == 16 && g.bits_v == 16; }
 // Workgroups of 8 wavefronts per sequence that fill the chip; 0 where there are too many sequences for one each.
 int fine_most(const Geom& g, bool bound) {
   const int streams = g.batch * g.kv_heads, waves = device_compute_units() * 4 * KVQ_WAVES_PER_SIMD;
@@ -2114,7 +2123,7 @@ int32_t decode_records_bound(const Geom& g, int32_t seq_len, bool least) {
   if (n_steps == 0) return 1;
   const int splits = wave_budget(g, n_steps, true).splits;
   if (g.resid) return least && g.axis_k == KVQ_AXIS_SEQ ? splits : splits + 1;
-  const int fine = least ? 0 : fine_bound(n_steps, fine_most(g, true));
+  const int fine = least ? 0 : fine_bound(n_steps, fine_most(g, true), wide_rows(g));
   const int dealt = least ? 0 : deal_bound(g, n_steps);
   return dealt > fine && dealt > splits ? dealt : fine > splits ? fine : splits;
 }
@@ -2123,7 +2132,7 @@ int32_t decode_records_bound(const Geom& g, int32_t seq_len, bool least) {
 static DecodePlan plan_parts(const Geom& g, int32_t seq_len, int heads, int64_t room) {
   const int n_steps = plan_steps(g, seq_len), most = n_steps ? fine_most(g, false) : 0;
   if (most < 1) return plan_coarse(g, seq_len);
-  const FinePlan f = fine_plan(n_steps, most, heads);
+  const FinePlan f = fine_plan(n_steps, most, heads, wide_rows(g));
   if (f.splits == 0 || (f.splits > 1 && f.splits > room)) return plan_coarse(g, seq_len);
   // (fewer than 8 steps and one or two heads: four wavefronts have less to merge.  7 steps, 4 and 8 wavefronts, 1 head 5.02 and 5.10 us,
   // 2 heads 5.10 and 5.20, 3 heads 5.56 and 5.14, 8 heads 6.62 and 6.23; 8 steps, 1 head 5.63 and 5.29, 8 heads 7.26 and 6.45)

@@ -303,6 +303,28 @@ def test_attention_ignores_garbage_beyond_seq_len(kvq, oracle):
     assert np.isfinite(out).all() and _rel_err(out, ref) < TOL
 
 
+@pytest.mark.parametrize("H,R", [(2, 1), (3, 7), (2, 8)])
+def test_unquantized_sequences_in_parts_of_one_step_per_wavefront(kvq, oracle, H, R):
+    """Unquantized rows are cut down to one step per wavefront from 14 steps on: lengths on both sides of that, of whole and ragged
+    parts; with the reported workspace and with the least that a call takes (it is then cut as quantized rows are)."""
+    B, T = 2, 1300
+    K, V, q = synth.make_kvq(41 + R, B, H, H * R, T, dtype=torch.float16)
+    Lg, Lo = _layouts(kvq, oracle, B, H, T, 16, 16, 128, 128)
+    cache, planes = _fill_both(kvq, oracle, Lg, Lo, K, V, [(0, T)])
+    scale, qd = 1 / math.sqrt(128), q.cuda()
+    for n in (416, 417, 448, 449, 512, 513, 700, T):
+        ref = oracle.decode_attention(Lo, planes, q.numpy(), n, scale)
+        need = kvq.decode_workspace_bytes(Lg, H * R, n)
+        for size in sorted({need, need // 2, 0}, reverse=True):
+            out = torch.empty(B, H * R, 128, dtype=torch.float32, device="cuda")
+            try:
+                kvq.decode_attention(Lg, cache, qd, n, scale, out, torch.empty(size // 16 * 16, dtype=torch.uint8, device="cuda") if size else None)
+            except kvq.KvqError as e:
+                assert e.status == kvq.ERR_WORKSPACE and size < need
+                continue
+            assert _rel_err(out.cpu().numpy(), ref) < TOL, (n, size)
+
+
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
 @pytest.mark.parametrize("R", [1, 4, 8])
 def test_unquantized_cache_attention(kvq, oracle, dtype, R):
