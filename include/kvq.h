@@ -180,7 +180,7 @@ kvq_status kvq_residual_bytes(const kvq_layout* layout, size_t bytes_out[2]);
  * workspace pointer may be NULL.  Never shrinks as seq_len grows: a workspace sized once for the longest sequence
  * serves every shorter one.  A call also accepts fewer bytes, down to the records of a plan of at least two steps of 32 tokens
  * per wavefront (none for short sequences, none for the tokens in the residual buffer of channel-wise keys), and then cuts the
- * sequence into fewer parts: the plan, and with it the rounding of the result, follows the number of bytes that a call is
+ * sequence into fewer parts, or deals fewer workgroups out to sequences of different lengths: the plan, and with it the rounding of the result, follows the number of bytes that a call is
  * given, so calls that are to agree bit for bit bring the same number.  Touches no device memory; the split plan follows the
  * compute-unit count of the CURRENT device (256 when no device is usable), so size the workspace with the device current that the
  * decode calls run on.
@@ -226,8 +226,9 @@ kvq_status kvq_decode_attention(const kvq_layout* layout, const kvq_cache* cache
  * KVQ_STATIC_SCRATCH_BYTES that is part of the library's device code (every GPU the library runs on holds its own copy
  * until the process ends; the array's device address is looked up once per device, on the first call with that device
  * current).  The call allocates nothing, frees nothing and calls no allocating routine.
- *   - a call that needs more than KVQ_STATIC_SCRATCH_BYTES of records (kvq_decode_workspace_bytes tells) returns
- *     KVQ_ERR_STATIC_SCRATCH and launches nothing;
+ *   - a call on a cache with a residual buffer that needs more than KVQ_STATIC_SCRATCH_BYTES of records
+ *     (kvq_decode_workspace_bytes tells) returns KVQ_ERR_STATIC_SCRATCH and launches nothing (without a buffer only sequences
+ *     of different lengths could want more, which this call does not take);
  *   - every call on one GPU shares that GPU's array, whatever its stream: calls that can overlap in time on one GPU
  *     race on it (calls on one stream, or ordered by events, do not), and only they: the array keeps the last call's
  *     records and counters, but every record a call reads is one that the same call wrote, and a counter without the

@@ -298,6 +298,9 @@ template <int BV> __device__ __forceinline__ u32x4 unpack_v(const uint32_t* w, i
 // first fill, which every wavefront asks for at once, and the code longer.  With 6, 4, 3, 2 and 1 steps, K4V2: 8 x 8 heads x 8192 tokens
 // 16.7, 15.2, 14.4, 14.1 and 15.4 us, 8 heads x 131071 26.9, 25.4, 24.4, 24.1 and 26.3, 32 x 8 x 8 heads x 32768 143.3, 141.7, 142.0, 140.6 and
 // 164.1; K4V4 with 3, 2 and 1: 8 x 8 x 8192 17.1, 16.7 and 17.1, 40 x 8 x 3000 30.8, 29.6 and 33.4; K2V2 with 4, 3, 2: 13.4, 12.6, 12.5.
+// Three where the columns fill a tile and a row has up to 5 bits (one step of the walk then takes as long as the data of the next to come, and
+// walks of three steps are common): 8 query heads, with 4, 2 and 3, K2V2 2 x 8 heads x 6000 tokens 10.1, 10.5 and 10.1, x 8 x 8192 15.7, 15.1
+// and 15.1; K4V1 in 32-channel value groups 5 x 8 x 6049 13.5, 13.8 and 13.3; K3V2 8 x 8 x 2000 10.4, 10.6 and 10.5.
 template <int BK, int BV, int NCK = 1, int NCV = 1, bool ROTV = false, bool HALF = false>
 constexpr int ring_stages() {
   if (HALF) return KVQ_STAGES;
@@ -308,7 +311,8 @@ constexpr int ring_stages() {
                        + (code_hi_bits<BV>() ? 1 : 0)              // of keys or a high part of values (its weights)
                        + (ROTV ? 1 : 0)                            // (rotated values: the unrounded weights stay live)
                        + (BK == 2 && regs >= 16 ? 1 : 0);         // (moved 2-bit fields: two shifted copies of a word live)
-  return base - less >= KVQ_STAGES ? KVQ_STAGES : base - less >= 1 ? base - less : 1;
+  constexpr int most = regs <= 14 ? KVQ_STAGES + 1 : KVQ_STAGES;
+  return base - less >= most ? most : base - less >= 1 ? base - less : 1;
 }
 
 // Everything one lane loads for one 32-token step (two 16-token tiles).
