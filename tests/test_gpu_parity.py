@@ -937,7 +937,7 @@ def _assert_seq_planes_equal(cache, planes):
 def test_buffered_values_at_the_edges_of_four_tokens(kvq, oracle, axis, gk, rl):
     """The buffer's value patterns are stored four tokens at a time: calls that begin and end on every remainder of four, inside one
     16-token tile, across tiles, across 32-token blocks and across flushed blocks, with tokens that a later one of the call replaces."""
-    B, H, cap = 2, 5, 640
+    B, H, cap = 2, 32, 640                                    # (64 sequences and heads: from there on four at a time)
     slots = rl or gk
     K, V, _ = synth.make_kvq(77 + gk, B, H, H, cap, dtype=torch.bfloat16)
     kw = dict(axis_k=axis, raw_dtype=1, resid_len=rl)
