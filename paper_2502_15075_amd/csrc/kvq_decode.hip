@@ -2057,9 +2057,13 @@ struct FinePlan { int splits, steps; };            // steps per wavefront; split
 // Rows of 512 bytes (wide: both tensors unquantized; K8V8 takes half) are the other way round: one step of eight wavefronts is 128 KB, so the parts
 // are as many as fill the chip down to one step per wavefront, from 14 steps on (13: 8 query heads, 8 x 8 heads 11.5 and 10.4 us, 2 x 8 9.1 and 9.3).  Attention, with the lines above and so: 2 x 8 heads x 700 tokens, 4 query
 // heads, 12.4 and 8.8 us; 17 x 4 heads x 907, 7 query heads, 18.0 and 15.0, x 500 12.3 and 10.4; 4 x 8 x 2000 14.1 and 10.9; K8V8 2 x 8 x 700 8.6 and 7.8.
+// Where the chip has room for two parts, 17 to 20 steps (more than 4 heads: to 22) stay in one: one part per step of a wavefront would be three, and
+// of two parts of two steps the second would get 1 to 4 steps of 8 wavefronts.  In two parts and in one, 16 x 8 heads, 17, 18, 20, 21 and 24
+// steps, 8 query heads, 13.5 to 6.0 % slower up to 21 and 1.8 % faster at 24; 4 query heads 12.0, 8.0, 3.6, 1.1 % slower and 2.4 % faster; 11 x 8, 4
+// query heads, 10.5, 8.0, 1.6 % slower, 2.4 and 7.3 % faster (16 x 8 x 573 tokens, 8 query heads, 15.5 and 14.3 us).
 FinePlan fine_plan(int n_steps, int most, int heads, bool wide) {
   const int n8 = (n_steps + 7) / 8;
-  if (wide && most > 1 && n_steps >= 14) {
+  if (wide && most > 1 && n_steps >= 14 && !(most == 2 && n_steps > 16 && n_steps <= (heads > 4 ? 22 : 20))) {
     const int steps = (n8 + most - 1) / most;
     return FinePlan{(n8 + steps - 1) / steps, steps};
   }

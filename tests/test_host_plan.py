@@ -1,0 +1,31 @@
+"""The library's own split plan, asked on the CPU."""
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+PKG = os.path.join(os.path.dirname(HERE), "paper_2502_15075_amd")
+
+
+@pytest.fixture(scope="module")
+def check(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("plan") / "plan_check")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-D__HIP_PLATFORM_AMD__=1", "-I", os.path.join(PKG, "csrc"), "-I", os.path.join(os.path.dirname(HERE), "include"),
+                    "-isystem", "/opt/rocm/include", "-o", exe, os.path.join(HERE, "plan_check.cpp"), "-L", PKG, "-lkvq", f"-Wl,-rpath,{PKG}",
+                    "-L", "/opt/rocm/lib", "-Wl,-rpath,/opt/rocm/lib", "-lamdhip64"], check=True)
+    return lambda *a: subprocess.run([exe, *map(str, a)], capture_output=True, text=True)
+
+
+def _plan(check, *a):
+    r = check(*a)
+    assert r.returncode == 0, r.stdout + r.stderr
+    return tuple(map(int, r.stdout.split()))
+
+
+@pytest.mark.parametrize("batch,heads,tokens,parts,steps", [(16, 4, 512, 2, 8), (16, 8, 513, 1, 24), (16, 8, 704, 1, 24), (16, 8, 705, 2, 16), (12, 1, 640, 1, 24),
+                                                            (16, 4, 641, 2, 16), (11, 4, 577, 1, 24), (11, 4, 768, 2, 16), (10, 4, 577, 3, 8), (17, 4, 577, 1, 24)])
+def test_unquantized_sequences_of_two_parts_at_most(check, batch, heads, tokens, parts, steps):
+    """Unquantized rows where the chip has room for two parts a sequence: 17 to 20 steps (22 for more than 4 heads) are one part, as two
+    would be one of two steps per wavefront and a nearly empty one; with room for three they are three."""
+    assert _plan(check, batch, 8, heads, 16, 16, tokens)[:3] == (parts, steps, 8)
