@@ -2108,10 +2108,11 @@ namespace {
 bool deals(const Geom& g, int nw, int steps_per_split) { return !g.resid && g.batch >= 2 && g.batch <= 64 && steps_per_split >= 6 * nw; }
 int full_slots(const Geom& g, int nw) { return device_compute_units() * 4 * KVQ_WAVES_PER_SIMD / nw / g.kv_heads; }
 int deal_records(const Geom& g, int slots) { return (slots + g.batch - 1) / g.batch; }      // of the workspace, per (batch, kv head)
-// No plan of more than half the chip in up to 4 parts a sequence, for lengths up to n_steps, takes more.
+// No plan of more than half the chip in up to 4 parts a sequence, for lengths up to n_steps, takes more.  (The plan rounds a part up to whole
+// wavefronts before it asks whether it is long enough, and so does this.)
 int deal_bound(const Geom& g, int n_steps) {
   const int streams = g.batch * g.kv_heads, nw = streams <= device_compute_units() ? 8 : 4;
-  if (!deals(g, nw, n_steps) || 8 * streams <= device_compute_units()) return 1;
+  if (!deals(g, nw, (n_steps + nw - 1) / nw * nw) || 8 * streams <= device_compute_units()) return 1;
   const int records = deal_records(g, full_slots(g, nw));
   return records < 8 ? records : 8;
 }

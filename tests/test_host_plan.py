@@ -29,3 +29,11 @@ def test_unquantized_sequences_of_two_parts_at_most(check, batch, heads, tokens,
     """Unquantized rows where the chip has room for two parts a sequence: 17 to 20 steps (22 for more than 4 heads) are one part, as two
     would be one of two steps per wavefront and a nearly empty one; with room for three they are three."""
     assert _plan(check, batch, 8, heads, 16, 16, tokens)[:3] == (parts, steps, 8)
+
+
+def test_plans_stay_inside_the_workspace_and_reach_the_whole_of_it(check):
+    """No plan writes more records than the workspace it is given holds or the size query counts, and with the workspace that the
+    query reports a call takes the plan of any larger one."""
+    r = check()
+    assert r.returncode == 0, r.stdout + r.stderr
+    assert int(r.stdout.split("plans=")[1].split()[0]) > 1000000
