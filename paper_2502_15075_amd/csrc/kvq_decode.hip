@@ -978,12 +978,10 @@ __device__ __forceinline__ void store_unrotated_row(const float* row, int lane16
 // ---- sequences of different lengths: which part of which sequence a workgroup takes ------------------------------------
 // A launch planned for the longest sequence cuts every sequence at the same places, and the workgroups behind a short one's
 // end have nothing to do while those of the longest run on.  Instead all workgroups of a kv head (slots 0 .. slots - 1)
-// are dealt out by the lengths: sequence b gets ceil(N_b / q) of them, q steps each, with the smallest q (of 64 evenly
-// spaced ones) for which they are enough.  Every wavefront works that out for itself from the lengths (at most 64, one per
-// lane); the answer depends on nothing else, so all workgroups agree.  Where the plan's q leaves fewer than an eighth of the
-// workgroups without a part, or 7/8 of it would not do, it stays, without the search: a smaller one would need more parts for the
-// long sequences than there are left, and looking for it costs 0.6 to 0.9 us (16 sequences of 8 kv heads, K4V2, 14000 to 16384 tokens: 45.7 us
-// and 46.4 with the search, 45.5 when nothing is dealt out; 2800 to 4000 tokens 16.2, 17.0 and 16.2).
+// are dealt out by the lengths: sequence b gets ceil(N_b / q) of them, q steps each, with the smallest q (a multiple of the wavefronts,
+// and no more parts than kDealParts for the longest sequence, whose records one workgroup merges) for which they are enough.  Every wavefront works that out for itself from the lengths (at
+// most 64, one per lane); the answer depends on nothing else, so all workgroups agree.  Where q would not come down to what pays
+// (q_pay, from the plan: deal_pays), the plan's q stays, without the search.  One pass over the lanes counts the parts of both.
 __device__ __forceinline__ int wave_scan(int v) {  // sum over the lanes up to and including this one
   v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);     // row_shr 1, 2, 4, 8
   v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
@@ -993,10 +991,13 @@ __device__ __forceinline__ int wave_scan(int v) {  // sum over the lanes up to a
   v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);     // row_bcast 31 into rows 2 and 3
   return v;
 }
+// (9 x 8 heads, one sequence of 12000 tokens among others of 1200, K4V2, in 16 parts 13.1 us, in 10 12.2; K8V8, 7 x 8, one of 16000, in 11 parts
+// 22.1, in 17 19.1)
+constexpr int kDealParts = 12;
 struct Share { int b, split, count, q, slot0, len; };   // sequence, part of it, its parts, steps per part, slot of its first part, tokens
-template <int UNIT>                                // q is a multiple of UNIT steps (a workgroup's wavefronts)
+template <int UNIT, int MOST>                      // q is a multiple of UNIT steps (a workgroup's wavefronts); MOST: parts of the longest sequence
 __device__ __forceinline__ Share balanced_share(const int32_t* __restrict__ seq_lens, int offset, int bound, int batch, int slots,
-                                                int q_max, int slot, int lane) {
+                                                int splits, int q_max, int q_pay, int slot, int lane) {
   const int len = min(max(seq_lens[min(lane, batch - 1)] + offset, 1), bound);
   const int n = lane < batch ? (len + 31) >> 5 : 0;           // steps, 2^19 at most
   // parts of q steps; (n + q - 1) / q in binary32: half a unit above the quotient of integers below 2^21 rounds to the right side
@@ -1006,17 +1007,16 @@ __device__ __forceinline__ Share balanced_share(const int32_t* __restrict__ seq_
   };
   Share s;
   s.q = q_max;                                     // (always enough: no sequence is longer than the plan's)
-  int mine = parts(q_max), end = wave_scan(mine);
-  const int q_less = (q_max * 7 / 8 + UNIT - 1) / UNIT * UNIT;
-  if (8 * (slots - __builtin_amdgcn_readlane(end, 63)) >= slots &&
-      __builtin_amdgcn_readlane(wave_scan(parts(q_less)), 63) <= slots) {        // (uniform)
-    int lo = 1, hi = 64;                           // q = q_max i / 64, at least one unit (rounded up twice)
+  // (up to 4 parts of q_max a sequence, and q_pay is at least an eighth of it: 64 sequences count to 2048)
+  const int both = wave_scan(parts(q_max) | parts(q_pay) << 16);
+  int end = both & 0xFFFF, mine = parts(q_max);
+  if (__builtin_amdgcn_readlane(both, 63) >> 16 <= slots) {   // (uniform)
+    int lo = min(((splits * q_max + MOST - 1) / MOST + UNIT - 1) / UNIT, q_pay / UNIT), hi = q_pay / UNIT;
     while (lo < hi) {
       const int mid = (lo + hi) >> 1;
-      const int q = min((int)((((int64_t)q_max * mid + 63) / 64 + UNIT - 1) / UNIT) * UNIT, q_max);
-      const bool enough = __builtin_amdgcn_readlane(wave_scan(parts(q)), 63) <= slots;
-      if (enough) { hi = mid; s.q = q; } else { lo = mid + 1; }
+      if (__builtin_amdgcn_readlane(wave_scan(parts(mid * UNIT)), 63) <= slots) hi = mid; else lo = mid + 1;
     }
+    s.q = hi * UNIT;
     mine = parts(s.q); end = wave_scan(mine);
   }
   const unsigned long long hit = __ballot(slot >= end - mine && slot < end);       // (one lane, or none)
@@ -1101,7 +1101,7 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   if constexpr (!KSEQ) {
     if (a.balance) {                               // (uniform)
       slot = b;
-      const Share sh = balanced_share<NW>(a.seq_lens, a.lens_offset, a.lens_bound, g.batch, a.balance, a.steps_per_split, slot, lane);
+      const Share sh = balanced_share<NW, BK + BV <= 8 ? kDealParts : 2 * kDealParts>(a.seq_lens, a.lens_offset, a.lens_bound, g.batch, a.balance, a.n_splits, a.steps_per_split, a.deal_pays, slot, lane);
       if (sh.b < 0) return;                        // more workgroups than parts
       b = sh.b; split = sh.split; steps_per_split = sh.q; n_rec = sh.count; slot0 = sh.slot0;
       seq_len = sh.len; have_len = true;
@@ -2025,13 +2025,13 @@ DecodePlan plan_coarse(const Geom& g, int32_t seq_len) {
   // nothing flushed yet: a launch of their own).
   const int unit = g.axis_k == KVQ_AXIS_SEQ ? 2 : 1;
   const int n_steps = plan_steps(g, seq_len);
-  if (n_steps == 0) return DecodePlan{0, 0, 4, 0};
+  if (n_steps == 0) return DecodePlan{0, 0, 4};
   const WaveBudget wb = wave_budget(g, n_steps, false);
   const int nw = wb.nw;
   int sps = (n_steps + wb.splits - 1) / wb.splits;
   sps = (sps + nw * unit - 1) / (nw * unit) * (nw * unit);
   const int splits = (n_steps + sps - 1) / sps;
-  return DecodePlan{splits, sps, nw, 0};
+  return DecodePlan{splits, sps, nw};
 }
 
 // Sequences without a residual buffer (whose plan takes whole blocks as it is) are cut with their parts' size in view.  n8: steps per
@@ -2097,22 +2097,41 @@ int fine_most(const Geom& g, bool bound) {
 }
 }  // namespace
 
-// Sequences of different lengths: a launch deals its workgroups of nw wavefronts out by the lengths (balanced_share) where a part planned
-// for the longest has at least 6 steps per wavefront (of more than two parts: 12); with less, looking at all the lengths first outweighs
-// it.  Both ways in turn, K4V2, 16 sequences of 8 kv heads, dealt out (and not): lengths even between 512 and 8192 tokens 19.9 us
-// (22.8), 1024 and 16384 30.8 (35.9), 250 and 4000 14.5 (15.3), half of them 8192 and half 1024 19.9 (22.4); equal lengths 26.3 (26.2) and
-// 49.1 (49.0).  With eight splits it loses (4 sequences up to 8000: 14.4 against 12.3).
-// How many: as many as fill the chip, where the plan takes more than half of it; sequences of one part each, 129 to 255 and 257 to 511 streams,
-// leave some over for the longest.  Where the plan takes less (few, short sequences), its own number.
+// Sequences of different lengths: a launch may deal its workgroups of nw wavefronts out by the lengths (balanced_share).  How many: as
+// many as fill the chip, where the plan takes more than half of it; sequences of one part each, 129 to 255 and 257 to 511 streams, leave
+// some over for the longest.  Where the plan takes less (few, short sequences), its own number.
+// Which plans: parts of at least 6 steps per wavefront (of more than two parts: 12; with eight it loses, 4 sequences up to 8000 tokens: 14.4
+// us against 12.3), sequences of one part from deal_line1 on.  With less, looking at all the lengths first outweighs it.
 namespace {
-bool deals(const Geom& g, int nw, int steps_per_split) { return !g.resid && g.batch >= 2 && g.batch <= 64 && steps_per_split >= 6 * nw; }
+// The steps that a dealt-out part has to save to pay, and the lines, are drawn on rows of up to 8 bits (codes of key and value); a step of wider
+// rows takes longer, in proportion.
+int by_width(const Geom& g, int steps) { const int bits = g.bits_k + g.bits_v; return bits > 8 ? (8 * steps + bits - 1) / bits : steps; }
+int deal_line1(const Geom& g, int nw) { return by_width(g, nw == 8 ? 80 : 56); }
+bool deals(const Geom& g, const DecodePlan& p) {
+  if (g.resid || g.batch < 2 || g.batch > 64 || p.n_splits < 1 || p.n_splits > 4) return false;
+  return p.steps_per_split >= (p.n_splits == 1 ? deal_line1(g, p.waves_per_wg) : (p.n_splits == 2 ? 6 : 12) * p.waves_per_wg);
+}
+// The longest part that pays.  Sequences of one part have no records yet: the search, the records and their merge are 2 to 3 us, six steps of
+// eight wavefronts (ten of four, two workgroups of which share a unit), and a quarter of the part at least (an eighth), because the workgroups that
+// come on top share the memory.  Sequences of several parts merge in any case: two steps, and 3/16.
+// K4V2, 4 query heads, in turn with nothing dealt out.  One part, steps per wavefront planned and dealt out: 17 x 8 heads x 3500 tokens, lengths even
+// from 0.65 of it on, 14 -> 10: 15.2 us for 13.8, from 0.5 on, 14 -> 8: 13.2 for 13.8, from 0.05 on, 14 -> 6: 11.7 for 13.7; 24 x 8 x 8000, 32 -> 28: 31.4
+// for 30.1, 32 -> 23: 26.1 for 27.0; four wavefronts, 40 x 8 x 2500, 20 -> 11: 4 % slower, 20 -> 8: 9 % faster; K8V8 from three steps (five) on.
+// Several parts, against the plan's own number dealt out: 11 x 8 x 3500, 7 -> 7: 12.8 for 11.6, 7 -> 6: 12.2; 7 x 8 x 16000, 16 -> 14: 21.8 for
+// 21.0; 11 x 8 x 8000, 16 -> 9: 14.5 for 18.7.
+int deal_most(const Geom& g, const DecodePlan& p) {
+  const int nw = p.waves_per_wg, q = p.steps_per_split;
+  const int steps = by_width(g, p.n_splits == 1 ? (nw == 8 ? 48 : 40) : 2 * nw), share = by_width(g, p.n_splits > 1 ? q * 3 / 16 : nw == 8 ? q / 4 : q / 8);
+  return (q - (steps > share ? steps : share)) / nw * nw;
+}
 int full_slots(const Geom& g, int nw) { return device_compute_units() * 4 * KVQ_WAVES_PER_SIMD / nw / g.kv_heads; }
 int deal_records(const Geom& g, int slots) { return (slots + g.batch - 1) / g.batch; }      // of the workspace, per (batch, kv head)
-// No plan of more than half the chip in up to 4 parts a sequence, for lengths up to n_steps, takes more.  (The plan rounds a part up to whole
-// wavefronts before it asks whether it is long enough, and so does this.)
+// No plan of more than half the chip in up to 4 parts a sequence, for lengths up to n_steps, takes more.  (A part is rounded up to whole
+// wavefronts before it is held against the line, and so is the length here.)
 int deal_bound(const Geom& g, int n_steps) {
   const int streams = g.batch * g.kv_heads, nw = streams <= device_compute_units() ? 8 : 4;
-  if (!deals(g, nw, (n_steps + nw - 1) / nw * nw) || 8 * streams <= device_compute_units()) return 1;
+  const int line = deal_line1(g, nw) < 6 * nw ? deal_line1(g, nw) : 6 * nw;
+  if (g.resid || g.batch < 2 || g.batch > 64 || (n_steps + nw - 1) / nw * nw < line || 8 * streams <= device_compute_units()) return 1;
   const int records = deal_records(g, full_slots(g, nw));
   return records < 8 ? records : 8;
 }
@@ -2145,13 +2164,13 @@ static DecodePlan plan_parts(const Geom& g, int32_t seq_len, int heads, int64_t 
   if (f.splits == 0 || (f.splits > 1 && f.splits > room)) return plan_coarse(g, seq_len);
   // (fewer than 8 steps and one or two heads: four wavefronts have less to merge.  7 steps, 4 and 8 wavefronts, 1 head 5.02 and 5.10 us,
   // 2 heads 5.10 and 5.20, 3 heads 5.56 and 5.14, 8 heads 6.62 and 6.23; 8 steps, 1 head 5.63 and 5.29, 8 heads 7.26 and 6.45)
-  return DecodePlan{f.splits, 8 * f.steps, n_steps < 8 && heads < 3 ? 4 : 8, 0};
+  return DecodePlan{f.splits, 8 * f.steps, n_steps < 8 && heads < 3 ? 4 : 8};
 }
 
 DecodePlan plan_decode(const Geom& g, int32_t seq_len, int heads, int64_t room, bool ragged) {
   DecodePlan p = plan_parts(g, seq_len, heads, room);
-  if (!ragged || p.n_splits < 1 || p.n_splits > 4 || !deals(g, p.waves_per_wg, p.steps_per_split)) return p;
-  if (p.n_splits > 2 && p.steps_per_split < 12 * p.waves_per_wg) return p;
+  if (!ragged || !deals(g, p)) return p;
+  p.deal_pays = deal_most(g, p);
   const int own = p.n_splits * g.batch, full = full_slots(g, p.waves_per_wg);
   if (full > own && full < 2 * own && deal_records(g, full) <= room) p.slots = full;
   else if (p.n_splits > 1) p.slots = own;
@@ -2249,7 +2268,7 @@ hipError_t launch_decode_attention(const Geom& g, const kvq_cache& c, const void
       t.seq_len = tail; t.n_splits = 1; t.steps_per_split = 4; t.lens_mode = 2;
       t.rec_splits = records; t.rec_base = records - 1;
       if (tail_merges) { t.rec_splits = 1; t.rec_base = 0; t.extra_splits = records; }
-      e = launch_decode_inst_16_16(R, t, DecodePlan{1, 4, 4, 0}, stream);
+      e = launch_decode_inst_16_16(R, t, DecodePlan{1, 4, 4}, stream);
       if (e != hipSuccess) return e;
     }
     if (records > 1 && !(n_flushed && !tail) && !tail_merges) {     // (a launch that wrote all the records has merged them itself)
@@ -2259,7 +2278,7 @@ hipError_t launch_decode_attention(const Geom& g, const kvq_cache& c, const void
     return e;
   }
   a.lens_mode = 0; a.lens_bound = seq_len; a.lens_block = 1;
-  a.balance = plan.slots;
+  a.balance = plan.slots; a.deal_pays = plan.deal_pays;
   if (a.balance) a.rec_splits = deal_records(g, plan.slots);
   a.merge_tag = a.balance ? next_merge_tag()
                           : merge_tag_for(a.rec_splits, !app && a.heads_per_kv > kAloneHeads ? kMergeHereMostAlone : kMergeHereMost);

@@ -78,7 +78,8 @@ struct DecodePlan {
   int32_t n_splits;         // workgroups per (b, h_kv)
   int32_t steps_per_split;  // 32-token steps each workgroup walks (a multiple of waves_per_wg)
   int32_t waves_per_wg;     // 4 or 8 wavefronts per workgroup
-  int32_t slots;            // != 0: sequences of different lengths; this many workgroups per kv head are dealt out by the lengths
+  int32_t slots = 0;        // != 0: sequences of different lengths; this many workgroups per kv head are dealt out by the lengths
+  int32_t deal_pays = 0;    // ... in parts of at most so many steps; where they do not suffice for that, the parts stay as planned
 };
 
 // The single new token of a fused decode step: [B][H_kv][D] rows with element strides.
@@ -107,7 +108,7 @@ struct DecodeArgs {
   int32_t buf_len;            // channel-wise keys: tokens in the residual buffer (uniform lengths; the new one of a fused step counts)
   // != 0 (with seq_lens): this many workgroups per kv head are dealt out to the sequences by their lengths, instead of n_splits to
   // each; workgroup w of a kv head writes the records of slot w
-  int32_t balance;
+  int32_t balance, deal_pays;   // (deal_pays: the longest part that is dealt out, see DecodePlan)
   float* ws; void* out; int out_dtype;
   int32_t n_splits, steps_per_split;
   // partial records: a workgroup writes record rec_base + split of rec_splits per (batch, query head); rec_splits == 1

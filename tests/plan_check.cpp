@@ -46,6 +46,8 @@ void check(kvq_layout L, const std::vector<int>& lengths) {
           if (records(g, p) > 1 && records(g, p) > have) fault(ragged ? "ragged, beyond the workspace" : "beyond the workspace", g, heads, len, records(g, p), have);
           if (have == full && !same(p, any)) fault(ragged ? "ragged, not the full plan" : "not the full plan", g, heads, len, records(g, p), records(g, any));
           if (p.n_splits && (long)p.n_splits * p.steps_per_split < n_steps) fault("steps left out", g, heads, len, (long)p.n_splits * p.steps_per_split, n_steps);
+          if (p.slots && (p.deal_pays < p.waves_per_wg || p.deal_pays % p.waves_per_wg || 8 * p.deal_pays < p.steps_per_split || p.deal_pays >= p.steps_per_split))
+            fault("a part that cannot pay", g, heads, len, p.deal_pays, p.steps_per_split);
           if (p.slots && p.slots < p.n_splits * g.batch) fault("fewer workgroups than parts", g, heads, len, p.slots, p.n_splits * g.batch);
         }
       }

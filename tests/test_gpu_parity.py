@@ -2449,14 +2449,16 @@ def test_ragged_batch_dealt_out_by_its_lengths(kvq, B, H, R, bk, bv, page, rotv,
     assert float(err.max()) < 2e-3, float(err.max())
 
 
-@pytest.mark.parametrize("B,H,R,bk,bv,page", [(9, 8, 4, 4, 2, 0), (11, 8, 2, 4, 4, 64), (18, 8, 1, 4, 2, 0), (28, 4, 7, 2, 4, 0), (30, 8, 4, 4, 2, 256),
-                                              (33, 8, 4, 4, 2, 0), (37, 8, 8, 8, 2, 64)])
-def test_workgroups_that_fill_the_chip_dealt_out_by_lengths(kvq, B, H, R, bk, bv, page):
+@pytest.mark.parametrize("B,H,R,bk,bv,page,T,splits,slots", [(9, 8, 4, 4, 2, 0, 12000, 3, 32), (11, 8, 2, 4, 4, 64, 6000, 2, 32), (28, 4, 7, 2, 4, 0, 4000, 2, 64),
+                                                             (7, 8, 4, 8, 8, 0, 12000, 4, 32), (18, 8, 1, 4, 2, 0, 2700, 1, 32), (30, 8, 4, 4, 2, 256, 2700, 1, 32),
+                                                             (33, 8, 4, 4, 2, 0, 1790, 1, 64), (37, 8, 8, 8, 8, 64, 1300, 1, 64)])
+def test_workgroups_that_fill_the_chip_dealt_out_by_lengths(kvq, B, H, R, bk, bv, page, T, splits, slots):
     """Stream counts that do not divide the chip, one or several parts a sequence (on 256 compute units): with the reported workspace
     the workgroups left over go to the longest sequences.  Against attention over each sequence on its own; with the least workspace a
-    call takes (none from 129 streams that are not split up), which deals out the plan's own number or none, too.  Uniform
-    lengths of the same counts, which the plan cuts so that they fit the chip in one round."""
-    D, scale, T = 128, 1 / math.sqrt(128), 1700
+    call takes (none from 129 streams that are not split up), which deals out the plan's own number or none, too; and the fused step.
+    Which route ran shows in the counters behind the records (ceil(slots / B) of them a query head, or the plan's own): a sequence of one
+    part counts nothing.  One long sequence among short ones is dealt out, equal lengths stay as planned."""
+    D, scale = 128, 1 / math.sqrt(128)
     kw = dict(page_tokens=page, n_pages=B * -(-T // page) + 1) if page else {}
     L = kvq.Layout(B, H, T, D, bk, bv, 64, 64, raw_dtype=kvq.KVQ_BF16, **kw)
     one = replace(L, batch=1)
@@ -2465,15 +2467,18 @@ def test_workgroups_that_fill_the_chip_dealt_out_by_lengths(kvq, B, H, R, bk, bv
     if page:
         cache.page_table = torch.randperm(L.n_pages, device="cuda")[:L.n_pages - 1].to(torch.int32).view(B, -1).contiguous()
     kvq.quantize_append(L, cache, K, V, 0)
+    record, counters = B * H * R * 132 * 4, (B * H * 8 + 15) // 16 * 16
     need = kvq.decode_workspace_bytes(L, H * R, T)
-    assert need > 0
+    full, coarse = -(-slots // B), max(1, -(-2048 // (B * H)) // 8)        # records: all dealt out; the plan that rounds up
+    least = coarse * record + counters if coarse > 1 else 0
+    assert full > splits and need >= full * record + counters and least <= need
     rng = np.random.RandomState(B)
-    cases = [np.full(B, T), np.r_[T, np.ones(B - 1)], rng.randint(1, T + 1, B), np.linspace(60, T, B).astype(int), np.r_[T, T - 1, np.full(B - 2, T // 3)]]
+    few, equal = np.r_[T, np.ones(B - 1)], np.full(B, T)
+    cases = [equal, few, rng.randint(1, T + 1, B), np.linspace(60, T, B).astype(int), np.r_[T, T - 1, np.full(B - 2, T // 3)]]
     alone = torch.empty(B, H * R, D, dtype=torch.float32, device="cuda")
     ws1 = torch.empty(max(16, kvq.decode_workspace_bytes(one, H * R, T)), dtype=torch.uint8, device="cuda")
-    least = 0 if B * H > 146 else need                       # (88 and 72 streams: the plan's parts need records of their own)
-    for lens in cases:
-        dev = torch.tensor(lens.astype(np.int64), device="cuda").to(torch.int32)
+
+    def each(lens, out):
         for b in range(B):
             if page:
                 sub = kvq.Cache.__new__(kvq.Cache)
@@ -2481,22 +2486,40 @@ def test_workgroups_that_fill_the_chip_dealt_out_by_lengths(kvq, B, H, R, bk, bv
                 sub.page_table = cache.page_table[b:b + 1].contiguous()
             else:
                 sub = cache.batch_element(b, one)
-            kvq.decode_attention(one, sub, q[b:b + 1].contiguous(), int(lens[b]), scale, alone[b:b + 1], ws1)
-        for size in {need, least}:
-            ws = torch.full((size + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
-            got = [kvq.decode_attention_varlen(L, cache, q, dev, T, scale, torch.empty(B, H * R, D, dtype=torch.float32, device="cuda"),
-                                               ws[:size] if size else None) for _ in range(2)]
-            assert torch.equal(got[0], got[1]) and ws[size:].eq(0xFF).all()
-            err = (got[0] - alone).abs().amax(-1) / alone.abs().amax(-1)
-            assert float(err.max()) < 2e-3, (lens, size, float(err.max()))
-    got = kvq.decode_attention(L, cache, q, T, scale, torch.empty(B, H * R, D, dtype=torch.float32, device="cuda"),
-                               torch.full((need,), 0x5A, dtype=torch.uint8, device="cuda"))
-    for b in range(B):
-        sub = cache.batch_element(b, one) if not page else None
-        if sub is not None:
-            kvq.decode_attention(one, sub, q[b:b + 1].contiguous(), T, scale, alone[b:b + 1], ws1)
-    if not page:
-        assert float(((got - alone).abs().amax(-1) / alone.abs().amax(-1)).max()) < 2e-3
+            kvq.decode_attention(one, sub, q[b:b + 1].contiguous(), int(lens[b]), scale, out[b:b + 1], ws1)
+        return out
+
+    def off(got, lens, *what):
+        err = float(((got - alone).abs().amax(-1) / alone.abs().amax(-1)).max())
+        assert err < 2e-3, (lens, *what, err)
+
+    for lens in cases:
+        dev = torch.tensor(lens.astype(np.int64), device="cuda").to(torch.int32)
+        each(lens, alone)
+        for size, records in ((need, full), (least, full if coarse >= full else splits)):
+            for fill in (0xFF, 0):
+                ws = torch.full((size + 4096,), fill, dtype=torch.uint8, device="cuda")
+                got = [kvq.decode_attention_varlen(L, cache, q, dev, T, scale, torch.empty(B, H * R, D, dtype=torch.float32, device="cuda"),
+                                                   ws[:size] if size else None) for _ in range(2)]
+                assert torch.equal(got[0], got[1]) and ws[size:].eq(fill).all()
+                off(got[0], lens, size, fill)
+            if size and (lens is few or lens is equal):     # (the last workspace was clear)
+                words = _counters(ws, B, H, H * R, records).view(B, H)
+                counted = lens is few or splits > 1
+                assert words[0].ne(0).all() == counted and words[1:].ne(0).all() == (lens is equal and splits > 1), (lens, size)
+                assert lens is equal or words[1:].eq(0).all()
+        at = (dev.long() - 1).view(-1, 1, 1, 1).expand(-1, H, 1, D)       # the fused step stores the tokens that are there
+        before = [p.clone() for p in cache.planes[:4]]
+        got = kvq.decode_step_varlen(L, cache, K.gather(2, at)[:, :, 0].contiguous(), V.gather(2, at)[:, :, 0].contiguous(), dev - 1, T - 1, q, scale,
+                                     torch.empty(B, H * R, D, dtype=torch.float32, device="cuda"), torch.full((need,), 0x5A, dtype=torch.uint8, device="cuda"))
+        off(got, lens, "fused")
+        assert all(torch.equal(x, y) for x, y in zip(before, cache.planes[:4]))
+    if least:
+        with pytest.raises(kvq.KvqError):
+            kvq.decode_attention_varlen(L, cache, q, dev, T, scale, got, torch.empty(least - 16, dtype=torch.uint8, device="cuda"))
+    each(equal, alone)                                       # uniform lengths, which the plan cuts so that they fit the chip in one round
+    off(kvq.decode_attention(L, cache, q, T, scale, torch.empty(B, H * R, D, dtype=torch.float32, device="cuda"),
+                             torch.full((need,), 0x5A, dtype=torch.uint8, device="cuda")), equal, "uniform")
 
 
 def test_ragged_batch_replayed_from_a_hip_graph(kvq):

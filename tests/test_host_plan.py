@@ -37,3 +37,12 @@ def test_plans_stay_inside_the_workspace_and_reach_the_whole_of_it(check):
     r = check()
     assert r.returncode == 0, r.stdout + r.stderr
     assert int(r.stdout.split("plans=")[1].split()[0]) > 1000000
+
+
+@pytest.mark.parametrize("batch,heads,bits_k,bits_v,tokens,want", [(18, 4, 4, 2, 1400, (1, 48, 8, 0)), (18, 4, 4, 2, 2528, (1, 80, 8, 32)), (18, 4, 4, 2, 2304, (1, 72, 8, 0)),
+                                                                   (33, 4, 4, 2, 1665, (1, 56, 4, 64)), (33, 4, 4, 2, 1664, (1, 52, 4, 0)),
+                                                                   (18, 4, 8, 8, 1281, (1, 48, 8, 32)), (18, 4, 8, 8, 1024, (1, 32, 8, 0)),
+                                                                   (11, 4, 4, 2, 3500, (2, 56, 8, 32)), (9, 4, 4, 2, 12000, (3, 128, 8, 32))])
+def test_which_ragged_batches_may_be_dealt_out(check, batch, heads, bits_k, bits_v, tokens, want):
+    """Sequences of one part: from ten steps per wavefront on (fourteen of four), half as many of rows twice as wide."""
+    assert _plan(check, batch, 8, heads, bits_k, bits_v, tokens, "ragged") == want
