@@ -38,7 +38,8 @@ def _scratch_allowed(kernel_name: str) -> int:
 # (source, object name, extra flags).  The quantizer must round every operation once: no contraction.
 UNITS = [("kvq_api.hip", "kvq_api.o", []),
          ("kvq_quant.hip", "kvq_quant.o", ["-ffp-contract=off"]),
-         ("kvq_seq_append.hip", "kvq_seq_append.o", ["-ffp-contract=off"]),
+         ("kvq_seq_append.hip", "kvq_seq_append.o", ["-ffp-contract=off"]),      # (value patterns one at a time, and the launchers)
+         ("kvq_seq_append.hip", "kvq_seq_append_quads.o", ["-ffp-contract=off", "-DKVQ_SA_QUADS"]),      # (four at a time)
          ("kvq_readback.hip", "kvq_readback.o", ["-ffp-contract=off"]),
          ("kvq_decode.hip", "kvq_decode.o", [])]
 UNITS += [("kvq_decode.hip", f"kvq_decode_k{bk}v{bv}.o",

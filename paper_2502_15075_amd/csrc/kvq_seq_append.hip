@@ -4,6 +4,14 @@
 // file too is compiled with floating-point contraction off.
 #include "kvq_stage.h"
 
+// Compiled twice: with KVQ_SA_QUADS the kernels that store value patterns four tokens at a time, without it those that store
+// them one by one, and the launchers.
+#ifdef KVQ_SA_QUADS
+#define KVQ_QUADS true
+#else
+#define KVQ_QUADS false
+#endif
+
 namespace kvq {
 namespace {
 
@@ -66,6 +74,7 @@ __device__ __forceinline__ void store_value_quads(uint8_t* block, int j, int lan
 // launcher makes sure that no other workgroup of the same launch writes there), keys are quantized channel by channel
 // (a group is g.seq_g = 32, 64 or 128 consecutive tokens of one channel, RLT / g.seq_g groups per channel and block),
 // values token-wise exactly as in quantize_append_kernel.
+// QUADS: value patterns go to the buffer four tokens at a time where four stay (store_value_quads), the others one by one.
 // KTOK: the keys of a flushed block are quantized row by row like the values (a residual buffer in front of token-wise
 // keys); otherwise channel by channel.
 // What bounds it: vector instructions (with rotated keys about 1300 per thread and 64-token block) and memory in about equal
@@ -74,7 +83,7 @@ __device__ __forceinline__ void store_value_quads(uint8_t* block, int j, int lan
 // K4V2: with rotated keys 111 us before and 78 us now (4.2 TB/s), without 81 and 64 us.  (Several blocks per workgroup with
 // the next one's rows loaded ahead, which pays in quantize_append_kernel, costs this one its occupancy: 210 registers,
 // 115 us with rotated keys at 2 wavefronts per unit's SIMD, 126 at 3.)
-template <int BK, int BV, bool BF, bool KTOK, int RLT, bool STREAM_IN>
+template <int BK, int BV, bool BF, bool KTOK, int RLT, bool STREAM_IN, bool QUADS>
 __global__ __launch_bounds__(256) void seq_append_kernel(Geom g, kvq_cache c, const uint16_t* __restrict__ k_new,
                                                          const uint16_t* __restrict__ v_new, int64_t sb, int64_t sh,
                                                          int64_t st, int32_t pos, int32_t n_new,
@@ -93,9 +102,11 @@ __global__ __launch_bounds__(256) void seq_append_kernel(Geom g, kvq_cache c, co
   // sequences: they begin at another one each there (43 x 8 heads x 2036 tokens 89.7 us without, 83.0; 128-token buffers, 10 x 8 x 1937, 31.9
   // and 26.5).  Elsewhere the parts share them anyway, and the order costs (8 x 8 x 8229 61.9 and 64.3).
   int turn = blockIdx.x;
-  if ((gridDim.x & 7) == 0) {                              // (uniform)
-    turn += blockIdx.y & 7;
-    if (turn >= (int)gridDim.x) turn -= gridDim.x;
+  if constexpr (QUADS) {
+    if ((gridDim.x & 7) == 0) {                            // (uniform)
+      turn += blockIdx.y & 7;
+      if (turn >= (int)gridDim.x) turn -= gridDim.x;
+    }
   }
   const int blk = pos / RLT + turn;
   const int lo = max(pos, blk * RLT) - blk * RLT;
@@ -123,14 +134,13 @@ __global__ __launch_bounds__(256) void seq_append_kernel(Geom g, kvq_cache c, co
   // the rows [keep, hi) are the last tokens of this call that land in their slots
   const int keep = max(lo, pos + n_new - RLT - blk * RLT);
   const int quad = 4 * __builtin_amdgcn_readfirstlane(tid >> 6);           // a wavefront's rows: 16 it + quad .. + 3
-  // (few sequences have few requests to save, and the code is 0.3 to 0.5 us in a launch of one round: 3 x 8 heads x 700 tokens 6.9 us
-  // without and 7.4 with it, 2 x 8 x 565 7.1 and 7.4; 11 x 8 x 1921 25.3 and 23.6)
-  const bool quads = gridDim.y >= 64;
-  if (quads && keep < hi) {                                // (uniform)
+  if constexpr (QUADS) {
+    if (keep < hi) {                                       // (uniform)
 #pragma unroll
-    for (int it = 0; it < NIT; it += 2) {
-      const bool full0 = 16 * it + quad >= keep && 16 * it + quad + 4 <= hi, full1 = 16 * it + quad + 16 >= keep && 16 * it + quad + 20 <= hi;
-      if (full0 || full1) store_value_quads(vr + (it >> 1) * (512 * 16), quad >> 2, lane16, rg & 3, vraw[it], vraw[it + 1], full0, full1);
+      for (int it = 0; it < NIT; it += 2) {
+        const bool full0 = 16 * it + quad >= keep && 16 * it + quad + 4 <= hi, full1 = 16 * it + quad + 16 >= keep && 16 * it + quad + 20 <= hi;
+        if (full0 || full1) store_value_quads(vr + (it >> 1) * (512 * 16), quad >> 2, lane16, rg & 3, vraw[it], vraw[it + 1], full0, full1);
+      }
     }
   }
 #pragma unroll
@@ -139,7 +149,7 @@ __global__ __launch_bounds__(256) void seq_append_kernel(Geom g, kvq_cache c, co
     if (row >= lo && row < hi) {
       if (row >= keep) {
         *reinterpret_cast<uint4*>(kr + row * (kHeadDim * 2) + d0 * 2) = kraw[it];
-        if (!quads || 16 * it + quad < keep || 16 * it + quad + 4 > hi) {            // (uniform: a quad at an end of the rows that stay)
+        if (!QUADS || 16 * it + quad < keep || 16 * it + quad + 4 > hi) {            // (uniform: a quad at an end of the rows that stay)
           const uint32_t rw[4] = {vraw[it].x, vraw[it].y, vraw[it].z, vraw[it].w};
           int dw, bit;
           v_field(row & 31, d0, 16, &dw, &bit);
@@ -298,7 +308,7 @@ void launch_sa_in(const Geom& g, const kvq_cache& c, const void* k_new, const vo
                   int64_t st, int32_t pos, int32_t n_new, const int32_t* pos_arr, int32_t max_pos, dim3 grid, hipStream_t stream) {
   const bool bf = in_dtype == KVQ_BF16, ktok = g.axis_k != KVQ_AXIS_SEQ;
 #define KVQ_SA_LAUNCH(BF_, KTOK_, RL_)                                                                                     \
-  hipLaunchKernelGGL((seq_append_kernel<BK, BV, BF_, KTOK_, RL_, STREAM_IN>), grid, dim3(256), 0, stream, g, c,            \
+  hipLaunchKernelGGL((seq_append_kernel<BK, BV, BF_, KTOK_, RL_, STREAM_IN, KVQ_QUADS>), grid, dim3(256), 0, stream, g, c,            \
                      (const uint16_t*)k_new, (const uint16_t*)v_new, sb, sh, st, pos, n_new, pos_arr, max_pos)
   if (ktok) { if (bf) KVQ_SA_LAUNCH(true, true, 64); else KVQ_SA_LAUNCH(false, true, 64); }
   else if (g.resid == 128) { if (bf) KVQ_SA_LAUNCH(true, false, 128); else KVQ_SA_LAUNCH(false, false, 128); }
@@ -344,6 +354,33 @@ hipError_t launch_sa_bits(const Geom& g, const kvq_cache& c, const void* k_new, 
 }
 }  // namespace
 
+#ifdef KVQ_SA_QUADS
+hipError_t launch_sa_quads(const Geom& g, const kvq_cache& c, const void* k_new, const void* v_new, int in_dtype, int64_t sb, int64_t sh,
+                           int64_t st, int32_t pos, int32_t n_new, hipStream_t stream) {
+  return launch_sa_bits(g, c, k_new, v_new, in_dtype, sb, sh, st, pos, n_new, nullptr, 0, stream);
+}
+#else
+hipError_t launch_sa_quads(const Geom& g, const kvq_cache& c, const void* k_new, const void* v_new, int in_dtype, int64_t sb, int64_t sh,
+                           int64_t st, int32_t pos, int32_t n_new, hipStream_t stream);
+
+// Whether value patterns leave four tokens at a time (store_value_quads): in launches of two workgroups per unit and more always; in
+// smaller ones, which end with the slowest block, where a block that is quantized stores a quarter of the buffer or more as well, and
+// where none is quantized.  With less, the transposition's code costs the launch 0.1 to 0.4 us.  Stored one by one and so, 64-token
+// buffers, 8 kv heads, by sequences x tokens: 2 x 700 (4 tokens in the last quantized block) 6.1 us and 6 % more, 4 x 440 (8) 6.6 and 4 % more, 3 x 565 (11) 6.6
+// and 2 % more, 1 x 1900 (20) 7.0 and 6 % less, 3 x 900 (60) 10.1 and 16 % less, 8 x 60 (none) 5.4 and 42 % less; 512 workgroups and more 0 to 45 % less.
+// Where the blocks of a sequence are a multiple of 8, the last ones of all sequences share a part of the chip, and it pays from 24 of them and
+// more than one workgroup per unit on: 3 x 1012 9.1 us and 10 % less, 5 x 500 9.4 and 12 % less, 2 x 1524 3 % more, 4 x 500 (256 workgroups) 2 % more.
+bool stores_quads(const Geom& g, int32_t pos, int32_t n_new) {
+  const int32_t first = pos / g.resid, end = pos + n_new, tail = end % g.resid;
+  if (n_new < 4) return false;
+  const int64_t streams = g.batch * g.kv_heads, blocks = (end - 1) / g.resid - first + 1;
+  if (blocks * streams >= 2 * device_compute_units()) return true;
+  if (blocks % 8 == 0 && streams >= 24 && blocks * streams > device_compute_units()) return true;
+  const bool quantizes = end / g.resid > first;
+  const int32_t stored = n_new < g.resid - tail ? n_new : g.resid - tail;      // by the last block that is quantized
+  return !quantizes || 4 * stored >= g.resid;
+}
+
 hipError_t launch_seq_append_one(const Geom& g, const kvq_cache& c, const void* k_new, const void* v_new, int in_dtype,
                                  int64_t sb, int64_t sh, const int32_t* pos_arr, int32_t max_pos, hipStream_t stream) {
   return launch_sa_bits(g, c, k_new, v_new, in_dtype, sb, sh, kHeadDim, 0, 1, pos_arr, max_pos, stream);
@@ -363,7 +400,9 @@ hipError_t launch_seq_append(const Geom& g, const kvq_cache& c, const void* k_ne
     return launch_seq_append(g, c, (const uint16_t*)k_new + (int64_t)n1 * st, (const uint16_t*)v_new + (int64_t)n1 * st,
                              in_dtype, sb, sh, st, first_end, n_new - n1, stream);
   }
+  if (stores_quads(g, pos, n_new)) return launch_sa_quads(g, c, k_new, v_new, in_dtype, sb, sh, st, pos, n_new, stream);
   return launch_sa_bits(g, c, k_new, v_new, in_dtype, sb, sh, st, pos, n_new, nullptr, 0, stream);
 }
+#endif
 
 }  // namespace kvq

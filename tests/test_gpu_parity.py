@@ -935,15 +935,19 @@ def _assert_seq_planes_equal(cache, planes):
 
 @pytest.mark.parametrize("axis,gk,rl", [(1, 64, 0), (1, 128, 128), (1, 32, 64), (0, 64, 64)])
 def test_buffered_values_at_the_edges_of_four_tokens(kvq, oracle, axis, gk, rl):
-    """The buffer's value patterns are stored four tokens at a time: calls that begin and end on every remainder of four, inside one
-    16-token tile, across tiles, across 32-token blocks and across flushed blocks, with tokens that a later one of the call replaces."""
-    B, H, cap = 2, 32, 640                                    # (64 sequences and heads: from there on four at a time)
-    slots = rl or gk
+    """The buffer's value patterns are stored four tokens at a time, or one by one where a launch is small and the last block it
+    quantizes keeps little of them: calls that begin and end on every remainder of four, inside one 16-token tile, across tiles, across
+    32-token blocks and across flushed blocks, with tokens that a later one of the call replaces; on both sides of that choice, and in launches
+    of 8 blocks a sequence, whose workgroups begin at another block for every sequence."""
+    B, H = 2, 32
+    slots = rl or gk if axis else 64
+    cap = 8 * slots + 40
     K, V, _ = synth.make_kvq(77 + gk, B, H, H, cap, dtype=torch.bfloat16)
     kw = dict(axis_k=axis, raw_dtype=1, resid_len=rl)
     Lg, Lo = kvq.Layout(B, H, cap, 128, 4, 2, gk, 64, **kw), oracle.Layout(B, H, cap, 128, 4, 2, gk, 64, **kw)
     for a, b in ((0, 3), (1, 4), (2, 9), (3, 16), (5, 23), (4, 20), (12, 37), (15, 60), (slots - 3, slots + 6), (0, slots + 21), (7, 2 * slots + 18),
-                 (0, 4 * slots + 37), (0, 4 * slots - 2)):
+                 (0, 4 * slots + 37), (0, 4 * slots - 2), (0, 3 * slots + slots * 3 // 4), (0, 3 * slots + slots * 3 // 4 + 1), (0, 8 * slots - 2), (0, 8 * slots),
+                 (slots // 2, 8 * slots + 27)):
         cache, planes = _seq_fill_both(kvq, oracle, Lg, Lo, K, V, ([(0, a)] if a else []) + [(a, b)])
         _assert_seq_planes_equal(cache, planes)
 
