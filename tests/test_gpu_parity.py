@@ -306,7 +306,8 @@ def test_attention_ignores_garbage_beyond_seq_len(kvq, oracle):
 @pytest.mark.parametrize("H,R", [(2, 1), (3, 7), (2, 8)])
 def test_unquantized_sequences_in_parts_of_one_step_per_wavefront(kvq, oracle, H, R):
     """Unquantized rows are cut down to one step per wavefront from 14 steps on: lengths on both sides of that, of whole and ragged
-    parts; with the reported workspace and with the least that a call takes (it is then cut as quantized rows are)."""
+    parts; with the reported workspace, with room for all records but one and with the least that a call takes (it is then cut as quantized
+    rows are: parts of two steps per wavefront); with less than that it is refused."""
     B, T = 2, 1300
     K, V, q = synth.make_kvq(41 + R, B, H, H * R, T, dtype=torch.float16)
     Lg, Lo = _layouts(kvq, oracle, B, H, T, 16, 16, 128, 128)
@@ -314,15 +315,20 @@ def test_unquantized_sequences_in_parts_of_one_step_per_wavefront(kvq, oracle, H
     scale, qd = 1 / math.sqrt(128), q.cuda()
     for n in (416, 417, 448, 449, 512, 513, 700, T):
         ref = oracle.decode_attention(Lo, planes, q.numpy(), n, scale)
-        need = kvq.decode_workspace_bytes(Lg, H * R, n)
-        for size in sorted({need, need // 2, 0}, reverse=True):
+        steps, record, counters = -(-n // 32), B * H * R * 132 * 4, (B * H * 8 + 15) // 16 * 16
+        parts, fewest = 1 if steps < 14 else -(-steps // 8), max(1, (steps + 1) // 16)
+        need, least = (records * record + counters if records > 1 else 0 for records in (parts, fewest))
+        assert kvq.decode_workspace_bytes(Lg, H * R, n) == need
+        for size in {need, max(need - record, least), least}:
             out = torch.empty(B, H * R, 128, dtype=torch.float32, device="cuda")
-            try:
-                kvq.decode_attention(Lg, cache, qd, n, scale, out, torch.empty(size // 16 * 16, dtype=torch.uint8, device="cuda") if size else None)
-            except kvq.KvqError as e:
-                assert e.status == kvq.ERR_WORKSPACE and size < need
-                continue
+            ws = torch.full((size + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
+            kvq.decode_attention(Lg, cache, qd, n, scale, out, ws[:size] if size else None)
+            assert ws[size:].eq(0xFF).all()
             assert _rel_err(out.cpu().numpy(), ref) < TOL, (n, size)
+        if least:
+            with pytest.raises(kvq.KvqError) as e:
+                kvq.decode_attention(Lg, cache, qd, n, scale, out, torch.empty(least - 16, dtype=torch.uint8, device="cuda"))
+            assert e.value.status == kvq.ERR_WORKSPACE
 
 
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
