@@ -1062,22 +1062,29 @@ def test_merge_launch_of_many_records(kvq, oracle, T, records):
     assert _rel_err(_decode(kvq, Lg, cache, q, T).cpu().numpy(), ref) < TOL
 
 
-@pytest.mark.parametrize("T,records", [(2000, 4), (2500, 5), (4000, 7), (4620, 9), (8192, 32), (8200, 33), (10000, 40)])
+@pytest.mark.parametrize("T,records", [(416, 1), (500, 2), (700, 3), (1000, 4), (1200, 5), (2000, 8), (2100, 9), (8192, 32), (8200, 33), (10000, 40)])
 def test_infinite_values_survive_every_merge(kvq, T, records):
     """Values of an unquantized cache are whatever they are: an infinite one makes its channel's result infinite, of its sign, wherever the
-    record that holds it stands among the others and whichever way they are merged (in the launch, up to 8 at once, up to 32 per
-    pass); the other channels are what they are without it."""
+    record that holds it stands among the others and whichever way they are merged (up to 4 in the launch, up to 8 at once, up to 32 per
+    pass); the other channels are what they are without it.  How many records there are and whether the launch merged them shows
+    in the workspace: every record's maximum and sum are written, and the counter behind them is if the launch counted."""
     R, D = 4, 128
     K, V, q = synth.make_kvq(T + 1, 1, 1, R, T, D, dtype=torch.float16, sigma_k=0.1)
     L = kvq.Layout(1, 1, T, D, 16, 16, raw_dtype=kvq.KVQ_F16)
-    if records > 1:
-        assert kvq.decode_workspace_bytes(L, R, T) >= records * R * 132 * 4
+    need = kvq.decode_workspace_bytes(L, R, T)
+    assert need == (records * R * 132 * 4 + 16 if records > 1 else 0)
     for token in (0, T // 2, T - 1):
         Vi = V.clone()
         Vi[0, 0, token, 3], Vi[0, 0, token, 70] = float("inf"), float("-inf")
         cache = kvq.Cache(L, fill=0)
         kvq.quantize_append(L, cache, K.cuda(), Vi.cuda(), 0)
-        out = _decode(kvq, L, cache, q, T).cpu()
+        ws = torch.full((need + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
+        ws[max(need - 16, 0):need] = 0
+        out = kvq.decode_attention(L, cache, q.cuda(), T, 1 / math.sqrt(D), torch.empty(q.shape, dtype=torch.float32, device="cuda"), ws[:need] if need else None).cpu()
+        if records > 1:
+            assert not ws[:need - 16].view(torch.float32).view(R, records, 132)[..., 128:130].isnan().any()
+            assert bool(_counters(ws, 1, 1, R, records).ne(0).all()) == (records <= 4)
+        assert ws[need:].eq(0xFF).all()
         assert (out[..., 3] == float("inf")).all() and (out[..., 70] == float("-inf")).all(), token
         want = torch.softmax(q[0].double() @ K[0, 0].double().T / math.sqrt(D), dim=-1) @ V[0, 0].double()
         rest = [d for d in range(D) if d not in (3, 70)]
