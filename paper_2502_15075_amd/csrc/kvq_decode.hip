@@ -2103,25 +2103,34 @@ int fine_most(const Geom& g, bool bound) {
 // Which plans: parts of at least 6 steps per wavefront (of more than two parts: 12; with eight it loses, 4 sequences up to 8000 tokens: 14.4
 // us against 12.3), sequences of one part from deal_line1 on.  With less, looking at all the lengths first outweighs it.
 namespace {
-// The steps that a dealt-out part has to save to pay, and the lines, are drawn on rows of up to 8 bits (codes of key and value); a step of wider
-// rows takes longer, in proportion.
+// The steps that a dealt-out part of eight wavefronts has to save to pay, and the lines, are drawn on rows of up to 8 bits (codes of key and
+// value); a step of wider rows takes longer, in proportion.  (Of four wavefronts it does not: two workgroups share a unit, and what is dealt
+// out on top shares its memory rate.)
 int by_width(const Geom& g, int steps) { const int bits = g.bits_k + g.bits_v; return bits > 8 ? (8 * steps + bits - 1) / bits : steps; }
-int deal_line1(const Geom& g, int nw) { return by_width(g, nw == 8 ? 80 : 56); }
+int deal_line1(const Geom& g, int nw) { return nw == 8 ? by_width(g, 80) : 56; }
 bool deals(const Geom& g, const DecodePlan& p) {
   if (g.resid || g.batch < 2 || g.batch > 64 || p.n_splits < 1 || p.n_splits > 4) return false;
   return p.steps_per_split >= (p.n_splits == 1 ? deal_line1(g, p.waves_per_wg) : (p.n_splits == 2 ? 6 : 12) * p.waves_per_wg);
 }
 // The longest part that pays.  Sequences of one part have no records yet: the search, the records and their merge are 2 to 3 us, six steps of
-// eight wavefronts (ten of four, two workgroups of which share a unit), and a quarter of the part at least (an eighth), because the workgroups that
-// come on top share the memory.  Sequences of several parts merge in any case: two steps, and 3/16.
+// eight wavefronts (ten of four, two workgroups of which share a unit; twelve where there are more than 4 heads to merge), and a quarter of the
+// part at least (an eighth; a third), because the workgroups that come on top share the memory.  Sequences of several parts merge in any case: two
+// steps, and 3/16.
 // K4V2, 4 query heads, in turn with nothing dealt out.  One part, steps per wavefront planned and dealt out: 17 x 8 heads x 3500 tokens, lengths even
 // from 0.65 of it on, 14 -> 10: 15.2 us for 13.8, from 0.5 on, 14 -> 8: 13.2 for 13.8, from 0.05 on, 14 -> 6: 11.7 for 13.7; 24 x 8 x 8000, 32 -> 28: 31.4
-// for 30.1, 32 -> 23: 26.1 for 27.0; four wavefronts, 40 x 8 x 2500, 20 -> 11: 4 % slower, 20 -> 8: 9 % faster; K8V8 from three steps (five) on.
+// for 30.1, 32 -> 23: 26.1 for 27.0; four wavefronts, 40 x 8 x 2500, 20 -> 11: 4 % slower, 20 -> 8: 9 % faster; K8V8 of eight
+// wavefronts from three steps on.  Four wavefronts, 8 query heads: 40 x 8, K4V2 36 -> 25 10 % slower, 36 -> 18 2 % faster, 63 -> 30 18 % faster;
+// K8V8 14 -> 7 4 to 8 % slower, 21 -> 10 4 % slower, 40 -> 19 3 % faster; 48 x 8, 14 -> 9 7 % slower.  4 query heads, K8V8: 40 x 8, 11 -> 6 8 %
+// slower, 21 -> 10 level, 40 -> 28 8 % faster.
 // Several parts, against the plan's own number dealt out: 11 x 8 x 3500, 7 -> 7: 12.8 for 11.6, 7 -> 6: 12.2; 7 x 8 x 16000, 16 -> 14: 21.8 for
 // 21.0; 11 x 8 x 8000, 16 -> 9: 14.5 for 18.7.
-int deal_most(const Geom& g, const DecodePlan& p) {
+int deal_most(const Geom& g, const DecodePlan& p, int heads) {
   const int nw = p.waves_per_wg, q = p.steps_per_split;
-  const int steps = by_width(g, p.n_splits == 1 ? (nw == 8 ? 48 : 40) : 2 * nw), share = by_width(g, p.n_splits > 1 ? q * 3 / 16 : nw == 8 ? q / 4 : q / 8);
+  int steps, share;
+  if (p.n_splits > 1) { steps = by_width(g, 2 * nw); share = by_width(g, q * 3 / 16); }
+  else if (nw == 8) { steps = by_width(g, 48); share = by_width(g, q / 4); }
+  else if (heads <= 4) { steps = 40; share = q / 8; }
+  else { steps = 48; share = q / 3; }
   return (q - (steps > share ? steps : share)) / nw * nw;
 }
 int full_slots(const Geom& g, int nw) { return device_compute_units() * 4 * KVQ_WAVES_PER_SIMD / nw / g.kv_heads; }
@@ -2170,7 +2179,7 @@ static DecodePlan plan_parts(const Geom& g, int32_t seq_len, int heads, int64_t 
 DecodePlan plan_decode(const Geom& g, int32_t seq_len, int heads, int64_t room, bool ragged) {
   DecodePlan p = plan_parts(g, seq_len, heads, room);
   if (!ragged || !deals(g, p)) return p;
-  p.deal_pays = deal_most(g, p);
+  p.deal_pays = deal_most(g, p, heads);
   const int own = p.n_splits * g.batch, full = full_slots(g, p.waves_per_wg);
   if (full > own && full < 2 * own && deal_records(g, full) <= room) p.slots = full;
   else if (p.n_splits > 1) p.slots = own;

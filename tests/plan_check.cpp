@@ -3,7 +3,8 @@
 //   plan_check                                                      every length, batch and head count of a range against the bounds;
 //                                                                   prints a line per fault and the number of plans
 //   plan_check BATCH KV_HEADS HEADS BITS_K BITS_V TOKENS [ragged]   prints parts per sequence, steps per part, wavefronts per
-//                                                                   workgroup and the workgroups that are dealt out
+//                                                                   workgroup, the workgroups that are dealt out and the longest
+//                                                                   part of those that pays
 #include "kvq_internal.h"
 
 #include <cstdio>
@@ -82,6 +83,6 @@ int main(int argc, char** argv) {
   L.bits_k = atoi(argv[4]); L.bits_v = atoi(argv[5]); L.group_k = L.group_v = 64;
   L.axis_k = L.axis_v = KVQ_AXIS_HEAD_DIM;
   const kvq::DecodePlan p = kvq::plan_decode(kvq::make_geom(L), atoi(argv[6]), atoi(argv[3]), 1L << 40, argc > 7);
-  printf("%d %d %d %d\n", p.n_splits, p.steps_per_split, p.waves_per_wg, p.slots);
+  printf("%d %d %d %d %d\n", p.n_splits, p.steps_per_split, p.waves_per_wg, p.slots, p.deal_pays);
   return 0;
 }
