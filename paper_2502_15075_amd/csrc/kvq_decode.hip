@@ -2100,17 +2100,21 @@ int fine_most(const Geom& g, bool bound) {
 // Sequences of different lengths: a launch may deal its workgroups of nw wavefronts out by the lengths (balanced_share).  How many: as
 // many as fill the chip, where the plan takes more than half of it; sequences of one part each, 129 to 255 and 257 to 511 streams, leave
 // some over for the longest.  Where the plan takes less (few, short sequences), its own number.
-// Which plans: parts of at least 6 steps per wavefront (of more than two parts: 12; with eight it loses, 4 sequences up to 8000 tokens: 14.4
-// us against 12.3), sequences of one part from deal_line1 on.  With less, looking at all the lengths first outweighs it.
+// Which plans: two parts of at least 6 steps per wavefront (wide rows: in proportion to their width, 4 at least), more of at least 12 (with
+// eight it loses, 4 sequences up to 8000 tokens: 14.4 us against 12.3), sequences of one part from deal_line1 on.  With less, looking at all the
+// lengths first outweighs it.  Two parts of wide rows, nothing dealt out and so, lengths even from a share of the longest up to it: K8V8, 11 x 8
+// heads x 2200 tokens, 4 query heads, from 0.03 on 15.4 and 11.9 us, from 0.2 on 15.7 and 12.9, from 0.8 on 16.9 and 16.7; of three steps per
+// wavefront, 16 x 8 x 1300, 8 query heads, from 0.03 on 5 % faster and from 0.8 on 5 % slower.
 namespace {
 // The steps that a dealt-out part of eight wavefronts has to save to pay, and the lines, are drawn on rows of up to 8 bits (codes of key and
 // value); a step of wider rows takes longer, in proportion.  (Of four wavefronts it does not: two workgroups share a unit, and what is dealt
 // out on top shares its memory rate.)
 int by_width(const Geom& g, int steps) { const int bits = g.bits_k + g.bits_v; return bits > 8 ? (8 * steps + bits - 1) / bits : steps; }
 int deal_line1(const Geom& g, int nw) { return nw == 8 ? by_width(g, 80) : 56; }
+int deal_line2(const Geom& g, int nw) { return by_width(g, 6 * nw) > 4 * nw ? by_width(g, 6 * nw) : 4 * nw; }
 bool deals(const Geom& g, const DecodePlan& p) {
   if (g.resid || g.batch < 2 || g.batch > 64 || p.n_splits < 1 || p.n_splits > 4) return false;
-  return p.steps_per_split >= (p.n_splits == 1 ? deal_line1(g, p.waves_per_wg) : (p.n_splits == 2 ? 6 : 12) * p.waves_per_wg);
+  return p.steps_per_split >= (p.n_splits == 1 ? deal_line1(g, p.waves_per_wg) : p.n_splits == 2 ? deal_line2(g, p.waves_per_wg) : 12 * p.waves_per_wg);
 }
 // The longest part that pays.  Sequences of one part have no records yet: the search, the records and their merge are 2 to 3 us, six steps of
 // eight wavefronts (ten of four, two workgroups of which share a unit; twelve where there are more than 4 heads to merge), and a quarter of the
@@ -2139,7 +2143,7 @@ int deal_records(const Geom& g, int slots) { return (slots + g.batch - 1) / g.ba
 // wavefronts before it is held against the line, and so is the length here.)
 int deal_bound(const Geom& g, int n_steps) {
   const int streams = g.batch * g.kv_heads, nw = streams <= device_compute_units() ? 8 : 4;
-  const int line = deal_line1(g, nw) < 6 * nw ? deal_line1(g, nw) : 6 * nw;
+  const int line = deal_line1(g, nw) < deal_line2(g, nw) ? deal_line1(g, nw) : deal_line2(g, nw);
   if (g.resid || g.batch < 2 || g.batch > 64 || (n_steps + nw - 1) / nw * nw < line || 8 * streams <= device_compute_units()) return 1;
   const int records = deal_records(g, full_slots(g, nw));
   return records < 8 ? records : 8;

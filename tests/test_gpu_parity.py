@@ -2468,7 +2468,7 @@ def test_ragged_batch_dealt_out_by_its_lengths(kvq, B, H, R, bk, bv, page, rotv,
 
 @pytest.mark.parametrize("B,H,R,bk,bv,page,T,splits,slots", [(9, 8, 4, 4, 2, 0, 12000, 3, 32), (11, 8, 2, 4, 4, 64, 6000, 2, 32), (28, 4, 7, 2, 4, 0, 4000, 2, 64),
                                                              (7, 8, 4, 8, 8, 0, 12000, 4, 32), (18, 8, 1, 4, 2, 0, 2700, 1, 32), (30, 8, 4, 4, 2, 256, 2700, 1, 32),
-                                                             (33, 8, 4, 4, 2, 0, 1790, 1, 64), (37, 8, 8, 8, 8, 64, 2030, 1, 64)])
+                                                             (33, 8, 4, 4, 2, 0, 1790, 1, 64), (37, 8, 8, 8, 8, 64, 2030, 1, 64), (11, 8, 4, 8, 8, 0, 2040, 2, 32)])
 def test_workgroups_that_fill_the_chip_dealt_out_by_lengths(kvq, B, H, R, bk, bv, page, T, splits, slots):
     """Stream counts that do not divide the chip, one or several parts a sequence (on 256 compute units): with the reported workspace
     the workgroups left over go to the longest sequences.  Against attention over each sequence on its own; with the least workspace a

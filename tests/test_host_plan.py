@@ -43,9 +43,11 @@ def test_plans_stay_inside_the_workspace_and_reach_the_whole_of_it(check):
                                                                    (33, 4, 4, 2, 1665, (1, 56, 4, 64)), (33, 4, 4, 2, 1664, (1, 52, 4, 0)),
                                                                    (18, 4, 8, 8, 1281, (1, 48, 8, 32)), (18, 4, 8, 8, 1024, (1, 32, 8, 0)),
                                                                    (11, 4, 4, 2, 3500, (2, 56, 8, 32)), (9, 4, 4, 2, 12000, (3, 128, 8, 32)),
+                                                                   (11, 4, 8, 8, 2048, (2, 32, 8, 32)), (11, 4, 8, 8, 1536, (2, 24, 8, 0)), (11, 4, 8, 4, 1537, (2, 32, 8, 32)),
                                                                    (40, 4, 8, 8, 1665, (1, 56, 4, 64)), (40, 4, 8, 8, 1664, (1, 52, 4, 0))])
 def test_which_ragged_batches_may_be_dealt_out(check, batch, heads, bits_k, bits_v, tokens, want):
-    """Sequences of one part: from ten steps per wavefront on (fourteen of four), half as many of rows twice as wide (not of four)."""
+    """Sequences of one part: from ten steps per wavefront on (fourteen of four), half as many of rows twice as wide (not of four); of two
+    parts from six steps on, of wide rows four."""
     assert _plan(check, batch, 8, heads, bits_k, bits_v, tokens, "ragged")[:4] == want
 
 
