@@ -290,7 +290,7 @@ template <int BV> __device__ __forceinline__ u32x4 unpack_v(const uint32_t* w, i
 #define KVQ_STAGES 2           // 32-token steps resident or in flight per wavefront (register ring)
 #endif
 #ifndef KVQ_WAVES_PER_SIMD
-#define KVQ_WAVES_PER_SIMD 2   // occupancy the register allocation is held to
+#define KVQ_WAVES_PER_SIMD 2   // what the register allocation leaves room for at least, and the plan counts on
 #endif
 
 // Ring depth per instantiation: two steps, one where the registers of a step (2 b_K + 2 b_V + 4 per lane) leave no room for a second.
@@ -1467,13 +1467,15 @@ __global__ __launch_bounds__(64 * NW, KVQ_WAVES_PER_SIMD) void decode_kernel(con
   // Two wavefronts share a SIMD (w and w + 4 of a workgroup of 8; of 4, two workgroups), and at equal priority it serves the
   // older one first: wavefronts 0-3 of the 70B layer's step were done after 103 us and 4-7 after 136, those of 8 x 8 heads x 8192
   // tokens after 9.0 and 12.3, and what a wavefront walks alone comes at half the rate.  So whoever is behind goes first.  Short
-  // walks give their turns (kStages steps) falling priorities; from 4 turns on a wavefront notes each turn in LDS and goes
+  // walks give their turns (kStages steps) falling priorities; from 4 turns on (8 steps, 12 of a ring of three) a wavefront notes each turn in LDS and goes
   // last where its partner has not come as far (a stale or early look costs a turn at the wrong priority, nothing else); a
-  // workgroup of 4 does not know its partner and takes a priority per quarter of its walk.  In turn, K4V2, before and with it:
+  // workgroup of 4 does not know its partner and takes a priority per quarter of its walk.  In turn, K4V2, turns of four steps, before and with it:
   // 70B step 148.3 and 143.3 us, 8 x 8 heads x 32768 tokens 47.7 and 44.4, x 16384 26.1 and 25.3, x 8192 17.1 and 16.7, 32 x 8 x 8 heads x
   // 4096 tokens 25.9 and 24.9, 40 x 8 x 8 heads x 2000 tokens 22.2 and 21.3.  (Falling quarters for all 145.6, 45.6, 25.4, 16.8, 24.9; by the partner
   // for all 143.6, 44.3, 25.3, 17.3, 25.1; steps drawn from a counter in LDS 146.1, 44.2, 25.9, 17.4, 25.8: a wavefront draws
-  // a ring ahead of what it computes, so the last steps still meet at the slow ones.)
+  // a ring ahead of what it computes, so the last steps still meet at the slow ones.)  By the partner from 8 steps on and only from 16, turns of two
+  // steps, 56 fused steps of K4V2 and K4V4, 4 and 8 query heads, 1 to 32 sequences: 0.2 % slower in the mean from 16, 32 x 8 heads x 3600 tokens
+  // 21.0 and 21.4 us (8 query heads 22.0 and 22.3), 16 x 8 x 4096 14.7 and 14.5.
   // Not where memory alone binds: the sum of the widths, and 8-bit keys with values of one run (K8V8, 8 x 8 heads x 32768 tokens: 85.5 us
   // before, 86.6 with it).  Equal priorities and these, 32 x 8 x 8 heads, in turn, means over eight placements of the planes (a call's time
   // differs by up to 8 % between them, above all where sequences lie powers of two apart): K8V2 x 24576 tokens 185.9 and 192.5,
@@ -1994,6 +1996,8 @@ namespace {
 // records, which callers have sized workspaces by, rounds up as the plan once did.  Rounded up and down, K4V2: 11 x 8 heads x 6000
 // tokens (88 streams in 3 and 2 parts) 21.5 and 14.4 us, x 16000 43.0 and 29.1; 17 x 8 x 6000 (2 parts and 1) 28.5 and 20.6; 33 x 8
 // (one workgroup of 8 wavefronts and of 4, two of which share a unit) x 700 11.7 and 9.3, x 6000 45.0 and 38.4.
+// Two wavefronts per SIMD are counted for every instance.  Token-wise K4V2 of one column set needs 144 to 167 registers, which leave room for a
+// third (channel-wise and two-set ones mostly need more); no plan by three has been measured.
 struct WaveBudget { int waves, nw, splits; };
 WaveBudget wave_budget(const Geom& g, int n_steps, bool bound) {
   const int streams = g.batch * g.kv_heads;

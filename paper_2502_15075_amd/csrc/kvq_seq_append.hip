@@ -100,7 +100,9 @@ __global__ __launch_bounds__(256) void seq_append_kernel(Geom g, kvq_cache c, co
   if (pos_arr) pos = min(max(pos_arr[b], 0), max_pos);     // one token per sequence at its own position (n_new == 1)
   // Where the blocks of a sequence are a multiple of 8, its last two, which fill the buffer, would fall to the same part of the chip for all
   // sequences: they begin at another one each there (43 x 8 heads x 2036 tokens 89.7 us without, 83.0; 128-token buffers, 10 x 8 x 1937, 31.9
-  // and 26.5).  Elsewhere the parts share them anyway, and the order costs (8 x 8 x 8229 61.9 and 64.3).
+  // and 26.5).  With 8, 16, 32, 64, 128, 256 and 512 blocks, without and with it, 8 kv heads: 32 x 500 tokens 25.2 and 24.0, 32 x 1012 42.0 and 38.0, 32 x
+  // 2036 72.3 and 66.9, 32 x 4084 125.6 and 124.4, 16 x 8180 121.4 and 119.8, 8 x 16372 121.7 and 120.4, 1 x 32756 36.9 and 36.6; of few sequences between
+  // 1 % more and 7 % less.  Elsewhere the parts share them anyway, and the order costs (8 x 8 x 8229 61.9 and 64.3).
   int turn = blockIdx.x;
   if constexpr (QUADS) {
     if ((gridDim.x & 7) == 0) {                            // (uniform)
