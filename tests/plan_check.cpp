@@ -62,12 +62,12 @@ int all() {
   for (int len = 5121; len <= 131072; len += len / 9 + 13) lengths.push_back(len);
   for (int kv_heads : {1, 2, 4, 5, 8, 16})
     for (int batch = 1; batch <= 80; batch += batch < 66 ? 1 : 7)
-      for (int form = 0; form < 5; ++form) {
+      for (int form = 0; form < 6; ++form) {
         kvq_layout L{};
         L.batch = batch; L.kv_heads = kv_heads; L.max_seq = 1 << 18; L.head_dim = 128;
-        L.bits_k = form == 1 ? 16 : 4; L.bits_v = form == 1 ? 16 : 2;
+        L.bits_k = form == 1 ? 16 : form == 5 ? 8 : 4; L.bits_v = form == 1 ? 16 : form == 5 ? 8 : 2;
         L.group_k = L.group_v = 64;
-        L.axis_k = form >= 3 ? KVQ_AXIS_SEQ : KVQ_AXIS_HEAD_DIM; L.axis_v = KVQ_AXIS_HEAD_DIM;
+        L.axis_k = form == 3 || form == 4 ? KVQ_AXIS_SEQ : KVQ_AXIS_HEAD_DIM; L.axis_v = KVQ_AXIS_HEAD_DIM;
         L.resid_len = form == 2 ? 64 : form == 4 ? 128 : 0;
         check(L, lengths);
       }
