@@ -2114,32 +2114,34 @@ namespace {
 // value); a step of wider rows takes longer, in proportion.  (Of four wavefronts it does not: two workgroups share a unit, and what is dealt
 // out on top shares its memory rate.)
 int by_width(const Geom& g, int steps) { const int bits = g.bits_k + g.bits_v; return bits > 8 ? (8 * steps + bits - 1) / bits : steps; }
-int deal_line1(const Geom& g, int nw) { return nw == 8 ? by_width(g, 80) : 56; }
+int deal_line1(const Geom& g, int nw) { return nw == 8 ? by_width(g, 72) : 56; }
 int deal_line2(const Geom& g, int nw) { return by_width(g, 6 * nw) > 4 * nw ? by_width(g, 6 * nw) : 4 * nw; }
 bool deals(const Geom& g, const DecodePlan& p) {
   if (g.resid || g.batch < 2 || g.batch > 64 || p.n_splits < 1 || p.n_splits > 4) return false;
   return p.steps_per_split >= (p.n_splits == 1 ? deal_line1(g, p.waves_per_wg) : p.n_splits == 2 ? deal_line2(g, p.waves_per_wg) : 12 * p.waves_per_wg);
 }
-// The longest part that pays.  Sequences of one part have no records yet: the search, the records and their merge are 2 to 3 us, six steps of
-// eight wavefronts (ten of four, two workgroups of which share a unit; twelve where there are more than 4 heads to merge), and a quarter of the
-// part at least (an eighth; a third), because the workgroups that come on top share the memory.  Sequences of several parts merge in any case: two
-// steps, and 3/16.
-// K4V2, 4 query heads, in turn with nothing dealt out.  One part, steps per wavefront planned and dealt out: 17 x 8 heads x 3500 tokens, lengths even
-// from 0.65 of it on, 14 -> 10: 15.2 us for 13.8, from 0.5 on, 14 -> 8: 13.2 for 13.8, from 0.05 on, 14 -> 6: 11.7 for 13.7; 24 x 8 x 8000, 32 -> 28: 31.4
-// for 30.1, 32 -> 23: 26.1 for 27.0; four wavefronts, 40 x 8 x 2500, 20 -> 11: 4 % slower, 20 -> 8: 9 % faster; K8V8 of eight
-// wavefronts from three steps on.  Four wavefronts, 8 query heads: 40 x 8, K4V2 36 -> 25 10 % slower, 36 -> 18 2 % faster, 63 -> 30 18 % faster;
-// K8V8 14 -> 7 4 to 8 % slower, 21 -> 10 4 % slower, 40 -> 19 3 % faster; 48 x 8, 14 -> 9 7 % slower.  4 query heads, K8V8: 40 x 8, 11 -> 6 8 %
-// slower, 21 -> 10 level, 40 -> 28 8 % faster.
+// The longest part that pays.  Sequences of one part have no records yet: the search, the records and their merge are 2 to 3 us, five steps of
+// eight wavefronts, and an eighth of the part at least, because the workgroups that come on top share the memory.  Of four wavefronts, two workgroups
+// of which share a unit, ten steps (and an eighth), or eight and nearly half of a short part; twelve and a third where there are more than 4 heads to
+// merge.  Sequences of several parts merge in any case: two steps, and 3/16.
+// One part, in turn with nothing dealt out, K4V2 and 4 query heads unless said, steps per wavefront planned and dealt out, lengths even from a share of the
+// longest up to it: 17 x 8 heads x 3500 tokens, from 0.65 on, 14 -> 10: 15.2 us for 13.8, from 0.05 on, 14 -> 6: 11.7 for 13.7; 24 x 8 x 8000, 32 -> 28:
+// 31.4 for 30.1, 32 -> 23: 26.1 for 27.0; 18 to 30 x 8, shares from 0.02 to 0.8, 36 -> 29 to 30 1 to 4 % faster (K2V2 2 to 6, K3V2 3 to 7), 36 -> 31 between 2 % slower and 4 % faster, 18 -> 13 0 to 5 %, 12 -> 7
+// 5 to 13 %, 9 -> 4 1 to 10 %; four steps saved between 6 % faster and 5 % slower (12 -> 8, 9 -> 5), three 2 % faster to 9 % slower; K8V8 gains from three
+// steps on.  Four wavefronts, 38 to 60 x 8: 17 -> 8 to 9 between 11 % faster and 4 % slower (-4 in the mean), 24 -> 15 5 % faster to 2 % slower, 24 -> 19 1 to 9 % slower, 36
+// -> 30 3 to 8 % slower.  8 query heads: 40 x 8, 36 -> 25 10 % slower, 36 -> 18 2 % faster, 63 -> 30 18 % faster, 17 -> 8 1 % slower; K8V8 14 -> 7 4 to 8 %
+// slower, 21 -> 10 4 % slower, 40 -> 19 3 % faster.  4 query heads, K8V8: 11 -> 6 8 % slower, 21 -> 10 level, 40 -> 28 8 % faster.
 // Several parts, against the plan's own number dealt out: 11 x 8 x 3500, 7 -> 7: 12.8 for 11.6, 7 -> 6: 12.2; 7 x 8 x 16000, 16 -> 14: 21.8 for
 // 21.0; 11 x 8 x 8000, 16 -> 9: 14.5 for 18.7.
 int deal_most(const Geom& g, const DecodePlan& p, int heads) {
   const int nw = p.waves_per_wg, q = p.steps_per_split;
-  int steps, share;
-  if (p.n_splits > 1) { steps = by_width(g, 2 * nw); share = by_width(g, q * 3 / 16); }
-  else if (nw == 8) { steps = by_width(g, 48); share = by_width(g, q / 4); }
-  else if (heads <= 4) { steps = 40; share = q / 8; }
-  else { steps = 48; share = q / 3; }
-  return (q - (steps > share ? steps : share)) / nw * nw;
+  auto larger = [](int a, int b) { return a > b ? a : b; };
+  int saved;
+  if (p.n_splits > 1) saved = larger(by_width(g, 2 * nw), by_width(g, q * 3 / 16));
+  else if (nw == 8) saved = larger(by_width(g, 40), by_width(g, q / 8));
+  else if (heads > 4) saved = larger(48, q / 3);
+  else saved = q < 88 ? larger(32, q * 9 / 20) : larger(40, q / 8);
+  return (q - saved) / nw * nw;
 }
 int full_slots(const Geom& g, int nw) { return device_compute_units() * 4 * KVQ_WAVES_PER_SIMD / nw / g.kv_heads; }
 int deal_records(const Geom& g, int slots) { return (slots + g.batch - 1) / g.batch; }      // of the workspace, per (batch, kv head)
