@@ -51,7 +51,7 @@ def test_which_ragged_batches_may_be_dealt_out(check, batch, heads, bits_k, bits
     assert _plan(check, batch, 8, heads, bits_k, bits_v, tokens, "ragged")[:4] == want
 
 
-@pytest.mark.parametrize("batch,heads,tokens,want", [(40, 4, 3600, 76), (40, 5, 3600, 68), (40, 8, 6500, 136), (40, 4, 6500, 164), (40, 4, 2170, 36), (18, 8, 6500, 168), (18, 8, 9500, 264), (18, 8, 15000, 416)])
+@pytest.mark.parametrize("batch,heads,tokens,want", [(40, 4, 3600, 76), (40, 5, 3600, 68), (40, 8, 6500, 136), (40, 4, 6500, 164), (40, 4, 2170, 36), (18, 8, 6500, 168), (18, 8, 9500, 264), (18, 8, 15000, 408)])
 def test_longest_part_that_pays(check, batch, heads, tokens, want):
     """Steps: of four wavefronts, ten each and an eighth less than planned, or eight and nearly half of a short part; more than 4 heads twelve
     and a third; of eight, five and an eighth."""
