@@ -2188,12 +2188,11 @@ static DecodePlan plan_parts(const Geom& g, int32_t seq_len, int heads, int64_t 
 
 DecodePlan plan_decode(const Geom& g, int32_t seq_len, int heads, int64_t room, bool ragged) {
   // Where up to an eighth more streams than units, of different lengths, have wide rows, one workgroup of eight wavefronts each: the short
-  // ones make room for those that wait, and four wavefronts take twice as long over the longest.  Up to twenty steps per wavefront: parts of
-  // four wavefronts that long are dealt out and pay.  33 to 36 x 8 heads, lengths even from 0.01 to 0.8 of the longest up to it, four wavefronts (dealt out where that
-  // pays) against eight, means of 15, K8V8, 1, 4 and 8 query heads: 1300 tokens 6.0, 8.4, 6.0 % slower, 2500 1.2, 5.9, 10.6, 5200 -2.3, 0.2, 2.5, 8000 -4.7, -3.0,
-  // 0.5; K8V4 1300 4.6, 6.6, 3.1, 2500 2.4, 6.4, 10.4, 5200 -2.1, 1.0, 4.5, 8000 -3.7, -2.2, 1.9 (from 0.25 on up to 21, from 0.8 on -12 to 5).  Of up to 8 bits it
-  // is a draw of means, 18 % less for the most uneven batches and 20 % more for nearly equal ones, and they keep the four.
-  const bool up = ragged && g.bits_k + g.bits_v > 8 && g.batch * g.kv_heads > device_compute_units() && plan_steps(g, seq_len) <= 160;
+  // ones make room for those that wait, and four wavefronts take twice as long over the longest.  33 to 36 x 8 heads, 900 to 5000 tokens,
+  // lengths even from 0.02, 0.2, 0.5 and 0.8 of the longest up to it, eight wavefronts against four (with the best of them dealt out), mean and
+  // range: K8V8, 8 query heads 7 % less (-21 to 7 %), 1 query head 1 % less (-13 to 14 %).  Of up to 8 bits it is a draw of means, 18 % less for the
+  // most uneven batches and 20 % more for nearly equal ones, and they keep the four.
+  const bool up = ragged && g.bits_k + g.bits_v > 8 && g.batch * g.kv_heads > device_compute_units();
   DecodePlan p = plan_parts(g, seq_len, heads, room, up);
   if (!ragged || !deals(g, p)) return p;
   p.deal_pays = deal_most(g, p, heads);
