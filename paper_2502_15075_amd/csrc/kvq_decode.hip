@@ -2176,8 +2176,8 @@ int32_t decode_records_bound(const Geom& g, int32_t seq_len, bool least) {
 }
 
 // heads: query heads per kv head; room: records per query head that the workspace holds.
-static DecodePlan plan_parts(const Geom& g, int32_t seq_len, int heads, int64_t room, bool up) {
-  const int n_steps = plan_steps(g, seq_len), most = n_steps ? fine_most(g, up) : 0;
+static DecodePlan plan_parts(const Geom& g, int32_t seq_len, int heads, int64_t room) {
+  const int n_steps = plan_steps(g, seq_len), most = n_steps ? fine_most(g, false) : 0;
   if (most < 1) return plan_coarse(g, seq_len);
   const FinePlan f = fine_plan(n_steps, most, heads, wide_rows(g));
   if (f.splits == 0 || (f.splits > 1 && f.splits > room)) return plan_coarse(g, seq_len);
@@ -2187,13 +2187,7 @@ static DecodePlan plan_parts(const Geom& g, int32_t seq_len, int heads, int64_t 
 }
 
 DecodePlan plan_decode(const Geom& g, int32_t seq_len, int heads, int64_t room, bool ragged) {
-  // Where up to an eighth more streams than units, of different lengths, have wide rows, one workgroup of eight wavefronts each: the short
-  // ones make room for those that wait, and four wavefronts take twice as long over the longest.  33 to 36 x 8 heads, 900 to 5000 tokens,
-  // lengths even from 0.02, 0.2, 0.5 and 0.8 of the longest up to it, eight wavefronts against four (with the best of them dealt out), mean and
-  // range: K8V8, 8 query heads 7 % less (-21 to 7 %), 1 query head 1 % less (-13 to 14 %).  Of up to 8 bits it is a draw of means, 18 % less for the
-  // most uneven batches and 20 % more for nearly equal ones, and they keep the four.
-  const bool up = ragged && g.bits_k + g.bits_v > 8 && g.batch * g.kv_heads > device_compute_units();
-  DecodePlan p = plan_parts(g, seq_len, heads, room, up);
+  DecodePlan p = plan_parts(g, seq_len, heads, room);
   if (!ragged || !deals(g, p)) return p;
   p.deal_pays = deal_most(g, p, heads);
   const int own = p.n_splits * g.batch, full = full_slots(g, p.waves_per_wg);

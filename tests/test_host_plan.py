@@ -56,11 +56,3 @@ def test_longest_part_that_pays(check, batch, heads, tokens, want):
     """Steps: of four wavefronts, ten each and an eighth less than planned, or eight and nearly half of a short part; more than 4 heads twelve
     and a third; of eight, five and an eighth."""
     assert _plan(check, batch, 8, heads, 4, 2, tokens, "ragged")[4] == want
-
-
-@pytest.mark.parametrize("batch,bits_k,bits_v,tokens,ragged,want", [(33, 8, 8, 3000, True, (1, 96, 8, 0)), (36, 8, 4, 3000, True, (1, 96, 8, 0)), (37, 8, 8, 1500, True, (1, 48, 4, 0)),
-                                                                    (33, 4, 4, 1500, True, (1, 48, 4, 0)), (33, 8, 8, 3000, False, (1, 96, 4, 0))])
-def test_wide_ragged_batches_a_little_over_the_chip_keep_eight_wavefronts(check, batch, bits_k, bits_v, tokens, ragged, want):
-    """257 to 292 sequences and heads of wide rows and different lengths: workgroups of eight wavefronts, the last of which wait for
-    the short ones; of equal lengths, narrow rows or more of them: of four."""
-    assert _plan(check, batch, 8, 4, bits_k, bits_v, tokens, *(["ragged"] if ragged else []))[:4] == want
