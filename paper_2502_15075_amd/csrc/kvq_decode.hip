@@ -2110,37 +2110,41 @@ int fine_most(const Geom& g, bool bound) {
 // heads x 2200 tokens, 4 query heads, from 0.03 on 15.4 and 11.9 us, from 0.2 on 15.7 and 12.9, from 0.8 on 16.9 and 16.7; of three steps per
 // wavefront, 16 x 8 x 1300, 8 query heads, from 0.03 on 5 % faster and from 0.8 on 5 % slower.
 namespace {
-// The steps that a dealt-out part of eight wavefronts has to save to pay, and the lines, are drawn on rows of up to 8 bits (codes of key and
-// value); a step of wider rows takes longer, in proportion.  (Of four wavefronts it does not: two workgroups share a unit, and what is dealt
-// out on top shares its memory rate.)
+// The steps that a dealt-out part has to save to pay, and the lines, are drawn on rows of up to 8 bits (codes of key and value); a step of wider
+// rows takes longer, in proportion (of four wavefronts deal_most has figures of its own).
 int by_width(const Geom& g, int steps) { const int bits = g.bits_k + g.bits_v; return bits > 8 ? (8 * steps + bits - 1) / bits : steps; }
-int deal_line1(const Geom& g, int nw) { return nw == 8 ? by_width(g, 72) : 56; }
+int deal_line1(const Geom& g, int nw) { return nw == 8 ? by_width(g, 72) : g.bits_k + g.bits_v > 8 ? 40 : 44; }
 int deal_line2(const Geom& g, int nw) { return by_width(g, 6 * nw) > 4 * nw ? by_width(g, 6 * nw) : 4 * nw; }
 bool deals(const Geom& g, const DecodePlan& p) {
   if (g.resid || g.batch < 2 || g.batch > 64 || p.n_splits < 1 || p.n_splits > 4) return false;
   return p.steps_per_split >= (p.n_splits == 1 ? deal_line1(g, p.waves_per_wg) : p.n_splits == 2 ? deal_line2(g, p.waves_per_wg) : 12 * p.waves_per_wg);
 }
 // The longest part that pays.  Sequences of one part have no records yet: the search, the records and their merge are 2 to 3 us, five steps of
-// eight wavefronts, and an eighth of the part at least, because the workgroups that come on top share the memory.  Of four wavefronts, two workgroups
-// of which share a unit, ten steps (and an eighth), or eight and nearly half of a short part; twelve and a third where there are more than 4 heads to
-// merge.  Sequences of several parts merge in any case: two steps, and 3/16.
+// eight wavefronts, and an eighth of the part at least, because the workgroups that come on top share the memory.  Of four wavefronts two workgroups
+// share a unit: seven steps and 3/10 (nine and a quarter where there are more than 4 heads to merge), of wide rows four and 2/9 (six and a quarter),
+// and nine to twelve steps always do.  Sequences of several parts merge in any case: two steps, and 3/16.
 // One part, in turn with nothing dealt out, K4V2 and 4 query heads unless said, steps per wavefront planned and dealt out, lengths even from a share of the
-// longest up to it: 17 x 8 heads x 3500 tokens, from 0.65 on, 14 -> 10: 15.2 us for 13.8, from 0.05 on, 14 -> 6: 11.7 for 13.7; 24 x 8 x 8000, 32 -> 28:
-// 31.4 for 30.1, 32 -> 23: 26.1 for 27.0; 18 to 30 x 8, shares from 0.02 to 0.8, 36 -> 29 to 30 1 to 4 % faster (K2V2 2 to 6, K3V2 3 to 7), 36 -> 31 between 2 % slower and 4 % faster, 18 -> 13 0 to 5 %, 12 -> 7
-// 5 to 13 %, 9 -> 4 1 to 10 %; four steps saved between 6 % faster and 5 % slower (12 -> 8, 9 -> 5), three 2 % faster to 9 % slower; K8V8 gains from three
-// steps on.  Four wavefronts, 38 to 60 x 8: 17 -> 8 to 9 between 11 % faster and 4 % slower (-4 in the mean), 24 -> 15 5 % faster to 2 % slower, 24 -> 19 1 to 9 % slower, 36
-// -> 30 3 to 8 % slower.  8 query heads: 40 x 8, 36 -> 25 10 % slower, 36 -> 18 2 % faster, 63 -> 30 18 % faster, 17 -> 8 1 % slower; K8V8 14 -> 7 4 to 8 %
-// slower, 21 -> 10 4 % slower, 40 -> 19 3 % faster.  4 query heads, K8V8: 11 -> 6 8 % slower, 21 -> 10 level, 40 -> 28 8 % faster.
+// longest up to it.  Eight wavefronts: 17 x 8 heads x 3500 tokens, from 0.65 on, 14 -> 10: 15.2 us for 13.8, from 0.05 on, 14 -> 6: 11.7 for 13.7; 24 x 8 x 8000,
+// 32 -> 28: 31.4 for 30.1, 32 -> 23: 26.1 for 27.0; 18 to 30 x 8, shares from 0.02 to 0.8, 36 -> 29 to 30 1 to 4 % faster (K2V2 2 to 6, K3V2 3 to 7), 36 -> 31 between 2 %
+// slower and 4 % faster, 18 -> 13 0 to 5 %, 12 -> 7 5 to 13 %, 9 -> 4 1 to 10 %; four steps saved between 6 % faster and 5 % slower (12 -> 8, 9 -> 5), three 2 % faster to 9 %
+// slower; K8V8 gains from three steps on.
+// Four wavefronts, 33 to 60 x 8 heads, shares from 0.03 to 0.7, means of up to 6 batches, per cent faster than nothing dealt out (-: slower).  The sequences
+// in random order: in falling order of their lengths the planned parts share the units best, and it pays up to 15 less.  K4V2, 4 query heads: 11 -> 4 5, 11 -> 5 0,
+// 15 -> 8 0, 15 -> 11 -8, 20 -> 12 1, 20 -> 14 -1, 25 -> 16 3, 25 -> 17 -1, 25 -> 18 -3, 25 -> 20 -8, 40 -> 31 -1, 71 -> 62 -2 (1 query head 2 to 5 better); 8 query heads: 11 -> 5
+// -5, 15 -> 6 2, 15 -> 8 1, 20 -> 9 7, 20 -> 10 1, 20 -> 12 2, 20 -> 15 -8, 25 -> 14 13, 25 -> 16 2, 25 -> 18 -2, 40 -> 30 2, 40 -> 31 -3, 71 -> 50 7, 71 -> 59 4.  K8V8, 4 query
+// heads: 11 -> 5 21, 11 -> 7 9, 15 -> 8 15, 15 -> 11 4, 20 -> 14 13, 20 -> 16 3, 25 -> 19 5, 25 -> 20 -4, 40 -> 31 5, 71 -> 62 2; 8 query heads: 11 -> 5 15, 11 -> 7 3, 15 -> 9 1, 15
+// -> 11 -2, 20 -> 14 9, 20 -> 16 -2, 25 -> 18 7, 25 -> 20 -6, 40 -> 31 3, 71 -> 59 11, 71 -> 62 2.  Of eight steps planned the means are level or worse.
 // Several parts, against the plan's own number dealt out: 11 x 8 x 3500, 7 -> 7: 12.8 for 11.6, 7 -> 6: 12.2; 7 x 8 x 16000, 16 -> 14: 21.8 for
 // 21.0; 11 x 8 x 8000, 16 -> 9: 14.5 for 18.7.
 int deal_most(const Geom& g, const DecodePlan& p, int heads) {
   const int nw = p.waves_per_wg, q = p.steps_per_split;
   auto larger = [](int a, int b) { return a > b ? a : b; };
+  auto smaller = [](int a, int b) { return a < b ? a : b; };
   int saved;
   if (p.n_splits > 1) saved = larger(by_width(g, 2 * nw), by_width(g, q * 3 / 16));
   else if (nw == 8) saved = larger(by_width(g, 40), by_width(g, q / 8));
-  else if (heads > 4) saved = larger(48, q / 3);
-  else saved = q < 88 ? larger(32, q * 9 / 20) : larger(40, q / 8);
+  else if (g.bits_k + g.bits_v > 8) saved = heads > 4 ? larger(24, smaller(q / 4, 36)) : larger(16, smaller(q * 2 / 9, 36));
+  else saved = heads > 4 ? larger(36, smaller(q / 4, 48)) : larger(28, smaller(q * 3 / 10, 40));
   return (q - saved) / nw * nw;
 }
 int full_slots(const Geom& g, int nw) { return device_compute_units() * 4 * KVQ_WAVES_PER_SIMD / nw / g.kv_heads; }

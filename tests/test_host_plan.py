@@ -40,19 +40,21 @@ def test_plans_stay_inside_the_workspace_and_reach_the_whole_of_it(check):
 
 
 @pytest.mark.parametrize("batch,heads,bits_k,bits_v,tokens,want", [(18, 4, 4, 2, 1400, (1, 48, 8, 0)), (18, 4, 4, 2, 2272, (1, 72, 8, 32)), (18, 4, 4, 2, 2048, (1, 64, 8, 0)),
-                                                                   (33, 4, 4, 2, 1665, (1, 56, 4, 64)), (33, 4, 4, 2, 1664, (1, 52, 4, 0)),
+                                                                   (33, 4, 4, 2, 1281, (1, 44, 4, 64)), (33, 4, 4, 2, 1280, (1, 40, 4, 0)),
                                                                    (18, 4, 8, 8, 1281, (1, 48, 8, 32)), (18, 4, 8, 8, 1024, (1, 32, 8, 0)),
                                                                    (11, 4, 4, 2, 3500, (2, 56, 8, 32)), (9, 4, 4, 2, 12000, (3, 128, 8, 32)),
                                                                    (11, 4, 8, 8, 2048, (2, 32, 8, 32)), (11, 4, 8, 8, 1536, (2, 24, 8, 0)), (11, 4, 8, 4, 1537, (2, 32, 8, 32)),
-                                                                   (40, 4, 8, 8, 1665, (1, 56, 4, 64)), (40, 4, 8, 8, 1664, (1, 52, 4, 0))])
+                                                                   (40, 4, 8, 8, 1153, (1, 40, 4, 64)), (40, 4, 8, 8, 1152, (1, 36, 4, 0))])
 def test_which_ragged_batches_may_be_dealt_out(check, batch, heads, bits_k, bits_v, tokens, want):
-    """Sequences of one part: from nine steps per wavefront on (fourteen of four), half as many of rows twice as wide (not of four); of two
+    """Sequences of one part: from nine steps per wavefront on, half as many of rows twice as wide, of four wavefronts from eleven (ten); of two
     parts from six steps on, of wide rows four."""
     assert _plan(check, batch, 8, heads, bits_k, bits_v, tokens, "ragged")[:4] == want
 
 
-@pytest.mark.parametrize("batch,heads,tokens,want", [(40, 4, 3600, 76), (40, 5, 3600, 68), (40, 8, 6500, 136), (40, 4, 6500, 164), (40, 4, 2170, 36), (18, 8, 6500, 168), (18, 8, 9500, 264), (18, 8, 15000, 408)])
-def test_longest_part_that_pays(check, batch, heads, tokens, want):
-    """Steps: of four wavefronts, ten each and an eighth less than planned, or eight and nearly half of a short part; more than 4 heads twelve
-    and a third; of eight, five and an eighth."""
-    assert _plan(check, batch, 8, heads, 4, 2, tokens, "ragged")[4] == want
+@pytest.mark.parametrize("batch,heads,bits,tokens,want", [(40, 4, 3, 1400, 16), (40, 4, 3, 2500, 52), (40, 4, 3, 9000, 244), (40, 5, 3, 1400, 8), (40, 8, 3, 3600, 80), (40, 8, 3, 9000, 236),
+                                                          (40, 4, 8, 1400, 28), (40, 1, 8, 3600, 88), (40, 4, 8, 9000, 248), (40, 8, 8, 1400, 20), (40, 7, 8, 3600, 84), (40, 8, 8, 9000, 248),
+                                                          (18, 8, 3, 6500, 168), (18, 8, 3, 9500, 264), (18, 8, 3, 15000, 408), (18, 1, 8, 3000, 72)])
+def test_longest_part_that_pays(check, batch, heads, bits, tokens, want):
+    """Steps: of four wavefronts at least seven each and 3/10 less than planned, for more than 4 heads nine and a quarter, of wide rows four and
+    2/9 (six and a quarter); of eight, five and an eighth, of wide rows half of that."""
+    assert _plan(check, batch, 8, heads, bits, bits, tokens, "ragged")[4] == want
