@@ -2120,13 +2120,13 @@ bool deals(const Geom& g, const DecodePlan& p) {
   return p.steps_per_split >= (p.n_splits == 1 ? deal_line1(g, p.waves_per_wg) : p.n_splits == 2 ? deal_line2(g, p.waves_per_wg) : 12 * p.waves_per_wg);
 }
 // The longest part that pays.  Sequences of one part have no records yet: the search, the records and their merge are 2 to 3 us, five steps of
-// eight wavefronts, and an eighth of the part at least, because the workgroups that come on top share the memory.  Of four wavefronts two workgroups
+// eight wavefronts (four of the shortest), and an eighth of the part at least, because the workgroups that come on top share the memory.  Of four wavefronts two workgroups
 // share a unit: seven steps and 3/10 (nine and a quarter where there are more than 4 heads to merge), of wide rows four and 2/9 (six and a quarter),
 // and nine to twelve steps always do.  Sequences of several parts merge in any case: two steps, and 3/16.
 // One part, in turn with nothing dealt out, K4V2 and 4 query heads unless said, steps per wavefront planned and dealt out, lengths even from a share of the
 // longest up to it.  Eight wavefronts: 17 x 8 heads x 3500 tokens, from 0.65 on, 14 -> 10: 15.2 us for 13.8, from 0.05 on, 14 -> 6: 11.7 for 13.7; 24 x 8 x 8000,
 // 32 -> 28: 31.4 for 30.1, 32 -> 23: 26.1 for 27.0; 18 to 30 x 8, shares from 0.02 to 0.8, 36 -> 29 to 30 1 to 4 % faster (K2V2 2 to 6, K3V2 3 to 7), 36 -> 31 between 2 %
-// slower and 4 % faster, 18 -> 13 0 to 5 %, 12 -> 7 5 to 13 %, 9 -> 4 1 to 10 %; four steps saved between 6 % faster and 5 % slower (12 -> 8, 9 -> 5), three 2 % faster to 9 %
+// slower and 4 % faster, 18 -> 13 0 to 5 %, 12 -> 7 5 to 13 %, 9 -> 4 1 to 10 %, 9 -> 5 3 to 10 %; four steps of more saved 4 % faster (K3V2) to 3 % slower (K4V4; 12 -> 8, 14 -> 10, 17 -> 13), three 2 % faster to 9 %
 // slower; K8V8 gains from three steps on.
 // Four wavefronts, 33 to 60 x 8 heads, shares from 0.03 to 0.7, means of up to 6 batches, per cent faster than nothing dealt out (-: slower).  The sequences
 // in random order: in falling order of their lengths the planned parts share the units best, and it pays up to 15 less.  K4V2, 4 query heads: 11 -> 4 5, 11 -> 5 0,
@@ -2138,12 +2138,13 @@ bool deals(const Geom& g, const DecodePlan& p) {
 // 21.0; 11 x 8 x 8000, 16 -> 9: 14.5 for 18.7.
 int deal_most(const Geom& g, const DecodePlan& p, int heads) {
   const int nw = p.waves_per_wg, q = p.steps_per_split;
+  const bool wide = g.bits_k + g.bits_v > 8;
   auto larger = [](int a, int b) { return a > b ? a : b; };
   auto smaller = [](int a, int b) { return a < b ? a : b; };
   int saved;
   if (p.n_splits > 1) saved = larger(by_width(g, 2 * nw), by_width(g, q * 3 / 16));
-  else if (nw == 8) saved = larger(by_width(g, 40), by_width(g, q / 8));
-  else if (g.bits_k + g.bits_v > 8) saved = heads > 4 ? larger(24, smaller(q / 4, 36)) : larger(16, smaller(q * 2 / 9, 36));
+  else if (nw == 8) saved = larger(!wide && q <= 80 ? 32 : by_width(g, 40), by_width(g, q / 8));
+  else if (wide) saved = heads > 4 ? larger(24, smaller(q / 4, 36)) : larger(16, smaller(q * 2 / 9, 36));
   else saved = heads > 4 ? larger(36, smaller(q / 4, 48)) : larger(28, smaller(q * 3 / 10, 40));
   return (q - saved) / nw * nw;
 }

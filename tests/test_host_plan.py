@@ -53,8 +53,9 @@ def test_which_ragged_batches_may_be_dealt_out(check, batch, heads, bits_k, bits
 
 @pytest.mark.parametrize("batch,heads,bits,tokens,want", [(40, 4, 3, 1400, 16), (40, 4, 3, 2500, 52), (40, 4, 3, 9000, 244), (40, 5, 3, 1400, 8), (40, 8, 3, 3600, 80), (40, 8, 3, 9000, 236),
                                                           (40, 4, 8, 1400, 28), (40, 1, 8, 3600, 88), (40, 4, 8, 9000, 248), (40, 8, 8, 1400, 20), (40, 7, 8, 3600, 84), (40, 8, 8, 9000, 248),
-                                                          (18, 8, 3, 6500, 168), (18, 8, 3, 9500, 264), (18, 8, 3, 15000, 408), (18, 1, 8, 3000, 72)])
+                                                          (18, 8, 3, 2272, 40), (18, 8, 3, 2561, 48), (18, 8, 3, 6500, 168), (18, 8, 3, 9500, 264), (18, 8, 3, 15000, 408), (18, 1, 8, 3000, 72)])
 def test_longest_part_that_pays(check, batch, heads, bits, tokens, want):
     """Steps: of four wavefronts at least seven each and 3/10 less than planned, for more than 4 heads nine and a quarter, of wide rows four and
-    2/9 (six and a quarter); of eight, five and an eighth, of wide rows half of that."""
+    2/9 (six and a quarter); of eight, five and an eighth (four of up to ten), of wide rows half of
+    the five."""
     assert _plan(check, batch, 8, heads, bits, bits, tokens, "ragged")[4] == want
